@@ -319,8 +319,11 @@ pq_status pq_export_canonical(const pq_ctx *ctx, pq_kind kind, const uint8_t *co
  * the device: the work is split there into equal shares of 64-token tiles
  * per wavefront, whatever the mix of lengths, so a ragged batch costs what
  * its total number of cached tokens costs.
- * workspace (device): at least pq_attn_workspace_bytes(B, Hq, Hkv, max_ctx)
- * bytes, PQ_ENOMEM otherwise; contents need not be preserved between calls.
+ * workspace (device): pq_attn_workspace_bytes(B, Hq, Hkv, max_ctx) bytes; contents
+ * need not be preserved between calls.  A small problem is split into shares of
+ * one tile; a workspace that only holds the partial results of shares of four
+ * tiles is accepted as well (the work is then split that way, which changes the
+ * last bits of the result), less is PQ_ENOMEM.
  * ------------------------------------------------------------------------- */
 pq_status pq_attn_decode_polar(const pq_ctx *ctx, const void *q, void *out, pq_dtype out_dtype,
                                const uint8_t *k_codes, const uint16_t *k_radii,

@@ -63,8 +63,6 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kProbShift = 9.0f;
 constexpr float kRefSlack = 6.0f;
 
-/* LDS table block: layout in pq_common.h (PQ_TAB_*), image built on the host */
-constexpr int kTabDwords = PQ_TAB_DWORDS;
 /* The tables as the kernel lays them out in LDS (dwords).  Random gathers from a table collide in the LDS banks
  * unless every lane that is served in the same cycle reads its own bank: a 4-byte gather is served 32 lanes at a
  * time, a 16-byte gather 16 lanes at a time, so the small tables are replicated into one column per lane (mod 32,
@@ -107,19 +105,18 @@ struct AttnArgs {
 /* Work plan of one attention call, built on the device from ctx_len by the launch that
  * precedes the partial kernel (the host never reads the context lengths).  The tiles of all
  * (sequence, kv head) streams form one global sequence, stream (b, hk) before (b, hk + 1)
- * before (b + 1, 0); wavefront w of the partial kernel takes global tiles
- * [w * share, (w + 1) * share): every wavefront gets the same number of tiles whatever
- * the mix of context lengths, and a wavefront whose range crosses a stream boundary works
- * through one piece per stream.  Piece ids are w + (b * Hkv + hk): along the global
+ * before (b + 1, 0).  W = min(wavefronts of the launch, tiles) wavefronts work; the first
+ * `rem` take base + 1 consecutive tiles each, the others base: the shares differ by at most one
+ * tile whatever the mix of context lengths, and a wavefront whose range crosses a stream
+ * boundary works through one piece per stream.  Piece ids are w + (b * Hkv + hk): along the global
  * sequence either w or the stream index grows from one piece to the next, so the id is unique
  * and the pieces of one stream are consecutive ids.
  * All counts fit 31 bits (the launch code refuses batches whose tile count could not).
- *   plan[0] = total tiles (all streams), plan[1] = share (tiles per wavefront),
+ *   plan[0] = total tiles (all streams), plan[1] = W,
  *   plan[2 + b] = tiles of sequences 0 .. b-1 of ONE kv head (b = 0 .. B), then for every
  *   stream s = b * Hkv + hk, from plan[2 + B + 1 + 2 s]: the wavefront of its first piece and
  *   the number of its pieces (what the combine kernel needs). */
 constexpr int kPlanHeader = 2;
-constexpr int kMinShareTiles = 4;
 
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 
@@ -490,7 +487,7 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
     __shared__ int sCtx[64];
     __shared__ int64_t sTile0[64];
     const bool staged = a.B <= 64;
-    const int total = a.plan[0], share = a.plan[1];
+    const int total = a.plan[0], working = a.plan[1];
     int st_pre = 0, st_last = 0, st_len = 0;
     int64_t st_start = 0;
     constexpr int kStager = kThreads - 64; /* first thread of the last wavefront */
@@ -554,10 +551,16 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
     /* the wavefront index is the same in all lanes: telling the compiler so keeps everything
        derived from it (work range, pointers, loop bounds) in scalar registers */
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int w = (int)blockIdx.x * kWavesPerBlock + wave;
-    if (share <= 0 || (int64_t)w * share >= total) return;
-    int gpos = w * share;
-    const int gend = min(gpos + share, total);
+    const int base = working > 0 ? total / working : 0, rem = total - base * working;
+    /* Short shares: consecutive ones go to different workgroups, so that fewer shares than the launch has wavefronts
+       occupy every CU (and its four SIMDs in turn) instead of filling the first CUs, and the wavefronts with one tile
+       more spread evenly (8700 tiles: 35.3 us per decode step against 37.4).  From four tiles on the order makes
+       1 % at most, and a CU whose wavefronts read neighbouring tiles is the better one (117.0 against 117.8 us at
+       65536 tiles, 126.9 against 127.9 at 25400 in four column groups). */
+    const int w = base < 4 ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kWavesPerBlock + wave;
+    if (w >= working) return;
+    int gpos = w * base + min(w, rem);
+    const int gend = min(gpos + base + (w < rem ? 1 : 0), total);
     /* wave-uniform reads of the per-sequence data (LDS values come back in vector registers:
        readfirstlane returns them to scalar ones) */
     auto prefix_at = [&](int i) -> int {
@@ -914,18 +917,18 @@ struct PlanArgs {
     const int32_t *ctx_len;
     int B, Hkv;
     int64_t max_ctx, pool_tiles;
-    int slots;     /* wavefronts of the partial kernel's launch */
+    int slots;     /* wavefronts of the partial kernel that may take a share */
     int32_t *plan; /* [kPlanHeader + (B + 1) + 2 * B * Hkv] */
 };
 
 /* Builds the work plan (one workgroup of 512 threads): running sum of the sequences' tile
  * counts, 512 sequences per round (a shuffle scan inside each wavefront, then the
- * wavefronts' totals), the total and the share of a wavefront, and from those the first
+ * wavefronts' totals), the total and the shares of the wavefronts, and from those the first
  * wavefront and the piece count of every stream. */
 __device__ __forceinline__ void build_plan(const PlanArgs &a)
 {
     __shared__ int wave_sum[8];
-    __shared__ int s_share;
+    __shared__ uint32_t s_base, s_rem;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     int carry = 0;
     for (int base = 0; base < a.B; base += 512) {
@@ -951,24 +954,27 @@ __device__ __forceinline__ void build_plan(const PlanArgs &a)
     }
     if (tid == 0) {
         const uint32_t total = (uint32_t)carry * (uint32_t)a.Hkv;
-        uint32_t share = (total + (uint32_t)a.slots - 1u) / (uint32_t)a.slots;
-        if (share < (uint32_t)kMinShareTiles) share = kMinShareTiles;
+        const uint32_t working = total < (uint32_t)a.slots ? total : (uint32_t)a.slots;
+        const uint32_t base = working ? total / working : 0u, rem = working ? total - base * working : 0u;
         a.plan[0] = (int)total;
-        a.plan[1] = (int)share;
+        a.plan[1] = (int)working;
         a.plan[kPlanHeader] = 0;
-        s_share = (int)share;
+        s_base = base;
+        s_rem = rem;
     }
     __syncthreads(); /* also orders this workgroup's plan[] stores before the loads below */
-    const uint32_t share = (uint32_t)s_share;
+    const uint32_t base = s_base, rem = s_rem, long_tiles = rem * (base + 1u);
+    /* wavefront that owns global tile t (below the total: base >= 1) */
+    auto owner = [&](uint32_t t) { return t < long_tiles ? t / (base + 1u) : rem + (t - long_tiles) / base; };
     int32_t *streams = a.plan + kPlanHeader + a.B + 1;
     for (int s = tid; s < a.B * a.Hkv; s += 512) {
         const int b = s / a.Hkv, hk = s - b * a.Hkv;
         const uint32_t before = (uint32_t)a.plan[kPlanHeader + b];
         const uint32_t seq_tiles = (uint32_t)a.plan[kPlanHeader + b + 1] - before;
         const uint32_t first_tile = before * (uint32_t)a.Hkv + (uint32_t)hk * seq_tiles; /* in the global tile sequence */
-        const uint32_t w_first = first_tile / share;
+        const uint32_t w_first = seq_tiles > 0 ? owner(first_tile) : 0u;
         streams[2 * s] = (int)w_first;
-        streams[2 * s + 1] = seq_tiles > 0 ? (int)((first_tile + seq_tiles - 1) / share - w_first) + 1 : 0;
+        streams[2 * s + 1] = seq_tiles > 0 ? (int)(owner(first_tile + seq_tiles - 1) - w_first) + 1 : 0;
     }
 }
 
@@ -979,19 +985,29 @@ __global__ __launch_bounds__(512) void pq_rotate_q_kernel(RotateArgs a, PlanArgs
     else build_plan(p);
 }
 
-/* First launch of a whole decode step: workgroups [0, n) append the new key vectors,
-   [n, 2n) the new value vectors, the next row_blocks rotate kRotateRows query rows each and the
-   last one builds the work plan; the jobs are independent of each other and all of them precede
-   the attention proper. */
-template <int XT>
-__global__ __launch_bounds__(512) void pq_step_prologue_kernel(RotateArgs r, AppendArgs k, AppendArgs v, int n,
-                                                               PlanArgs p, int rows, int row_blocks)
+/* First launch of a whole decode step: the first workgroup builds the work plan (a chain of loads and scans, the
+   longest job when the batch is large), the next n_blocks append the n new key vectors, NV per workgroup, the next
+   n_blocks the new value vectors, and the last row_blocks rotate kRotateRows query rows each; the jobs are
+   independent of each other and all of them precede the attention proper. */
+template <int XT, int NV>
+__global__ __launch_bounds__(512) void pq_step_prologue_kernel(RotateArgs r, AppendArgs k, AppendArgs v, int n, int n_blocks,
+                                                               PlanArgs p, int rows)
 {
-    const int blk = (int)blockIdx.x;
-    if (blk < n) append_vector<XT>(k, PQ_KEY, blk);
-    else if (blk < 2 * n) append_vector<XT>(v, PQ_VALUE, blk - n);
-    else if (blk < 2 * n + row_blocks) rotate_query_rows(r, kRotateRows * (blk - 2 * n), rows);
-    else build_plan(p);
+    const int blk = (int)blockIdx.x - 1;
+    if (blk < 0) build_plan(p);
+    else if (blk < n_blocks) append_vectors<XT, NV>(k, PQ_KEY, NV * blk, n);
+    else if (blk < 2 * n_blocks) append_vectors<XT, NV>(v, PQ_VALUE, NV * (blk - n_blocks), n);
+    else rotate_query_rows(r, kRotateRows * (blk - 2 * n_blocks), rows);
+}
+
+template <int XT>
+void launch_step_prologue(const RotateArgs &r, const AppendArgs &k, const AppendArgs &v, int n, const PlanArgs &p, int rows,
+                          int row_blocks, hipStream_t s)
+{
+    const int nv = append_vectors_per_block(2 * (int64_t)n), n_blocks = (n + nv - 1) / nv;
+    const dim3 grid((unsigned)(2 * n_blocks + row_blocks + 1)), blk(512);
+    if (nv == 1) hipLaunchKernelGGL((pq_step_prologue_kernel<XT, 1>), grid, blk, 0, s, r, k, v, n, n_blocks, p, rows);
+    else hipLaunchKernelGGL((pq_step_prologue_kernel<XT, 4>), grid, blk, 0, s, r, k, v, n, n_blocks, p, rows);
 }
 
 __device__ __forceinline__ float wave_max(float x)
@@ -1018,18 +1034,28 @@ struct CombineArgs {
 
 /* HYBRID adds the partial results of the unquantised window.  They live in the original
  * domain, so they join after the un-rotation of the prefix sum:
- * out = (S^T-product of (sum_c w_c o'_c) + sum_w w_w o_w) / (sum of all w l). */
-template <bool HYBRID>
-__global__ __launch_bounds__(512) void pq_attn_combine_kernel(CombineArgs a)
+ * out = (S^T-product of (sum_c w_c o'_c) + sum_w w_w o_w) / (sum of all w l).
+ *
+ * ROWS output rows per workgroup of 512 threads: the merge of a row's pieces is a chain of loads, so
+ * CQ = 16 / ROWS thread groups of 32 lanes (four coordinates each) share a row, group cq taking pieces cq, cq + CQ, ...;
+ * the un-rotation then multiplies the ROWS sums by one fetch of the 64 KB of S^T.  All sums have a fixed order.
+ * Bound by the latency of its chain (plan, maxima, partial results, S^T product) up to some hundred rows, by the
+ * fetches of S^T beyond: 3.9 -> 4.1 us at 32 rows, 9.2 -> 6.8 at 1024, 21.8 -> 9.4 at 2048 rows of 64 ragged
+ * sequences, 17.7 -> 8.4 at 2048 rows of four query tokens (one row per workgroup, all pieces in four groups -> this). */
+template <int ROWS, bool HYBRID>
+__global__ __launch_bounds__(512) void pq_attn_combine_kernel(CombineArgs a, int n_rows)
 {
-    __shared__ float so[PQ_D];
-    __shared__ float spart[4][PQ_D];
-    __shared__ float sl[4][PQ_D];
-    __shared__ float sw[4][PQ_D];
-    const int tid = threadIdx.x, cq = tid >> 7, j = tid & 127;
-    const int row = blockIdx.x;
+    constexpr int CQ = 16 / ROWS;
+    __shared__ __attribute__((aligned(16))) float sm[ROWS][CQ][PQ_D];                    /* prefix sums of a group */
+    __shared__ __attribute__((aligned(16))) float swin[HYBRID ? ROWS : 1][HYBRID ? CQ : 1][PQ_D]; /* the same of the window */
+    __shared__ float sl[ROWS][CQ];
+    __shared__ float so[ROWS][PQ_D], sow[HYBRID ? ROWS : 1][PQ_D];
+    __shared__ float spart[ROWS][4][PQ_D];
+    const int tid = threadIdx.x;
     MatrixSlice ms; /* requested first: its latency overlaps the reads of the partial results */
     if (!a.had.on) matrix_slice_load(ms, a.St, tid);
+    const int r = tid / (32 * CQ), cq = (tid >> 5) % CQ, col = 4 * (tid & 31);
+    const int row = min((int)blockIdx.x * ROWS + r, n_rows - 1); /* threads beyond the last row repeat it and store nothing */
     const int b = row / (a.M * a.Hq), mq = (row / a.Hq) % a.M, head = row % a.Hq;
     /* the pieces of this row's stream (sequence b, kv head hk): the wavefronts whose tile ranges
        meet the stream's, in order; their ids are consecutive.  A piece beyond what query token
@@ -1041,7 +1067,12 @@ __global__ __launch_bounds__(512) void pq_attn_combine_kernel(CombineArgs a)
     const int64_t slot0 = ((int64_t)w_first + s_index) * pairs + pair;
     const int64_t ml_stride = 2 * (int64_t)pairs, o_stride = (int64_t)pairs * PQ_D;
     const float *ml = a.ws_ml + slot0 * 2;
-    const float *op = a.ws_o + slot0 * PQ_D + j;
+    const float *op = a.ws_o + slot0 * PQ_D + col;
+    /* a group's first piece is requested before the maximum is known: one trip to memory less in the chain
+       (requesting four ahead measured slower: 37.4 against 36.8 us per step on 32 short sequences) */
+    const int c0 = max(min(cq, used - 1), 0); /* an empty stream reads the slot it would start at */
+    const float2 ml0 = *reinterpret_cast<const float2 *>(ml + c0 * ml_stride);
+    const float4 v0 = *reinterpret_cast<const float4 *>(op + c0 * o_stride);
     int used_w = 0;
     const float *wml = nullptr, *wop = nullptr;
     if (HYBRID) {
@@ -1049,71 +1080,98 @@ __global__ __launch_bounds__(512) void pq_attn_combine_kernel(CombineArgs a)
         w = w < 0 ? 0 : (w > a.win_cap ? a.win_cap : w);
         used_w = (w + 63) >> 6;
         wml = a.win_ml + (int64_t)row * a.n_wchunks * 2;
-        wop = a.win_o + (int64_t)row * a.n_wchunks * PQ_D + j;
+        wop = a.win_o + (int64_t)row * a.n_wchunks * PQ_D + col;
     }
-    /* overall maximum first (every wavefront on its own: lane i reads the maximum of piece i, 64 + i, ...,
-       so the reads are in flight together), then the weighted sums; thread group cq takes chunks cq, cq+4, ...
-       and the four group sums are added in a fixed order: the result does not depend on scheduling */
+    /* overall maximum first: the 32 lanes of a group read the maxima of pieces i, 32 + i, ... together */
     float m = -INFINITY;
     {
-        const int lane = tid & 63;
-        for (int c = lane; c < used; c += 64) m = fmaxf(m, ml[c * ml_stride]);
+        const int lane = tid & 31;
+        for (int c = lane; c < used; c += 32) m = fmaxf(m, ml[c * ml_stride]);
         if (HYBRID)
-            for (int c = lane; c < used_w; c += 64) m = fmaxf(m, wml[2 * c]);
-        m = wave_max(m);
+            for (int c = lane; c < used_w; c += 32) m = fmaxf(m, wml[2 * c]);
+#pragma unroll
+        for (int d = 16; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
     }
-    float l = 0.f, o = 0.f, ow = 0.f;
+    float l = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f), ow = o;
+    auto add = [&](const float2 &p, const float4 &v) {
+        const float w = exp2f(p.x - m);
+        l = fmaf(p.y, w, l);
+        o.x = fmaf(v.x, w, o.x); o.y = fmaf(v.y, w, o.y); o.z = fmaf(v.z, w, o.z); o.w = fmaf(v.w, w, o.w);
+    };
     if (m != -INFINITY) {
+        if (cq < used) add(ml0, v0);
 #pragma unroll 4
-        for (int c = cq; c < used; c += 4) {
-            const float w = exp2f(ml[c * ml_stride] - m);
-            l = fmaf(ml[c * ml_stride + 1], w, l);
-            o = fmaf(op[c * o_stride], w, o);
-        }
+        for (int c = cq + CQ; c < used; c += CQ)
+            add(*reinterpret_cast<const float2 *>(ml + c * ml_stride), *reinterpret_cast<const float4 *>(op + c * o_stride));
     }
     if (HYBRID) {
-        for (int c = cq; c < used_w; c += 4) {
+        for (int c = cq; c < used_w; c += CQ) {
             const float w = exp2f(wml[2 * c] - m);
+            const float4 v = *reinterpret_cast<const float4 *>(wop + (int64_t)c * PQ_D);
             l = fmaf(wml[2 * c + 1], w, l);
-            ow = fmaf(wop[(int64_t)c * PQ_D], w, ow);
+            ow.x = fmaf(v.x, w, ow.x); ow.y = fmaf(v.y, w, ow.y); ow.z = fmaf(v.z, w, ow.z); ow.w = fmaf(v.w, w, ow.w);
         }
-        sw[cq][j] = ow;
+        *reinterpret_cast<float4 *>(&swin[r][cq][col]) = ow;
     }
-    spart[cq][j] = o;
-    sl[cq][j] = l;
+    *reinterpret_cast<float4 *>(&sm[r][cq][col]) = o;
+    if ((tid & 31) == 0) sl[r][cq] = l;
     __syncthreads();
-    float lt = 0.f, owt = 0.f;
-    if (tid < PQ_D) {
-        const float ot = ((spart[0][j] + spart[1][j]) + spart[2][j]) + spart[3][j];
-        lt = ((sl[0][j] + sl[1][j]) + sl[2][j]) + sl[3][j];
+    for (int t = tid; t < ROWS * PQ_D; t += 512) {
+        const int rr = t >> 7, j = t & 127;
+        float ot = sm[rr][0][j], lt = sl[rr][0], owt = HYBRID ? swin[rr][0][j] : 0.f;
+#pragma unroll
+        for (int k = 1; k < CQ; ++k) {
+            ot += sm[rr][k][j];
+            lt += sl[rr][k];
+            if (HYBRID) owt += swin[rr][k][j];
+        }
         if (HYBRID) {
-            owt = ((sw[0][j] + sw[1][j]) + sw[2][j]) + sw[3][j];
-            so[j] = ot;
+            so[rr][j] = ot;
+            sow[rr][j] = owt;
         } else {
-            so[j] = lt > 0.f ? ot / lt : 0.f; /* lt == 0: no visible token */
+            so[rr][j] = lt > 0.f ? ot / lt : 0.f; /* lt == 0: no visible token */
         }
     }
     __syncthreads();
-    float acc; /* out_j = sum_k o'_k S[j][k] */
-    if (a.had.on) { /* = D_j / sqrt(128) times the Walsh-Hadamard transform of o' */
-        if (tid < 64) {
-            float lo = so[tid], hi = so[tid + 64];
-            pq_fwht128(lo, hi, tid);
-            spart[0][tid] = lo * PQ_INV_SQRT_D * pq_hadamard_sign(a.had, tid);
-            spart[0][tid + 64] = hi * PQ_INV_SQRT_D * pq_hadamard_sign(a.had, tid + 64);
+    /* out_j = sum_k o'_k S[j][k] */
+    if (a.had.on) { /* = D_j / sqrt(128) times the Walsh-Hadamard transform of o', one wavefront per row */
+        const int wv = tid >> 6, lane = tid & 63;
+        if (wv < ROWS) {
+            float lo = so[wv][lane], hi = so[wv][lane + 64];
+            pq_fwht128(lo, hi, lane);
+            spart[wv][0][lane] = lo * PQ_INV_SQRT_D * pq_hadamard_sign(a.had, lane);
+            spart[wv][0][lane + 64] = hi * PQ_INV_SQRT_D * pq_hadamard_sign(a.had, lane + 64);
         }
-        __syncthreads();
-        acc = spart[0][j];
     } else {
-        acc = vector_times_slice(so, ms, spart, tid);
+        const int kq = tid >> 7, j = tid & 127;
+        float acc[ROWS];
+#pragma unroll
+        for (int rr = 0; rr < ROWS; ++rr) acc[rr] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 32; ++k)
+#pragma unroll
+            for (int rr = 0; rr < ROWS; ++rr) acc[rr] = fmaf(so[rr][32 * kq + k], ms.m[k], acc[rr]);
+#pragma unroll
+        for (int rr = 0; rr < ROWS; ++rr) spart[rr][kq][j] = acc[rr];
     }
-    if (tid < PQ_D) {
-        if (HYBRID) acc = lt > 0.f ? (acc + owt) / lt : 0.f;
+    __syncthreads();
+    for (int t = tid; t < ROWS * PQ_D; t += 512) {
+        const int rr = t >> 7, j = t & 127, orow = (int)blockIdx.x * ROWS + rr;
+        if (orow >= n_rows) break;
+        float acc = spart[rr][0][j];
+        if (!a.had.on) acc = ((acc + spart[rr][1][j]) + spart[rr][2][j]) + spart[rr][3][j];
+        if (HYBRID) {
+            float lt = sl[rr][0];
+#pragma unroll
+            for (int k = 1; k < CQ; ++k) lt += sl[rr][k];
+            acc = lt > 0.f ? (acc + sow[rr][j]) / lt : 0.f;
+        }
         if (a.out_f32) {
-            static_cast<float *>(a.out)[(int64_t)row * PQ_D + j] = acc;
+            static_cast<float *>(a.out)[(int64_t)orow * PQ_D + j] = acc;
         } else {
             uint32_t u = __float_as_uint(acc);
-            static_cast<uint16_t *>(a.out)[(int64_t)row * PQ_D + j] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+            static_cast<uint16_t *>(a.out)[(int64_t)orow * PQ_D + j] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
         }
     }
 }
@@ -1272,8 +1330,10 @@ __global__ __launch_bounds__(512) void pq_rotate_window_kernel(RotateArgs r, Pla
     }
 }
 
+constexpr int kFineShareTiles = 1, kCoarseShareTiles = 4;
+
 struct Plan {
-    int slots;       /* wavefronts of the partial kernel's launch */
+    int slots;       /* wavefronts of the partial kernel that may take a share */
     unsigned blocks; /* its workgroups */
     size_t off_plan, off_ml, off_o, total;
     size_t pieces, o_bytes; /* piece ids run below `pieces`; bytes of their o' */
@@ -1283,7 +1343,7 @@ struct Plan {
 };
 
 /* Workspace: rotated queries | work plan | (m, l) of every piece | o' of every piece | window partials. */
-Plan make_plan(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap = 0, int M = 1)
+Plan make_plan_slots(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap, int M, int64_t min_share)
 {
     Plan p;
     int64_t max_tiles = (max_ctx + 63) / 64;
@@ -1291,18 +1351,18 @@ Plan make_plan(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap = 0, int
     const int G = Hq / Hkv > 0 ? Hq / Hkv : 1;
     const int pairs = M * G;
     /* One wavefront per resident slot: 256 CUs x 4 SIMDs x the wavefronts per SIMD the kernel variant's
-       register budget allows.  Every wavefront gets an equal share of the tiles (see DevicePlan above), so one
+       register budget allows.  Every wavefront gets an equal share of the tiles (see the work plan above), so one
        round of resident wavefronts does the whole job and all of them finish together; more, smaller
        work items measured slower on the 32k-context batch (143 us against 149-156 us for 3/2 or 2 times
        as many) and write more partial results.  Small problems: no more wavefronts than shares of
-       kMinShareTiles tiles. */
+       min_share tiles. */
     const int per_simd = pairs <= 4 ? 4 : (pairs <= 8 ? 3 : 2);
-    int64_t slots = 256 * 4 * per_simd;
-    const int64_t most = ((int64_t)B * Hkv * max_tiles + kMinShareTiles - 1) / kMinShareTiles;
-    if (slots > most) slots = most;
     const int block_waves = 4 * per_simd; /* = waves_per_block of the variant: one workgroup fills a CU */
-    p.blocks = (unsigned)((slots + block_waves - 1) / block_waves);
-    p.slots = (int)(p.blocks * block_waves);
+    int64_t slots = 256 * block_waves;
+    const int64_t most = ((int64_t)B * Hkv * max_tiles + min_share - 1) / min_share;
+    if (slots > most) slots = (most + block_waves - 1) / block_waves * block_waves;
+    p.slots = (int)slots;
+    p.blocks = (unsigned)(slots < 256 ? slots : 256); /* every CU takes part as soon as there is a share for each */
     const size_t pieces = (size_t)p.slots + (size_t)B * Hkv; /* ids run below slots + streams */
     p.pieces = pieces;
     p.o_bytes = pieces * pairs * PQ_D * sizeof(float);
@@ -1316,6 +1376,19 @@ Plan make_plan(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap = 0, int
     p.off_wo = (p.off_wml + rows * p.n_wchunks * 2 * sizeof(float) + 255) & ~(size_t)255;
     if (p.n_wchunks > 0) p.total = p.off_wo + rows * p.n_wchunks * PQ_D * sizeof(float);
     return p;
+}
+
+/* Shares of one tile -- a wavefront alone on its SIMD takes about 2 us per tile, and what a short batch waits for is the
+   longest share (128 tiles: partial kernel 25.8 us with shares of four on two CUs, 8.0 with shares of one on 128) -- if the
+   partial results then fit what a plan with shares of four tiles takes, or the static
+   scratch array (of which pq_attn_decode_polar_static must not need more than it did with the coarser plan, and must
+   split the work as pq_attn_decode_polar does). */
+Plan make_plan(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap = 0, int M = 1)
+{
+    const Plan fine = make_plan_slots(B, Hq, Hkv, max_ctx, win_cap, M, kFineShareTiles);
+    if (fine.total <= (size_t)PQ_STATIC_SCRATCH_BYTES) return fine;
+    const Plan coarse = make_plan_slots(B, Hq, Hkv, max_ctx, win_cap, M, kCoarseShareTiles);
+    return fine.slots == coarse.slots ? fine : coarse;
 }
 
 } // namespace
@@ -1371,6 +1444,24 @@ void launch_partial(int NG, bool deep, dim3 grid, dim3 blk, hipStream_t s, const
     else launch_partial_depth<false>(NG, grid, blk, s, aa);
 }
 
+template <int ROWS>
+void launch_combine_rows(int rows, bool hybrid, hipStream_t s, const CombineArgs &ca)
+{
+    const dim3 grid((unsigned)((rows + ROWS - 1) / ROWS)), blk(512);
+    if (hybrid) hipLaunchKernelGGL((pq_attn_combine_kernel<ROWS, true>), grid, blk, 0, s, ca, rows);
+    else hipLaunchKernelGGL((pq_attn_combine_kernel<ROWS, false>), grid, blk, 0, s, ca, rows);
+}
+
+void launch_combine(int rows, bool hybrid, hipStream_t s, const CombineArgs &ca)
+{
+    /* One workgroup per CU has the shortest chain (32 rows: 16.3 us per decode step with one row per workgroup, 16.7 with
+       two, 17.5 with four); with more rows than CUs the fetches of S^T count (512 rows: 116.6 us with two, 117.2 with four;
+       1024: 34.6, 34.7 and 37.1 with one; 2048: 489 with four, 493 with two, 496 with one). */
+    if (rows <= 256) launch_combine_rows<1>(rows, hybrid, s, ca);
+    else if (rows <= 1024) launch_combine_rows<2>(rows, hybrid, s, ca);
+    else launch_combine_rows<4>(rows, hybrid, s, ca);
+}
+
 pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const StepWindow *win, int M, const void *q,
                              void *out, pq_dtype out_dtype,
                              uint8_t *k_codes, uint16_t *k_radii, uint8_t *v_codes, uint16_t *v_radii,
@@ -1406,7 +1497,9 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
         if (win->win_cap <= 0 || win->win_cap > 0x7FFFFFFF) return PQ_EINVAL;
         if (!pq_aligned16(win->win_k) || !pq_aligned16(win->win_v)) return PQ_EALIGN;
     }
-    const Plan p = make_plan(B, Hq, Hkv, max_ctx, win ? win->win_cap : 0, M);
+    Plan p = make_plan(B, Hq, Hkv, max_ctx, win ? win->win_cap : 0, M);
+    if (workspace_bytes < p.total) /* a smaller workspace does with larger shares */
+        p = make_plan_slots(B, Hq, Hkv, max_ctx, win ? win->win_cap : 0, M, kCoarseShareTiles);
     if ((int64_t)B * Hkv * p.n_wchunks > 0x7FFFFFFF) return PQ_EINVAL;
     /* the partial kernel addresses the rotated queries and its partial results with 32-bit byte offsets */
     if ((uint64_t)B * M * Hq * (PQ_D * 2) > 0xFFFFFFFFull || p.o_bytes > 0xFFFFFFFFull) return PQ_EUNSUPPORTED;
@@ -1428,10 +1521,8 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
     if (app) {
         AppendArgs ak{app->xk, k_codes, k_radii, pool_tokens / 64, pool_tokens, app->dst_token, Hkv, ds->S_f32, ds->consts, ctx->hadamard};
         AppendArgs av{app->xv, v_codes, v_radii, pool_tokens / 64, pool_tokens, app->dst_token, Hkv, ds->S_f32, ds->consts, ctx->hadamard};
-        const int n = B * Hkv;
-        const dim3 grid((unsigned)(2 * n + row_blocks + 1)), blk(512);
-        if (app->xt == PQ_BF16) hipLaunchKernelGGL((pq_step_prologue_kernel<PQ_BF16>), grid, blk, 0, s, ra, ak, av, n, pa, rows, row_blocks);
-        else hipLaunchKernelGGL((pq_step_prologue_kernel<PQ_F32>), grid, blk, 0, s, ra, ak, av, n, pa, rows, row_blocks);
+        if (app->xt == PQ_BF16) launch_step_prologue<PQ_BF16>(ra, ak, av, B * Hkv, pa, rows, row_blocks, s);
+        else launch_step_prologue<PQ_F32>(ra, ak, av, B * Hkv, pa, rows, row_blocks, s);
     } else if (win) {
         WindowArgs wa{static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(win->win_k),
                       static_cast<const uint16_t *>(win->win_v), win->win_len, B, Hq, Hkv, (int)win->win_cap,
@@ -1468,8 +1559,7 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
                    ds->St_f32, out, out_dtype == PQ_F32 ? 1 : 0, ds->consts,
                    reinterpret_cast<const float *>(ws + p.off_wml), reinterpret_cast<const float *>(ws + p.off_wo),
                    win ? win->win_len : nullptr, p.n_wchunks, win ? (int)win->win_cap : 0, ctx->hadamard};
-    if (win) hipLaunchKernelGGL(pq_attn_combine_kernel<true>, dim3(rows), dim3(512), 0, s, ca);
-    else hipLaunchKernelGGL(pq_attn_combine_kernel<false>, dim3(rows), dim3(512), 0, s, ca);
+    launch_combine(rows, win != nullptr, s, ca);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
 }

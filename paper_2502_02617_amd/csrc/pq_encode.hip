@@ -480,9 +480,9 @@ __global__ __launch_bounds__(EncodeShape<XT>::waves * 64) void pq_encode_pair_ke
 }
 
 template <int XT, int KIND>
-__global__ __launch_bounds__(512) void pq_append_kernel(AppendArgs a)
+__global__ __launch_bounds__(512) void pq_append_kernel(AppendArgs a, int n)
 {
-    append_vector<XT>(a, KIND, (int)blockIdx.x);
+    append_vectors<XT, 1>(a, KIND, (int)blockIdx.x, n);
 }
 
 /* keys and values of the same tokens in one launch: workgroups [0, n) take the key vectors,
@@ -490,8 +490,8 @@ __global__ __launch_bounds__(512) void pq_append_kernel(AppendArgs a)
 template <int XT>
 __global__ __launch_bounds__(512) void pq_append_pair_kernel(AppendArgs k, AppendArgs v, int n)
 {
-    if ((int)blockIdx.x < n) append_vector<XT>(k, PQ_KEY, (int)blockIdx.x);
-    else append_vector<XT>(v, PQ_VALUE, (int)blockIdx.x - n);
+    if ((int)blockIdx.x < n) append_vectors<XT, 1>(k, PQ_KEY, (int)blockIdx.x, n);
+    else append_vectors<XT, 1>(v, PQ_VALUE, (int)blockIdx.x - n, n);
 }
 
 template <int XT, int KIND, int NTERMS, bool GENERAL, bool DEEP>
@@ -681,11 +681,11 @@ extern "C" pq_status pq_append_kv(const pq_ctx *ctx, const void *x, pq_dtype xt,
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     dim3 grid((unsigned)(n_seq * n_heads)), block(512);
     if (xt == PQ_BF16) {
-        if (kind == PQ_KEY) hipLaunchKernelGGL((pq_append_kernel<PQ_BF16, PQ_KEY>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((pq_append_kernel<PQ_BF16, PQ_VALUE>), grid, block, 0, s, a);
+        if (kind == PQ_KEY) hipLaunchKernelGGL((pq_append_kernel<PQ_BF16, PQ_KEY>), grid, block, 0, s, a, n_seq * n_heads);
+        else hipLaunchKernelGGL((pq_append_kernel<PQ_BF16, PQ_VALUE>), grid, block, 0, s, a, n_seq * n_heads);
     } else {
-        if (kind == PQ_KEY) hipLaunchKernelGGL((pq_append_kernel<PQ_F32, PQ_KEY>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((pq_append_kernel<PQ_F32, PQ_VALUE>), grid, block, 0, s, a);
+        if (kind == PQ_KEY) hipLaunchKernelGGL((pq_append_kernel<PQ_F32, PQ_KEY>), grid, block, 0, s, a, n_seq * n_heads);
+        else hipLaunchKernelGGL((pq_append_kernel<PQ_F32, PQ_VALUE>), grid, block, 0, s, a, n_seq * n_heads);
     }
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;

@@ -213,9 +213,9 @@ __device__ __forceinline__ BlockCodes polar_quant_block(const Y16 &y, const Thre
 }
 
 /* ---- decode-time append: one vector per (sequence, head) ----
- * Too little work for the matrix cores: one workgroup per vector computes
- * y_j = sum_i x_i S[i][j] in fp32 (S read from L2, four partial sums per
- * coordinate added in a fixed order), the first wavefront then runs the polar recursion
+ * Too little work for the matrix cores: a workgroup computes
+ * y_j = sum_i x_i S[i][j] of its vectors in fp32 (S read from L2, four partial sums per
+ * coordinate added in a fixed order), a wavefront per vector then runs the polar recursion
  * (one lane per level-1 pair) and patches the fields into the tile in place.  Fields share dwords with other
  * slots of the tile, so they are updated with dword atomics. */
 struct AppendArgs {
@@ -274,52 +274,71 @@ __device__ __forceinline__ void pql_put_block(uint32_t *tile_dwords, int kind, i
     }
 }
 
-/* one (sequence, head) vector of kind `kind`, by one workgroup */
-template <int XT>
-__device__ __forceinline__ void append_vector(const AppendArgs &a, int kind, int vec)
+/* NV (sequence, head) vectors of kind `kind`, vec0 .. vec0 + NV - 1 as far as they are below n_vec, by one workgroup of
+ * 512 threads: the 64 KB of S are fetched once for the NV products, then wavefront r runs the recursion of vector r.
+ * Per vector the operations and their order do not depend on NV. */
+template <int XT, int NV>
+__device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, int vec0, int n_vec)
 {
-    __shared__ float sx[PQ_D];
-    __shared__ float sy[PQ_D];
-    __shared__ float spart[4][PQ_D];
-    const int seq = vec / a.n_heads, head = vec % a.n_heads, tid = threadIdx.x, j = tid & 127;
+    __shared__ float sx[NV][PQ_D];
+    __shared__ float sy[NV][PQ_D];
+    __shared__ float spart[NV][4][PQ_D];
+    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
     MatrixSlice ms;
     if (!a.had.on) matrix_slice_load(ms, a.S, tid);
+    /* wavefront r < NV looks after vector vec0 + r; a vector beyond the range repeats the last one and writes nothing */
+    const int vec = min(vec0 + min(wv, NV - 1), n_vec - 1);
+    const int seq = vec / a.n_heads, head = vec % a.n_heads;
     const int64_t dst = a.dst_token[seq];
-    if (dst < 0 || dst >= a.pool_tokens) return; /* slot outside the pool: nothing is written */
-    const int64_t row = ((int64_t)seq * a.n_heads + head) * PQ_D;
-    if (tid < PQ_D) {
-        if (XT == PQ_BF16) sx[j] = __uint_as_float((uint32_t)static_cast<const uint16_t *>(a.x)[row + j] << 16);
-        else sx[j] = static_cast<const float *>(a.x)[row + j];
+    for (int t = tid; t < NV * PQ_D; t += 512) {
+        const int64_t at = (int64_t)min(vec0 + (t >> 7), n_vec - 1) * PQ_D + (t & 127);
+        if (XT == PQ_BF16) sx[t >> 7][t & 127] = __uint_as_float((uint32_t)static_cast<const uint16_t *>(a.x)[at] << 16);
+        else sx[t >> 7][t & 127] = static_cast<const float *>(a.x)[at];
     }
     __syncthreads();
     /* y_j = sum_i x_i S[i][j].  Hadamard S: the transform of D x, left unscaled -- the angles do not see the
        common factor 1/sqrt(128), which goes into the radius (as in the encode kernel's one-term product) */
     float radius_scale = 1.0f;
     if (a.had.on) {
-        if (tid < 64) {
-            float lo = sx[tid] * pq_hadamard_sign(a.had, tid), hi = sx[tid + 64] * pq_hadamard_sign(a.had, tid + 64);
-            pq_fwht128(lo, hi, tid);
-            sy[tid] = lo;
-            sy[tid + 64] = hi;
+        if (wv < NV) {
+            float lo = sx[wv][lane] * pq_hadamard_sign(a.had, lane), hi = sx[wv][lane + 64] * pq_hadamard_sign(a.had, lane + 64);
+            pq_fwht128(lo, hi, lane);
+            sy[wv][lane] = lo;
+            sy[wv][lane + 64] = hi;
         }
         radius_scale = PQ_INV_SQRT_D;
     } else {
-        const float acc = vector_times_slice(sx, ms, spart, tid);
-        if (tid < PQ_D) sy[j] = acc;
+        const int kq = tid >> 7, j = tid & 127;
+        float acc[NV];
+#pragma unroll
+        for (int r = 0; r < NV; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 32; ++k)
+#pragma unroll
+            for (int r = 0; r < NV; ++r) acc[r] = fmaf(sx[r][32 * kq + k], ms.m[k], acc[r]);
+#pragma unroll
+        for (int r = 0; r < NV; ++r) spart[r][kq][j] = acc[r];
+        __syncthreads();
+        for (int t = tid; t < NV * PQ_D; t += 512) {
+            const int r = t >> 7, c = t & 127;
+            sy[r][c] = ((spart[r][0][c] + spart[r][1][c]) + spart[r][2][c]) + spart[r][3][c];
+        }
     }
     __syncthreads();
-    __shared__ float sq4[8];
+    __shared__ float sq4[NV][8];
     const bool deep = a.consts->depth == 7;
+    /* a vector beyond the range or a slot outside the pool: nothing is written */
+    const bool write = wv < NV && vec0 + wv < n_vec && dst >= 0 && dst < a.pool_tokens;
     const int64_t tile = dst >> 6;
     const int tau = (int)(dst & 63);
-    if (tid < 64) {
-        /* The first wavefront runs the recursion with one lane per level-1 pair: lane p holds pair p & 7
+    if (write) {
+        /* The wavefront runs the recursion with one lane per level-1 pair: lane p holds pair p & 7
            of block p >> 3; the nodes of the upper levels sit in the lanes of their first leaf and fetch
            the sibling's squared radius with a shuffle (the other lanes compute along and are ignored).
            Operations and operand order per node are those of polar_quant_block. */
-        const int p = tid, i = p & 7, b = p >> 3;
+        const int p = lane, i = p & 7, b = p >> 3;
         const Thresholds th = load_thresholds(*a.consts, radius_scale);
-        const float ya = sy[2 * p], yb = sy[2 * p + 1];
+        const float ya = sy[wv][2 * p], yb = sy[wv][2 * p + 1];
         uint32_t code1;
         if (a.consts->general) { /* the level-1 table is read from the constants in global memory */
             code1 = level1_code_general(ya, yb, th.lut1);
@@ -357,14 +376,15 @@ __device__ __forceinline__ void append_vector(const AppendArgs &a, int kind, int
         if (i == 0) {
             uint8_t *gcodes = a.codes + ((int64_t)head * a.pool_tiles + tile) * PQL_CODE_BYTES;
             pql_put_block<true>(reinterpret_cast<uint32_t *>(gcodes), kind, tau, b, bc);
-            if (deep) sq4[b] = q4;
+            if (deep) sq4[wv][b] = q4;
             else a.radii[((int64_t)head * a.pool_tiles + tile) * PQL_RADII + pql_pos(kind, tau, b).radius_half] = bc.radius;
         }
     }
-    if (deep) { /* levels 5..7 over the eight block radii: one thread, one whole word of the radius plane */
+    if (deep) { /* levels 5..7 over the eight block radii: one lane per vector, one whole word of the radius plane */
         __syncthreads();
-        if (tid == 0) {
-            const float lo4[4] = {sq4[0], sq4[1], sq4[2], sq4[3]}, hi4[4] = {sq4[4], sq4[5], sq4[6], sq4[7]};
+        if (write && lane == 0) {
+            const float *q = sq4[wv];
+            const float lo4[4] = {q[0], q[1], q[2], q[3]}, hi4[4] = {q[4], q[5], q[6], q[7]};
             const UpperTables ut = load_upper_tables(*a.consts);
             const UpperHalf lo = polar_upper_half(lo4, 0, ut), hi = polar_upper_half(hi4, 1, ut);
             uint32_t *top = reinterpret_cast<uint32_t *>(a.radii) +
@@ -373,6 +393,11 @@ __device__ __forceinline__ void append_vector(const AppendArgs &a, int kind, int
         }
     }
 }
+
+/* Vectors per workgroup of an append of n vectors in all: one while two workgroups per CU hold them (the chain of
+   loads and barriers is what such a launch takes: 4.9 us for 16 vectors, 6.3 for 256), four when the fetches of S weigh
+   more (1024 vectors: 12.8 us with one, 9.6 with four, query rotation and work plan included). */
+static inline int append_vectors_per_block(int64_t n) { return n <= 512 ? 1 : 4; }
 
 #endif /* __HIPCC__ */
 #endif /* PQ_POLAR_H */

@@ -256,3 +256,19 @@ def test_bench_refuses_more_than_one_gpu():
                          timeout=120)
     assert res.returncode != 0
     assert "one GPU" in res.stderr and res.stdout.strip() == ""
+
+
+def test_workspace_stays_inside_the_static_scratch_where_it_did():
+    """Finer shares must not push a problem beyond the static scratch array that fits it with shares of four tiles."""
+    def up(n):
+        return (n + 255) & ~255
+
+    for B in (1, 3, 16, 64, 300):
+        for Hkv, G in ((1, 1), (8, 4), (8, 8), (2, 16), (4, 7)):
+            for ctx_len in (1, 64, 1000, 5000, 33000):
+                per_simd = 4 if G <= 4 else 3 if G <= 8 else 2
+                tiles = B * Hkv * ((ctx_len + 63) // 64)
+                slots = min(1024 * per_simd, (-(-tiles // 4) + 4 * per_simd - 1) // (4 * per_simd) * (4 * per_simd))
+                pieces = slots + B * Hkv
+                coarse = up(up(up(B * Hkv * G * 256) + 4 * (2 + B + 1 + 2 * B * Hkv)) + pieces * G * 8) + pieces * G * 512
+                assert coarse <= Context.attn_workspace_bytes(B, Hkv * G, Hkv, ctx_len) <= max(coarse, Context.static_scratch_bytes())

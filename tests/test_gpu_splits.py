@@ -1,0 +1,91 @@
+"""GPU tests of how the attention calls divide their work: shares of the partial kernel, output rows and appended
+vectors per workgroup, each at the sizes where a rule changes sides and at its remainders."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_02617_amd import Context, PQ_KEY, PQ_VALUE, PolarQuantError, synth
+from tests import helpers
+from tests.test_gpu_parity import DEV, build_cache, env, gpu_attention, say  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+# rows per workgroup of the combine kernel: 1 up to 256 rows, 2 up to 1024, then 4; the last group is incomplete
+@pytest.mark.parametrize("B,Hq,Hkv,hi", [(64, 4, 1, 80), (37, 7, 1, 200), (79, 13, 1, 150), (147, 7, 1, 130)])
+def test_combine_row_groups(env, B, Hq, Hkv, hi):  # noqa: F811
+    ctx, S, cb = env
+    rng = np.random.default_rng(B)
+    lens = [int(n) for n in rng.integers(0, hi + 1, size=B)]
+    lens[B - 1] = 1000                      # the last row group merges sixteen pieces
+    say(f"combine row groups: {B * Hq} rows")
+    caches, starts, _, k_rec, v_rec = build_cache(ctx, S, cb, lens, Hkv, seed=31000 + B)
+    q = synth.queries(B, Hq, seed=31000 + B)
+    got = gpu_attention(ctx, q, caches, starts, lens)
+    ref = oracle.attention(q.double().numpy(), k_rec, v_rec, starts, np.array(lens, np.int32), S, cb, helpers.softmax_scale())
+    assert all(np.all(got[b] == 0.0) for b in range(B) if lens[b] == 0)
+    rows = [helpers.rel_l2(got[b], ref[b]) for b in range(B) if lens[b]]
+    say(f"  rel L2 {helpers.rel_l2(got, ref):.2e}, worst sequence {max(rows):.2e}")
+    assert helpers.rel_l2(got, ref) <= 2e-3 and max(rows) <= 4e-3
+
+
+@pytest.mark.parametrize("lens", [[64], [1, 64, 65], [2000, 3, 129]])
+def test_a_smaller_workspace_takes_larger_shares(env, lens):  # noqa: F811
+    """The workspace of shares of one tile is what the size function returns; one that only holds the pieces of
+    four-tile shares is accepted too, anything below that refused."""
+    ctx, S, cb = env
+    B, Hq, Hkv = len(lens), 8, 2
+    say(f"workspace sizes, lens={lens}")
+    caches, starts, _, k_rec, v_rec = build_cache(ctx, S, cb, lens, Hkv, seed=32000 + B)
+    q = synth.queries(B, Hq, seed=32000 + B)
+    ref = oracle.attention(q.double().numpy(), k_rec, v_rec, starts, np.array(lens, np.int32), S, cb, helpers.softmax_scale())
+
+    def up(n):
+        return (n + 255) & ~255
+
+    tiles = B * Hkv * ((max(lens) + 63) // 64)
+    pieces = (-(-tiles // 4) + 15) // 16 * 16 + B * Hkv
+    coarse = up(up(up(B * Hq * 256) + 4 * (2 + B + 1 + 2 * B * Hkv)) + pieces * 4 * 8) + pieces * 4 * 512
+    out = torch.empty((B, Hq, 128), dtype=torch.float32, device=DEV)
+    args = (torch.from_numpy(starts).to(DEV), torch.tensor(lens, dtype=torch.int32, device=DEV), max(lens), helpers.softmax_scale())
+    assert coarse <= Context.attn_workspace_bytes(B, Hq, Hkv, max(lens))
+    for nbytes in (Context.attn_workspace_bytes(B, Hq, Hkv, max(lens)), coarse):
+        out.fill_(float("nan"))
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+        ctx.attn_decode_polar(q.to(DEV), out, *caches, *args, ws)
+        torch.cuda.synchronize()
+        assert helpers.rel_l2(out.cpu().numpy(), ref) <= 2e-3
+    with pytest.raises(PolarQuantError, match="PQ_ENOMEM"):
+        ctx.attn_decode_polar(q.to(DEV), out, *caches, *args, ws[:coarse - 1])
+
+
+# the prologue of a decode step appends one vector per workgroup up to 512 vectors in all, then four
+@pytest.mark.parametrize("hadamard", [False, True])
+@pytest.mark.parametrize("B,Hkv,depth", [(32, 8, 4), (43, 6, 4), (87, 3, 4), (87, 3, 7)])
+def test_step_append_equals_bulk_append(B, Hkv, depth, hadamard):
+    say(f"decode step appends {2 * B * Hkv} vectors, depth {depth}, hadamard {hadamard}")
+    ctx = Context(seed=5, hadamard=hadamard)
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    lens = [1 + (b % 64) for b in range(B)]
+    g = torch.Generator().manual_seed(B)
+    xk, xv = (torch.randn((B, Hkv, 128), generator=g).bfloat16().to(DEV) for _ in range(2))
+    start = torch.arange(B, dtype=torch.int64, device=DEV) * 64
+    ln = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    slot = start + ln.long() - 1
+    slot[3] = -1                            # a slot outside the pool: nothing is written
+    caches = []
+    for _ in range(2):
+        pair = [ctx.alloc_cache_for(Hkv, 64 * B, DEV) for _ in (PQ_KEY, PQ_VALUE)]
+        for codes, radii in pair:
+            codes.fill_(0x5A)
+            radii.fill_(0x1234)
+        caches.append([t for p in pair for t in p])
+    q = torch.randn((B, Hkv, 128), generator=g).bfloat16().to(DEV)
+    out = torch.empty((B, Hkv, 128), dtype=torch.float32, device=DEV)
+    ws = torch.empty(Context.attn_workspace_bytes(B, Hkv, Hkv, 64), dtype=torch.uint8, device=DEV)
+    ctx.decode_step_polar(xk, xv, slot, q, out, *caches[0], start, ln, 64, helpers.softmax_scale(), ws)
+    ctx.append_kv_pair(xk, xv, *caches[1], slot)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*caches))
