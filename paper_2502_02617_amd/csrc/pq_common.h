@@ -59,6 +59,9 @@ struct PqDeviceConsts {
     /* The attention kernels' LDS table block, entry for entry (layout: PQ_TAB_* above), copied by a
        workgroup in 16-byte pieces. */
     alignas(16) uint32_t attn_tab[PQ_TAB_DWORDS];
+    /* DeQuant: the two pairs of a quarter in fp32, products formed in double and rounded once:
+       [0][Q & 63] = cos t2 (cos t1, sin t1), [1][Q >> 4] = sin t2 (cos t1', sin t1') */
+    alignas(16) float dq_quarter[2][64][2];
 };
 
 /* Radius plane of a tile.  Depth 4: 512 binary16 block radii (pq_layout.h).  Depth 7: 64 words,

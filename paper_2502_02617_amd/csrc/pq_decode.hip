@@ -8,99 +8,335 @@
  * radius of node j splits into (r cos theta, r sin theta) with theta the
  * centroid selected by the node's code; after level 1 the 16 coordinates of
  * the block are known.  The optional trailing product with S^T is a 128x128
- * mat-vec per vector, done in fp32 with the rebuilt vector staged in LDS.
- * These kernels serve testing, export and fallback use; they read the tile
- * through the generic field accessors and are not tuned.
+ * mat-vec per vector, on the matrix cores.  The export kernel reads the tile
+ * through the generic field accessors and is not tuned.
  */
+#include <type_traits>
+
 #include "pq_common.h"
 
 namespace {
 
-constexpr int kTok = 16; /* tokens per workgroup */
+typedef _Float16 dq_h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 dq_h8 __attribute__((ext_vector_type(8)));
+typedef float dq_f2 __attribute__((ext_vector_type(2)));
+typedef float dq_f16 __attribute__((ext_vector_type(16)));
+
+constexpr int kDecodeWaves = 16, kDecodeThreads = kDecodeWaves * 64;
+constexpr int kTileDwords = (PQL_CODE_BYTES + 2 * PQL_RADII) / 4; /* 992 */
 
 struct DecodeArgs {
     const uint8_t *codes;
     const uint16_t *radii;
     int64_t pool_tiles;
     int64_t token0, n_tokens;
-    int n_heads;
+    int64_t first_tile, n_tiles, n_items; /* tiles that the range touches; halves of them over all heads */
     void *out;
     int64_t ld_token, ld_head;
-    int rotated;
     const PqDeviceConsts *consts;
-    const float *St; /* St[j*128 + i] = S[i][j] */
-    int deep;        /* recursion depth 7: the radius plane holds one word per token */
+    const float *S;      /* S[i*128 + j] */
+    int paired;          /* both strides even: two neighbouring coordinates of the output can be written at once */
+    int deep;            /* recursion depth 7: the radius plane holds one word per token */
 };
 
-template <int KIND, int OT>
-__global__ __launch_bounds__(128) void pq_decode_kernel(DecodeArgs a)
+/* What a lane needs of its token: the indices of blocks 4 H .. 4 H + 3 and their radii (fp32). */
+struct TokenHalf {
+    uint32_t q[4][4], bi[4];
+    float r[4];
+    uint32_t top; /* largest stored radius of the token, binary16 bits */
+};
+
+__device__ __forceinline__ void dq_wave_sync()
 {
-    __shared__ float sy[kTok][PQ_D];
-    const int head = blockIdx.y;
-    const int64_t t_base = (int64_t)blockIdx.x * kTok;
-    const int tid = threadIdx.x;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+/* `width` bits at bit BIT of a string of dwords */
+template <int BIT, int WIDTH>
+__device__ __forceinline__ uint32_t dq_field(const uint32_t *w)
+{
+    constexpr int d = BIT >> 5, s = BIT & 31;
+    if constexpr (s + WIDTH <= 32) return (w[d] >> s) & ((1u << WIDTH) - 1u);
+    else return __builtin_amdgcn_alignbit(w[d + 1], w[d], s) & ((1u << WIDTH) - 1u);
+}
+
+template <int B>
+__device__ __forceinline__ void dq_key_block(TokenHalf &t, const uint32_t *w)
+{
+    t.q[B][0] = dq_field<PQL_BLOCK_BITS * B, 10>(w);
+    t.q[B][1] = dq_field<PQL_BLOCK_BITS * B + 10, 10>(w);
+    t.q[B][2] = dq_field<PQL_BLOCK_BITS * B + 20, 10>(w);
+    t.q[B][3] = dq_field<PQL_BLOCK_BITS * B + 30, 10>(w);
+    t.bi[B] = dq_field<PQL_BLOCK_BITS * B + 40, 6>(w);
+}
+
+/* Key tile: the token's 368-bit string and its eight radii straight from memory; blocks 4 H .. are its half
+   [184 H, 184 H + 184), brought to bit 0 so that every field sits at a fixed position. */
+__device__ __forceinline__ void dq_read_key(TokenHalf &t, const uint8_t *tc, const uint16_t *tr, int tau, int H, bool deep)
+{
+    const uint4 a = *reinterpret_cast<const uint4 *>(tc + PQL_OFF_P0 + 16 * tau);
+    const uint4 b = *reinterpret_cast<const uint4 *>(tc + PQL_OFF_P1 + 16 * tau);
+    const uint32_t *p2 = reinterpret_cast<const uint32_t *>(tc + PQL_OFF_P2 + 12 * tau);
+    const uint32_t w[12] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, p2[0], p2[1], p2[2],
+                            *reinterpret_cast<const uint16_t *>(tc + PQL_OFF_KP3 + 2 * tau)};
+    uint32_t s[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) s[k] = H ? __builtin_amdgcn_alignbit(w[6 + k > 11 ? 11 : 6 + k], w[5 + k], 24) : w[k];
+    dq_key_block<0>(t, s); dq_key_block<1>(t, s); dq_key_block<2>(t, s); dq_key_block<3>(t, s);
+    if (!deep) {
+        const uint4 r = *reinterpret_cast<const uint4 *>(tr + 8 * tau);
+        const uint32_t lo = H ? r.z : r.x, hi = H ? r.w : r.y;
+        t.r[0] = pq_half_bits_to_float(lo & 0xFFFFu); t.r[1] = pq_half_bits_to_float(lo >> 16);
+        t.r[2] = pq_half_bits_to_float(hi & 0xFFFFu); t.r[3] = pq_half_bits_to_float(hi >> 16);
+        const uint32_t h[4] = {r.x, r.y, r.z, r.w};
+        t.top = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t.top = max(t.top, max(h[k] & 0x7FFFu, (h[k] >> 16) & 0x7FFFu));
+    }
+}
+
+/* Value tile: staged in the wavefront's LDS image (codes, then radii); a token's slots are spread over the strings of
+   the 16 half-blocks at one bit position. */
+__device__ __forceinline__ void dq_read_value(TokenHalf &t, const uint32_t *img, int tau, int H, bool deep)
+{
+    const uint32_t g = ((uint32_t)tau >> 2) & 3u, s = 4u * ((uint32_t)tau >> 4) + ((uint32_t)tau & 3u);
+    auto base = [](uint32_t d) { return d < 4u ? d : d < 8u ? PQL_OFF_P1 / 4 + d - 4u : PQL_OFF_P2 / 4 + d - 8u; };
+    const uint32_t d0 = (PQL_SLOT_BITS * s) >> 5, d1 = min(d0 + 1u, 9u), sh = (PQL_SLOT_BITS * s) & 31u;
+    const uint32_t m0 = d0 < 8u ? 4u : 2u, m1 = d1 < 8u ? 4u : 2u, lam = 16u * g + 8u * (uint32_t)H;
+    const uint32_t *p0 = img + base(d0) + lam * m0, *p1 = img + base(d1) + lam * m1;
+    const uint32_t owner = 8u * g + 4u * (uint32_t)H;
+    const uint32_t *pb = img + PQL_OFF_VB / 4 + 3u * owner + ((6u * s) >> 5);
+    const uint16_t *pr = reinterpret_cast<const uint16_t *>(img) + PQL_CODE_BYTES / 2 + 16u * owner + s;
+    t.top = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t v = __builtin_amdgcn_alignbit(p1[(2 * b + h) * m1], p0[(2 * b + h) * m0], sh);
+            t.q[b][2 * h] = v & 1023u;
+            t.q[b][2 * h + 1] = (v >> 10) & 1023u;
+        }
+        /* the dword after a string's last one is the next string's, or the first radii: its bits are masked off */
+        t.bi[b] = __builtin_amdgcn_alignbit(pb[3 * b + 1], pb[3 * b], (6u * s) & 31u) & 63u;
+        if (!deep) {
+            const uint32_t r = pr[16 * b];
+            t.r[b] = pq_half_bits_to_float(r);
+            t.top = max(t.top, r & 0x7FFFu);
+        }
+    }
+    if (!deep) t.top = max(t.top, (uint32_t)__shfl_xor((int)t.top, 32));
+}
+
+__device__ __forceinline__ uint32_t dq_bf16(float f) /* round to nearest even, in the upper half */
+{
+    const uint32_t u = __float_as_uint(f);
+    return u + 0x7FFFu + ((u >> 16) & 1u);
+}
+
+/* output coordinates c and c + 1 of one token (`at`: element offset of the first) */
+template <int OT>
+__device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, float b, bool paired)
+{
+    if (OT == PQ_F32) {
+        float *p = static_cast<float *>(out) + at;
+        if (paired) *reinterpret_cast<float2 *>(p) = make_float2(a, b);
+        else { p[0] = a; p[1] = b; }
+    } else {
+        uint16_t *p = static_cast<uint16_t *>(out) + at;
+        const uint32_t ua = dq_bf16(a), ub = dq_bf16(b);
+        if (paired) *reinterpret_cast<uint32_t *>(p) = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+        else { p[0] = (uint16_t)(ua >> 16); p[1] = (uint16_t)(ub >> 16); }
+    }
+}
+
+/* DeQuant, one wavefront per half tile (32 tokens of one head plane; four wavefronts per SIMD); lane (H, j) rebuilds blocks
+ * 4 H .. 4 H + 3 of token j in fp32 from products of centroid cosines and sines (tables in LDS).
+ *
+ * The trailing S^T (not if ROTATED) runs on the matrix cores: out = y S^T with y and S each as two binary16 terms of 22
+ * significant bits (a power of two taken out of every token, so that its largest radius sits at 2^14, and out of S) and
+ * the three products above 2^-22.  UNIT: all entries of S are +-1/sqrt(128); +-1 is one exact term and two products.
+ * Against 64 bits the result is as exact as the fp32 sums in index order that this replaces (1.5e-7 of the vector's norm,
+ * 1.1e-7 for UNIT, against 2.2e-7).
+ * v_mfma_f32_32x32x16_f16 multiplies 32 tokens by 32 output coordinates.  Tokens are the rows of the product, so that a
+ * store writes whole lines: the columns of a pair of products are the even and the odd coordinates of 64, a lane
+ * holds two neighbouring ones and 32 lanes 128 or 256 consecutive bytes of a token.  (With tokens as columns a lane
+ * held 16 coordinates of one token and every store touched 64 lines: 52 us for the case below, 106 to fp32.)
+ *
+ * Bound by the vector and matrix instructions (about 600 and 96 per half tile); the bytes alone would take 18 us of a
+ * copy.  262144 vectors to bf16: 242 us with the generic bit reader and fp32 sums on 16 tokens per workgroup -> 32 us
+ * for keys, 37 for values; to fp32 243 -> 55.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
+ * spill 100 registers; value slots are read from an image in LDS because a token's 16 slots are spread over 16 strings. */
+template <int KIND, int OT, bool UNIT, bool ROTATED>
+__global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs a)
+{
+    constexpr int kChunks = 4 * 8 * 64; /* of eight halves: (64-coordinate group, parity), k-step, lane */
+    __shared__ uint4 sS[ROTATED ? 1 : (UNIT ? 1 : 2) * kChunks];
+    __shared__ __attribute__((aligned(16))) float tq[2][64][2], tb[64][4];
+    __shared__ float2 tup[24];
+    __shared__ __attribute__((aligned(16))) float sUn[kDecodeWaves][32];
+    __shared__ __attribute__((aligned(16))) uint32_t img[KIND == PQ_VALUE ? kDecodeWaves : 1][KIND == PQ_VALUE ? kTileDwords : 4];
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, H = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const PqDeviceConsts &K = *a.consts;
-    {
-        const int tl = tid >> 3, b = tid & 7; /* one thread per (token, block) */
-        const int64_t t = t_base + tl;
-        if (t < a.n_tokens) {
-            const int64_t slot = a.token0 + t;
-            const int64_t tile = slot >> 6;
-            const int tau = (int)(slot & 63);
-            const uint8_t *tc = a.codes + ((int64_t)head * a.pool_tiles + tile) * PQL_CODE_BYTES;
-            const uint16_t *tr = a.radii + ((int64_t)head * a.pool_tiles + tile) * (a.deep ? PQ_DEEP_RADII_HALVES : PQL_RADII);
-            PqBlockFields f = pql_read_block(KIND, tc, a.deep ? nullptr : tr, tau, b);
-            float r4;
-            if (a.deep)
-                r4 = pq_deep_block_radius(reinterpret_cast<const uint32_t *>(tr)[tau], K.up_bits[0], K.up_bits[1], K.up_bits[2],
-                                          reinterpret_cast<const float2 *>(&K.up_cs[0][0][0]), b);
-            else
-                r4 = (float)__builtin_bit_cast(_Float16, f.radius);
-            float r3[2] = {r4 * K.cs234[2][f.c4][0], r4 * K.cs234[2][f.c4][1]};
+    if (!ROTATED) {
+        /* chunk (grp, par, ks, lane): S[64 grp + 2 (lane & 31) + par][64 (lane >> 5) + 8 ks .. + 7], the k order of the
+           tokens' operand below */
+        float4 s[kChunks / kDecodeThreads][2]; /* all requested before the first is stored */
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t g6 = f.g6[h];
-                uint32_t c2a = g6 >> 4, c3 = (g6 >> 2) & 3, c2b = g6 & 3;
-                float r2a = r3[h] * K.cs234[1][c3][0], r2b = r3[h] * K.cs234[1][c3][1];
-                float r1[4] = {r2a * K.cs234[0][c2a][0], r2a * K.cs234[0][c2a][1],
-                               r2b * K.cs234[0][c2b][0], r2b * K.cs234[0][c2b][1]};
+        for (int i = 0; i < kChunks / kDecodeThreads; ++i) {
+            const int c = tid + i * kDecodeThreads, l = c & 63, ks = (c >> 6) & 7, gp = c >> 9;
+            const float4 *src = reinterpret_cast<const float4 *>(
+                a.S + (64 * (gp >> 1) + 2 * (l & 31) + (gp & 1)) * PQ_D + 64 * (l >> 5) + 8 * ks);
+            s[i][0] = src[0];
+            s[i][1] = src[1];
+        }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    uint32_t c1 = (f.l1 >> (4 * (4 * h + q))) & 15;
-                    sy[tl][16 * b + 8 * h + 2 * q] = r1[q] * K.cs1[c1][0];
-                    sy[tl][16 * b + 8 * h + 2 * q + 1] = r1[q] * K.cs1[c1][1];
+        for (int i = 0; i < kChunks / kDecodeThreads; ++i) {
+            const int c = tid + i * kDecodeThreads;
+            const float f[8] = {s[i][0].x, s[i][0].y, s[i][0].z, s[i][0].w, s[i][1].x, s[i][1].y, s[i][1].z, s[i][1].w};
+            dq_h8 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float v = UNIT ? (f[e] < 0.f ? -1.f : 1.f) : f[e] * 32768.f; /* entries are at most 1 */
+                hi[e] = (_Float16)v;
+                lo[e] = (_Float16)(v - (float)hi[e]);
+            }
+            sS[c] = __builtin_bit_cast(uint4, hi);
+            if (!UNIT) sS[(UNIT ? 0 : kChunks) + c] = __builtin_bit_cast(uint4, lo);
+        }
+    }
+    if (tid < 256) {
+        (&tq[0][0][0])[tid] = (&K.dq_quarter[0][0][0])[tid];
+        (&tb[0][0])[tid] = __uint_as_float(K.attn_tab[PQ_TAB_TBF + tid]);
+    }
+    if (tid < 48) reinterpret_cast<float *>(tup)[tid] = (&K.up_cs[0][0][0])[tid];
+    const int b5 = K.up_bits[0], b6 = K.up_bits[1], b7 = K.up_bits[2];
+    __syncthreads();
+
+    /* consecutive half tiles go to different workgroups: a short range occupies every CU */
+    for (int64_t item = (int64_t)wave * gridDim.x + blockIdx.x; item < a.n_items; item += (int64_t)kDecodeWaves * gridDim.x) {
+        const int64_t full_tile = item >> 1, head = full_tile / a.n_tiles, tile = a.first_tile + (full_tile - head * a.n_tiles);
+        const int half = (int)(item & 1), tau = 32 * half + j;
+        const int64_t row0 = tile * 64 + 32 * half - a.token0; /* output row of the half tile's first slot */
+        if (row0 + 32 <= 0 || row0 >= a.n_tokens) continue;
+        const uint8_t *tc = a.codes + (head * a.pool_tiles + tile) * PQL_CODE_BYTES;
+        const uint16_t *tr = a.radii + (head * a.pool_tiles + tile) * (a.deep ? PQ_DEEP_RADII_HALVES : PQL_RADII);
+        TokenHalf t;
+        if (KIND == PQ_KEY) {
+            dq_read_key(t, tc, tr, tau, H, a.deep != 0);
+        } else {
+            uint4 *im = reinterpret_cast<uint4 *>(img[wave]);
+            for (int c = lane; c < PQL_CODE_BYTES / 16; c += 64) im[c] = reinterpret_cast<const uint4 *>(tc)[c];
+            if (!a.deep) im[PQL_CODE_BYTES / 16 + lane] = reinterpret_cast<const uint4 *>(tr)[lane];
+            dq_wave_sync();
+            dq_read_value(t, img[wave], tau, H, a.deep != 0);
+        }
+        if (a.deep) {
+            const uint32_t word = reinterpret_cast<const uint32_t *>(tr)[tau];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) t.r[b] = pq_deep_block_radius(word, b5, b6, b7, tup, 4 * H + b);
+            t.top = (word >> 16) & 0x7FFFu;
+        }
+        float scale = 1.0f;
+        if (!ROTATED) { /* the token's largest radius goes to [2^14, 2^15) */
+            const uint32_t e = max(t.top >> 10, 1u);
+            scale = __uint_as_float((127u + 29u - e) << 23);
+            if (H == 0) sUn[wave][j] = UNIT ? __uint_as_float((127u - 29u + e) << 23) * PQ_INV_SQRT_D : __uint_as_float((127u - 44u + e) << 23);
+        }
+        dq_h8 yh[8], yl[8]; /* k-step ks: coordinates 64 H + 8 ks .. + 7 */
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const float4 f = *reinterpret_cast<const float4 *>(tb[t.bi[b]]);
+            const float rs = t.r[b] * scale;
+            const float rq[4] = {rs * f.x, rs * f.y, rs * f.z, rs * f.w};
+            float y[16];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float2 pa = *reinterpret_cast<const float2 *>(tq[0][t.q[b][k] & 63u]);
+                const float2 pb = *reinterpret_cast<const float2 *>(tq[1][t.q[b][k] >> 4]);
+                y[4 * k] = rq[k] * pa.x; y[4 * k + 1] = rq[k] * pa.y;
+                y[4 * k + 2] = rq[k] * pb.x; y[4 * k + 3] = rq[k] * pb.y;
+            }
+            if (ROTATED) {
+                const int64_t row = row0 + j;
+                if (row >= 0 && row < a.n_tokens) {
+                    const int64_t at = row * a.ld_token + head * a.ld_head + 64 * H + 16 * b;
+#pragma unroll
+                    for (int e = 0; e < 16; e += 2) dq_store_pair<OT>(a.out, at + e, y[e], y[e + 1], a.paired != 0);
                 }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    /* the two terms must come from one and the same rounded product (the compiler would otherwise
+                       round the exact product to binary16 for the one and the fp32 product for the other) */
+                    asm("" : "+v"(y[e]));
+                    const _Float16 hi = (_Float16)y[e];
+                    yh[2 * b + (e >> 3)][e & 7] = hi;
+                    yl[2 * b + (e >> 3)][e & 7] = (_Float16)(y[e] - (float)hi);
+                }
+                __builtin_amdgcn_sched_barrier(0); /* gathers of all four blocks at once would not fit the registers */
             }
         }
-    }
-    __syncthreads();
-    /* thread i produces output coordinate i of every token of the group */
-    const int i = tid;
-    float acc[kTok];
-    if (a.rotated) {
+        dq_wave_sync(); /* the image is read before the next one replaces it; the scales are written */
+        if (!ROTATED) {
+            const bool whole = a.paired && row0 >= 0 && row0 + 32 <= a.n_tokens; /* every store of the half tile is a pair */
+            /* element offset of this lane's first token, column pair 0; the rows of a register differ by scalar multiples */
+            const int64_t row_h = row0 + 4 * H;
+            int64_t at0 = row_h * a.ld_token + head * a.ld_head + 2 * j;
+#pragma unroll 1
+            for (int grp = 0; grp < 2; ++grp, at0 += 64) {
+                asm volatile("" : "+v"(at0)); /* 16 row addresses kept over both groups would spill */
+                dq_f16 acc[2]; /* even and odd coordinates of the group */
 #pragma unroll
-        for (int t = 0; t < kTok; ++t) acc[t] = sy[t][i];
-    } else {
+                for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int t = 0; t < kTok; ++t) acc[t] = 0.0f;
-        for (int j = 0; j < PQ_D; ++j) {
-            float s = a.St[j * PQ_D + i]; /* S[i][j] */
+                    for (int e = 0; e < 16; ++e) acc[p][e] = 0.f;
+                const uint4 *sg = sS + 2 * grp * 8 * 64 + lane;
 #pragma unroll
-            for (int t = 0; t < kTok; ++t) acc[t] += sy[t][j] * s;
+                for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        const dq_h8 s_hi = __builtin_bit_cast(dq_h8, sg[(p * 8 + ks) * 64]);
+                        if (!UNIT) {
+                            const dq_h8 s_lo = __builtin_bit_cast(dq_h8, sg[(UNIT ? 0 : kChunks) + (p * 8 + ks) * 64]);
+                            acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(yh[ks], s_lo, acc[p], 0, 0, 0);
+                        }
+                        acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(yl[ks], s_hi, acc[p], 0, 0, 0);
+                        acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_f16(yh[ks], s_hi, acc[p], 0, 0, 0);
+                    }
+                /* register r of lane (H, j): token 8 (r >> 2) + 4 H + (r & 3) of the half, coordinates 64 grp + 2 j, + 1 */
+                auto store = [&](auto whole_c) {
+                    constexpr bool WHOLE = decltype(whole_c)::value;
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        const float4 un4 = *reinterpret_cast<const float4 *>(&sUn[wave][8 * r4 + 4 * H]);
+                        const float un[4] = {un4.x, un4.y, un4.z, un4.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int64_t row = row_h + 8 * r4 + e;
+                            if (WHOLE || (row >= 0 && row < a.n_tokens))
+                                dq_store_pair<OT>(a.out, at0 + (8 * r4 + e) * a.ld_token, acc[0][4 * r4 + e] * un[e],
+                                                  acc[1][4 * r4 + e] * un[e], WHOLE || a.paired != 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                if (whole) store(std::true_type{});
+                else store(std::false_type{});
+            }
+            dq_wave_sync(); /* the scales are read before the next ones replace them */
         }
     }
-#pragma unroll
-    for (int t = 0; t < kTok; ++t) {
-        int64_t tt = t_base + t;
-        if (tt >= a.n_tokens) break;
-        int64_t at = tt * a.ld_token + (int64_t)head * a.ld_head + i;
-        if (OT == PQ_F32) static_cast<float *>(a.out)[at] = acc[t];
-        else {
-            uint32_t u = __float_as_uint(acc[t]);
-            uint32_t r = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-            static_cast<uint16_t *>(a.out)[at] = (uint16_t)r;
-        }
-    }
+}
+
+template <int KIND, int OT>
+void launch_decode(const DecodeArgs &a, bool unit, int rotated, unsigned blocks, hipStream_t s)
+{
+    if (rotated) hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, false, true>), dim3(blocks), dim3(kDecodeThreads), 0, s, a);
+    else if (unit) hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, true, false>), dim3(blocks), dim3(kDecodeThreads), 0, s, a);
+    else hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, false, false>), dim3(blocks), dim3(kDecodeThreads), 0, s, a);
 }
 
 struct ExportArgs {
@@ -178,16 +414,24 @@ extern "C" pq_status pq_decode_kv(const pq_ctx *ctx, pq_kind kind, const uint8_t
     const PqDeviceState *ds = nullptr;
     pq_status st = pq_device_state(ctx, &ds);
     if (st != PQ_OK) return st;
-    DecodeArgs a{codes, radii, pool_tokens / 64, token0, n_tokens, n_heads, out, ld_token, ld_head, rotated,
-                 ds->consts, ds->St_f32, ctx->depth == 7 ? 1 : 0};
-    dim3 grid((unsigned)((n_tokens + kTok - 1) / kTok), (unsigned)n_heads), block(128);
+    DecodeArgs a{};
+    a.codes = codes; a.radii = radii; a.pool_tiles = pool_tokens / 64;
+    a.token0 = token0; a.n_tokens = n_tokens;
+    a.first_tile = token0 / 64;
+    a.n_tiles = (token0 + n_tokens + 63) / 64 - a.first_tile;
+    a.n_items = 2 * a.n_tiles * n_heads;
+    a.out = out; a.ld_token = ld_token; a.ld_head = ld_head;
+    a.consts = ds->consts; a.S = ds->S_f32;
+    a.paired = ld_token % 2 == 0 && ld_head % 2 == 0; /* out itself is 16-byte aligned */
+    a.deep = ctx->depth == 7 ? 1 : 0;
+    const unsigned blocks = (unsigned)(a.n_items < 256 ? a.n_items : 256); /* one workgroup per CU */
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (kind == PQ_KEY) {
-        if (ot == PQ_F32) hipLaunchKernelGGL((pq_decode_kernel<PQ_KEY, PQ_F32>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((pq_decode_kernel<PQ_KEY, PQ_BF16>), grid, block, 0, s, a);
+        if (ot == PQ_F32) launch_decode<PQ_KEY, PQ_F32>(a, ctx->unit_entries, rotated, blocks, s);
+        else launch_decode<PQ_KEY, PQ_BF16>(a, ctx->unit_entries, rotated, blocks, s);
     } else {
-        if (ot == PQ_F32) hipLaunchKernelGGL((pq_decode_kernel<PQ_VALUE, PQ_F32>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((pq_decode_kernel<PQ_VALUE, PQ_BF16>), grid, block, 0, s, a);
+        if (ot == PQ_F32) launch_decode<PQ_VALUE, PQ_F32>(a, ctx->unit_entries, rotated, blocks, s);
+        else launch_decode<PQ_VALUE, PQ_BF16>(a, ctx->unit_entries, rotated, blocks, s);
     }
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
