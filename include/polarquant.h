@@ -426,8 +426,8 @@ size_t pq_attn_hybrid_workspace_bytes(int B, int Hq, int Hkv, int64_t max_ctx, i
  * Section 4.1's (Definition 1 recurses to log2 d; the remark after Theorem 1
  * leaves the codebook size of each level free).  A plain path next to the tuned
  * one: records in the canonical general layout, one after another, read through
- * a generic bit reader by simple fp32 kernels (one wavefront per vector, or per
- * (sequence, query head) in attention); not tuned.
+ * a generic bit reader by fp32 kernels on the vector ALU (attention: one workgroup
+ * per sequence and up to four query heads of a kv head, one token per lane).
  *   format: depth in 4..7; bits[l-1] bits for the angles of level l:
  *           level 1: 3 or 4; levels 2-4: 2 or 3; levels 5-7 (up to depth): 1, 2 or 3.
  *   record: the codes of level 1 (64, in coordinate order), then level 2 (32), ...,

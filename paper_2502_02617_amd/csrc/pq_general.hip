@@ -7,15 +7,15 @@
  * another in the canonical general layout (all codes of level 1, then level 2,
  * ..., in one little-endian bit stream padded to a byte, then the 128 >> depth
  * binary16 radii), every field goes through a generic bit reader, and the
- * kernels are simple fp32 code, one wavefront per vector or per (sequence,
- * query head):
+ * kernels are fp32 code on the vector ALU:
  *   encode     y = x S (fp32 sums in index order), procedure Polar level by
  *              level in LDS, procedure Quant as a count of the cell boundaries
  *              (midpoints of neighbouring centroids) below the angle
  *   decode     procedure DeQuant: centroid cos/sin products from the top level
- *              down, then the trailing S^T
+ *              down, then the trailing S^T; one wavefront per vector
  *   attention  Eq. 5 in the rotated domain: q' = q S once, every cached token
- *              dequantised without its S^T, online softmax, one S^T at the end
+ *              dequantised without its S^T, one token per lane, softmax
+ *              weights, one S^T at the end
  * Section 4.1's own configuration (depth 4, bits 4/2/2/2) and its depth-7
  * extension have the tuned kernels of pq_encode.hip / pq_attn.hip; this file
  * accepts them too (same numbers, other layout), which is how it is tested
@@ -35,8 +35,10 @@ struct GenFormat {
     int depth;
     int bits[7];
     int level_off[7];  /* first angle of level l inside the level-major numbering */
+    int bit_off[7];    /* first bit of level l in the record's bit stream */
     int code_bytes, rec_bytes, n_radii;
-    float bound[7][kGenMaxCells - 1]; /* inner cell boundaries */
+    int rec_dwords, rec_inv; /* dwords of a record (the last may be partial); 65536 / rec_dwords, rounded up */
+    float bound[7][kGenMaxCells - 1]; /* inner cell boundaries, +inf beyond the level's last one */
     float cosv[7][kGenMaxCells], sinv[7][kGenMaxCells];
 };
 
@@ -68,7 +70,9 @@ pq_status make_format(const pq_general_format *f, const double *cbg, GenFormat *
     for (int l = 0; l < f->depth; ++l) {
         const int K = 1 << f->bits[l];
         g->bits[l] = f->bits[l];
+        for (int k = K - 1; k < kGenMaxCells - 1; ++k) g->bound[l][k] = INFINITY;
         g->level_off[l] = off;
+        g->bit_off[l] = l == 0 ? 0 : g->bit_off[l - 1] + (PQ_D >> l) * f->bits[l - 1];
         off += PQ_D >> (l + 1);
         for (int k = 0; k < K; ++k) {
             const double c = cbg[cboff + k];
@@ -83,6 +87,8 @@ pq_status make_format(const pq_general_format *f, const double *cbg, GenFormat *
     g->code_bytes = (general_code_bits(f) + 7) / 8;
     g->n_radii = PQ_D >> f->depth;
     g->rec_bytes = g->code_bytes + 2 * g->n_radii;
+    g->rec_dwords = (g->rec_bytes + 3) / 4;
+    g->rec_inv = (65536 + g->rec_dwords - 1) / g->rec_dwords;
     return PQ_OK;
 }
 
@@ -105,60 +111,99 @@ __device__ __forceinline__ int gen_bit_pos(const GenFormat &f, int l, int j)
     return pos + j * f.bits[l];
 }
 
-/* ---- encode: one wavefront per vector ---- */
+/* ---- encode: sixteen vectors per workgroup of 512 threads ----
+ * Thread (g, c) sums column c of four vectors (y_c = sum_i x_i S[i][c], i ascending), so that an element of S is fetched
+ * once for the sixteen; the nodes of a level are spread over all threads, and the codes are OR-ed into an image
+ * of the sixteen records, which lie one after another.
+ * Bound by the fetches of S (64 KB per workgroup from L2) and the chain of levels.  4096 vectors 21.1 -> 10.1 us,
+ * 65536 236 -> 62 us (one wavefront per vector, S fetched for each -> this).  Same operations in the same order: the
+ * records are those of one wavefront per vector, bit for bit. */
+constexpr int kGenEncVecs = 16, kGenEncThreads = 512;
+
 template <int XT>
-__global__ __launch_bounds__(64) void pq_general_encode_kernel(GenFormat f, const void *x, int64_t ld_vector, int64_t n,
-                                                               const float *S, uint8_t *rec)
+__global__ __launch_bounds__(kGenEncThreads) void pq_general_encode_kernel(GenFormat f, const void *x, int64_t ld_vector, int64_t n,
+                                                                           const float *S, uint8_t *rec)
 {
-    __shared__ float sx[PQ_D];
-    __shared__ float buf[2][PQ_D];
-    __shared__ uint32_t srec[kGenMaxRecord / 4];
-    const int64_t v = blockIdx.x;
+    __shared__ __attribute__((aligned(16))) float buf[2][kGenEncVecs][PQ_D];
+    __shared__ uint32_t srec[kGenEncVecs * kGenMaxRecord / 4 + 1];
+    const int64_t v0 = (int64_t)blockIdx.x * kGenEncVecs;
     const int tid = threadIdx.x;
-    if (v >= n) return;
-    for (int c = tid; c < PQ_D; c += 64) {
-        const int64_t at = v * ld_vector + c;
-        sx[c] = XT == PQ_BF16 ? __uint_as_float((uint32_t)static_cast<const uint16_t *>(x)[at] << 16)
-                              : static_cast<const float *>(x)[at];
-    }
-    for (int c = tid; c < kGenMaxRecord / 4; c += 64) srec[c] = 0u;
-    __syncthreads();
-    {   /* y_j = sum_i x_i S[i][j], i ascending; this thread's two columns */
-        float a0 = 0.f, a1 = 0.f;
-        for (int i = 0; i < PQ_D; ++i) {
-            const float2 s2 = *reinterpret_cast<const float2 *>(S + i * PQ_D + 2 * tid);
-            a0 = fmaf(sx[i], s2.x, a0);
-            a1 = fmaf(sx[i], s2.y, a1);
+    const int nv = (int)(n - v0 < kGenEncVecs ? n - v0 : kGenEncVecs);
+    for (int t = tid; t < kGenEncVecs * PQ_D; t += kGenEncThreads) {
+        const int v = t >> 7, c = t & 127;
+        float val = 0.f; /* vectors beyond the last one: computed along, not written */
+        if (v < nv) {
+            const int64_t at = (v0 + v) * ld_vector + c;
+            val = XT == PQ_BF16 ? __uint_as_float((uint32_t)static_cast<const uint16_t *>(x)[at] << 16)
+                                : static_cast<const float *>(x)[at];
         }
-        buf[0][2 * tid] = a0;
-        buf[0][2 * tid + 1] = a1;
+        buf[1][v][c] = val;
+    }
+    for (int c = tid; c < kGenEncVecs * kGenMaxRecord / 4 + 1; c += kGenEncThreads) srec[c] = 0u;
+    __syncthreads();
+    {
+        const int g = tid >> 7, c = tid & 127;
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 16
+        for (int i = 0; i < PQ_D; i += 4) { /* 64 elements of S in flight */
+            float s[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s[k] = S[(i + k) * PQ_D + c];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float4 xv = *reinterpret_cast<const float4 *>(&buf[1][4 * g + v][i]);
+                acc[v] = fmaf(xv.x, s[0], acc[v]);
+                acc[v] = fmaf(xv.y, s[1], acc[v]);
+                acc[v] = fmaf(xv.z, s[2], acc[v]);
+                acc[v] = fmaf(xv.w, s[3], acc[v]);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) buf[0][4 * g + v][c] = acc[v];
     }
     __syncthreads();
     int cur = 0;
     for (int l = 0; l < f.depth; ++l) {
-        const int n_ang = PQ_D >> (l + 1), K = 1 << f.bits[l];
-        if (tid < n_ang) {
-            const float a = buf[cur][2 * tid], b = buf[cur][2 * tid + 1];
+        const int shift = 6 - l, n_ang = PQ_D >> (l + 1);
+        for (int t = tid; t < kGenEncVecs * n_ang; t += kGenEncThreads) {
+            const int v = t >> shift, j = t & (n_ang - 1);
+            const float a = buf[cur][v][2 * j], b = buf[cur][v][2 * j + 1];
             float ang = atan2f(b, a);
             if (l == 0 && ang < 0.f) ang += 6.28318530717958647692f;
             uint32_t code = 0;
-            for (int k = 0; k < K - 1; ++k) code += ang > f.bound[l][k] ? 1u : 0u; /* nearest centroid, ties to the lower cell */
-            const int pos = gen_bit_pos(f, l, tid);
+            /* nearest centroid, ties to the lower cell; boundaries a level does not have are +inf (reading them all at
+               once is a third of the time of a loop over those it has) */
+#pragma unroll
+            for (int k = 0; k < 7; ++k) code += ang > f.bound[l][k] ? 1u : 0u;
+            if (l == 0) {
+#pragma unroll
+                for (int k = 7; k < kGenMaxCells - 1; ++k) code += ang > f.bound[0][k] ? 1u : 0u;
+            }
+            const int pos = 8 * f.rec_bytes * v + f.bit_off[l] + j * f.bits[l];
             atomicOr(&srec[pos >> 5], code << (pos & 31));
             if ((pos & 31) + f.bits[l] > 32) atomicOr(&srec[(pos >> 5) + 1], code >> (32 - (pos & 31)));
-            buf[cur ^ 1][tid] = sqrtf(a * a + b * b);
+            buf[cur ^ 1][v][j] = sqrtf(a * a + b * b);
         }
         cur ^= 1;
         __syncthreads();
     }
-    uint8_t *out = rec + v * f.rec_bytes;
-    const uint8_t *img = reinterpret_cast<const uint8_t *>(srec);
-    for (int c = tid; c < f.code_bytes; c += 64) out[c] = img[c];
-    if (tid < f.n_radii) {
-        const uint16_t h = gen_radius_bits(buf[cur][tid]);
-        out[f.code_bytes + 2 * tid] = (uint8_t)(h & 0xFF);
-        out[f.code_bytes + 2 * tid + 1] = (uint8_t)(h >> 8);
+    uint8_t *img = reinterpret_cast<uint8_t *>(srec);
+    if (tid < kGenEncVecs * f.n_radii) {
+        const int v = tid / f.n_radii, k = tid - v * f.n_radii;
+        const uint16_t h = gen_radius_bits(buf[cur][v][k]);
+        const int at = v * f.rec_bytes + f.code_bytes + 2 * k;
+        img[at] = (uint8_t)(h & 0xFF);
+        img[at + 1] = (uint8_t)(h >> 8);
     }
+    __syncthreads();
+    uint8_t *out = rec + v0 * f.rec_bytes;
+    const int n_bytes = nv * f.rec_bytes;
+    int done = 0;
+    if ((reinterpret_cast<uintptr_t>(out) & 3) == 0) { /* sixteen records are a whole number of dwords */
+        for (int c = tid; c < n_bytes / 4; c += kGenEncThreads) reinterpret_cast<uint32_t *>(out)[c] = srec[c];
+        done = n_bytes & ~3;
+    }
+    for (int c = done + tid; c < n_bytes; c += kGenEncThreads) out[c] = img[c];
 }
 
 /* orders the LDS accesses of the lanes of one wavefront (the buffers below belong to a single wavefront) */
@@ -224,85 +269,282 @@ __device__ __forceinline__ float gen_wave_sum(float x)
     return x;
 }
 
-/* ---- attention: one workgroup of kGenAttnWaves wavefronts per (sequence, query head).  Wavefront w takes tokens
-   w, w + kGenAttnWaves, ... one after another (DeQuant of the key, score, DeQuant of the value, running softmax);
-   the wavefronts' partial results are then merged in wavefront order, so the result does not depend on timing. ---- */
-constexpr int kGenAttnWaves = 16;
+/* ---- attention: one workgroup of sixteen wavefronts per (sequence, HEADS query heads of one kv head) ----
+ * The entry point has no workspace, so a sequence is not split over workgroups; inside one, wavefront (tg, b) takes block
+ * b (sixteen coordinates) of 64 tokens at a time, one token per lane:
+ *   - the records of 128 tokens are copied to LDS, every record on a dword boundary, while the 128 before are worked on;
+ *   - a lane rebuilds its block from the codes on the path from the top radius down (the same fp32 products in the same
+ *     order as DeQuant; fields are read with wave-uniform positions, centroids gathered from a 16-entry table), and leaves
+ *     its part of the scores in LDS; the eight parts of a token are summed by every wavefront of its group;
+ *   - softmax weights against an exponent reference per lane that moves only when a score exceeds it by more than kGenSlack;
+ *   - the weighted values stay in the lane (sixteen sums per head); lanes, token groups and S^T come at the end.
+ * Bound by LDS reads (36 centroid gathers and 16 field reads per wavefront and 64 tokens), then by vector instructions
+ * (some 330).  4 sequences of 2048 tokens, 8 query heads: 646 us with one token per wavefront at a time -> 46 us.
+ * Rebuilding the values ahead of the weights measured the same here and 4 to 9 % slower on 512 rows and more. */
+constexpr int kGenAttnWaves = 16, kGenAttnTokens = 128;
+constexpr int kGenMaxDwords = (69 + 3) / 4 + 1; /* dwords of a record in LDS (an odd number: token strides spread over the banks) */
+constexpr float kGenSlack = 16.f;
 
+/* 32 bits at bit `pos` (the same in all lanes) of a lane's record */
+__device__ __forceinline__ uint32_t gen_bits_at(const uint32_t *rec, int pos)
+{
+    return __builtin_amdgcn_alignbit(rec[(pos >> 5) + 1], rec[pos >> 5], pos & 31);
+}
+
+/* The sixteen coordinates of block `blk` (the same in all lanes) of a lane's record. */
+__device__ __forceinline__ void gen_block(const GenFormat &f, const uint32_t *rec, const float2 (&cs)[7][kGenMaxCells], int blk,
+                                          float (&v)[16])
+{
+    float r = (float)__builtin_bit_cast(_Float16, (uint16_t)gen_bits_at(rec, 8 * f.code_bytes + 16 * (blk >> (f.depth - 4))));
+#pragma unroll
+    for (int l = 6; l >= 4; --l) { /* levels above 4: the branch that leads to the block */
+        if (l >= f.depth) continue;
+        const uint32_t code = gen_bits_at(rec, f.bit_off[l] + (blk >> (l - 3)) * f.bits[l]) & ((1u << f.bits[l]) - 1u);
+        const float2 t = cs[l][code];
+        r *= ((blk >> (l - 4)) & 1) ? t.y : t.x;
+    }
+    const int b1 = f.bits[0], b2 = f.bits[1], b3 = f.bits[2], b4 = f.bits[3];
+    const uint32_t g4 = gen_bits_at(rec, f.bit_off[3] + blk * b4), g3 = gen_bits_at(rec, f.bit_off[2] + 2 * blk * b3);
+    const uint32_t g2 = gen_bits_at(rec, f.bit_off[1] + 4 * blk * b2), g1 = gen_bits_at(rec, f.bit_off[0] + 8 * blk * b1);
+    const float2 t4 = cs[3][g4 & ((1u << b4) - 1u)];
+    const float r3[2] = {r * t4.x, r * t4.y};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float2 t3 = cs[2][__builtin_amdgcn_ubfe(g3, h * b3, b3)];
+        const float r2[2] = {r3[h] * t3.x, r3[h] * t3.y};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float2 t2 = cs[1][__builtin_amdgcn_ubfe(g2, (2 * h + q) * b2, b2)];
+            const float r1[2] = {r2[q] * t2.x, r2[q] * t2.y};
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int k = 4 * h + 2 * q + p;
+                const float2 t1 = cs[0][__builtin_amdgcn_ubfe(g1, k * b1, b1)];
+                v[2 * k] = r1[p] * t1.x;
+                v[2 * k + 1] = r1[p] * t1.y;
+            }
+        }
+    }
+}
+
+/* Dword k of a record in memory (no alignment); a last, partial one is read with the record's last four bytes and has to be
+   shifted right by gen_dword_shift bits, which is left to where the value is used: the loads then all go out together. */
+__device__ __forceinline__ uint32_t gen_load_dword(const uint8_t *rec, int k, int rec_bytes)
+{
+    uint32_t w;
+    __builtin_memcpy(&w, rec + min(4 * k, rec_bytes - 4), 4);
+    return w;
+}
+
+__device__ __forceinline__ int gen_dword_shift(int k, int rec_bytes) { return 8 * max(4 * k + 4 - rec_bytes, 0); }
+
+template <int HEADS>
 __global__ __launch_bounds__(kGenAttnWaves * 64) void pq_general_attn_kernel(GenFormat f, const uint16_t *q, float *out,
                                                                              const uint8_t *k_rec, const uint8_t *v_rec,
                                                                              const int64_t *seq_start, const int32_t *ctx_len,
                                                                              int Hq, int Hkv, int64_t pool_tokens, float scale,
                                                                              const float *S, const float *St)
 {
-    __shared__ float sq[PQ_D];
-    __shared__ float sqr[PQ_D];                         /* q' = q S */
-    __shared__ float buf[kGenAttnWaves][2][PQ_D];       /* a wavefront's DeQuant buffers */
-    __shared__ float part_o[kGenAttnWaves][PQ_D];
-    __shared__ float part_ml[kGenAttnWaves][2];
-    const int row = blockIdx.x, b = row / Hq, head = row % Hq, hk = head / (Hq / Hkv);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid < PQ_D) sq[tid] = __uint_as_float((uint32_t)q[(int64_t)row * PQ_D + tid] << 16);
-    __syncthreads();
-    if (tid < 64) {
-        float a0 = 0.f, a1 = 0.f; /* this thread's two coordinates of q' */
-        for (int i = 0; i < PQ_D; ++i) {
-            const float2 s2 = *reinterpret_cast<const float2 *>(S + i * PQ_D + 2 * tid);
-            a0 = fmaf(sq[i], s2.x, a0);
-            a1 = fmaf(sq[i], s2.y, a1);
-        }
-        sqr[2 * tid] = a0;
-        sqr[2 * tid + 1] = a1;
-    }
-    __syncthreads();
-    const float q0 = sqr[2 * lane], q1 = sqr[2 * lane + 1];
+    constexpr int kThreads = kGenAttnWaves * 64;
+    __shared__ uint32_t srec[2][2][kGenAttnTokens * kGenMaxDwords + 1]; /* [buffer][keys, values] */
+    __shared__ float2 cs[7][kGenMaxCells];
+    __shared__ float spart[HEADS][8][kGenAttnTokens];  /* a block's part of the scores; at the ends partial products with S */
+    __shared__ __attribute__((aligned(16))) float sq[HEADS][PQ_D];
+    __shared__ float so[HEADS][PQ_D]; /* sq: q, then its rotation; so: the weighted values */
+    __shared__ float part_o[HEADS][2][PQ_D], part_m[HEADS][2], part_l[HEADS][2];
+    const int groups = Hq / HEADS, b = blockIdx.x / groups, head0 = (blockIdx.x % groups) * HEADS, hk = head0 / (Hq / Hkv);
+    const int64_t row0 = (int64_t)b * Hq + head0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tg = wave >> 3, blk = wave & 7;
     int64_t n = ctx_len[b];
     const int64_t t0 = seq_start[b];
     if (n < 0 || t0 < 0 || t0 + n > pool_tokens) n = 0; /* a sequence outside the pool is treated as empty */
-    float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int64_t t = wave; t < n; t += kGenAttnWaves) {
-        const int64_t slot = (int64_t)hk * pool_tokens + t0 + t;
-        int cur = gen_dequant_rotated(f, k_rec + slot * f.rec_bytes, buf[wave], lane);
-        const float s = gen_wave_sum(q0 * buf[wave][cur][2 * lane] + q1 * buf[wave][cur][2 * lane + 1]) * scale;
-        gen_wave_sync();
-        cur = gen_dequant_rotated(f, v_rec + slot * f.rec_bytes, buf[wave], lane);
-        const float m_new = fmaxf(m, s);
-        const float alpha = expf(m - m_new), p = expf(s - m_new); /* exp(-inf) = 0 at the first token */
-        l = l * alpha + p;
-        o0 = o0 * alpha + p * buf[wave][cur][2 * lane];
-        o1 = o1 * alpha + p * buf[wave][cur][2 * lane + 1];
-        m = m_new;
-        gen_wave_sync();
-    }
-    part_o[wave][2 * lane] = o0;
-    part_o[wave][2 * lane + 1] = o1;
-    if (lane == 0) { part_ml[wave][0] = m; part_ml[wave][1] = l; }
-    __syncthreads();
-    if (tid < 64) {
-        float mm = -INFINITY;
-        for (int w = 0; w < kGenAttnWaves; ++w) mm = fmaxf(mm, part_ml[w][0]);
-        float lt = 0.f, a0 = 0.f, a1 = 0.f;
-        for (int w = 0; w < kGenAttnWaves; ++w) {
-            const float mw = part_ml[w][0];
-            const float wgt = mw == -INFINITY ? 0.f : expf(mw - mm); /* a wavefront without a token */
-            lt = fmaf(part_ml[w][1], wgt, lt);
-            a0 = fmaf(part_o[w][2 * tid], wgt, a0);
-            a1 = fmaf(part_o[w][2 * tid + 1], wgt, a1);
+
+    /* records of tokens [first, first + 128) of the sequence: dword (stream, token, k) -> registers -> LDS */
+    const int per_stream = kGenAttnTokens * f.rec_dwords;
+    constexpr int kMaxStage = (2 * kGenAttnTokens * (kGenMaxDwords - 1) + kThreads - 1) / kThreads;
+    uint32_t stage[kMaxStage];
+    const int64_t slot0 = (int64_t)hk * pool_tokens + t0;
+    struct Place { int stream, t, k; };
+    auto place = [&](int at) { /* threads beyond the last dword repeat it */
+        at = min(at, 2 * per_stream - 1);
+        Place p;
+        p.stream = at >= per_stream ? 1 : 0;
+        const int in = at - p.stream * per_stream; /* below 2304: the multiplication by the inverse is exact */
+        p.t = (int)(((uint32_t)in * (uint32_t)f.rec_inv) >> 16);
+        p.k = in - p.t * f.rec_dwords;
+        return p;
+    };
+    auto fetch = [&](int64_t first) {
+#pragma unroll
+        for (int i = 0; i < kMaxStage; ++i) {
+            const Place p = place(tid + i * kThreads);
+            const int64_t t = first + p.t < n ? first + p.t : n - 1; /* tokens beyond the sequence repeat its last one */
+            stage[i] = gen_load_dword((p.stream ? v_rec : k_rec) + (slot0 + t) * f.rec_bytes, p.k, f.rec_bytes);
         }
-        sq[2 * tid] = lt > 0.f ? a0 / lt : 0.f;   /* o' in the rotated domain (sq is free by now) */
-        sq[2 * tid + 1] = lt > 0.f ? a1 / lt : 0.f;
+    };
+    auto store = [&](int buffer) {
+#pragma unroll
+        for (int i = 0; i < kMaxStage; ++i) {
+            const Place p = place(tid + i * kThreads);
+            srec[buffer][p.stream][p.t * kGenMaxDwords + p.k] = stage[i] >> gen_dword_shift(p.k, f.rec_bytes);
+        }
+    };
+    if (n > 0) fetch(0);
+    if (tid < 7 * kGenMaxCells) cs[tid >> 4][tid & 15] = make_float2((&f.cosv[0][0])[tid], (&f.sinv[0][0])[tid]);
+    for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = __uint_as_float((uint32_t)q[row0 * PQ_D + t] << 16);
+    __syncthreads();
+    /* product of HEADS vectors with a matrix: thread (part, c) sums sixteen terms of column c, eight parts */
+    auto times_matrix = [&](const float (&in)[HEADS][PQ_D], const float *M) {
+        const int part = tid >> 7, c = tid & 127;
+        float acc[HEADS];
+#pragma unroll
+        for (int h = 0; h < HEADS; ++h) acc[h] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float m = M[(16 * part + k) * PQ_D + c];
+#pragma unroll
+            for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(in[h][16 * part + k], m, acc[h]);
+        }
+#pragma unroll
+        for (int h = 0; h < HEADS; ++h) spart[h][part][c] = acc[h];
+        __syncthreads();
+    };
+    auto product = [&](int h, int c) {
+        float a[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a[k] = spart[h][k][c];
+        return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+    };
+    times_matrix(sq, S); /* q' = q S */
+    for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = product(t >> 7, t & 127);
+    if (n > 0) store(0);
+    __syncthreads();
+    /* q' of the wavefront's block: the same in all lanes, in scalar registers */
+    float qv[HEADS][16];
+#pragma unroll
+    for (int h = 0; h < HEADS; ++h)
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            qv[h][c] = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(sq[h][16 * blk + c])));
+
+    float m[HEADS], l[HEADS], acc[HEADS][16];
+#pragma unroll
+    for (int h = 0; h < HEADS; ++h) {
+        m[h] = -INFINITY;
+        l[h] = 0.f;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) acc[h][c] = 0.f;
+    }
+    const int tok = 64 * tg + lane;
+    int cur = 0;
+    for (int64_t first = 0; first < n; first += kGenAttnTokens, cur ^= 1) { /* n is the same in all threads */
+        const bool more = first + kGenAttnTokens < n;
+        if (more) fetch(first + kGenAttnTokens);
+        {
+            float v[16];
+            gen_block(f, srec[cur][0] + tok * kGenMaxDwords, cs, blk, v);
+#pragma unroll
+            for (int h = 0; h < HEADS; ++h) {
+                float d[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < 16; ++c) d[c & 3] = fmaf(qv[h][c], v[c], d[c & 3]);
+                spart[h][blk][tok] = (d[0] + d[1]) + (d[2] + d[3]);
+            }
+        }
+        __syncthreads(); /* the parts are written, and everyone is through with the other buffer */
+        if (more) store(cur ^ 1);
+        const bool valid = first + tok < n;
+        float p[HEADS];
+#pragma unroll
+        for (int h = 0; h < HEADS; ++h) {
+            /* The parts are summed, scaled and compared with the reference in 64 bits: a score of 20 rounded to fp32
+               would put 1e-6 on its token's weight, the largest error of the whole result. */
+            double sum = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sum += (double)spart[h][k][tok];
+            const double s = sum * (double)scale;
+            float over = (float)(s - (double)m[h]); /* +inf at a lane's first token */
+            const bool move = valid && over > kGenSlack;
+            if (__ballot(move) != 0ull) {
+                const float alpha = move ? expf(-over) : 1.f; /* exp(-inf) = 0 */
+                if (move) {
+                    m[h] = (float)s;
+                    over = (float)(s - (double)m[h]);
+                }
+                l[h] *= alpha;
+#pragma unroll
+                for (int c = 0; c < 16; ++c) acc[h][c] *= alpha;
+            }
+            p[h] = valid ? expf(over) : 0.f;
+            l[h] += p[h];
+        }
+        {
+            float v[16];
+            gen_block(f, srec[cur][1] + tok * kGenMaxDwords, cs, blk, v);
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+#pragma unroll
+                for (int h = 0; h < HEADS; ++h) acc[h][c] = fmaf(p[h], v[c], acc[h][c]);
+        }
+        __syncthreads(); /* the next records are in place, and the parts have been read */
+    }
+    /* the lanes of a wavefront: everything to one reference, then sums; after four halving steps a lane holds the
+       coordinate that its upper four lane bits name */
+#pragma unroll
+    for (int h = 0; h < HEADS; ++h) {
+        float mw = m[h];
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) mw = fmaxf(mw, __shfl_xor(mw, d));
+        const float w = m[h] == -INFINITY ? 0.f : expf(m[h] - mw);
+        const float lw = gen_wave_sum(l[h] * w);
+        float a[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) a[c] = acc[h][c] * w;
+#pragma unroll
+        for (int half = 8; half >= 1; half >>= 1) {
+            const bool up = (lane & (4 * half)) != 0;
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (c < half) {
+                    const float keep = up ? a[c + half] : a[c], give = up ? a[c] : a[c + half];
+                    a[c] = keep + __shfl_xor(give, 4 * half);
+                }
+        }
+        float o = a[0];
+        o += __shfl_xor(o, 2);
+        o += __shfl_xor(o, 1);
+        if ((lane & 3) == 0) part_o[h][tg][16 * blk + (lane >> 2)] = o;
+        if (blk == 0 && lane == 0) {
+            part_m[h][tg] = mw;
+            part_l[h][tg] = lw;
+        }
     }
     __syncthreads();
-    if (tid < 64) {
-        float a0 = 0.f, a1 = 0.f;
-        for (int j = 0; j < PQ_D; ++j) {
-            const float2 s2 = *reinterpret_cast<const float2 *>(St + j * PQ_D + 2 * tid);
-            a0 = fmaf(sq[j], s2.x, a0);
-            a1 = fmaf(sq[j], s2.y, a1);
+    for (int t = tid; t < HEADS * PQ_D; t += kThreads) {
+        const int h = t >> 7, c = t & 127;
+        const float mm = fmaxf(part_m[h][0], part_m[h][1]);
+        float lt = 0.f, a = 0.f;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const float w = part_m[h][g] == -INFINITY ? 0.f : expf(part_m[h][g] - mm); /* a group without a token */
+            lt = fmaf(part_l[h][g], w, lt);
+            a = fmaf(part_o[h][g][c], w, a);
         }
-        out[(int64_t)row * PQ_D + 2 * tid] = a0;
-        out[(int64_t)row * PQ_D + 2 * tid + 1] = a1;
+        so[h][c] = lt > 0.f ? a / lt : 0.f;
     }
+    __syncthreads();
+    times_matrix(so, St);
+    for (int t = tid; t < HEADS * PQ_D; t += kThreads) out[row0 * PQ_D + t] = product(t >> 7, t & 127);
+}
+
+template <int HEADS>
+void launch_general_attn(const GenFormat &g, const void *q, float *out, const uint8_t *k, const uint8_t *v, const int64_t *start,
+                         const int32_t *len, int64_t rows, int Hq, int Hkv, int64_t pool, float scale, const PqDeviceState *ds,
+                         hipStream_t s)
+{
+    hipLaunchKernelGGL(pq_general_attn_kernel<HEADS>, dim3((unsigned)(rows / HEADS)), dim3(kGenAttnWaves * 64), 0, s, g,
+                       static_cast<const uint16_t *>(q), out, k, v, start, len, Hq, Hkv, pool, scale, ds->S_f32, ds->St_f32);
 }
 
 } // namespace
@@ -355,9 +597,9 @@ extern "C" pq_status pq_general_encode(const pq_ctx *ctx, const pq_general_forma
     if (st != PQ_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (xt == PQ_BF16)
-        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_BF16>, dim3((unsigned)n_vectors), dim3(64), 0, s, g, x, ld_vector, n_vectors, ds->S_f32, records);
+        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_BF16>, dim3((unsigned)((n_vectors + kGenEncVecs - 1) / kGenEncVecs)), dim3(kGenEncThreads), 0, s, g, x, ld_vector, n_vectors, ds->S_f32, records);
     else
-        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_F32>, dim3((unsigned)n_vectors), dim3(64), 0, s, g, x, ld_vector, n_vectors, ds->S_f32, records);
+        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_F32>, dim3((unsigned)((n_vectors + kGenEncVecs - 1) / kGenEncVecs)), dim3(kGenEncThreads), 0, s, g, x, ld_vector, n_vectors, ds->S_f32, records);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
 }
@@ -394,9 +636,18 @@ extern "C" pq_status pq_general_attn_decode(const pq_ctx *ctx, const pq_general_
     const PqDeviceState *ds = nullptr;
     st = pq_device_state(ctx, &ds);
     if (st != PQ_OK) return st;
-    hipLaunchKernelGGL(pq_general_attn_kernel, dim3((unsigned)(B * Hq)), dim3(kGenAttnWaves * 64), 0, static_cast<hipStream_t>(hip_stream), g,
-                       static_cast<const uint16_t *>(q), out, k_records, v_records, seq_start, ctx_len, Hq, Hkv, pool_tokens,
-                       softmax_scale, ds->S_f32, ds->St_f32);
+    /* Heads of a kv head in one workgroup rebuild its tokens once for all of them: as soon as that leaves a workgroup for
+       every CU (2048 rows of 600 tokens: 146 us with four heads, 154 with two, 167 with one; 512 rows: 55 with two,
+       59 with one).  Below, a workgroup per head has more of the chip at work. */
+    const int64_t rows = (int64_t)B * Hq;
+    const int G = Hq / Hkv;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (G % 4 == 0 && rows >= 4 * 256)
+        launch_general_attn<4>(g, q, out, k_records, v_records, seq_start, ctx_len, rows, Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
+    else if (G % 2 == 0 && rows >= 2 * 256)
+        launch_general_attn<2>(g, q, out, k_records, v_records, seq_start, ctx_len, rows, Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
+    else
+        launch_general_attn<1>(g, q, out, k_records, v_records, seq_start, ctx_len, rows, Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
 }

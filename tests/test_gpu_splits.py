@@ -5,7 +5,8 @@ import pytest
 import torch
 
 import oracle
-from paper_2502_02617_amd import Context, PQ_KEY, PQ_VALUE, PolarQuantError, synth
+from paper_2502_02617_amd import (Context, GeneralFormat, PQ_KEY, PQ_VALUE, PolarQuantError, general_attn_decode,
+                                  general_encode, synth)
 from tests import helpers
 from tests.test_gpu_parity import DEV, build_cache, env, gpu_attention, say  # noqa: F401
 
@@ -89,3 +90,59 @@ def test_step_append_equals_bulk_append(B, Hkv, depth, hadamard):
     ctx.append_kv_pair(xk, xv, *caches[1], slot)
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(*caches))
+
+
+# the general format: heads per workgroup 1, 2 (512 rows) and 4 (1024 rows); lengths around the 128 tokens of a round
+@pytest.mark.parametrize("B,Hq,Hkv,bits", [(6, 7, 1, (4, 2, 2, 2, 2)), (130, 4, 2, (3, 3, 2, 3)), (130, 8, 2, (4, 3, 3, 3)),
+                                           (33, 32, 8, (3, 2, 3, 2, 3, 1))])
+def test_general_attention_heads_per_workgroup(B, Hq, Hkv, bits):
+    say(f"general attention, {B * Hq} rows, {Hq // Hkv} heads per kv head, bits {bits}")
+    ctx = Context(seed=14)
+    S, L = ctx.preconditioner(), len(bits)
+    fmt = GeneralFormat(L, bits)
+    cbg = oracle.general_codebooks(L, bits)
+    rng = np.random.default_rng(B)
+    lens = rng.integers(0, 70, size=B)
+    lens[:6] = [127, 128, 129, 256, 1, 0]
+    starts = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int64)
+    pool = int(lens.sum())
+    recs = []
+    for part in (0, 1):
+        x = synth.kv_stream(pool, Hkv, seed=600 + part).double().numpy().reshape(-1, 128)
+        recs.append(oracle.encode_general(x, S, L, bits, cbg).reshape(Hkv, pool, -1))
+    q = synth.queries(B, Hq, seed=78)
+    out = torch.full((B, Hq, 128), float("nan"), dtype=torch.float32, device=DEV)
+    # the records end where their allocation ends, and start one byte into it
+    dev = [torch.zeros(r.size + 1, dtype=torch.uint8, device=DEV)[1:].view(*r.shape) for r in recs]
+    for d, r in zip(dev, recs):
+        d.copy_(torch.from_numpy(r))
+    general_attn_decode(ctx, fmt, cbg, q.to(DEV), out, *dev, torch.from_numpy(starts).to(DEV),
+                        torch.from_numpy(lens.astype(np.int32)).to(DEV), helpers.softmax_scale())
+    torch.cuda.synchronize()
+    got = out.double().cpu().numpy()
+    ref = oracle.attention_general(q.double().numpy(), *recs, starts, lens.astype(np.int32), S, L, bits, cbg, helpers.softmax_scale())
+    assert np.all(np.isfinite(got)) and np.all(got[5] == 0.0)
+    err = helpers.rel_l2(got, ref)
+    say(f"  rel L2 {err:.2e}")
+    # fp32 throughout: an element of a key carries five roundings of 2^-24, a score of up to some 30 its product with them
+    assert err <= 5e-6
+
+
+@pytest.mark.parametrize("n,ld,shift", [(1, 128, 0), (15, 131, 1), (16, 128, 2), (17, 256, 3), (100, 129, 0)])
+def test_general_encode_groups(n, ld, shift):
+    """Sixteen vectors per workgroup: incomplete groups, rows at any stride, records at any byte."""
+    say(f"general encode of {n} vectors, stride {ld}")
+    ctx = Context(seed=15)
+    bits = (4, 2, 2, 2)
+    fmt = GeneralFormat(4, bits)
+    cbg = fmt.codebooks()
+    x = torch.randn((n, ld), generator=torch.Generator().manual_seed(n))
+    rec_or = oracle.encode_general(x[:, :128].double().numpy(), ctx.preconditioner(), 4, bits, oracle.general_codebooks(4, bits))
+    rb = fmt.record_bytes()
+    buf = torch.full((shift + n * rb + 5,), 0xA5, dtype=torch.uint8, device=DEV)
+    general_encode(ctx, fmt, cbg, x.to(DEV)[:, :128], buf[shift:])
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert np.all(got[:shift] == 0xA5) and np.all(got[shift + n * rb:] == 0xA5)
+    # at most one tie (an angle or a radius on a boundary) among these few values
+    assert np.count_nonzero(got[shift:shift + n * rb].reshape(n, rb) != rec_or) <= 1
