@@ -26,6 +26,12 @@
  *   host part knows the edges and treats the angles of a bin as spread evenly
  *   between them.
  * Counts are integers: the result does not depend on scheduling.
+ * Bound by the vector instructions of a tile (about 2000, a quarter of them
+ * reciprocals and square roots) and its 128 matrix instructions; the LDS
+ * atomics keep the LDS busy a third of the time.  262144 vectors 54.7 -> 44.1 us
+ * with the clear, 32768 (512 tiles) 35.0 -> 26.6: hardware square roots (a
+ * correctly rounded one takes a dozen instructions; 3900 per tile before),
+ * counters added to the call's in pairs, and short inputs spread over all CUs.
  */
 #include "pq_common.h"
 
@@ -68,12 +74,24 @@ __device__ __forceinline__ uint32_t fit_bf16_rne(float f)
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-/* bin of the angle of (u, v), both >= 0, among kBinsU bins uniform in t = v / (u + v); atan2(0, 0) counts as 0 */
-__device__ __forceinline__ int upper_bin(float u, float v)
+/* (u^2 + v^2)^(1/2) by the hardware's square root (1 ulp; a bin is some 4000 ulps wide) */
+__device__ __forceinline__ float fit_radius(float u, float v) { return __builtin_amdgcn_sqrtf(__builtin_fmaf(u, u, v * v)); }
+
+/* byte offset of the counter of t = part / sum among `bins` equal ones; atan2(0, 0) counts as 0 */
+template <int BINS>
+__device__ __forceinline__ uint32_t bin_offset(float part, float sum)
 {
-    const float t = v * __builtin_amdgcn_rcpf(fmaxf(u + v, 1e-37f));
-    return min((int)(t * (float)kBinsU), kBinsU - 1);
+    const float t = part * __builtin_amdgcn_rcpf(fmaxf(sum, 1e-37f));
+    return min((uint32_t)(t * (float)BINS), (uint32_t)BINS - 1u) << 2;
 }
+
+__device__ __forceinline__ void count_at(uint32_t *hist, uint32_t byte_offset)
+{
+    atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(hist) + byte_offset), 1u);
+}
+
+/* Counts the angle of (u, v), both >= 0, in a histogram of kBinsU bins uniform in t = v / (u + v). */
+__device__ __forceinline__ void count_upper(uint32_t *hist, float u, float v) { count_at(hist, bin_offset<kBinsU>(v, u + v)); }
 
 /* Angles of one block of 16 rotated coordinates into the LDS histograms; returns the block's radius. */
 __device__ __forceinline__ float count_block_angles(const f32x16 &y, uint32_t *sh)
@@ -82,14 +100,14 @@ __device__ __forceinline__ float count_block_angles(const f32x16 &y, uint32_t *s
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
         const float a = y[2 * p], b = y[2 * p + 1];
-        const float fa = fabsf(a), fb = fabsf(b);
-        const uint32_t sa = __float_as_uint(a) >> 31, sb = __float_as_uint(b) >> 31;
-        const uint32_t odd = sa ^ sb, quadrant = 2u * sb + odd; /* [0, 2 pi): (+,+), (-,+), (-,-), (+,-) */
-        const float t = (odd ? fa : fb) * __builtin_amdgcn_rcpf(fmaxf(fa + fb, 1e-37f));
-        const int bin = (int)quadrant * (kBins1 / 4) + min((int)(t * (float)(kBins1 / 4)), kBins1 / 4 - 1);
-        atomicAdd(&sh[bin], 1u);
-        r[p] = sqrtf(a * a + b * b);
+        /* quadrants of [0, 2 pi): (+,+), (-,+), (-,-), (+,-); the sign bits go straight to their places in the offset */
+        const uint32_t ub = __float_as_uint(b), x = __float_as_uint(a) ^ ub; /* sign of x: an odd quadrant */
+        const uint32_t quadrant = ((ub >> 17) & 0x4000u) | ((x >> 18) & 0x2000u);
+        const uint32_t in = bin_offset<kBins1 / 4>((int32_t)x < 0 ? fabsf(a) : fabsf(b), fabsf(a) + fabsf(b));
+        count_at(sh, quadrant | in);
+        r[p] = fit_radius(a, b);
     }
+    static_assert(kBins1 == 8192, "0x2000 bytes are a quadrant's 2048 counters");
     int base = kBins1;
 #pragma unroll
     for (int n = 4; n >= 1; n >>= 1) {
@@ -97,8 +115,8 @@ __device__ __forceinline__ float count_block_angles(const f32x16 &y, uint32_t *s
         for (int p = 0; p < 4; ++p) {
             if (p < n) {
                 const float u = r[2 * p], v = r[2 * p + 1];
-                atomicAdd(&sh[base + upper_bin(u, v)], 1u);
-                r[p] = sqrtf(u * u + v * v);
+                count_upper(sh + base, u, v);
+                r[p] = fit_radius(u, v);
             }
         }
         base += kBinsU;
@@ -106,11 +124,23 @@ __device__ __forceinline__ float count_block_angles(const f32x16 &y, uint32_t *s
     return r[0];
 }
 
+/* Adds a workgroup's counters to the call's, two at a time: no total reaches 2^32, so nothing carries from one into the
+   other. */
+__device__ __forceinline__ void add_counts(uint32_t *total, const uint32_t *sh, int n)
+{
+    const uint2 *pairs = reinterpret_cast<const uint2 *>(sh);
+    unsigned long long *out = reinterpret_cast<unsigned long long *>(total);
+    for (int c = threadIdx.x; c < n / 2; c += kFitThreads) {
+        const uint2 v = pairs[c];
+        if (v.x | v.y) atomicAdd(&out[c], ((unsigned long long)v.y << 32) | v.x);
+    }
+}
+
 template <int XT>
 __global__ __launch_bounds__(kFitThreads, 1) void pq_angle_histogram_kernel(FitArgs a)
 {
     __shared__ uint4 sS[kFitTerms * 4 * 8 * 64];    /* 64 KB */
-    __shared__ uint32_t sh[kHistSize + kHistUpper]; /* 80 KB */
+    __shared__ __attribute__((aligned(16))) uint32_t sh[kHistSize + kHistUpper]; /* 80 KB */
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     {
@@ -125,7 +155,8 @@ __global__ __launch_bounds__(kFitThreads, 1) void pq_angle_histogram_kernel(FitA
 
     const int j = lane & 31, H = lane >> 5; /* vector within a 32-vector half, lane half */
     constexpr int NXT = (XT == PQ_BF16) ? 1 : 2; /* bf16 terms of x */
-    for (int64_t item = (int64_t)blockIdx.x * kFitWaves + wave; item < a.n_items; item += (int64_t)gridDim.x * kFitWaves) {
+    /* consecutive tiles go to different workgroups: a short input occupies every CU */
+    for (int64_t item = (int64_t)wave * gridDim.x + blockIdx.x; item < a.n_items; item += (int64_t)gridDim.x * kFitWaves) {
         const int head = (int)(item / a.tiles_per_head);
         const int64_t t0 = (item % a.tiles_per_head) * kTileVecs;
         float rb[2][4]; /* radii of blocks 4H .. 4H+3 of this lane's two vectors */
@@ -185,26 +216,22 @@ __global__ __launch_bounds__(kFitThreads, 1) void pq_angle_histogram_kernel(FitA
             /* levels 5 and 6 inside the lane (blocks 4H .. 4H+3), level 7 joins the two lane halves */
 #pragma unroll
             for (int v = 0; v < 2; ++v) {
-                const float r50 = sqrtf(rb[v][0] * rb[v][0] + rb[v][1] * rb[v][1]);
-                const float r51 = sqrtf(rb[v][2] * rb[v][2] + rb[v][3] * rb[v][3]);
-                const float r6 = sqrtf(r50 * r50 + r51 * r51);
+                const float r50 = fit_radius(rb[v][0], rb[v][1]), r51 = fit_radius(rb[v][2], rb[v][3]);
+                const float r6 = fit_radius(r50, r51);
                 const float other = __shfl_xor(r6, 32);
                 if (valid[v]) {
                     uint32_t *up = sh + kHistSize;
-                    atomicAdd(&up[upper_bin(rb[v][0], rb[v][1])], 1u);
-                    atomicAdd(&up[upper_bin(rb[v][2], rb[v][3])], 1u);
-                    atomicAdd(&up[kBinsU + upper_bin(r50, r51)], 1u);
-                    if (H == 0) atomicAdd(&up[2 * kBinsU + upper_bin(r6, other)], 1u);
+                    count_upper(up, rb[v][0], rb[v][1]);
+                    count_upper(up, rb[v][2], rb[v][3]);
+                    count_upper(up + kBinsU, r50, r51);
+                    if (H == 0) count_upper(up + 2 * kBinsU, r6, other);
                 }
             }
         }
     }
     __syncthreads();
-    for (int c = tid; c < kHistSize; c += kFitThreads)
-        if (sh[c]) atomicAdd(&a.hist[c], sh[c]);
-    if (a.hist_up)
-        for (int c = tid; c < kHistUpper; c += kFitThreads)
-            if (sh[kHistSize + c]) atomicAdd(&a.hist_up[c], sh[kHistSize + c]);
+    add_counts(a.hist, sh, kHistSize);
+    if (a.hist_up) add_counts(a.hist_up, sh + kHistSize, kHistUpper);
 }
 
 /* angle of the lower edge of bin b of a level's histogram (b = bins gives the upper end of the range) */
@@ -337,8 +364,7 @@ extern "C" pq_status pq_fit_count_angles(const pq_ctx *ctx, const void *x, pq_dt
     a.S_bf16x3 = reinterpret_cast<const uint4 *>(ds->S_bf16x3);
     a.hist = hist;
     a.hist_up = upper ? hist + kHistSize : nullptr;
-    int64_t blocks = (a.n_items + kFitWaves - 1) / kFitWaves;
-    if (blocks > 256) blocks = 256;
+    const int64_t blocks = a.n_items < 256 ? a.n_items : 256;
     if (xt == PQ_BF16) hipLaunchKernelGGL(pq_angle_histogram_kernel<PQ_BF16>, dim3((unsigned)blocks), dim3(kFitThreads), 0, s, a);
     else hipLaunchKernelGGL(pq_angle_histogram_kernel<PQ_F32>, dim3((unsigned)blocks), dim3(kFitThreads), 0, s, a);
     PQ_HIP_TRY(hipGetLastError());

@@ -146,3 +146,36 @@ def test_general_encode_groups(n, ld, shift):
     assert np.all(got[:shift] == 0xA5) and np.all(got[shift + n * rb:] == 0xA5)
     # at most one tie (an angle or a radius on a boundary) among these few values
     assert np.count_nonzero(got[shift:shift + n * rb].reshape(n, rb) != rec_or) <= 1
+
+
+@pytest.mark.parametrize("depth", [4, 7])
+@pytest.mark.parametrize("n,H,dtype", [(1, 1, torch.float32), (63, 1, torch.bfloat16), (65, 3, torch.float32), (64, 255, torch.bfloat16),
+                                       (64, 257, torch.bfloat16), (2100, 130, torch.bfloat16)])
+def test_fit_counts(n, H, dtype, depth):
+    """Every angle is counted once whatever the spread of the tiles over the workgroups, and the histograms have the mean
+    of the exact angles to half a bin."""
+    say(f"angle counts of {n} x {H} vectors, depth {depth}")
+    ctx = Context(seed=6)
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    x = torch.randn((n, H, 128), generator=torch.Generator().manual_seed(n + H)).to(dtype)
+    ws = torch.full((Context.fit_workspace_bytes(),), 0xFF, dtype=torch.uint8, device=DEV)
+    ctx.fit_count_angles(x.to(DEV), ws)
+    torch.cuda.synchronize()
+    hist = ws.cpu().numpy().view(np.uint32)
+    r = x.reshape(-1, 128).double().numpy() @ ctx.preconditioner()
+    off = 0
+    for level in range(1, 8):
+        bins, per = (8192, 2048) if level == 1 else (2048, 2048)
+        h = hist[off:off + bins].astype(np.float64)
+        off += bins
+        assert h.sum() == (n * H * (128 >> level) if level <= depth else 0)
+        psi = np.arctan2(r[:, 1::2], r[:, 0::2])
+        if level == 1:
+            psi = np.where(psi < 0, psi + 2 * np.pi, psi)
+        r = np.hypot(r[:, 0::2], r[:, 1::2])
+        if level <= depth:
+            k = np.arange(bins + 1)
+            e = (k // per) * (np.pi / 2) + np.arctan2(k % per, per - k % per)
+            # half of the widest bin (9.8e-4 rad); the two-term product with S moves an angle by some 1e-5
+            assert abs((h * 0.5 * (e[1:] + e[:-1])).sum() / h.sum() - psi.mean()) <= 5.1e-4
