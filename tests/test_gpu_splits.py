@@ -179,3 +179,36 @@ def test_fit_counts(n, H, dtype, depth):
             e = (k // per) * (np.pi / 2) + np.arctan2(k % per, per - k % per)
             # half of the widest bin (9.8e-4 rad); the two-term product with S moves an angle by some 1e-5
             assert abs((h * 0.5 * (e[1:] + e[:-1])).sum() / h.sum() - psi.mean()) <= 5.1e-4
+
+
+@pytest.mark.parametrize("depth", [4, 7])
+@pytest.mark.parametrize("T,H,dtype", [(1, 1, torch.float32), (64, 127, torch.bfloat16), (64, 257, torch.float32), (130, 90, torch.bfloat16),
+                                       (64, 2050, torch.bfloat16)])
+def test_encode_spread_over_workgroups(T, H, dtype, depth):
+    """Whatever the number of tiles against the number of workgroups (and 256 x 8 wavefronts), a head's tiles are what a call
+    with that head alone writes; keys and values, single and paired calls."""
+    say(f"encode {T} tokens x {H} heads, depth {depth}")
+    ctx = Context(seed=7)
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    g = torch.Generator().manual_seed(T + H)
+    xk, xv = (torch.randn((T, H, 128), generator=g).to(dtype).to(DEV) for _ in range(2))
+    first, pool = 5, (5 + T + 63) // 64 * 64
+
+    def cache(heads):
+        c, r = ctx.alloc_cache_for(heads, pool, DEV)
+        return c.fill_(0x5A), r.fill_(0x1234)
+
+    single = [cache(H), cache(H)]
+    pair = [cache(H), cache(H)]
+    for (c, r), x, kind in zip(single, (xk, xv), (PQ_KEY, PQ_VALUE)):
+        ctx.encode_kv(x, kind, c, r, dst_token0=first)
+    ctx.encode_kv_pair(xk, xv, *pair[0], *pair[1], dst_token0=first)
+    torch.cuda.synchronize()
+    for (c, r), (c2, r2), x, kind in zip(single, pair, (xk, xv), (PQ_KEY, PQ_VALUE)):
+        assert torch.equal(c, c2) and torch.equal(r, r2)
+        for h in {0, H // 2, H - 1}:
+            c1, r1 = cache(1)
+            ctx.encode_kv(x[:, h:h + 1].contiguous(), kind, c1, r1, dst_token0=first)
+            torch.cuda.synchronize()
+            assert torch.equal(c[h], c1[0]) and torch.equal(r[h], r1[0])
