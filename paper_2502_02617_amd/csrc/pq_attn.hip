@@ -371,6 +371,9 @@ __device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &
         for (int j = 0; j < 4; ++j) {
             constexpr int set = b >> 2;         /* quarters 0..15 | 16..31 */
             const int abid = (4 * b + j) & 15;  /* compile-time after unrolling */
+            /* the groups' products first, then their sums: a sum would wait for the product just before it, and with two
+               wavefronts per SIMD nobody fills that wait (115.4 -> 112.4 us for the case above) */
+            f4 dg[NG];
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
                 f4 d;
@@ -386,9 +389,13 @@ __device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &
                     default: PQ_SCORE_CASE(15)
 #undef PQ_SCORE_CASE
                 }
-#pragma unroll
-                for (int h = 0; h < 4; ++h) s[g][h] = __builtin_fmaf(d[h], rq[j], s[g][h]);
+                dg[g] = d;
             }
+            if (NG > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+#pragma unroll
+                for (int h = 0; h < 4; ++h) s[g][h] = __builtin_fmaf(dg[g][h], rq[j], s[g][h]);
         }
     };
     block(std::integral_constant<int, 0>{}); block(std::integral_constant<int, 1>{});
@@ -463,19 +470,33 @@ __device__ __forceinline__ float wave_max_f(float x)
  * v_mfma_f32_16x16x32_f16.  The (cos, sin)-like pairs of a table entry are two coordinates of one
  * token, while a matrix-core operand wants several tokens of one coordinate per lane; instead of
  * transposing, the contraction index is widened to (token, parity): operand rows are coordinate
- * pairs, and the probability operand has one column per (pair, parity) with zeros in the slots of
- * the other parity.  The result accumulates o' for the even coordinates in the parity-0 columns and
+ * pairs, and the probability operand has one column per (pair, parity) -- up to eight pairs -- with zeros in the
+ * slots of the other parity.  The result accumulates o' for the even coordinates in the parity-0 columns and
  * for the odd ones in parity 1. */
 template <int NG, bool DEEP>
 __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_kernel(AttnArgs a)
 {
     constexpr int kWavesPerBlock = waves_per_block(NG), kThreads = kWavesPerBlock * 64;
+    /* The sixteen columns of a value product are up to eight pairs times two parities (with four pairs half of the columns
+       repeat the other half): NV products serve the NG groups of four pairs.  Four query tokens of four heads: a product
+       per group of four kept half of the matrix work idle and 32 more registers, 126.9 -> 117.3 us per call; 224 against
+       248 at twice the context.  The registers freed do not pay for a third wavefront per SIMD (121.2, it spills), nor
+       do those of two groups for a fourth (80.5 against 77.8). */
+    constexpr int kCols = NG == 1 ? 8 : 16, kPairs = kCols / 2, NV = NG == 1 ? 1 : NG / 2;
     const int G = a.Hq / a.Hkv; /* query heads per kv head: only the set-up and the epilogue of a piece depend on it */
-    __shared__ __attribute__((aligned(16))) uint32_t tab[kLdsTabDwords];
-    /* probabilities of a tile: sP[wave][group][column = pair slot + 4 parity][token] as dwords; a parity-0 column
+    /* One block, the tables first: the offset of a table inside LDS then fits a gather's 16-bit immediate.  (Laid out by
+       the compiler they came after the probabilities, beyond 64 KB with four groups: one more addition per gather, 117.3 against 115.4 us
+       for four query tokens of four heads.) */
+    struct Lds {
+        __attribute__((aligned(16))) uint32_t tab[kLdsTabDwords];
+        __attribute__((aligned(16))) uint32_t p[kWavesPerBlock][NV][kCols][64];
+    };
+    __shared__ Lds lds;
+    uint32_t (&tab)[kLdsTabDwords] = lds.tab;
+    /* probabilities of a tile: sP[wave][product][column = pair slot + kPairs * parity][token] as dwords; a parity-0 column
        keeps its binary16 value in the low half, a parity-1 column in the high half, and the other halves stay
        zero from the start of the kernel (nothing ever writes them) */
-    __shared__ __attribute__((aligned(16))) uint32_t sP[kWavesPerBlock][NG][8][64];
+    auto &sP = lds.p;
     __shared__ __attribute__((aligned(16))) uint16_t sVrad[DEEP ? kWavesPerBlock : 1][DEEP ? 512 : 8];
     /* per-sequence data of batches of up to 64 sequences is staged in LDS with the tables, so that
        nothing between the barrier and the first tile request waits for global memory; its loads
@@ -519,7 +540,7 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
         }
         if (threadIdx.x < 48) tup = src[PQ_TAB_UP + threadIdx.x];
         uint4 *pz = reinterpret_cast<uint4 *>(&sP[0][0][0][0]);
-        for (int t = threadIdx.x; t < kWavesPerBlock * NG * 8 * 64 / 4; t += kThreads) pz[t] = make_uint4(0, 0, 0, 0);
+        for (int t = threadIdx.x; t < kWavesPerBlock * NV * kCols * 64 / 4; t += kThreads) pz[t] = make_uint4(0, 0, 0, 0);
         if (threadIdx.x < 16) sDone[threadIdx.x >> 2][threadIdx.x & 3] = threadIdx.x < kWavesPerBlock ? 0 : 0x7FFFFFFF;
 #pragma unroll
         for (int i = 0; i < kR2; ++i) {
@@ -607,7 +628,7 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
     const char *tbh = reinterpret_cast<const char *>(tab + kTBH);
     /* where this lane (token) leaves its probabilities and where it (column) picks its operand up */
     uint32_t *p_mine = &sP[wave][0][0][lane];
-    const uint32_t *p_col = &sP[wave][0][n & 7][4 * g];
+    const uint32_t *p_col = &sP[wave][0][n & (kCols - 1)][4 * g];
     /* rotated queries and partial results: the launch code keeps all three below 4 GB */
     const __amdgpu_buffer_rsrc_t q_rsrc = stream_descriptor(a.qrot, (uint32_t)a.B * a.M * a.Hq * (PQ_D * 2u));
     const __amdgpu_buffer_rsrc_t o_rsrc = stream_descriptor(a.ws_o, (uint32_t)a.n_pieces * (a.M * G) * (PQ_D * 4u));
@@ -655,16 +676,17 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
                 qo.a[k][set].w[1] = real ? v.y : 0u;
             }
         }
-        f4 acc_o[NG][4];
+        f4 acc_o[NV][4];
         /* exponent reference of a pair: the same in all lanes; l: this lane's share of the sum of its token's weights */
         float m_ref[NG][4], l_run[NG][4];
 #pragma unroll
-        for (int k = 0; k < NG; ++k) {
+        for (int v = 0; v < NV; ++v)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc_o[k][c] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < 4; ++c) acc_o[v][c] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < NG; ++k)
 #pragma unroll
             for (int h = 0; h < 4; ++h) { m_ref[k][h] = 0.f; l_run[k][h] = 0.f; }
-        }
         bool have_ref = false; /* m_ref is a place holder until the first tile of the piece has set it */
 
         /* One tile.  MASKED: the tile holds tokens beyond the context, or beyond what one of the query
@@ -690,9 +712,11 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
 #pragma unroll
                 for (int h = 0; h < 4; ++h) top = fmaxf(top, s[k][h]);
             if (!have_ref || __ballot(top > kProbShift + kRefSlack) != 0ull) { /* wave-uniform */
+                float alpha_lane[NV]; /* factor of this lane's output column (pair n & (kPairs - 1) of the product) */
+#pragma unroll
+                for (int v = 0; v < NV; ++v) alpha_lane[v] = 1.f;
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
-                    float alpha_lane = 1.f; /* factor of this lane's output column (pair n & 3 of the group) */
 #pragma unroll
                     for (int h = 0; h < 4; ++h) {
                         const float smax = __builtin_amdgcn_readfirstlane(wave_max_f(s[k][h]));
@@ -704,11 +728,13 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
                         m_ref[k][h] += delta;
                         s[k][h] -= delta;
                         l_run[k][h] *= alpha;
-                        if ((n & 3) == h) alpha_lane = alpha;
+                        if ((n & (kPairs - 1)) == 4 * (k & 1) + h) alpha_lane[k / 2] = alpha;
                     }
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) acc_o[k][c] *= alpha_lane;
                 }
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc_o[v][c] *= alpha_lane[v];
                 have_ref = true;
             }
             wave_lds_fence(); /* the passes of the previous tile have read their operands */
@@ -721,11 +747,11 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
                     l_run[k][h] += p;
                     ph[h] = (_Float16)p;
                 }
-                _Float16 *dst = reinterpret_cast<_Float16 *>(p_mine + k * (8 * 64));
+                _Float16 *dst = reinterpret_cast<_Float16 *>(p_mine + ((k / 2) * kCols + 4 * (k & 1)) * 64);
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
-                    dst[2 * (h * 64)] = ph[h];                /* column (h, parity 0): low half */
-                    dst[2 * ((4 + h) * 64) + 1] = ph[h];      /* column (h, parity 1): high half */
+                    dst[2 * (h * 64)] = ph[h];                     /* column (pair, parity 0): low half */
+                    dst[2 * ((kPairs + h) * 64) + 1] = ph[h];      /* column (pair, parity 1): high half */
                 }
             }
             if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
@@ -735,12 +761,12 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
                 H8 va[4];
                 value_operand<i, MASKED, DEEP>(tab, tbh, vraw, va, nv, g, dr, lane);
 #pragma unroll
-                for (int k = 0; k < NG; ++k) {
+                for (int w = 0; w < NV; ++w) {
                     H8 pb;
-                    pb.q = *reinterpret_cast<const uint4 *>(p_col + k * (8 * 64) + 16 * i);
+                    pb.q = *reinterpret_cast<const uint4 *>(p_col + w * (kCols * 64) + 16 * i);
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        acc_o[k][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[c].v, pb.v, acc_o[k][c], 0, 0, 0);
+                        acc_o[w][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[c].v, pb.v, acc_o[w][c], 0, 0, 0);
                 }
             };
             pass(std::integral_constant<int, 0>{}); pass(std::integral_constant<int, 1>{});
@@ -804,20 +830,22 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
         /* ---- partial results: l summed over the tokens (lanes); o' scattered to coordinate order ---- */
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));
+        const int ne = lane_e & 15, ge = lane_e >> 4;
 #pragma unroll
-        for (int k = 0; k < NG; ++k) {
-            float l_pair[4];
+        for (int v = 0; v < NV; ++v) {
+            const int slot = ne & (kPairs - 1), pair = kPairs * v + slot;
+            float mm = 0.f, ll = 0.f; /* of this lane's pair */
 #pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                float l = l_run[k][h];
+            for (int k = 2 * v; k < 2 * v + kPairs / 4; ++k)
 #pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) l += __shfl_xor(l, d); /* the same order in every lane */
-                l_pair[h] = l;
-            }
-            const int ne = lane_e & 15, ge = lane_e >> 4;
-            const int pair = 4 * k + (ne & 3);
-            if (ne < 8 && pair < a.M * G) {
-                const int par = (ne >> 2) & 1;
+                for (int h = 0; h < 4; ++h) {
+                    float l = l_run[k][h];
+#pragma unroll
+                    for (int d = 32; d >= 1; d >>= 1) l += __shfl_xor(l, d); /* the same order in every lane */
+                    if (slot == 4 * (k & 1) + h) { mm = m_ref[k][h]; ll = l; }
+                }
+            if (ne < kCols && pair < a.M * G) {
+                const int par = ne / kPairs;
                 /* stores through descriptors as well: scalar piece offset, 32-bit lane offset */
                 const uint32_t piece_o = (uint32_t)piece * (uint32_t)(a.M * G) * (PQ_D * 4u);
                 const uint32_t lane_o = (uint32_t)(pair * PQ_D + 2 * 16 * ge + par) * 4u;
@@ -825,12 +853,9 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
                 for (int c = 0; c < 4; ++c)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc_o[k][c][e]), o_rsrc,
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc_o[v][c][e]), o_rsrc,
                                                               lane_o + 8u * (4 * e + c), piece_o, 0);
                 if (ge == 0 && par == 0) {
-                    const int h = ne & 3;
-                    const float mm = h == 0 ? m_ref[k][0] : (h == 1 ? m_ref[k][1] : (h == 2 ? m_ref[k][2] : m_ref[k][3]));
-                    const float ll = h == 0 ? l_pair[0] : (h == 1 ? l_pair[1] : (h == 2 ? l_pair[2] : l_pair[3]));
                     const uint32_t piece_ml = (uint32_t)piece * (uint32_t)(a.M * G) * 8u;
                     /* a pair that saw no token reports (-inf, 0), which the combine step drops */
                     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ll > 0.f ? mm : -INFINITY), ml_rsrc, pair * 8u, piece_ml, 0);
