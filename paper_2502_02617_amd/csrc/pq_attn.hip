@@ -1268,6 +1268,14 @@ __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, i
     uint4 krow_v[16]; /* the whole 256-byte row is requested at once: one memory round trip */
 #pragma unroll
     for (int c = 0; c < 16; ++c) krow_v[c] = krow[c];
+    /* and the value rows behind it (lane c: coordinates 2c, 2c + 1 of all 64; rows beyond the window re-read the last one
+       and get weight 0): they arrive while the scores are formed (fetched eight at a time after the scores, the launch took
+       12.1 us for 4 sequences of 256 window tokens, now 8.8; 64 sequences of 512: 86.5 -> 82.5 us per call) */
+    const uint32_t *vbase = reinterpret_cast<const uint32_t *>(a.win_v + (plane + t0) * PQ_D) + lane;
+    uint32_t vrow[64];
+#pragma unroll
+    for (int t = 0; t < 64; ++t) vrow[t] = vbase[(int64_t)min(t, n_valid - 1) * (PQ_D / 2)];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 16; ++c) { /* 8 coordinates per step */
         const uint4 kv = krow_v[c];
@@ -1303,23 +1311,17 @@ __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, i
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 
     /* weighted values: lane c owns coordinates 2c, 2c+1; tokens in order */
-    const uint32_t *vbase = reinterpret_cast<const uint32_t *>(a.win_v + (plane + t0) * PQ_D) + lane;
     float o0[G], o1[G];
 #pragma unroll
     for (int h = 0; h < G; ++h) { o0[h] = 0.f; o1[h] = 0.f; }
-    for (int tb = 0; tb < n_valid; tb += 8) { /* eight value rows in flight; rows beyond the window re-read the last one with weight 0 */
-        uint32_t two[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) two[k] = vbase[(int64_t)min(tb + k, n_valid - 1) * (PQ_D / 2)];
+    for (int t = 0; t < 64; ++t) {
+        const float v0 = __uint_as_float(vrow[t] << 16), v1 = __uint_as_float(vrow[t] & 0xFFFF0000u);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float v0 = __uint_as_float(two[k] << 16), v1 = __uint_as_float(two[k] & 0xFFFF0000u);
-#pragma unroll
-            for (int h = 0; h < G; ++h) {
-                const float p = tb + k < n_valid ? sp[wave][h][tb + k] : 0.f;
-                o0[h] = fmaf(p, v0, o0[h]);
-                o1[h] = fmaf(p, v1, o1[h]);
-            }
+        for (int h = 0; h < G; ++h) {
+            const float p = sp[wave][h][t]; /* 0 beyond the window */
+            o0[h] = fmaf(p, v0, o0[h]);
+            o1[h] = fmaf(p, v1, o1[h]);
         }
     }
 #pragma unroll
