@@ -21,9 +21,10 @@
  *      squared radii above level 1), which is the nearest-centroid rule of
  *      procedure Quant without evaluating an arctangent or, but for the
  *      block radius, a square root.
- *   3. The fields are assembled into whole dwords in registers (full tiles) or
- *      scattered with LDS atomics (partially written tiles) into an image of
- *      the tile in LDS, and the image is written out with full-width stores.
+ *   3. Whole tiles: the blocks' indices go through LDS to the lanes that own the
+ *      tile's bit strings, which join them in registers and store them.
+ *      Partially written tiles: the fields are scattered with LDS atomics into an
+ *      image of the tile, and the image is written out.
  *   At recursion depth 7 the recursion goes on over the block radii of a vector
  *   (levels 5, 6, 7) and one word per token replaces the block radii.
  */
@@ -81,25 +82,21 @@ union BOperand {
     uint32_t w[4];
 };
 
-/* Scatter the fields of block b of slot tau into the tile image (codes, then radii), without branches: every
- * field is shifted to its place inside a pair of dwords and OR-ed in.  The image is shared by the lanes of one
- * wavefront and the fields of different slots share dwords: LDS atomics.  CLEAR = false: the image started as
- * zeros (a tile written whole); CLEAR = true: it holds the tile's present contents and the field's bits are
- * cleared first.  The positions are those of pq_layout.h, written out per plane. */
-template <bool CLEAR>
+/* ---- partially written tiles: an image of the tile's present contents in LDS, into which the fields of block b of slot
+ * tau are scattered without branches: every field's bits are cleared and the field, shifted to its place inside a pair of
+ * dwords, is OR-ed in.  The image is shared by the lanes of one wavefront and the fields of different slots share
+ * dwords: LDS atomics.  The positions are those of pq_layout.h, written out per plane. ---- */
 __device__ __forceinline__ void put_pair(uint32_t *img, uint32_t at0, uint32_t at1, uint32_t field, uint32_t width, uint32_t sh)
 {
-    if (CLEAR) {
-        const uint64_t m = (uint64_t)((1u << width) - 1u) << sh;
-        atomicAnd(&img[at0], ~(uint32_t)m);
-        atomicAnd(&img[at1], ~(uint32_t)(m >> 32));
-    }
+    const uint64_t m = (uint64_t)((1u << width) - 1u) << sh;
+    atomicAnd(&img[at0], ~(uint32_t)m);
+    atomicAnd(&img[at1], ~(uint32_t)(m >> 32));
     const uint64_t w = (uint64_t)field << sh;
     atomicOr(&img[at0], (uint32_t)w);
     atomicOr(&img[at1], (uint32_t)(w >> 32));
 }
 
-template <int KIND, bool CLEAR, bool DEEP>
+template <int KIND, bool DEEP>
 __device__ __forceinline__ void emit_block(uint32_t *img, int tau, int b, const BlockCodes &bc)
 {
     const uint32_t q0 = bc.q[0], q1 = bc.q[1], q2 = bc.q[2], q3 = bc.q[3], bi = bc.bi;
@@ -116,12 +113,10 @@ __device__ __forceinline__ void emit_block(uint32_t *img, int tau, int b, const 
         /* 46 bits reach into a third dword when they start above bit 18 (never in the string's last dwords) */
         const bool third = sh > 18u;
         const uint32_t a0 = at(d), a1 = at(d + 1u), a2 = at(third ? d + 2u : d);
-        if (CLEAR) {
-            const uint64_t m = ((1ull << PQL_BLOCK_BITS) - 1ull) << sh;
-            atomicAnd(&img[a0], ~(uint32_t)m);
-            atomicAnd(&img[a1], ~((uint32_t)(m >> 32) << sh1));
-            if (third) atomicAnd(&img[a2], ~(0x3FFFu >> (32u - sh)));
-        }
+        const uint64_t m = ((1ull << PQL_BLOCK_BITS) - 1ull) << sh;
+        atomicAnd(&img[a0], ~(uint32_t)m);
+        atomicAnd(&img[a1], ~((uint32_t)(m >> 32) << sh1));
+        if (third) atomicAnd(&img[a2], ~(0x3FFFu >> (32u - sh)));
         const uint32_t lo = q0 | (q1 << 10) | (q2 << 20) | (q3 << 30), hi = (q3 >> 2) | (bi << 8); /* 32 + 14 bits */
         const uint64_t w = (((uint64_t)hi << 32) | lo) << sh;
         atomicOr(&img[a0], (uint32_t)w);
@@ -137,13 +132,109 @@ __device__ __forceinline__ void emit_block(uint32_t *img, int tau, int b, const 
         const uint32_t bit = PQL_SLOT_BITS * s, d = bit >> 5, sh = bit & 31u;
         /* the dword after a string's last one belongs to the next lane (or the next plane): it gets zeros */
         const uint32_t lam0 = 16u * g + 2u * b;
-        put_pair<CLEAR>(img, at(lam0, d), at(lam0, d + 1u), q0 | (q1 << 10), PQL_SLOT_BITS, sh);
-        put_pair<CLEAR>(img, at(lam0 + 1u, d), at(lam0 + 1u, d + 1u), q2 | (q3 << 10), PQL_SLOT_BITS, sh);
+        put_pair(img, at(lam0, d), at(lam0, d + 1u), q0 | (q1 << 10), PQL_SLOT_BITS, sh);
+        put_pair(img, at(lam0 + 1u, d), at(lam0 + 1u, d + 1u), q2 | (q3 << 10), PQL_SLOT_BITS, sh);
         const uint32_t bbit = 6u * s, base = PQL_OFF_VB / 4 + 3u * (8u * g + b) + (bbit >> 5);
-        put_pair<CLEAR>(img, base, base + 1u, bi, 6u, bbit & 31u);
+        put_pair(img, base, base + 1u, bi, 6u, bbit & 31u);
         radius_half = 16u * (8u * g + b) + s;
     }
     if (!DEEP) reinterpret_cast<uint16_t *>(img)[PQL_CODE_BYTES / 2 + radius_half] = bc.radius;
+}
+
+/* ---- whole tiles: every block leaves its indices and radius in LDS at a place of its own (plain writes, compile-time
+ * shifts), and once the tile is complete a lane reads the blocks of its strings, joins them and stores
+ * full-width dwords.  An image for whole tiles too, with its addresses and atomics, made the keys and values of 32768
+ * tokens 64.1 us against 57.6 (235 against 219 at four times as many; one-term S 43.3 against 41.8; value tiles
+ * gain most: 34.9 against 30.6 for 262144 vectors, keys 30.7 against 30.2).
+ *   keys:   [block][token] of two dwords: Q0 | Q1 << 10 | Q2 << 20 | Q3 << 30, then Q3 >> 2 | B << 8 | radius << 16
+ *   values: [half-block][token] of one dword: its two indices, for the first half also B << 20; behind them the
+ *           radii [block][token].  Rows of 68 dwords and 68 halves: the reads of 16 half-blocks (8 blocks) at one token
+ *           then fall on different banks. ---- */
+constexpr int kRow = 68, kRadiiAt = 16 * kRow /* dwords */, kWaveDwords = kRadiiAt + 8 * kRow / 2;
+
+template <int KIND, bool DEEP>
+__device__ __forceinline__ void leave_block(uint32_t *buf, int tau, int b, const BlockCodes &bc)
+{
+    if (KIND == PQ_KEY) {
+        const uint32_t lo = bc.q[0] | (bc.q[1] << 10) | (bc.q[2] << 20) | (bc.q[3] << 30);
+        uint32_t hi = (bc.q[3] >> 2) | (bc.bi << 8);
+        if (!DEEP) hi |= (uint32_t)bc.radius << 16;
+        *reinterpret_cast<uint2 *>(buf + 2 * (64 * b + tau)) = make_uint2(lo, hi);
+    } else {
+        buf[(2 * b) * kRow + tau] = bc.q[0] | (bc.q[1] << 10) | (bc.bi << 20);
+        buf[(2 * b + 1) * kRow + tau] = bc.q[2] | (bc.q[3] << 10);
+        if (!DEEP) reinterpret_cast<uint16_t *>(buf + kRadiiAt)[b * kRow + tau] = bc.radius;
+    }
+}
+
+/* `width` bits of v (the others zero) to bit BIT of the string w, whose bits from there on are zero */
+template <int BIT, int WIDTH>
+__device__ __forceinline__ void put_field(uint32_t *w, uint32_t v)
+{
+    constexpr int d = BIT >> 5, s = BIT & 31;
+    if constexpr (s == 0) w[d] = v;
+    else {
+        w[d] |= v << s;
+        if constexpr (s + WIDTH > 32) w[d + 1] = v >> (32 - s);
+    }
+}
+
+template <bool DEEP, int B>
+__device__ __forceinline__ void join_key_block(uint32_t (&w)[12], uint32_t (&rad)[4], const uint32_t *buf, int lane)
+{
+    const uint2 f = *reinterpret_cast<const uint2 *>(buf + 2 * (64 * B + lane));
+    put_field<PQL_BLOCK_BITS * B, 32>(w, f.x);
+    put_field<PQL_BLOCK_BITS * B + 32, 14>(w, DEEP ? f.y : f.y & 0x3FFFu);
+    if (!DEEP) rad[B / 2] = (B & 1) ? __builtin_amdgcn_perm(f.y, rad[B / 2], 0x07060100u) : f.y >> 16;
+}
+
+template <int I, bool DEEP>
+__device__ __forceinline__ void join_value_slots(uint32_t (&w)[10], uint32_t (&vb)[3], uint32_t (&rad)[4], const uint32_t *buf, int lane)
+{
+    const int g = lane >> 4, n = lane & 15;
+    const uint4 f = *reinterpret_cast<const uint4 *>(buf + n * kRow + 16 * I + 4 * g); /* slots 4 I .. 4 I + 3 */
+    put_field<PQL_SLOT_BITS * (4 * I), 20>(w, f.x & 0xFFFFFu);
+    put_field<PQL_SLOT_BITS * (4 * I + 1), 20>(w, f.y & 0xFFFFFu);
+    put_field<PQL_SLOT_BITS * (4 * I + 2), 20>(w, f.z & 0xFFFFFu);
+    put_field<PQL_SLOT_BITS * (4 * I + 3), 20>(w, f.w & 0xFFFFFu);
+    put_field<6 * (4 * I), 6>(vb, f.x >> 20);
+    put_field<6 * (4 * I + 1), 6>(vb, f.y >> 20);
+    put_field<6 * (4 * I + 2), 6>(vb, f.z >> 20);
+    put_field<6 * (4 * I + 3), 6>(vb, f.w >> 20);
+    if (!DEEP && I < 2) { /* half n & 1 of the block stores slots 8 (n & 1) .. + 7 of its radii */
+        const uint2 r = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(buf + kRadiiAt) + (n >> 1) * kRow +
+                                                         16 * (2 * (n & 1) + I) + 4 * g);
+        rad[2 * I] = r.x;
+        rad[2 * I + 1] = r.y;
+    }
+}
+
+/* the strings and radii of a whole tile, one lane per token (keys) or half-block of 16 tokens (values) */
+template <int KIND, bool DEEP>
+__device__ __forceinline__ void store_tile(const uint32_t *buf, uint8_t *gcodes, uint16_t *gradii, int lane)
+{
+    struct Three { uint32_t x, y, z; };
+    uint32_t rad[4];
+    if (KIND == PQ_KEY) {
+        uint32_t w[12];
+        join_key_block<DEEP, 0>(w, rad, buf, lane); join_key_block<DEEP, 1>(w, rad, buf, lane);
+        join_key_block<DEEP, 2>(w, rad, buf, lane); join_key_block<DEEP, 3>(w, rad, buf, lane);
+        join_key_block<DEEP, 4>(w, rad, buf, lane); join_key_block<DEEP, 5>(w, rad, buf, lane);
+        join_key_block<DEEP, 6>(w, rad, buf, lane); join_key_block<DEEP, 7>(w, rad, buf, lane);
+        reinterpret_cast<uint4 *>(gcodes + PQL_OFF_P0)[lane] = make_uint4(w[0], w[1], w[2], w[3]);
+        reinterpret_cast<uint4 *>(gcodes + PQL_OFF_P1)[lane] = make_uint4(w[4], w[5], w[6], w[7]);
+        reinterpret_cast<Three *>(gcodes + PQL_OFF_P2)[lane] = Three{w[8], w[9], w[10]};
+        reinterpret_cast<uint16_t *>(gcodes + PQL_OFF_KP3)[lane] = (uint16_t)w[11];
+    } else {
+        uint32_t w[10], vb[3];
+        join_value_slots<0, DEEP>(w, vb, rad, buf, lane); join_value_slots<1, DEEP>(w, vb, rad, buf, lane);
+        join_value_slots<2, DEEP>(w, vb, rad, buf, lane); join_value_slots<3, DEEP>(w, vb, rad, buf, lane);
+        reinterpret_cast<uint4 *>(gcodes + PQL_OFF_P0)[lane] = make_uint4(w[0], w[1], w[2], w[3]);
+        reinterpret_cast<uint4 *>(gcodes + PQL_OFF_P1)[lane] = make_uint4(w[4], w[5], w[6], w[7]);
+        reinterpret_cast<uint2 *>(gcodes + PQL_OFF_P2)[lane] = make_uint2(w[8], w[9]);
+        if ((lane & 1) == 0) reinterpret_cast<Three *>(gcodes + PQL_OFF_VB)[lane >> 1] = Three{vb[0], vb[1], vb[2]};
+    }
+    if (!DEEP) reinterpret_cast<uint4 *>(gradii)[lane] = make_uint4(rad[0], rad[1], rad[2], rad[3]);
 }
 
 /* lanes 0..31: the value of lane + 32; lanes 32..63: the value of lane - 32 */
@@ -163,10 +254,10 @@ __device__ __forceinline__ uint32_t from_other_half(uint32_t x, int upper_half)
    lane, level 7 joins the two halves with one lane exchange, and the vector's radius and upper
    codes go into its word of the radius plane. */
 /* LDS of the encode kernels, shared by all their variants (a workgroup runs alone on its CU):
-   S in A-operand order, 32 KB per bf16 term; one tile image per wavefront; the level-1 cell table of
-   caller-set codebooks. */
+   S in A-operand order, 32 KB per bf16 term; a tile's blocks, or the image of a partially written tile, per wavefront;
+   the level-1 cell table of caller-set codebooks. */
 __shared__ uint4 sS[3 * 4 * 8 * 64];
-__shared__ __align__(16) uint32_t sImg[8][TileImage<false>::dwords];
+__shared__ __align__(16) uint32_t sImg[8][kWaveDwords];
 __shared__ PqDeviceConsts::Lut1Cell sLut[512];
 
 /* The tiles of one launch share: wavefront w of workgroup `block` takes items w * n_blocks + block and then every
@@ -176,7 +267,7 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
 {
     constexpr int kImgDwords = TileImage<DEEP>::dwords, kRadiiHalves = TileImage<DEEP>::radii_halves;
     constexpr int kWaves = EncodeShape<XT>::waves, kThreads = kWaves * 64;
-    static_assert(kWaves == 8, "sImg holds eight tile images");
+    static_assert(kWaves == 8 && kImgDwords <= kWaveDwords && 8 * 64 * 2 <= kWaveDwords, "sImg: eight wavefronts, an image or the blocks of a tile");
     constexpr int kSChunks = NTERMS * 4 * 8 * 64;   /* 16-byte chunks of the copy of S that is used */
 
     const int lane = threadIdx.x & 63;
@@ -304,16 +395,13 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
         uint8_t *gcodes = a.codes + ((int64_t)head * a.pool_tiles + tile) * PQL_CODE_BYTES;
         uint16_t *gradii = a.radii + ((int64_t)head * a.pool_tiles + tile) * kRadiiHalves;
 
-        /* ---- tile image: zeros, or the tile's present contents if only part of it is written ---- */
-        if (full) {
-            for (int c = lane; c < kImgDwords / 4; c += 64) reinterpret_cast<uint4 *>(img)[c] = make_uint4(0u, 0u, 0u, 0u);
-        } else {
+        if (!full) { /* ---- image of a partially written tile: its present contents ---- */
             const uint32_t *gc = reinterpret_cast<const uint32_t *>(gcodes);
             const uint32_t *gr = reinterpret_cast<const uint32_t *>(gradii);
             for (int c = lane; c < PQL_CODE_BYTES / 4; c += 64) img[c] = gc[c];
             for (int c = lane; c < kRadiiHalves / 2; c += 64) img[PQL_CODE_BYTES / 4 + c] = gr[c];
+            wave_lds_sync();
         }
-        wave_lds_sync();
 
         for (int vt0 = 0; vt0 < 2; vt0 += NVT) {
             /* wave-uniform skip of a pass with nothing to write */
@@ -431,11 +519,11 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
                        recursion behind the branch and undo the interleaving above.) */
                     if (full) {
 #pragma unroll
-                        for (int v = 0; v < NVT; ++v) emit_block<KIND, false, DEEP>(img, tau[v], b, ps[v].out);
+                        for (int v = 0; v < NVT; ++v) leave_block<KIND, DEEP>(img, tau[v], b, ps[v].out);
                     } else {
 #pragma unroll
                         for (int v = 0; v < NVT; ++v)
-                            if (valid[v]) emit_block<KIND, true, DEEP>(img, tau[v], b, ps[v].out);
+                            if (valid[v]) emit_block<KIND, DEEP>(img, tau[v], b, ps[v].out);
                     }
                 }
             }
@@ -448,14 +536,18 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
                     other.q6 = __uint_as_float(from_other_half(__float_as_uint(mine.q6), H));
                     const uint32_t word = H == 0 ? polar_upper_join(mine, other, th.radius_scale, ut)
                                                  : polar_upper_join(other, mine, th.radius_scale, ut);
-                    if (H == 0 && valid[v]) img[PQL_CODE_BYTES / 4 + tau[v]] = word;
+                    if (H == 0 && valid[v]) {
+                        if (full) reinterpret_cast<uint32_t *>(gradii)[tau[v]] = word;
+                        else img[PQL_CODE_BYTES / 4 + tau[v]] = word;
+                    }
                 }
             }
         }
         wave_lds_sync();
 
-        /* ---- image -> global, 16 bytes per lane per store ---- */
-        {
+        if (full) {
+            store_tile<KIND, DEEP>(img, gcodes, gradii, lane);
+        } else { /* ---- image -> global, 16 bytes per lane per store ---- */
             const uint4 *src = reinterpret_cast<const uint4 *>(img);
             uint4 *dc = reinterpret_cast<uint4 *>(gcodes);
             uint4 *dr = reinterpret_cast<uint4 *>(gradii);
