@@ -53,6 +53,15 @@ __device__ __forceinline__ void dq_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
+/* The lane, as a value that the compiler takes for a new one at each call: what is derived from it is computed where it is
+   used and not kept in registers over the whole loop. */
+__device__ __forceinline__ int dq_lane()
+{
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 /* `width` bits at bit BIT of a string of dwords */
 template <int BIT, int WIDTH>
 __device__ __forceinline__ uint32_t dq_field(const uint32_t *w)
@@ -165,8 +174,10 @@ __device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, fl
  * held 16 coordinates of one token and every store touched 64 lines: 52 us for the case below, 106 to fp32.)
  *
  * Bound by the vector and matrix instructions (about 600 and 96 per half tile); the bytes alone would take 18 us of a
- * copy.  262144 vectors to bf16: 242 us with the generic bit reader and fp32 sums on 16 tokens per workgroup -> 32 us
- * for keys, 37 for values; to fp32 243 -> 55.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
+ * copy.  262144 vectors to bf16: 242 us with the generic bit reader and fp32 sums on 16 tokens per workgroup -> 33 us
+ * for keys, 35 for values; to fp32 243 -> 48 and 51.  Every register counts: with what follows from the lane number kept
+ * over the loop, up to 11 spilled registers cost values 39.5 us (fp32 57; Hadamard 34 against 28 now), and requesting the
+ * next half tile ahead of the products spills more than it hides (45).  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
  * spill 100 registers; value slots are read from an image in LDS because a token's 16 slots are spread over 16 strings. */
 template <int KIND, int OT, bool UNIT, bool ROTATED>
 __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs a)
@@ -177,7 +188,7 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
     __shared__ float2 tup[24];
     __shared__ __attribute__((aligned(16))) float sUn[kDecodeWaves][32];
     __shared__ __attribute__((aligned(16))) uint32_t img[KIND == PQ_VALUE ? kDecodeWaves : 1][KIND == PQ_VALUE ? kTileDwords : 4];
-    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, H = lane >> 5;
+    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const PqDeviceConsts &K = *a.consts;
     if (!ROTATED) {
@@ -217,6 +228,7 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
 
     /* consecutive half tiles go to different workgroups: a short range occupies every CU */
     for (int64_t item = (int64_t)wave * gridDim.x + blockIdx.x; item < a.n_items; item += (int64_t)kDecodeWaves * gridDim.x) {
+        const int lane = dq_lane(), j = lane & 31, H = lane >> 5;
         const int64_t full_tile = item >> 1, head = full_tile / a.n_tiles, tile = a.first_tile + (full_tile - head * a.n_tiles);
         const int half = (int)(item & 1), tau = 32 * half + j;
         const int64_t row0 = tile * 64 + 32 * half - a.token0; /* output row of the half tile's first slot */
@@ -283,6 +295,8 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
         if (!ROTATED) {
             const bool whole = a.paired && row0 >= 0 && row0 + 32 <= a.n_tokens; /* every store of the half tile is a pair */
             /* element offset of this lane's first token, column pair 0; the rows of a register differ by scalar multiples */
+            __builtin_amdgcn_sched_barrier(0);
+            const int lane = dq_lane(), j = lane & 31, H = lane >> 5;
             const int64_t row_h = row0 + 4 * H;
             int64_t at0 = row_h * a.ld_token + head * a.ld_head + 2 * j;
 #pragma unroll 1
