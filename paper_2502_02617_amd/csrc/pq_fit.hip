@@ -243,53 +243,88 @@ double bin_edge(int b, int bins, bool level1)
     return q * half_pi + atan2((double)k, (double)(per - k));
 }
 
-/* the bin edges of a level, ascending; formed once per process */
-const std::vector<double> &bin_edges(bool level1)
+/* the bins of a level: their edges, ascending, and the middle of each in units of 2^-60 rad; formed once per process */
+struct Bins {
+    std::vector<double> edge;
+    std::vector<uint64_t> middle;
+};
+
+const Bins &bins_of(bool level1)
 {
     auto make = [](int bins, bool first) {
-        std::vector<double> e((size_t)bins + 1);
-        for (int b = 0; b <= bins; ++b) e[b] = bin_edge(b, bins, first);
+        Bins e;
+        for (int b = 0; b <= bins; ++b) e.edge.push_back(bin_edge(b, bins, first));
+        for (int b = 0; b < bins; ++b) e.middle.push_back((uint64_t)ldexp(0.5 * (e.edge[b] + e.edge[b + 1]), 60));
         return e;
     };
-    static const std::vector<double> edges1 = make(kBins1, true), edges_upper = make(kBinsU, false);
-    return level1 ? edges1 : edges_upper;
+    static const Bins first = make(kBins1, true), upper = make(kBinsU, false);
+    return level1 ? first : upper;
 }
 
 /* k-means rounds on one level's histogram.  The angles of a bin are taken as spread evenly over
    it: a bin that a cell boundary (midpoint of two centroids) cuts gives each side its share of
    the count, centred on its part of the bin; an uncut bin stands for its centre.  Nearest
    centroid by linear distance (procedure Quant); a centroid whose cell is empty stays.
-   Running sums of the counts and of their first moments are formed once; a round then only looks up its cell
-   boundaries (walking over all bins in every round, and forming the edges in every call, took 430 us for
-   ten rounds on the four histograms of 262144 vectors; pq_fit_codebooks as a whole 565 -> 115 us). */
+   A cell is its part of its first bin, the whole bins behind it and its part of its last bin.  The parts are formed by
+   themselves; the whole bins come from running sums of counts and of counts times middles, which are integers (below 2^45 and
+   2^108), so that their differences are exact: a cell of a sliver of one bin keeps its centroid next to any count elsewhere.
+   (Running sums make a round a few lookups; walking over all bins in every round, and forming the edges in every call,
+   took 430 us for ten rounds on the four histograms of 262144 vectors; pq_fit_codebooks as a whole 565 -> 115 us.) */
 void lloyd_on_histogram(const uint32_t *hist, int bins, bool level1, int K, int iterations, double *c)
 {
-    const std::vector<double> &edges = bin_edges(level1);
-    std::vector<double> mass((size_t)bins + 1), moment((size_t)bins + 1); /* of the bins below b; counts are exact */
-    mass[0] = moment[0] = 0.0;
-    for (int b = 0; b < bins; ++b) {
-        mass[b + 1] = mass[b] + (double)hist[b];
-        moment[b + 1] = moment[b] + (double)hist[b] * 0.5 * (edges[b] + edges[b + 1]);
+    typedef unsigned __int128 wide;
+    const std::vector<double> &edge = bins_of(level1).edge;
+    const std::vector<uint64_t> &middle = bins_of(level1).middle;
+    struct Sum {
+        uint64_t count;
+        wide moment;
+    };
+    std::vector<Sum> run((size_t)bins / 8 + 1); /* of the bins below 8 r */
+    auto grow = [&](Sum &s, int b, int end) {
+        for (; b < end; ++b) {
+            s.count += hist[b];
+            s.moment += (wide)middle[b] * hist[b];
+        }
+    };
+    Sum all{0, 0};
+    for (int b = 0; b < bins; b += 8) {
+        run[b / 8] = all;
+        grow(all, b, b + 8);
     }
+    run[bins / 8] = all;
+    auto below = [&](int b) {
+        Sum s = run[b / 8];
+        grow(s, b & ~7, b);
+        return s;
+    };
+    auto bin_at = [&](double x) { return (int)(std::upper_bound(edge.begin(), edge.end(), x) - edge.begin()) - 1; };
     for (int it = 0; it < iterations; ++it) {
-        double below = 0.0, moment_below = 0.0; /* of the angles below the cell's lower boundary */
-        double next[16];
+        double next[16], from = edge[0];
+        int first = 0; /* the bin that `from` lies in */
         for (int k = 0; k < K; ++k) {
-            double upto = mass[bins], moment_upto = moment[bins];
-            if (k + 1 < K) {
-                const double edge = 0.5 * (c[k] + c[k + 1]);
-                const int b = (int)(std::upper_bound(edges.begin(), edges.end(), edge) - edges.begin()) - 1;
-                if (b < 0) {
-                    upto = moment_upto = 0.0;
-                } else if (b < bins) {
-                    const double lo = edges[b], part = (double)hist[b] * (edge - lo) / (edges[b + 1] - lo);
-                    upto = mass[b] + part;
-                    moment_upto = moment[b] + part * 0.5 * (lo + edge);
-                }
+            const double cut = k + 1 < K ? 0.5 * (c[k] + c[k + 1]) : edge[bins];
+            const double to = cut < edge[bins] ? cut : edge[bins];
+            next[k] = c[k];
+            if (!(to > from)) continue; /* the cell lies outside the range */
+            const int last = bin_at(to);
+            double mass = 0.0, sum = 0.0;
+            auto add = [&](int b, double lo, double hi) {
+                const double m = (double)hist[b] * ((hi - lo) / (edge[b + 1] - edge[b]));
+                mass += m;
+                sum += m * (0.5 * (lo + hi));
+            };
+            if (first == last) {
+                add(first, from, to);
+            } else {
+                add(first, from, edge[first + 1]);
+                const Sum hi = below(last), lo = below(first + 1);
+                mass += (double)(hi.count - lo.count);
+                sum += (double)(hi.moment - lo.moment) * 0x1p-60;
+                if (last < bins) add(last, edge[last], to);
             }
-            next[k] = upto > below ? (moment_upto - moment_below) / (upto - below) : c[k];
-            below = upto;
-            moment_below = moment_upto;
+            if (mass > 0.0) next[k] = std::min(std::max(sum / mass, from), to);
+            from = to;
+            first = last;
         }
         for (int k = 0; k < K; ++k) c[k] = next[k];
     }
