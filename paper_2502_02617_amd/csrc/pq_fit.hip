@@ -26,12 +26,13 @@
  *   host part knows the edges and treats the angles of a bin as spread evenly
  *   between them.
  * Counts are integers: the result does not depend on scheduling.
- * Bound by the vector instructions of a tile (about 2000, a quarter of them
- * reciprocals and square roots) and its 128 matrix instructions; the LDS
- * atomics keep the LDS busy a third of the time.  262144 vectors 54.7 -> 44.1 us
- * with the clear, 32768 (512 tiles) 35.0 -> 26.6: hardware square roots (a
- * correctly rounded one takes a dozen instructions; 3900 per tile before),
- * counters added to the call's in pairs, and short inputs spread over all CUs.
+ * Bound by the vector instructions of a tile, half of them in its square roots.
+ * Those are correctly rounded ones (a dozen instructions each): the hardware's
+ * alone would take 42.6 us instead of 51.8 for 262144 vectors with the clear, but
+ * it returns 0 for subnormal squares (every upper angle of a vector below 1e-19
+ * would count as 0), and its last bit moves nodes next to a bin edge.  Counters
+ * added to the call's in pairs and short inputs spread over all CUs: 8000 vectors
+ * 34.2 -> 21.7 us, 32768 34.3 -> 29.3, 262144 51.3 -> 51.8.
  */
 #include "pq_common.h"
 
@@ -74,8 +75,8 @@ __device__ __forceinline__ uint32_t fit_bf16_rne(float f)
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-/* (u^2 + v^2)^(1/2) by the hardware's square root (1 ulp; a bin is some 4000 ulps wide) */
-__device__ __forceinline__ float fit_radius(float u, float v) { return __builtin_amdgcn_sqrtf(__builtin_fmaf(u, u, v * v)); }
+/* (u^2 + v^2)^(1/2), correctly rounded */
+__device__ __forceinline__ float fit_radius(float u, float v) { return sqrtf(__builtin_fmaf(u, u, v * v)); }
 
 /* byte offset of the counter of t = part / sum among `bins` equal ones; atan2(0, 0) counts as 0 */
 template <int BINS>

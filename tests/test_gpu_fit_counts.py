@@ -1,0 +1,33 @@
+"""GPU test of the angle counts of vectors so small that the squares of their coordinates are subnormal numbers."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_02617_amd import Context
+from tests.test_gpu_parity import DEV, say
+
+pytestmark = pytest.mark.gpu
+
+
+def counts(ctx, x):
+    ws = torch.empty(Context.fit_workspace_bytes(), dtype=torch.uint8, device=DEV)
+    ctx.fit_count_angles(x.to(DEV), ws)
+    torch.cuda.synchronize()
+    return ws.view(torch.int32).cpu().long()
+
+
+@pytest.mark.parametrize("depth", [4, 7])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_counts_do_not_depend_on_the_scale_of_the_vectors(dtype, depth):
+    say(f"angle counts of small vectors, {dtype}, depth {depth}")
+    ctx = Context(S=np.eye(128))
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    x = torch.randn((3001, 2, 128), generator=torch.Generator().manual_seed(3)).to(dtype)
+    ref = counts(ctx, x)
+    assert torch.equal(counts(ctx, x * 2.0 ** -40), ref)       # all squares are normal numbers: the same operations
+    small = counts(ctx, x * 2.0 ** -63)
+    assert small.sum() == ref.sum()
+    # A square of z 2^-63 keeps z^2 2^23 units: an angle is off by about 1e-7 / z^2, a bin 5e-4 to 1e-3 wide, so fewer than
+    # one node in a hundred changes its bin (it leaves one and enters another).
+    assert (small - ref).abs().sum() <= 0.02 * ref.sum()
