@@ -1268,8 +1268,8 @@ __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, i
     uint4 krow_v[16]; /* the whole 256-byte row is requested at once: one memory round trip */
 #pragma unroll
     for (int c = 0; c < 16; ++c) krow_v[c] = krow[c];
-    /* and the value rows behind it (lane c: coordinates 2c, 2c + 1 of all 64; rows beyond the window re-read the last one
-       and get weight 0): they arrive while the scores are formed (fetched eight at a time after the scores, the launch took
+    /* and the value rows behind it (lane c: coordinates 2c, 2c + 1 of all 64; rows beyond the window re-read the last one):
+       they arrive while the scores are formed (fetched eight at a time after the scores, the launch took
        12.1 us for 4 sequences of 256 window tokens, now 8.8; 64 sequences of 512: 86.5 -> 82.5 us per call) */
     const uint32_t *vbase = reinterpret_cast<const uint32_t *>(a.win_v + (plane + t0) * PQ_D) + lane;
     uint32_t vrow[64];
@@ -1315,13 +1315,19 @@ __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, i
 #pragma unroll
     for (int h = 0; h < G; ++h) { o0[h] = 0.f; o1[h] = 0.f; }
 #pragma unroll
-    for (int t = 0; t < 64; ++t) {
-        const float v0 = __uint_as_float(vrow[t] << 16), v1 = __uint_as_float(vrow[t] & 0xFFFF0000u);
+    for (int t8 = 0; t8 < 64; t8 += 8) {
+        if (t8 >= n_valid) break; /* the same in all lanes */
 #pragma unroll
-        for (int h = 0; h < G; ++h) {
-            const float p = sp[wave][h][t]; /* 0 beyond the window */
-            o0[h] = fmaf(p, v0, o0[h]);
-            o1[h] = fmaf(p, v1, o1[h]);
+        for (int t = t8; t < t8 + 8; ++t) {
+            /* a row beyond the window is zeros: the repeated row times 0 would not be 0 where it holds an infinity */
+            const uint32_t two = t < n_valid ? vrow[t] : 0u;
+            const float v0 = __uint_as_float(two << 16), v1 = __uint_as_float(two & 0xFFFF0000u);
+#pragma unroll
+            for (int h = 0; h < G; ++h) {
+                const float p = sp[wave][h][t];
+                o0[h] = fmaf(p, v0, o0[h]);
+                o1[h] = fmaf(p, v1, o1[h]);
+            }
         }
     }
 #pragma unroll
