@@ -575,10 +575,12 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
     const int base = working > 0 ? total / working : 0, rem = total - base * working;
     /* Short shares: consecutive ones go to different workgroups, so that fewer shares than the launch has wavefronts
        occupy every CU (and its four SIMDs in turn) instead of filling the first CUs, and the wavefronts with one tile
-       more spread evenly (8700 tiles: 35.3 us per decode step against 37.4).  From four tiles on the order makes
+       more spread evenly (8700 tiles: 35.3 us per decode step against 37.4; 2048 tiles in shares of four, four column groups:
+       41.4 against 47.1).  From four tiles on, once every wavefront has a share, the order makes
        1 % at most, and a CU whose wavefronts read neighbouring tiles is the better one (117.0 against 117.8 us at
        65536 tiles, 126.9 against 127.9 at 25400 in four column groups). */
-    const int w = base < 4 ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kWavesPerBlock + wave;
+    const bool spread = base < 4 || working < (int)gridDim.x * kWavesPerBlock;
+    const int w = spread ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kWavesPerBlock + wave;
     if (w >= working) return;
     int gpos = w * base + min(w, rem);
     const int gend = min(gpos + base + (w < rem ? 1 : 0), total);

@@ -212,3 +212,35 @@ def test_encode_spread_over_workgroups(T, H, dtype, depth):
             ctx.encode_kv(x[:, h:h + 1].contiguous(), kind, c1, r1, dst_token0=first)
             torch.cuda.synchronize()
             assert torch.equal(c[h], c1[0]) and torch.equal(r[h], r1[0])
+
+
+# shares of exactly four tiles with wavefronts to spare (a workspace that holds no smaller shares), in each variant of the partial
+# kernel: 16, 12 and 8 wavefronts per workgroup
+@pytest.mark.parametrize("M,G,waves", [(1, 4, 16), (2, 4, 12), (4, 4, 8)])
+def test_four_tile_shares_of_a_full_batch(env, M, G, waves):  # noqa: F811
+    ctx, S, cb = env
+    B, Hkv, n = 1, 2, 2 * waves * 64
+    say(f"shares of four tiles: {B * Hkv * n // 64} tiles, {M} x {G} pairs")
+    caches, starts, _, k_rec, v_rec = build_cache(ctx, S, cb, [n], Hkv, seed=33000 + M)
+    q = synth.queries(B * M, Hkv * G, seed=33000 + M).reshape(B, M, Hkv * G, 128).contiguous()
+
+    def up(k):
+        return (k + 255) & ~255
+
+    pieces = waves + B * Hkv
+    coarse = up(up(up(B * M * Hkv * G * 256) + 4 * (2 + B + 1 + 2 * B * Hkv)) + pieces * M * G * 8) + pieces * M * G * 512
+    fine = Context.attn_mq_workspace_bytes(B, M, Hkv * G, Hkv, n)
+    assert coarse < fine
+    for nbytes in (coarse, fine):
+        out = torch.full((B, M, Hkv * G, 128), float("nan"), dtype=torch.float32, device=DEV)
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+        ctx.attn_decode_polar_mq(q.to(DEV), out, *caches, torch.from_numpy(starts).to(DEV),
+                                 torch.tensor([n], dtype=torch.int32, device=DEV), n, helpers.softmax_scale(), ws)
+        got = out.cpu().double().numpy()
+        for m in range(M):
+            ref = oracle.attention(q[:, m].double().numpy(), k_rec, v_rec, starts, np.array([n - (M - 1 - m)], np.int32), S, cb,
+                                   helpers.softmax_scale())
+            assert helpers.rel_l2(got[:, m], ref) <= 2e-3
+    with pytest.raises(PolarQuantError, match="PQ_ENOMEM"):
+        ctx.attn_decode_polar_mq(q.to(DEV), out, *caches, torch.from_numpy(starts).to(DEV),
+                                 torch.tensor([n], dtype=torch.int32, device=DEV), n, helpers.softmax_scale(), ws[:coarse - 1])
