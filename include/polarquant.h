@@ -319,11 +319,13 @@ pq_status pq_export_canonical(const pq_ctx *ctx, pq_kind kind, const uint8_t *co
  * the device: the work is split there into equal shares of 64-token tiles
  * per wavefront, whatever the mix of lengths, so a ragged batch costs what
  * its total number of cached tokens costs.
- * workspace (device): pq_attn_workspace_bytes(B, Hq, Hkv, max_ctx) bytes; contents
- * need not be preserved between calls.  A small problem is split into shares of
+ * workspace (device): pq_attn_workspace_bytes(B, Hq, Hkv, max_ctx) bytes, which
+ * never shrinks with B or max_ctx; contents need not be preserved between calls,
+ * and a larger workspace changes nothing.  A small problem is split into shares of
  * one tile; a workspace that only holds the partial results of shares of four
  * tiles is accepted as well (the work is then split that way, which changes the
- * last bits of the result), less is PQ_ENOMEM.
+ * last bits of the result), less is PQ_ENOMEM.  The same goes for the multi-query
+ * and hybrid calls below and their size functions.
  * ------------------------------------------------------------------------- */
 pq_status pq_attn_decode_polar(const pq_ctx *ctx, const void *q, void *out, pq_dtype out_dtype,
                                const uint8_t *k_codes, const uint16_t *k_radii,
@@ -371,7 +373,8 @@ pq_status pq_attn_decode_polar_static(const pq_ctx *ctx, const void *q, void *ou
  * ctx_len[b] - (M-1-m) cached tokens, i.e. up to and including its own (causal order,
  * Eq. 4-5 with K_{:i}).  The keys and values are rebuilt once per kv head for all
  * M * (Hq/Hkv) query rows, which is what makes this cheaper than M separate calls.
- * M * (Hq/Hkv) <= 16, else PQ_EUNSUPPORTED.  workspace: pq_attn_mq_workspace_bytes. */
+ * M * (Hq/Hkv) <= 16, else PQ_EUNSUPPORTED.  workspace: pq_attn_mq_workspace_bytes,
+ * a smaller one as in pq_attn_decode_polar. */
 pq_status pq_attn_decode_polar_mq(const pq_ctx *ctx, const void *q, void *out, pq_dtype out_dtype,
                                   const uint8_t *k_codes, const uint16_t *k_radii,
                                   const uint8_t *v_codes, const uint16_t *v_radii,
@@ -406,7 +409,8 @@ pq_status pq_decode_step_polar(const pq_ctx *ctx, const void *xk, const void *xv
  * contiguous; win_len (device): B entries, clamped to [0, win_cap]; the order
  * of the window tokens does not matter.  All other arguments as for
  * pq_attn_decode_polar (ctx_len counts the quantised tokens only); workspace:
- * at least pq_attn_hybrid_workspace_bytes(B, Hq, Hkv, max_ctx, win_cap) bytes.
+ * pq_attn_hybrid_workspace_bytes(B, Hq, Hkv, max_ctx, win_cap) bytes, a smaller one
+ * as in pq_attn_decode_polar.
  * A sequence with neither prefix nor window gives a zero output row.
  * Hq/Hkv at most 16.
  * ------------------------------------------------------------------------- */

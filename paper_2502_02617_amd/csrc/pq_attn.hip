@@ -1426,6 +1426,15 @@ Plan make_plan(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap = 0, int
     return fine.slots == coarse.slots ? fine : coarse;
 }
 
+/* What the size functions return: where shares of four tiles are planned, a smaller problem may want up to the static
+   scratch's size for shares of one, and a workspace sized for the larger problem has to hold that too. */
+size_t workspace_size(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap, int M)
+{
+    const Plan p = make_plan(B, Hq, Hkv, max_ctx, win_cap, M);
+    const bool fine = p.slots == make_plan_slots(B, Hq, Hkv, max_ctx, win_cap, M, kFineShareTiles).slots;
+    return fine || p.total > (size_t)PQ_STATIC_SCRATCH_BYTES ? p.total : (size_t)PQ_STATIC_SCRATCH_BYTES;
+}
+
 } // namespace
 
 extern "C" const char *pq_kernel_name_attn(void) { return "pq_attn_partial_kernel"; }
@@ -1433,19 +1442,19 @@ extern "C" const char *pq_kernel_name_attn(void) { return "pq_attn_partial_kerne
 extern "C" size_t pq_attn_workspace_bytes(int B, int Hq, int Hkv, int64_t max_ctx)
 {
     if (B <= 0 || Hq <= 0 || Hkv <= 0 || max_ctx < 0) return 0;
-    return make_plan(B, Hq, Hkv, max_ctx).total;
+    return workspace_size(B, Hq, Hkv, max_ctx, 0, 1);
 }
 
 extern "C" size_t pq_attn_mq_workspace_bytes(int B, int M, int Hq, int Hkv, int64_t max_ctx)
 {
     if (B <= 0 || M <= 0 || Hq <= 0 || Hkv <= 0 || max_ctx < 0) return 0;
-    return make_plan(B, Hq, Hkv, max_ctx, 0, M).total;
+    return workspace_size(B, Hq, Hkv, max_ctx, 0, M);
 }
 
 extern "C" size_t pq_attn_hybrid_workspace_bytes(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap)
 {
     if (B <= 0 || Hq <= 0 || Hkv <= 0 || max_ctx < 0 || win_cap < 0) return 0;
-    return make_plan(B, Hq, Hkv, max_ctx, win_cap).total;
+    return workspace_size(B, Hq, Hkv, max_ctx, win_cap, 1);
 }
 
 namespace {
