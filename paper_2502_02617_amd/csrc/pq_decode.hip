@@ -8,8 +8,8 @@
  * radius of node j splits into (r cos theta, r sin theta) with theta the
  * centroid selected by the node's code; after level 1 the 16 coordinates of
  * the block are known.  The optional trailing product with S^T is a 128x128
- * mat-vec per vector, on the matrix cores.  The export kernel reads the tile
- * through the generic field accessors and is not tuned.
+ * mat-vec per vector, on the matrix cores.  Without it, and in the export
+ * kernel, the tile is read through the generic field accessors.
  */
 #include <type_traits>
 
@@ -163,7 +163,7 @@ __device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, fl
 /* DeQuant, one wavefront per half tile (32 tokens of one head plane; four wavefronts per SIMD); lane (H, j) rebuilds blocks
  * 4 H .. 4 H + 3 of token j in fp32 from products of centroid cosines and sines (tables in LDS).
  *
- * The trailing S^T (not if ROTATED) runs on the matrix cores: out = y S^T with y and S each as two binary16 terms of 22
+ * The trailing S^T runs on the matrix cores: out = y S^T with y and S each as two binary16 terms of 22
  * significant bits (a power of two taken out of every token, so that its largest radius sits at 2^14, and out of S) and
  * the three products above 2^-22.  UNIT: all entries of S are +-1/sqrt(128); +-1 is one exact term and two products.
  * Against 64 bits the result is as exact as the fp32 sums in index order that this replaces (1.5e-7 of the vector's norm,
@@ -179,11 +179,11 @@ __device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, fl
  * over the loop, up to 11 spilled registers cost values 39.5 us (fp32 57; Hadamard 34 against 28 now), and requesting the
  * next half tile ahead of the products spills more than it hides (45).  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
  * spill 100 registers; value slots are read from an image in LDS because a token's 16 slots are spread over 16 strings. */
-template <int KIND, int OT, bool UNIT, bool ROTATED>
+template <int KIND, int OT, bool UNIT>
 __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs a)
 {
     constexpr int kChunks = 4 * 8 * 64; /* of eight halves: (64-coordinate group, parity), k-step, lane */
-    __shared__ uint4 sS[ROTATED ? 1 : (UNIT ? 1 : 2) * kChunks];
+    __shared__ uint4 sS[(UNIT ? 1 : 2) * kChunks];
     __shared__ __attribute__((aligned(16))) float tq[2][64][2], tb[64][4];
     __shared__ float2 tup[24];
     __shared__ __attribute__((aligned(16))) float sUn[kDecodeWaves][32];
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const PqDeviceConsts &K = *a.consts;
-    if (!ROTATED) {
+    {
         /* chunk (grp, par, ks, lane): S[64 grp + 2 (lane & 31) + par][64 (lane >> 5) + 8 ks .. + 7], the k order of the
            tokens' operand below */
         float4 s[kChunks / kDecodeThreads][2]; /* all requested before the first is stored */
@@ -251,12 +251,11 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
             for (int b = 0; b < 4; ++b) t.r[b] = pq_deep_block_radius(word, b5, b6, b7, tup, 4 * H + b);
             t.top = (word >> 16) & 0x7FFFu;
         }
-        float scale = 1.0f;
-        if (!ROTATED) { /* the token's largest radius goes to [2^14, 2^15) */
-            const uint32_t e = max(t.top >> 10, 1u);
-            scale = __uint_as_float((127u + 29u - e) << 23);
-            if (H == 0) sUn[wave][j] = UNIT ? __uint_as_float((127u - 29u + e) << 23) * PQ_INV_SQRT_D : __uint_as_float((127u - 44u + e) << 23);
-        }
+        /* the token's largest radius goes to [2^14, 2^15) */
+        const uint32_t exponent = max(t.top >> 10, 1u);
+        const float scale = __uint_as_float((127u + 29u - exponent) << 23);
+        if (H == 0)
+            sUn[wave][j] = UNIT ? __uint_as_float((127u - 29u + exponent) << 23) * PQ_INV_SQRT_D : __uint_as_float((127u - 44u + exponent) << 23);
         dq_h8 yh[8], yl[8]; /* k-step ks: coordinates 64 H + 8 ks .. + 7 */
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
@@ -271,28 +270,19 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
                 y[4 * k] = rq[k] * pa.x; y[4 * k + 1] = rq[k] * pa.y;
                 y[4 * k + 2] = rq[k] * pb.x; y[4 * k + 3] = rq[k] * pb.y;
             }
-            if (ROTATED) {
-                const int64_t row = row0 + j;
-                if (row >= 0 && row < a.n_tokens) {
-                    const int64_t at = row * a.ld_token + head * a.ld_head + 64 * H + 16 * b;
 #pragma unroll
-                    for (int e = 0; e < 16; e += 2) dq_store_pair<OT>(a.out, at + e, y[e], y[e + 1], a.paired != 0);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    /* the two terms must come from one and the same rounded product (the compiler would otherwise
-                       round the exact product to binary16 for the one and the fp32 product for the other) */
-                    asm("" : "+v"(y[e]));
-                    const _Float16 hi = (_Float16)y[e];
-                    yh[2 * b + (e >> 3)][e & 7] = hi;
-                    yl[2 * b + (e >> 3)][e & 7] = (_Float16)(y[e] - (float)hi);
-                }
-                __builtin_amdgcn_sched_barrier(0); /* gathers of all four blocks at once would not fit the registers */
+            for (int e = 0; e < 16; ++e) {
+                /* the two terms must come from one and the same rounded product (the compiler would otherwise
+                   round the exact product to binary16 for the one and the fp32 product for the other) */
+                asm("" : "+v"(y[e]));
+                const _Float16 hi = (_Float16)y[e];
+                yh[2 * b + (e >> 3)][e & 7] = hi;
+                yl[2 * b + (e >> 3)][e & 7] = (_Float16)(y[e] - (float)hi);
             }
+            __builtin_amdgcn_sched_barrier(0); /* gathers of all four blocks at once would not fit the registers */
         }
         dq_wave_sync(); /* the image is read before the next one replaces it; the scales are written */
-        if (!ROTATED) {
+        {
             const bool whole = a.paired && row0 >= 0 && row0 + 32 <= a.n_tokens; /* every store of the half tile is a pair */
             /* element offset of this lane's first token, column pair 0; the rows of a register differ by scalar multiples */
             __builtin_amdgcn_sched_barrier(0);
@@ -345,12 +335,69 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
     }
 }
 
+/* DeQuant without the trailing S^T: sixteen tokens per workgroup, a thread per (token, block) rebuilds its sixteen
+ * coordinates, and every row is then written by the 128 threads as whole lines; any strides.  Bound by the generic reader's
+ * loads and the stores: 262144 vectors to bf16 36 us for keys, 38 for values, to fp32 62 and 64.  (Stored by the kernel above
+ * from the lanes that rebuild them, a pair of coordinates and a line of its own per lane, they took 78 to 82 and 171 to 175.) */
+constexpr int kRotatedTokens = 16;
+
 template <int KIND, int OT>
-void launch_decode(const DecodeArgs &a, bool unit, int rotated, unsigned blocks, hipStream_t s)
+__global__ __launch_bounds__(128) void pq_decode_rotated_kernel(DecodeArgs a)
 {
-    if (rotated) hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, false, true>), dim3(blocks), dim3(kDecodeThreads), 0, s, a);
-    else if (unit) hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, true, false>), dim3(blocks), dim3(kDecodeThreads), 0, s, a);
-    else hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, false, false>), dim3(blocks), dim3(kDecodeThreads), 0, s, a);
+    __shared__ float sy[kRotatedTokens][PQ_D];
+    const int head = blockIdx.y, tid = threadIdx.x;
+    const int64_t t_base = (int64_t)blockIdx.x * kRotatedTokens;
+    const PqDeviceConsts &K = *a.consts;
+    const int64_t t = t_base + (tid >> 3);
+    if (t < a.n_tokens) {
+        const int b = tid & 7, tau = (int)((a.token0 + t) & 63);
+        const int64_t tile = head * a.pool_tiles + ((a.token0 + t) >> 6);
+        const uint8_t *tc = a.codes + tile * PQL_CODE_BYTES;
+        const uint16_t *tr = a.radii + tile * (a.deep ? PQ_DEEP_RADII_HALVES : PQL_RADII);
+        const PqBlockFields f = pql_read_block(KIND, tc, a.deep ? nullptr : tr, tau, b);
+        float r4;
+        if (a.deep)
+            r4 = pq_deep_block_radius(reinterpret_cast<const uint32_t *>(tr)[tau], K.up_bits[0], K.up_bits[1], K.up_bits[2],
+                                      reinterpret_cast<const float2 *>(&K.up_cs[0][0][0]), b);
+        else
+            r4 = (float)__builtin_bit_cast(_Float16, f.radius);
+        const float r3[2] = {r4 * K.cs234[2][f.c4][0], r4 * K.cs234[2][f.c4][1]};
+        float *y = &sy[tid >> 3][16 * b];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t g6 = f.g6[h], c2a = g6 >> 4, c3 = (g6 >> 2) & 3, c2b = g6 & 3;
+            const float r2a = r3[h] * K.cs234[1][c3][0], r2b = r3[h] * K.cs234[1][c3][1];
+            const float r1[4] = {r2a * K.cs234[0][c2a][0], r2a * K.cs234[0][c2a][1], r2b * K.cs234[0][c2b][0], r2b * K.cs234[0][c2b][1]};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t c1 = (f.l1 >> (4 * (4 * h + q))) & 15;
+                y[8 * h + 2 * q] = r1[q] * K.cs1[c1][0];
+                y[8 * h + 2 * q + 1] = r1[q] * K.cs1[c1][1];
+            }
+        }
+    }
+    __syncthreads();
+    const int n = (int)min((int64_t)kRotatedTokens, a.n_tokens - t_base);
+#pragma unroll
+    for (int k = 0; k < kRotatedTokens; ++k) {
+        if (k >= n) break;
+        const int64_t at = (t_base + k) * a.ld_token + head * a.ld_head + tid;
+        if (OT == PQ_F32) static_cast<float *>(a.out)[at] = sy[k][tid];
+        else static_cast<uint16_t *>(a.out)[at] = (uint16_t)(dq_bf16(sy[k][tid]) >> 16);
+    }
+}
+
+template <int KIND, int OT>
+void launch_decode(const DecodeArgs &a, bool unit, int rotated, int n_heads, hipStream_t s)
+{
+    if (rotated) {
+        const dim3 grid((unsigned)((a.n_tokens + kRotatedTokens - 1) / kRotatedTokens), (unsigned)n_heads);
+        hipLaunchKernelGGL((pq_decode_rotated_kernel<KIND, OT>), grid, dim3(128), 0, s, a);
+        return;
+    }
+    const dim3 grid((unsigned)(a.n_items < 256 ? a.n_items : 256)); /* one workgroup per CU */
+    if (unit) hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, true>), grid, dim3(kDecodeThreads), 0, s, a);
+    else hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, false>), grid, dim3(kDecodeThreads), 0, s, a);
 }
 
 struct ExportArgs {
@@ -438,14 +485,13 @@ extern "C" pq_status pq_decode_kv(const pq_ctx *ctx, pq_kind kind, const uint8_t
     a.consts = ds->consts; a.S = ds->S_f32;
     a.paired = ld_token % 2 == 0 && ld_head % 2 == 0; /* out itself is 16-byte aligned */
     a.deep = ctx->depth == 7 ? 1 : 0;
-    const unsigned blocks = (unsigned)(a.n_items < 256 ? a.n_items : 256); /* one workgroup per CU */
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (kind == PQ_KEY) {
-        if (ot == PQ_F32) launch_decode<PQ_KEY, PQ_F32>(a, ctx->unit_entries, rotated, blocks, s);
-        else launch_decode<PQ_KEY, PQ_BF16>(a, ctx->unit_entries, rotated, blocks, s);
+        if (ot == PQ_F32) launch_decode<PQ_KEY, PQ_F32>(a, ctx->unit_entries, rotated, n_heads, s);
+        else launch_decode<PQ_KEY, PQ_BF16>(a, ctx->unit_entries, rotated, n_heads, s);
     } else {
-        if (ot == PQ_F32) launch_decode<PQ_VALUE, PQ_F32>(a, ctx->unit_entries, rotated, blocks, s);
-        else launch_decode<PQ_VALUE, PQ_BF16>(a, ctx->unit_entries, rotated, blocks, s);
+        if (ot == PQ_F32) launch_decode<PQ_VALUE, PQ_F32>(a, ctx->unit_entries, rotated, n_heads, s);
+        else launch_decode<PQ_VALUE, PQ_BF16>(a, ctx->unit_entries, rotated, n_heads, s);
     }
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
