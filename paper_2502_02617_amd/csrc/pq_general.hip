@@ -21,6 +21,8 @@
  * accepts them too (same numbers, other layout), which is how it is tested
  * against them.
  */
+#include <type_traits>
+
 #include "pq_common.h"
 
 #include <cmath>
@@ -269,10 +271,10 @@ __device__ __forceinline__ float gen_wave_sum(float x)
     return x;
 }
 
-/* ---- attention: one workgroup of sixteen wavefronts per (sequence, HEADS query heads of one kv head) ----
+/* ---- attention: one workgroup of eight or sixteen wavefronts per (sequence, HEADS query heads of one kv head) ----
  * The entry point has no workspace, so a sequence is not split over workgroups; inside one, wavefront (tg, b) takes block
  * b (sixteen coordinates) of 64 tokens at a time, one token per lane:
- *   - the records of 128 tokens are copied to LDS, every record on a dword boundary, while the 128 before are worked on;
+ *   - the records of 64 or 128 tokens are copied to LDS, every record on a dword boundary, while those before are worked on;
  *   - a lane rebuilds its block from the codes on the path from the top radius down (the same fp32 products in the same
  *     order as DeQuant; fields are read with wave-uniform positions, centroids gathered from a 16-entry table), and leaves
  *     its part of the scores in LDS; the eight parts of a token are summed by every wavefront of its group;
@@ -280,8 +282,10 @@ __device__ __forceinline__ float gen_wave_sum(float x)
  *   - the weighted values stay in the lane (sixteen sums per head); lanes, token groups and S^T come at the end.
  * Bound by LDS reads (36 centroid gathers and 16 field reads per wavefront and 64 tokens), then by vector instructions
  * (some 330).  4 sequences of 2048 tokens, 8 query heads: 646 us with one token per wavefront at a time -> 46 us.
- * Rebuilding the values ahead of the weights measured the same here and 4 to 9 % slower on 512 rows and more. */
-constexpr int kGenAttnWaves = 16, kGenAttnTokens = 128;
+ * Rebuilding the values ahead of the weights measured the same here and 4 to 9 % slower on 512 rows and more.
+ * Sixteen wavefronts leave a lane 128 registers: enough for one head (124); two heads spilled 29 of them and four 66, which made
+ * a workgroup of two or four heads take 20 to 30 us however short its sequence.  Eight wavefronts (163 and 195 registers) spill
+ * nothing: 1024 rows of 10 tokens in fours 30.5 -> 14.6 us, of 600 tokens 63.9 -> 43.8. */
 constexpr int kGenMaxDwords = (69 + 3) / 4 + 1; /* dwords of a record in LDS (an odd number: token strides spread over the banks) */
 constexpr float kGenSlack = 16.f;
 
@@ -338,20 +342,21 @@ __device__ __forceinline__ uint32_t gen_load_dword(const uint8_t *rec, int k, in
 
 __device__ __forceinline__ int gen_dword_shift(int k, int rec_bytes) { return 8 * max(4 * k + 4 - rec_bytes, 0); }
 
-template <int HEADS>
-__global__ __launch_bounds__(kGenAttnWaves * 64) void pq_general_attn_kernel(GenFormat f, const uint16_t *q, float *out,
-                                                                             const uint8_t *k_rec, const uint8_t *v_rec,
-                                                                             const int64_t *seq_start, const int32_t *ctx_len,
-                                                                             int Hq, int Hkv, int64_t pool_tokens, float scale,
-                                                                             const float *S, const float *St)
+template <int HEADS, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_attn_kernel(GenFormat f, const uint16_t *q, float *out,
+                                                                                     const uint8_t *k_rec, const uint8_t *v_rec,
+                                                                                     const int64_t *seq_start, const int32_t *ctx_len,
+                                                                                     int Hq, int Hkv, int64_t pool_tokens, float scale,
+                                                                                     const float *S, const float *St)
 {
-    constexpr int kThreads = kGenAttnWaves * 64;
-    __shared__ uint32_t srec[2][2][kGenAttnTokens * kGenMaxDwords + 1]; /* [buffer][keys, values] */
+    constexpr int kThreads = WAVES * 64, kTokens = kThreads / 8; /* eight blocks of a token, one per wavefront */
+    constexpr int kGroups = kTokens / 64;
+    __shared__ uint32_t srec[2][2][kTokens * kGenMaxDwords + 1]; /* [buffer][keys, values] */
     __shared__ float2 cs[7][kGenMaxCells];
-    __shared__ float spart[HEADS][8][kGenAttnTokens];  /* a block's part of the scores; at the ends partial products with S */
+    __shared__ float spart[HEADS][8][PQ_D];  /* a block's part of the scores; at the ends partial products with S */
     __shared__ __attribute__((aligned(16))) float sq[HEADS][PQ_D];
     __shared__ float so[HEADS][PQ_D]; /* sq: q, then its rotation; so: the weighted values */
-    __shared__ float part_o[HEADS][2][PQ_D], part_m[HEADS][2], part_l[HEADS][2];
+    __shared__ float part_o[HEADS][kGroups][PQ_D], part_m[HEADS][kGroups], part_l[HEADS][kGroups];
     const int groups = Hq / HEADS, b = blockIdx.x / groups, head0 = (blockIdx.x % groups) * HEADS, hk = head0 / (Hq / Hkv);
     const int64_t row0 = (int64_t)b * Hq + head0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -360,9 +365,9 @@ __global__ __launch_bounds__(kGenAttnWaves * 64) void pq_general_attn_kernel(Gen
     const int64_t t0 = seq_start[b];
     if (n < 0 || t0 < 0 || t0 + n > pool_tokens) n = 0; /* a sequence outside the pool is treated as empty */
 
-    /* records of tokens [first, first + 128) of the sequence: dword (stream, token, k) -> registers -> LDS */
-    const int per_stream = kGenAttnTokens * f.rec_dwords;
-    constexpr int kMaxStage = (2 * kGenAttnTokens * (kGenMaxDwords - 1) + kThreads - 1) / kThreads;
+    /* records of tokens [first, first + kTokens) of the sequence: dword (stream, token, k) -> registers -> LDS */
+    const int per_stream = kTokens * f.rec_dwords;
+    constexpr int kMaxStage = (2 * kTokens * (kGenMaxDwords - 1) + kThreads - 1) / kThreads;
     uint32_t stage[kMaxStage];
     const int64_t slot0 = (int64_t)hk * pool_tokens + t0;
     struct Place { int stream, t, k; };
@@ -396,18 +401,21 @@ __global__ __launch_bounds__(kGenAttnWaves * 64) void pq_general_attn_kernel(Gen
     __syncthreads();
     /* product of HEADS vectors with a matrix: thread (part, c) sums sixteen terms of column c, eight parts */
     auto times_matrix = [&](const float (&in)[HEADS][PQ_D], const float *M) {
-        const int part = tid >> 7, c = tid & 127;
-        float acc[HEADS];
+        const int c = tid & 127;
 #pragma unroll
-        for (int h = 0; h < HEADS; ++h) acc[h] = 0.f;
+        for (int part = tid >> 7; part < 8; part += kThreads / PQ_D) {
+            float acc[HEADS];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const float m = M[(16 * part + k) * PQ_D + c];
+            for (int h = 0; h < HEADS; ++h) acc[h] = 0.f;
 #pragma unroll
-            for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(in[h][16 * part + k], m, acc[h]);
+            for (int k = 0; k < 16; ++k) {
+                const float m = M[(16 * part + k) * PQ_D + c];
+#pragma unroll
+                for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(in[h][16 * part + k], m, acc[h]);
+            }
+#pragma unroll
+            for (int h = 0; h < HEADS; ++h) spart[h][part][c] = acc[h];
         }
-#pragma unroll
-        for (int h = 0; h < HEADS; ++h) spart[h][part][c] = acc[h];
         __syncthreads();
     };
     auto product = [&](int h, int c) {
@@ -438,9 +446,9 @@ __global__ __launch_bounds__(kGenAttnWaves * 64) void pq_general_attn_kernel(Gen
     }
     const int tok = 64 * tg + lane;
     int cur = 0;
-    for (int64_t first = 0; first < n; first += kGenAttnTokens, cur ^= 1) { /* n is the same in all threads */
-        const bool more = first + kGenAttnTokens < n;
-        if (more) fetch(first + kGenAttnTokens);
+    for (int64_t first = 0; first < n; first += kTokens, cur ^= 1) { /* n is the same in all threads */
+        const bool more = first + kTokens < n;
+        if (more) fetch(first + kTokens);
         {
             float v[16];
             gen_block(f, srec[cur][0] + tok * kGenMaxDwords, cs, blk, v);
@@ -523,10 +531,10 @@ __global__ __launch_bounds__(kGenAttnWaves * 64) void pq_general_attn_kernel(Gen
     __syncthreads();
     for (int t = tid; t < HEADS * PQ_D; t += kThreads) {
         const int h = t >> 7, c = t & 127;
-        const float mm = fmaxf(part_m[h][0], part_m[h][1]);
+        const float mm = fmaxf(part_m[h][0], part_m[h][kGroups - 1]);
         float lt = 0.f, a = 0.f;
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
+        for (int g = 0; g < kGroups; ++g) {
             const float w = part_m[h][g] == -INFINITY ? 0.f : expf(part_m[h][g] - mm); /* a group without a token */
             lt = fmaf(part_l[h][g], w, lt);
             a = fmaf(part_o[h][g][c], w, a);
@@ -538,12 +546,12 @@ __global__ __launch_bounds__(kGenAttnWaves * 64) void pq_general_attn_kernel(Gen
     for (int t = tid; t < HEADS * PQ_D; t += kThreads) out[row0 * PQ_D + t] = product(t >> 7, t & 127);
 }
 
-template <int HEADS>
+template <int HEADS, int WAVES>
 void launch_general_attn(const GenFormat &g, const void *q, float *out, const uint8_t *k, const uint8_t *v, const int64_t *start,
                          const int32_t *len, int64_t rows, int Hq, int Hkv, int64_t pool, float scale, const PqDeviceState *ds,
                          hipStream_t s)
 {
-    hipLaunchKernelGGL(pq_general_attn_kernel<HEADS>, dim3((unsigned)(rows / HEADS)), dim3(kGenAttnWaves * 64), 0, s, g,
+    hipLaunchKernelGGL((pq_general_attn_kernel<HEADS, WAVES>), dim3((unsigned)(rows / HEADS)), dim3(WAVES * 64), 0, s, g,
                        static_cast<const uint16_t *>(q), out, k, v, start, len, Hq, Hkv, pool, scale, ds->S_f32, ds->St_f32);
 }
 
@@ -637,17 +645,26 @@ extern "C" pq_status pq_general_attn_decode(const pq_ctx *ctx, const pq_general_
     st = pq_device_state(ctx, &ds);
     if (st != PQ_OK) return st;
     /* Heads of a kv head in one workgroup rebuild its tokens once for all of them: as soon as that leaves a workgroup for
-       every CU (2048 rows of 600 tokens: 146 us with four heads, 154 with two, 167 with one; 512 rows: 55 with two,
-       59 with one).  Below, a workgroup per head has more of the chip at work. */
+       every CU (2048 rows of 600 tokens: 85.5 us with four heads, 100.6 with two, 107.5 with one; 1024 rows of 10 tokens: 14.5, 18.0
+       and 18.3; 512 rows of 2000 tokens: 67 with two, 82 with one).  Below, a workgroup per head has more of the chip at work: sixteen
+       wavefronts while every one finds a CU, else eight, two workgroups to a CU (300 rows of 4 tokens: 11.3 us against
+       18.5 in two rounds of sixteen, of 600 tokens 30 against 38). */
     const int64_t rows = (int64_t)B * Hq;
     const int G = Hq / Hkv;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (G % 4 == 0 && rows >= 4 * 256)
-        launch_general_attn<4>(g, q, out, k_records, v_records, seq_start, ctx_len, rows, Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
-    else if (G % 2 == 0 && rows >= 2 * 256)
-        launch_general_attn<2>(g, q, out, k_records, v_records, seq_start, ctx_len, rows, Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
-    else
-        launch_general_attn<1>(g, q, out, k_records, v_records, seq_start, ctx_len, rows, Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
+    auto launch = [&](auto heads, auto waves) {
+        launch_general_attn<decltype(heads)::value, decltype(waves)::value>(g, q, out, k_records, v_records, seq_start, ctx_len, rows,
+                                                                            Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
+    };
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 4> four{};
+    constexpr std::integral_constant<int, 8> eight{};
+    constexpr std::integral_constant<int, 16> sixteen{};
+    if (G % 4 == 0 && rows >= 4 * 256) launch(four, eight);
+    else if (G % 2 == 0 && rows >= 2 * 256) launch(two, eight);
+    else if (rows > 256) launch(one, eight);
+    else launch(one, sixteen);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
 }

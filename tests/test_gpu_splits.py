@@ -244,3 +244,10 @@ def test_four_tile_shares_of_a_full_batch(env, M, G, waves):  # noqa: F811
     with pytest.raises(PolarQuantError, match="PQ_ENOMEM"):
         ctx.attn_decode_polar_mq(q.to(DEV), out, *caches, torch.from_numpy(starts).to(DEV),
                                  torch.tensor([n], dtype=torch.int32, device=DEV), n, helpers.softmax_scale(), ws[:coarse - 1])
+
+
+# one head per workgroup: sixteen wavefronts up to 256 rows, then eight
+@pytest.mark.parametrize("B,Hq,Hkv,bits", [(256, 1, 1, (4, 2, 2, 2, 2)), (257, 1, 1, (3, 3, 2, 3)), (40, 7, 1, (4, 3, 3, 3)),
+                                           (73, 7, 1, (4, 2, 2, 2, 2))])
+def test_general_attention_one_head_per_workgroup(B, Hq, Hkv, bits):
+    test_general_attention_heads_per_workgroup(B, Hq, Hkv, bits)
