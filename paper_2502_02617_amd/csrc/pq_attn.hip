@@ -135,7 +135,6 @@ union H4 {
 };
 
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
-__device__ __forceinline__ uint32_t as_u32(h2 v) { return __builtin_bit_cast(uint32_t, v); }
 
 __device__ __forceinline__ h2 bcast_lo(h2 v) { return h2{v.x, v.x}; }
 __device__ __forceinline__ h2 bcast_hi(h2 v) { return h2{v.y, v.y}; }
@@ -892,8 +891,7 @@ struct RotateArgs {
 
 /* Four query rows per workgroup: the workgroup's slice of S (64 KB, what bounds this launch) is
  * fetched once for the four.  Thread (kq, j) accumulates the quarter kq of the sum over i for
- * column j of each row; thread (r, j) then adds the four quarters of row r in a fixed order
- * (the same order as vector_times_slice). */
+ * column j of each row; thread (r, j) then adds the four quarters of row r in a fixed order. */
 constexpr int kRotateRows = 4;
 
 __device__ __forceinline__ void rotate_query_rows(const RotateArgs &a, int row0, int n_rows)

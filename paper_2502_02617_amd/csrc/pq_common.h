@@ -136,12 +136,12 @@ void pq_lloyd_max(int level, int K, double *centroids, double *boundaries);
 
 static inline bool pq_aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-/* ---- small dense products with S: one vector per 512-thread workgroup ----
- * out[j] = sum_k in[k] * M[k*128 + j].  Thread (kq, j) accumulates the k-quarter kq with
- * all 32 loads in flight at once (these kernels are latency bound, not bandwidth bound);
- * the four quarter sums are added in a fixed order by the threads of quarter 0.
- * The matrix part does not depend on the vector: a kernel requests it first
- * (matrix_slice_load) and overlaps its latency with fetching the vector. */
+/* ---- small dense products with S: one to four vectors per 512-thread workgroup ----
+ * out[j] = sum_k in[k] * M[k*128 + j].  Thread (kq, j) accumulates the k-quarter kq of every vector;
+ * the four quarter sums are then added in a fixed order.
+ * The thread's part of the matrix does not depend on the vectors: a kernel requests it first, all 32
+ * loads in flight at once (these kernels are latency bound, not bandwidth bound), and overlaps its
+ * latency with fetching the vectors. */
 struct MatrixSlice {
     float m[32];
 };
@@ -151,18 +151,6 @@ static __device__ __forceinline__ void matrix_slice_load(MatrixSlice &s, const f
     const int kq = tid >> 7, j = tid & 127;
 #pragma unroll
     for (int k = 0; k < 32; ++k) s.m[k] = M[(32 * kq + k) * PQ_D + j];
-}
-
-static __device__ __forceinline__ float vector_times_slice(const float (&sin)[PQ_D], const MatrixSlice &s,
-                                                           float (&spart)[4][PQ_D], int tid)
-{
-    const int kq = tid >> 7, j = tid & 127;
-    float acc = 0.f;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) acc = fmaf(sin[32 * kq + k], s.m[k], acc);
-    spart[kq][j] = acc;
-    __syncthreads();
-    return ((spart[0][j] + spart[1][j]) + spart[2][j]) + spart[3][j];
 }
 
 #if defined(__HIPCC__)
