@@ -100,6 +100,10 @@ struct pq_ctx {
     /* every entry of S is +-1/sqrt(d) (a sign-flipped Hadamard matrix, say): sqrt(d) * S is then
        exact in bf16 and the encode kernel multiplies by one term instead of three */
     bool unit_entries;
+    /* S spreads every coordinate over every pair (2 p, 2 p + 1) of the result: the larger of the pair's two entries is
+       2^-16 at least.  An error of 2^-40 of a vector's largest coordinate is then below the fp32 rounding of any
+       rotated pair. */
+    bool mixing;
     PqHadamard hadamard;    /* on: S is D H / sqrt(d) exactly (found by comparing the entries) */
     bool general_codebooks; /* codebooks replaced by pq_set_codebooks */
     double centroids[4][16];

@@ -3,14 +3,16 @@
  * lines 2 and 4 (precondition with S, procedure Polar, procedure Quant) plus
  * bit-packing into the tile layout, for gfx950.
  *
- * Bulk kernel (pq_encode_kv, and for keys and values in one launch
+ * Bulk kernels (pq_encode_kv, and for keys and values in one launch
  * pq_encode_kv_pair; the append kernel lives in pq_polar.h):
- * one wavefront owns one destination tile (64 token slots of one head plane).
+ * one wavefront owns one destination tile (64 token slots of one head plane);
+ * where there are few tiles, a workgroup does.
  *   1. y = x * S on the matrix cores.  S is held as three bf16 terms
  *      S1 + S2 + S3 (24 significant bits) so that bf16 MFMAs with fp32
  *      accumulation reproduce an fp32-accurate rotation; bf16 inputs are
- *      exact operands, fp32 inputs are split the same way (x1 + x2 + x3) and
- *      the six products above 2^-24 are accumulated.
+ *      exact operands.  fp32 inputs and S are two binary16 terms each and the
+ *      three products above 2^-24 are accumulated (three bf16 terms and six
+ *      products where S leaves coordinates unmixed).
  *      The product is computed transposed, D = S^T-tile (32 rotated
  *      coordinates) x X^T (32 vectors), with the rows of each S^T tile
  *      ordered so that a lane ends up with complete blocks of 16 consecutive
@@ -28,13 +30,17 @@
  *   At recursion depth 7 the recursion goes on over the block radii of a vector
  *   (levels 5, 6, 7) and one word per token replaces the block radii.
  */
+#include <type_traits>
+
 #include "pq_common.h"
 #include "pq_polar.h"
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 /* wavefronts per workgroup (two per SIMD: the kernel uses the whole register file).  Sixteen
    wavefronts working on one 32-vector half at a time in 128 registers measured slower: every
@@ -78,6 +84,7 @@ __device__ __forceinline__ uint32_t bf16_rne_bits(float f)
 
 union BOperand {
     bf16x8 v;
+    f16x8 h;
     uint4 q;
     uint32_t w[4];
 };
@@ -245,8 +252,105 @@ __device__ __forceinline__ uint32_t from_other_half(uint32_t x, int upper_half)
 }
 
 /* NTERMS = 3: S as three bf16 terms.  NTERMS = 1: every entry of S is +-1/sqrt(128), the
-   operand is sqrt(128) * S (exactly +-1 in bf16), one product per k-step replaces three and
-   the common factor is taken out of the block radius (the angles do not see it). */
+   operand is sqrt(128) * S (exactly +-1), one product per k-step replaces three and
+   the common factor is taken out of the block radius (the angles do not see it).
+   NTERMS = 2: S as two binary16 terms of 2^15 S, 23 significant bits.
+
+   fp32 input with NTERMS = 1 or 2 is two binary16 terms as well, after a power of two has brought the vector's
+   largest coordinate to [2^14, 2^15) (the factor comes out of the radius, the angles do not see it): three products
+   (two for a +-1 S) instead of the six (three) that three bf16 terms of 8 bits take, and a third of the vector
+   instructions to split an input: keys and values of 32768 tokens of 8 heads 116 -> 82 us, 89 -> 72 with a +-1 S.  Its error
+   against 64 bits is no larger: of 4.2 M radii 292 differ by a last bit, 341 with three bf16 terms.  A coordinate's two terms leave 2^-24 of it, or 2^-40 of the vector's
+   largest where that is more: an S that spreads every coordinate over all pairs of the result (pq_ctx::mixing) does not see
+   the latter; any other keeps NTERMS = 3. */
+template <int XT, int NTERMS> struct Operands {
+    static constexpr bool half = XT == PQ_F32 && NTERMS <= 2;             /* binary16 terms, else bf16 */
+    static constexpr int x_terms = XT == PQ_BF16 ? 1 : (half ? 2 : 3);
+    static constexpr int top = NTERMS == 3 ? 2 : 1;                       /* products of terms x + s <= top take part */
+    static constexpr int products = x_terms == 1 ? NTERMS : (NTERMS == 3 ? 6 : NTERMS + 1); /* of a k-step */
+    static constexpr int s_chunks = NTERMS * 4 * 8 * 64;                  /* 16-byte chunks of S in LDS */
+};
+
+template <int XT, int NTERMS>
+__device__ __forceinline__ f32x16 multiply(const BOperand &s, const BOperand &x, const f32x16 &c)
+{
+    if constexpr (Operands<XT, NTERMS>::half) return __builtin_amdgcn_mfma_f32_32x32x16_f16(s.h, x.h, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(s.v, x.v, c, 0, 0, 0);
+}
+
+/* Chunk of S as the matrix instructions take it, from the chunks of its bf16 terms (t[1], t[2]: NTERMS > 1). */
+template <int XT, int NTERMS>
+__device__ __forceinline__ void s_operand(BOperand (&out)[NTERMS], const uint4 *t)
+{
+    if constexpr (NTERMS == 2) {
+        BOperand b[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) b[k].q = t[k];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float f[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                f[k] = 32768.f * __uint_as_float((e & 1) ? b[k].w[e / 2] & 0xFFFF0000u : b[k].w[e / 2] << 16);
+            const _Float16 hi = (_Float16)(f[0] + f[1]);
+            out[0].h[e] = hi;
+            out[1].h[e] = (_Float16)((f[0] - (float)hi) + f[1] + f[2]);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < NTERMS; ++k) out[k].q = t[k];
+        if constexpr (Operands<XT, NTERMS>::half) { /* +-1 */
+#pragma unroll
+            for (int k = 0; k < 4; ++k) out[0].w[k] = (out[0].w[k] & 0x80008000u) | 0x3C003C00u;
+        }
+    }
+}
+
+/* Eight coordinates as three bf16 terms. */
+__device__ __forceinline__ void split_bf16(const float (&f)[8], BOperand (&out)[3])
+{
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        uint32_t b[3][2];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            float rest = f[e + z];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                b[k][z] = bf16_rne_bits(rest);
+                rest -= __uint_as_float(b[k][z] << 16);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) out[k].w[e / 2] = b[k][0] | (b[k][1] << 16);
+    }
+}
+
+/* The power of two that brings a vector with largest coordinate m to [2^14, 2^15), as a biased exponent: at least 13 (an
+   infinity among the inputs), and 2^103 at most. */
+__device__ __forceinline__ uint32_t half_exponent(float m) { return min(268u - (__float_as_uint(m) >> 23), 230u); }
+
+/* What the rotated coordinates have to be multiplied with: the power of two and, with two terms of S, its 2^15. */
+template <int NTERMS>
+__device__ __forceinline__ float half_unscale(uint32_t e) { return __uint_as_float(((NTERMS == 1 ? 254u : 239u) - e) << 23); }
+
+/* Eight coordinates times the power of two of exponent e as two binary16 terms. */
+__device__ __forceinline__ void split_half(const float (&f)[8], uint32_t e, BOperand (&out)[2])
+{
+    const float scale = __uint_as_float(e << 23);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const _Float16 hi = (_Float16)(f[i] * scale);
+        out[0].h[i] = hi;
+        out[1].h[i] = (_Float16)__builtin_fmaf(f[i], scale, -(float)hi);
+    }
+}
+
+__device__ __forceinline__ float max_abs(float m, const float4 &a)
+{
+    return fmaxf(fmaxf(m, fmaxf(fabsf(a.x), fabsf(a.y))), fmaxf(fabsf(a.z), fabsf(a.w)));
+}
+
 /* GENERAL: codebooks set by the caller; level 1 goes through the pseudo-angle cell table (staged
    in LDS), the upper levels compare against three free boundaries. */
 /* DEEP: recursion to level 7.  The squared radii of a vector's blocks are kept as the row tiles
@@ -267,23 +371,23 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
 {
     constexpr int kImgDwords = TileImage<DEEP>::dwords, kRadiiHalves = TileImage<DEEP>::radii_halves;
     constexpr int kWaves = EncodeShape<XT>::waves, kThreads = kWaves * 64;
+    typedef Operands<XT, NTERMS> Op;
     static_assert(kWaves == 8 && kImgDwords <= kWaveDwords && 8 * 64 * 2 <= kWaveDwords, "sImg: eight wavefronts, an image or the blocks of a tile");
-    constexpr int kSChunks = NTERMS * 4 * 8 * 64;   /* 16-byte chunks of the copy of S that is used */
-
     const int lane = threadIdx.x & 63;
     /* same value in all lanes: keeps the item geometry and the tile pointers in scalar registers */
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, H = lane >> 5; /* vector within the 32-vector group, lane half */
 
     /* bf16 input: both 32-vector halves of the tile share every A-operand fetch (halves the
-       LDS traffic); fp32 input carries three bf16 terms per value and goes one half at a time */
-    constexpr int NXT = (XT == PQ_BF16) ? 1 : 3; /* bf16 terms of x */
+       LDS traffic); fp32 input carries two or three terms per value and goes one half at a time */
+    constexpr int NXT = Op::x_terms;
     constexpr int NVT = (XT == PQ_BF16) ? 2 : 1; /* 32-vector halves per pass */
-    /* bf16 input: the operand registers of a tile are dead once its last row tile has been multiplied,
-       so the next tile's rows are requested then, under the last quantisation stage, and the first
-       tile's before S is staged */
-    constexpr bool kPipelined = (XT == PQ_BF16);
+    /* The operand registers of a pass are dead once its last row tile has been multiplied,
+       so the next pass's rows are requested then, under the last quantisation stage, and the first
+       one's before S is staged (not with three terms of fp32 input: twelve products' operands leave no room) */
+    constexpr bool kPipelined = XT == PQ_BF16 || Op::half;
     BOperand xb[NVT][NXT][8];
+    float4 raw[XT == PQ_BF16 ? 1 : 16]; /* fp32 input: the rows requested ahead */
 
     /* which tile and which source rows an item covers */
     struct Geometry {
@@ -333,38 +437,55 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
         const int64_t t_src = g.src_t0 + (ok ? tau_ - g.tau_lo : 0);
         return t_src * a.ld_token + (int64_t)g.head * a.ld_head;
     };
-    /* B operands of a bf16 tile: this lane's 8-coordinate slices of its two vectors, every k-step
-       (coordinates 64 H + 8 ks .. + 7: one contiguous half row per lane) */
-    auto load_bf16_rows = [&](const Geometry &g) {
-        if constexpr (XT == PQ_BF16) {
+    /* B operands of a pass: this lane's 8-coordinate slices of its vectors, every k-step
+       (coordinates 64 H + 8 ks .. + 7: one contiguous half row per lane); fp32 rows as they are */
+    auto load_rows = [&](const Geometry &g, int half0) {
 #pragma unroll
-            for (int v = 0; v < NVT; ++v) {
-                const int64_t row = source_row(g, 32 * v + j);
+        for (int v = 0; v < NVT; ++v) {
+            const int64_t row = source_row(g, 32 * (half0 + v) + j);
+            if constexpr (XT == PQ_BF16) {
                 const uint4 *xr = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(a.x) + row);
 #pragma unroll
                 for (int ks = 0; ks < 8; ++ks) xb[v][0][ks].q = xr[8 * H + ks];
+            } else {
+                const float4 *xr = reinterpret_cast<const float4 *>(static_cast<const float *>(a.x) + row);
+#pragma unroll
+                for (int k = 0; k < 16; ++k) raw[k] = xr[16 * H + k];
             }
         }
     };
+    /* the first pass of a tile that has something to write */
+    auto first_half = [&](const Geometry &g) { return NVT == 1 && g.tau_lo >= 32 ? 1 : 0; };
+    auto load_item = [&](const Position &p) {
+        const Geometry g = geometry(p);
+        load_rows(g, first_half(g));
+    };
     Position pos{(int)(item0 / a.n_tiles), item0 % a.n_tiles};
-    if (kPipelined && item0 < a.n_items) load_bf16_rows(geometry(pos));
+    if (kPipelined && item0 < a.n_items) load_item(pos);
 
     {   /* all of a thread's chunks are requested before the first one is stored: one round trip to L2
            instead of one per chunk */
-        constexpr int kPerThread = kSChunks / kThreads;
-        static_assert(kSChunks % kThreads == 0, "S chunks must divide evenly over the workgroup");
-        uint4 stage[kPerThread];
+        constexpr int kChunks = 4 * 8 * 64, kPerThread = kChunks / kThreads, kIn = NTERMS == 1 ? 1 : 3;
+        static_assert(kChunks % kThreads == 0, "S chunks must divide evenly over the workgroup");
+        uint4 stage[kPerThread][kIn];
 #pragma unroll
-        for (int i = 0; i < kPerThread; ++i) stage[i] = a.S_bf16x3[threadIdx.x + i * kThreads];
+        for (int i = 0; i < kPerThread; ++i)
 #pragma unroll
-        for (int i = 0; i < kPerThread; ++i) sS[threadIdx.x + i * kThreads] = stage[i];
+            for (int k = 0; k < kIn; ++k) stage[i][k] = a.S_bf16x3[k * kChunks + threadIdx.x + i * kThreads];
+#pragma unroll
+        for (int i = 0; i < kPerThread; ++i) {
+            BOperand s[NTERMS];
+            s_operand<XT, NTERMS>(s, stage[i]);
+#pragma unroll
+            for (int k = 0; k < NTERMS; ++k) sS[k * kChunks + threadIdx.x + i * kThreads] = s[k].q;
+        }
     }
     __syncthreads();
 
-    Thresholds th = load_thresholds(*a.consts, NTERMS == 1 ? 0.08838834764831845f /* 1/sqrt(128) */ : 1.0f);
+    Thresholds th0 = load_thresholds(*a.consts, NTERMS == 1 ? PQ_INV_SQRT_D : 1.0f);
     if (GENERAL) {
         for (int c = threadIdx.x; c < 512; c += kThreads) sLut[c] = a.consts->lut1[c];
-        th.lut1 = sLut;
+        th0.lut1 = sLut;
         __syncthreads();
     }
 
@@ -409,38 +530,34 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
 
             bool valid[NVT];
             int tau[NVT];
+            Thresholds th = th0;
 #pragma unroll
             for (int v = 0; v < NVT; ++v) {
                 tau[v] = 32 * (vt0 + v) + j;
                 valid[v] = tau[v] >= tau_lo && tau[v] < tau_hi;
                 /* ---- B operands: this lane's 8-coordinate slices of its vector, every k-step
                    (coordinates 64 H + 8 ks .. + 7: one contiguous half row per lane) ---- */
-                if constexpr (XT != PQ_BF16) { /* bf16 rows were requested ahead (load_bf16_rows) */
-                    const int64_t row = source_row(geo, tau[v]);
-                    const float4 *xr = reinterpret_cast<const float4 *>(static_cast<const float *>(a.x) + row);
+                if constexpr (XT != PQ_BF16) {
+                    uint32_t e = 0;
+                    if constexpr (Op::half) {
+                        float m = 0.f; /* of the vector: its other half is in the lane 32 further on */
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) m = max_abs(m, raw[k]);
+                        e = half_exponent(fmaxf(m, __uint_as_float(from_other_half(__float_as_uint(m), H))));
+                        th.radius_scale = th0.radius_scale * half_unscale<NTERMS>(e);
+                    } else {
+                        load_rows(geo, vt0);
+                    }
 #pragma unroll
                     for (int ks = 0; ks < 8; ++ks) {
-                        float f[8];
-                        const float4 p0 = xr[16 * H + 2 * ks], p1 = xr[16 * H + 2 * ks + 1]; /* coordinates 64 H + 8 ks .. + 7 */
-                        f[0] = p0.x; f[1] = p0.y; f[2] = p0.z; f[3] = p0.w;
-                        f[4] = p1.x; f[5] = p1.y; f[6] = p1.z; f[7] = p1.w;
+                        const float4 p0 = raw[2 * ks], p1 = raw[2 * ks + 1];
+                        const float f[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+                        BOperand t[NXT];
+                        if constexpr (Op::half) split_half(f, e, t);
+                        else split_bf16(f, t);
 #pragma unroll
-                        for (int e = 0; e < 8; e += 2) {
-                            uint32_t w1[2], w2[2], w3[2];
-#pragma unroll
-                            for (int z = 0; z < 2; ++z) {
-                                float val = f[e + z];
-                                uint32_t b1 = bf16_rne_bits(val);
-                                float r1 = val - __uint_as_float(b1 << 16);
-                                uint32_t b2 = bf16_rne_bits(r1);
-                                float r2 = r1 - __uint_as_float(b2 << 16);
-                                uint32_t b3 = bf16_rne_bits(r2);
-                                w1[z] = b1; w2[z] = b2; w3[z] = b3;
-                            }
-                            xb[v][0][ks].w[e / 2] = w1[0] | (w1[1] << 16);
-                            xb[v][NXT > 1 ? 1 : 0][ks].w[e / 2] = w2[0] | (w2[1] << 16);
-                            xb[v][NXT > 2 ? 2 : 0][ks].w[e / 2] = w3[0] | (w3[1] << 16);
-                        }
+                        for (int k = 0; k < NXT; ++k) xb[v][k][ks] = t[k];
+                        if (Op::half) __builtin_amdgcn_sched_barrier(0); /* a k-step after the other: all at once spills */
                     }
                 }
             }
@@ -458,14 +575,17 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
                 f32x16 (&cur)[NVT] = (st & 1) ? acc_odd : acc_even;   /* row tile st: quantised now */
                 f32x16 (&nxt)[NVT] = (st & 1) ? acc_even : acc_odd;   /* row tile st+1: accumulated now */
                 const bool mul = st < 3, quant = st >= 0;
-                if (kPipelined && st == 3 && item + item_stride < a.n_items) load_bf16_rows(geometry(advance(pos)));
+                if (kPipelined && st == 3) {
+                    if (NVT == 1 && vt0 == 0 && tau_hi > 32) load_rows(geo, 1);
+                    else if (item + item_stride < a.n_items) load_item(advance(pos));
+                }
                 PolarState ps[NVT];
                 BOperand sa_next;
                 if (mul) sa_next.q = sS[(((NTERMS - 1) * 4 + (st + 1)) * 8 + 0) * 64 + lane];
                 /* The vector work that goes with k-step ks comes in U units (level-1 pair ks in two parts
                    and the upper-level nodes it completes, per vector); they are spread evenly behind the
                    NM matrix instructions of the k-step. */
-                constexpr int NM = NXT == 1 ? NVT * NTERMS : NVT * (NTERMS == 3 ? 6 : 3);
+                constexpr int NM = NVT * Op::products;
                 constexpr int U = 3 * NVT;
                 auto unit = [&](int ks, int u) {
                     const int v = NVT == 2 ? (u < 4 ? u >> 1 : u - 4) : 0;
@@ -488,11 +608,11 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
                             for (int v = 0; v < NVT; ++v)
 #pragma unroll
                                 for (int xt = 0; xt < NXT; ++xt) {
-                                    if (xt + term > 2) continue; /* below 2^-24 of the leading product */
+                                    if (xt + term > Op::top) continue; /* below 2^-24 of the leading product */
                                     /* the first product of a row tile starts from a zero accumulator operand */
                                     const bool first = (ks == 0 && term == NTERMS - 1 && xt == 0);
                                     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                                    nxt[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa.v, xb[v][xt][ks].v, first ? zero : nxt[v], 0, 0, 0);
+                                    nxt[v] = multiply<XT, NTERMS>(sa, xb[v][xt][ks], first ? zero : nxt[v]);
                                     if (quant) {
 #pragma unroll
                                         for (int u = m * U / NM; u < (m + 1) * U / NM; ++u) unit(ks, u);
@@ -558,6 +678,205 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
     }
 }
 
+/* Short inputs: the eight wavefronts of a workgroup share a tile.  The tile's rows are fetched once, eight threads per vector,
+ * and left in LDS as matrix operands; wavefront (v, rt) rotates the 32 vectors of half v into row tile rt -- blocks rt and
+ * 4 + rt -- with its part of S in registers, straight from memory.  No wavefront does more than an eighth of a tile's
+ * chain, and a workgroup's next rows are under way meanwhile.  Bound by the latency of that chain and the launch: 3001 fp32
+ * tokens of 8 heads 15.2 -> 10.8 us (13.3 with a wavefront per tile and two binary16 terms), 2000 bf16 tokens, keys and values, 12.0 -> 9.6
+ * (then the host's calls).  Issuing the next tile's products between the steps of this one's recursion, as the long kernel
+ * does, gave nothing (14.4 against 14.1 us for 3000 fp32 tokens, keys and values). */
+__shared__ float sQ4[2][2][4][64]; /* DEEP: squared radii of the tile's blocks */
+__shared__ float sUnscale[2][64];
+
+template <int XT, int KIND, int NTERMS, bool GENERAL, bool DEEP>
+__device__ __forceinline__ void encode_tiles_together(const EncodeArgs &a, int block, int n_blocks)
+{
+    typedef Operands<XT, NTERMS> Op;
+    constexpr int kImgDwords = TileImage<DEEP>::dwords, kRadiiHalves = TileImage<DEEP>::radii_halves;
+    constexpr int kIn = NTERMS == 1 ? 1 : 3, kThreads = 512, NXT = Op::x_terms;
+    constexpr int kRows = NXT * 8 * 2 * 64; /* a tile's rows, [term][k-step][half][lane]: two buffers where the long kernels keep S */
+    static_assert(2 * kRows <= 3 * 4 * 8 * 64, "the rows of two tiles");
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, H = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), v = wave & 1, rt = wave >> 1;
+    struct Place {
+        int head, tau_lo, tau_hi; /* slots [tau_lo, tau_hi) of the tile are written */
+        int64_t tile, src_t0;     /* tile inside the head plane; source token of slot tau_lo */
+    };
+    auto place = [&](int64_t item) {
+        Place p;
+        p.head = (int)(item / a.n_tiles);
+        p.tile = a.first_tile + item % a.n_tiles;
+        const int64_t lo = max(p.tile * 64, a.dst0), hi = min((p.tile + 1) * 64, a.dst0 + a.n_tokens);
+        p.tau_lo = (int)(lo - p.tile * 64);
+        p.tau_hi = (int)(hi - p.tile * 64);
+        p.src_t0 = lo - a.dst0;
+        return p;
+    };
+    /* this thread's sixteen coordinates 16 part .. + 15 of vector vec; eight vectors on neighbouring lanes, so that their operands
+       go to neighbouring places.  A slot that is not written gets the first row of the range, and its results are not emitted. */
+    const int vec = 8 * wave + (lane & 7), part = lane >> 3;
+    u32x4 raw[XT == PQ_BF16 ? 2 : 4];
+    auto load_row = [&](const Place &p) {
+        const bool valid = vec >= p.tau_lo && vec < p.tau_hi;
+        const int64_t row = (p.src_t0 + (valid ? vec - p.tau_lo : 0)) * a.ld_token + (int64_t)p.head * a.ld_head + 16 * part;
+        constexpr int kBytes = XT == PQ_BF16 ? 2 : 4;
+        const u32x4 *xr = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.x) + row * kBytes);
+#pragma unroll
+        for (int k = 0; k < kBytes; ++k) raw[k] = xr[k];
+    };
+    auto leave_row = [&](int buffer) {
+        /* k-steps 2 (part & 3), + 1 of lane half part >> 2 */
+        uint4 *dst = sS + buffer * kRows + (4 * (part & 3) + (vec >> 5)) * 64 + 32 * (part >> 2) + (vec & 31);
+        if constexpr (XT == PQ_BF16) {
+            dst[0] = make_uint4(raw[0].x, raw[0].y, raw[0].z, raw[0].w);
+            dst[2 * 64] = make_uint4(raw[1].x, raw[1].y, raw[1].z, raw[1].w);
+        } else {
+            uint32_t e = 0;
+            if constexpr (Op::half) {
+                float m = 0.f;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) m = max_abs(m, __builtin_bit_cast(float4, raw[k]));
+#pragma unroll
+                for (int d = 8; d < 64; d <<= 1) m = fmaxf(m, __shfl_xor(m, d)); /* the vector's eight parts */
+                e = half_exponent(m);
+                if (part == 0) sUnscale[buffer][vec] = half_unscale<NTERMS>(e);
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float4 p0 = __builtin_bit_cast(float4, raw[2 * k]), p1 = __builtin_bit_cast(float4, raw[2 * k + 1]);
+                const float f[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+                BOperand t[NXT];
+                if constexpr (Op::half) split_half(f, e, t);
+                else split_bf16(f, t);
+#pragma unroll
+                for (int x = 0; x < NXT; ++x) dst[(8 * x + k) * 2 * 64] = t[x].q;
+            }
+        }
+    };
+    if (block >= a.n_items) return;
+    Place p = place(block);
+    load_row(p);
+    BOperand sa[8][NTERMS];
+    { /* requested behind the first rows: everything the first tile needs is in flight at once */
+        uint4 stage[8][kIn];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) stage[ks][k] = a.S_bf16x3[((k * 4 + rt) * 8 + ks) * 64 + lane];
+        leave_row(0);
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            if (NTERMS == 2) __builtin_amdgcn_sched_barrier(0); /* one chunk after the other: all at once spills */
+            s_operand<XT, NTERMS>(sa[ks], stage[ks]);
+        }
+    }
+    Thresholds th = load_thresholds(*a.consts, NTERMS == 1 ? PQ_INV_SQRT_D : 1.0f);
+    const float base_scale = th.radius_scale;
+    UpperTables ut = {};
+    if (DEEP) ut = load_upper_tables(*a.consts);
+    if (GENERAL) {
+        sLut[tid] = a.consts->lut1[tid];
+        th.lut1 = sLut;
+    }
+    const int tau = 32 * v + j;
+    int64_t next = (int64_t)block + n_blocks;
+    Place p_next = p;
+    if (next < a.n_items) {
+        p_next = place(next);
+        load_row(p_next);
+    }
+    __syncthreads();
+    /* buffers are used in turn and a tile has one barrier: what a wavefront writes for the tile after the next is behind the
+       next tile's barrier, which nobody reaches before having read this tile's */
+    for (int turn = 0, storer = 0;; turn ^= 1, storer = (storer + 1) & 7) {
+        const int tau_lo = p.tau_lo, tau_hi = p.tau_hi;
+        const bool full = tau_lo == 0 && tau_hi == 64, valid = tau >= tau_lo && tau < tau_hi;
+        uint8_t *gcodes = a.codes + ((int64_t)p.head * a.pool_tiles + p.tile) * PQL_CODE_BYTES;
+        uint16_t *gradii = a.radii + ((int64_t)p.head * a.pool_tiles + p.tile) * kRadiiHalves;
+        uint32_t *img = sImg[turn];
+        if (!full) { /* the tile's present contents */
+            const uint32_t *gc = reinterpret_cast<const uint32_t *>(gcodes);
+            const uint32_t *gr = reinterpret_cast<const uint32_t *>(gradii);
+            for (int c = tid; c < PQL_CODE_BYTES / 4; c += kThreads) img[c] = gc[c];
+            for (int c = tid; c < kRadiiHalves / 2; c += kThreads) img[PQL_CODE_BYTES / 4 + c] = gr[c];
+            __syncthreads();
+        }
+        if (Op::half) th.radius_scale = base_scale * sUnscale[turn][tau];
+        if (32 * v < tau_hi && 32 * v + 32 > tau_lo) {
+            f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) {
+                BOperand xb[NXT];
+#pragma unroll
+                for (int x = 0; x < NXT; ++x) xb[x].q = sS[turn * kRows + ((x * 8 + ks) * 2 + v) * 64 + lane];
+#pragma unroll
+                for (int term = NTERMS - 1; term >= 0; --term)
+#pragma unroll
+                    for (int x = 0; x < NXT; ++x)
+                        if (x + term <= Op::top) acc = multiply<XT, NTERMS>(sa[ks][term], xb[x], acc);
+            }
+            const BlockCodes bc = polar_quant_block<GENERAL>(acc, th);
+            if (full) leave_block<KIND, DEEP>(img, tau, 4 * H + rt, bc);
+            else if (valid) emit_block<KIND, DEEP>(img, tau, 4 * H + rt, bc);
+            if (DEEP) sQ4[turn][v][rt][lane] = bc.q4;
+        }
+        const bool more = next < a.n_items;
+        const int64_t after = next + n_blocks;
+        Place p_after = p_next;
+        if (more) {
+            leave_row(turn ^ 1);
+            if (after < a.n_items) {
+                p_after = place(after);
+                load_row(p_after);
+            }
+        }
+        __syncthreads();
+        if (DEEP && rt == 3) {
+            float q4[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q4[k] = sQ4[turn][v][k][lane];
+            const UpperHalf mine = polar_upper_half(q4, H, ut);
+            UpperHalf other;
+            other.codes = from_other_half(mine.codes, H);
+            other.q6 = __uint_as_float(from_other_half(__float_as_uint(mine.q6), H));
+            const uint32_t word = H == 0 ? polar_upper_join(mine, other, th.radius_scale, ut)
+                                         : polar_upper_join(other, mine, th.radius_scale, ut);
+            if (H == 0 && valid) {
+                if (full) reinterpret_cast<uint32_t *>(gradii)[tau] = word;
+                else img[PQL_CODE_BYTES / 4 + tau] = word;
+            }
+        }
+        if (full) {
+            if (wave == storer) store_tile<KIND, DEEP>(img, gcodes, gradii, lane);
+        } else {
+            if (DEEP) __syncthreads();
+            const uint4 *src = reinterpret_cast<const uint4 *>(img);
+            for (int c = tid; c < kImgDwords / 4; c += kThreads) {
+                if (c < PQL_CODE_BYTES / 16) reinterpret_cast<uint4 *>(gcodes)[c] = src[c];
+                else reinterpret_cast<uint4 *>(gradii)[c - PQL_CODE_BYTES / 16] = src[c];
+            }
+        }
+        if (!more) break;
+        p = p_next;
+        p_next = p_after;
+        next = after;
+    }
+}
+
+template <int XT, int KIND, int NTERMS, bool GENERAL, bool DEEP>
+__global__ __launch_bounds__(512) void pq_encode_short_kernel(EncodeArgs a)
+{
+    encode_tiles_together<XT, KIND, NTERMS, GENERAL, DEEP>(a, (int)blockIdx.x, (int)gridDim.x);
+}
+
+/* keys on the even workgroups, values on the odd ones */
+template <int XT, int NTERMS, bool GENERAL, bool DEEP>
+__global__ __launch_bounds__(512) void pq_encode_short_pair_kernel(EncodeArgs k, EncodeArgs v)
+{
+    if ((blockIdx.x & 1) == 0) encode_tiles_together<XT, PQ_KEY, NTERMS, GENERAL, DEEP>(k, (int)blockIdx.x >> 1, (int)gridDim.x >> 1);
+    else encode_tiles_together<XT, PQ_VALUE, NTERMS, GENERAL, DEEP>(v, (int)blockIdx.x >> 1, (int)gridDim.x >> 1);
+}
+
 template <int XT, int KIND, int NTERMS, bool GENERAL, bool DEEP>
 __global__ __launch_bounds__(EncodeShape<XT>::waves * 64) void pq_encode_kernel(EncodeArgs a)
 {
@@ -589,6 +908,12 @@ __global__ __launch_bounds__(512) void pq_append_pair_kernel(AppendArgs k, Appen
     else append_vectors<XT, 1>(v, PQ_VALUE, (int)blockIdx.x - n, n);
 }
 
+/* Tiles per CU up to which the workgroup-per-tile kernel is the faster one (keys and values of 8 heads, us, it against the
+   wavefront-per-tile kernel: bf16 4000 tokens 11.8 / 16.1, 12000 25.4 / 29.2, 16000 31.9 / 31.7, 32768 66 / 58; fp32 1000 tokens
+   9.7 / 15.4, 3000 14.1 / 19.5, 6000 21.5 / 24.0, 8000 24.6 / 23.7; bf16 10000 at depth 7, where two wavefronts do the upper
+   levels of a tile, 30.5 / 28.5).  The other kernel's rounds of 2048 tiles make its times steps. */
+template <int XT, bool DEEP> constexpr int short_tiles_per_cu() { return XT == PQ_BF16 && !DEEP ? 12 : 6; }
+
 template <int XT, int KIND, int NTERMS, bool GENERAL, bool DEEP>
 pq_status launch_encode(const EncodeArgs &a, hipStream_t stream)
 {
@@ -605,7 +930,10 @@ pq_status launch_encode(const EncodeArgs &a, hipStream_t stream)
     constexpr int kWaves = EncodeShape<XT>::waves, kThreads = kWaves * 64;
     const int64_t blocks = a.n_items < cus ? a.n_items : cus; /* n_items >= 1 */
     pq_prof_before(1, stream);
-    hipLaunchKernelGGL((pq_encode_kernel<XT, KIND, NTERMS, GENERAL, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, a);
+    if (a.n_items <= short_tiles_per_cu<XT, DEEP>() * (int64_t)cus)
+        hipLaunchKernelGGL((pq_encode_short_kernel<XT, KIND, NTERMS, GENERAL, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((pq_encode_kernel<XT, KIND, NTERMS, GENERAL, DEEP>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, a);
     pq_prof_after(1, stream);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
@@ -622,58 +950,38 @@ pq_status launch_encode_pair(const EncodeArgs &k, const EncodeArgs &v, hipStream
     int64_t per_kind = k.n_items < cus / 2 ? k.n_items : cus / 2;
     if (per_kind < 1) per_kind = 1;
     pq_prof_before(1, stream);
-    hipLaunchKernelGGL((pq_encode_pair_kernel<XT, NTERMS, GENERAL, DEEP>), dim3((unsigned)(2 * per_kind)), dim3(kThreads), 0,
-                       stream, k, v, (int)per_kind);
+    if (2 * k.n_items <= short_tiles_per_cu<XT, DEEP>() * (int64_t)cus)
+        hipLaunchKernelGGL((pq_encode_short_pair_kernel<XT, NTERMS, GENERAL, DEEP>), dim3((unsigned)(2 * per_kind)), dim3(kThreads), 0,
+                           stream, k, v);
+    else
+        hipLaunchKernelGGL((pq_encode_pair_kernel<XT, NTERMS, GENERAL, DEEP>), dim3((unsigned)(2 * per_kind)), dim3(kThreads), 0,
+                           stream, k, v, (int)per_kind);
     pq_prof_after(1, stream);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
 }
 
-template <int NTERMS, bool GENERAL, bool DEEP>
-pq_status dispatch_pair_terms(const EncodeArgs &k, const EncodeArgs &v, pq_dtype xt, hipStream_t stream)
-{
-    return xt == PQ_BF16 ? launch_encode_pair<PQ_BF16, NTERMS, GENERAL, DEEP>(k, v, stream)
-                         : launch_encode_pair<PQ_F32, NTERMS, GENERAL, DEEP>(k, v, stream);
-}
+/* bf16 terms of S for bf16 input, binary16 ones for fp32 input where S allows them (see Operands) */
+int s_terms(const pq_ctx *ctx, pq_dtype xt) { return ctx->unit_entries ? 1 : (xt == PQ_F32 && ctx->mixing ? 2 : 3); }
 
-pq_status dispatch_encode_pair(const EncodeArgs &k, const EncodeArgs &v, pq_dtype xt, bool unit_entries, bool general,
-                               bool deep, hipStream_t stream)
+/* launch(input type, terms of S, caller-set codebooks, full depth), each an integral_constant */
+template <typename F>
+pq_status dispatch_variant(const pq_ctx *ctx, pq_dtype xt, F launch)
 {
-    if (deep) {
-        if (general)
-            return unit_entries ? dispatch_pair_terms<1, true, true>(k, v, xt, stream) : dispatch_pair_terms<3, true, true>(k, v, xt, stream);
-        return unit_entries ? dispatch_pair_terms<1, false, true>(k, v, xt, stream) : dispatch_pair_terms<3, false, true>(k, v, xt, stream);
-    }
-    if (general)
-        return unit_entries ? dispatch_pair_terms<1, true, false>(k, v, xt, stream) : dispatch_pair_terms<3, true, false>(k, v, xt, stream);
-    return unit_entries ? dispatch_pair_terms<1, false, false>(k, v, xt, stream) : dispatch_pair_terms<3, false, false>(k, v, xt, stream);
-}
-
-template <int NTERMS, bool GENERAL, bool DEEP>
-pq_status dispatch_encode_terms(const EncodeArgs &a, pq_dtype xt, pq_kind kind, hipStream_t stream)
-{
-    if (xt == PQ_BF16)
-        return kind == PQ_KEY ? launch_encode<PQ_BF16, PQ_KEY, NTERMS, GENERAL, DEEP>(a, stream)
-                              : launch_encode<PQ_BF16, PQ_VALUE, NTERMS, GENERAL, DEEP>(a, stream);
-    return kind == PQ_KEY ? launch_encode<PQ_F32, PQ_KEY, NTERMS, GENERAL, DEEP>(a, stream)
-                          : launch_encode<PQ_F32, PQ_VALUE, NTERMS, GENERAL, DEEP>(a, stream);
-}
-
-pq_status dispatch_encode(const EncodeArgs &a, pq_dtype xt, pq_kind kind, bool unit_entries, bool general, bool deep,
-                          hipStream_t stream)
-{
-    if (deep) {
-        if (general)
-            return unit_entries ? dispatch_encode_terms<1, true, true>(a, xt, kind, stream)
-                                : dispatch_encode_terms<3, true, true>(a, xt, kind, stream);
-        return unit_entries ? dispatch_encode_terms<1, false, true>(a, xt, kind, stream)
-                            : dispatch_encode_terms<3, false, true>(a, xt, kind, stream);
-    }
-    if (general)
-        return unit_entries ? dispatch_encode_terms<1, true, false>(a, xt, kind, stream)
-                            : dispatch_encode_terms<3, true, false>(a, xt, kind, stream);
-    return unit_entries ? dispatch_encode_terms<1, false, false>(a, xt, kind, stream)
-                        : dispatch_encode_terms<3, false, false>(a, xt, kind, stream);
+    auto with_depth = [&](auto x, auto terms, auto general) {
+        return ctx->depth == 7 ? launch(x, terms, general, std::true_type{}) : launch(x, terms, general, std::false_type{});
+    };
+    auto with_books = [&](auto x, auto terms) {
+        return ctx->general_codebooks ? with_depth(x, terms, std::true_type{}) : with_depth(x, terms, std::false_type{});
+    };
+    constexpr std::integral_constant<int, PQ_BF16> bf16{};
+    constexpr std::integral_constant<int, PQ_F32> f32{};
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 3> three{};
+    const int terms = s_terms(ctx, xt);
+    if (xt == PQ_BF16) return terms == 1 ? with_books(bf16, one) : with_books(bf16, three);
+    return terms == 1 ? with_books(f32, one) : (terms == 2 ? with_books(f32, two) : with_books(f32, three));
 }
 
 } // namespace
@@ -728,8 +1036,12 @@ extern "C" pq_status pq_encode_kv(const pq_ctx *ctx, const void *x, pq_dtype xt,
     st = pq_device_state(ctx, &ds);
     if (st != PQ_OK) return st;
     set_device_tables(a, ds);
-    return dispatch_encode(a, xt, kind, ctx->unit_entries, ctx->general_codebooks, ctx->depth == 7,
-                           static_cast<hipStream_t>(hip_stream));
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    return dispatch_variant(ctx, xt, [&](auto x, auto terms, auto general, auto deep) {
+        constexpr int X = decltype(x)::value, T = decltype(terms)::value;
+        constexpr bool G = decltype(general)::value, D = decltype(deep)::value;
+        return kind == PQ_KEY ? launch_encode<X, PQ_KEY, T, G, D>(a, stream) : launch_encode<X, PQ_VALUE, T, G, D>(a, stream);
+    });
 }
 
 extern "C" pq_status pq_encode_kv_pair(const pq_ctx *ctx, const void *xk, const void *xv, pq_dtype xt,
@@ -750,8 +1062,10 @@ extern "C" pq_status pq_encode_kv_pair(const pq_ctx *ctx, const void *xk, const 
     if (st != PQ_OK) return st;
     set_device_tables(ak, ds);
     set_device_tables(av, ds);
-    return dispatch_encode_pair(ak, av, xt, ctx->unit_entries, ctx->general_codebooks, ctx->depth == 7,
-                                static_cast<hipStream_t>(hip_stream));
+    return dispatch_variant(ctx, xt, [&](auto x, auto terms, auto general, auto deep) {
+        return launch_encode_pair<decltype(x)::value, decltype(terms)::value, decltype(general)::value, decltype(deep)::value>(
+            ak, av, static_cast<hipStream_t>(hip_stream));
+    });
 }
 
 extern "C" pq_status pq_append_kv(const pq_ctx *ctx, const void *x, pq_dtype xt, pq_kind kind,

@@ -389,6 +389,9 @@ static pq_status init_context(pq_ctx **out, int d, uint64_t seed, const double *
     ctx->unit_entries = true;
     for (int i = 0; i < d * d; ++i)
         if (fabs(fabs(ctx->S[i]) * sqrt((double)d) - 1.0) > 1e-12) { ctx->unit_entries = false; break; }
+    ctx->mixing = true;
+    for (int i = 0; i < d * d; i += 2)
+        if (fmax(fabs(ctx->S[i]), fabs(ctx->S[i + 1])) < 0x1p-16) { ctx->mixing = false; break; }
     /* S = D H / sqrt(d) with the Sylvester H: row i is D_i = sign of S[i][0] times (-1)^popcount(i & j) */
     ctx->hadamard = PqHadamard{};
     if (ctx->unit_entries) {
