@@ -31,3 +31,18 @@ def test_counts_do_not_depend_on_the_scale_of_the_vectors(dtype, depth):
     # A square of z 2^-63 keeps z^2 2^23 units: an angle is off by about 1e-7 / z^2, a bin 5e-4 to 1e-3 wide, so fewer than
     # one node in a hundred changes its bin (it leaves one and enters another).
     assert (small - ref).abs().sum() <= 0.02 * ref.sum()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_counts_of_pieces_add_up(dtype):
+    say(f"angle counts of a long input and of its pieces, {dtype}")
+    ctx, n = Context(seed=4), 12800                # 8 heads: 1600 tiles; the pieces take 8 to 1408 of them
+    x = torch.randn((n, 8, 128), generator=torch.Generator().manual_seed(6)).to(dtype)
+    x[5], x[6], x[7, 0, :16], x[8] = 0.0, 1e30, 0.0, 1e-25     # zeros and squares outside the range of the short roots
+    whole, at = counts(ctx, x), 0
+    assert whole.sum() == 8 * n * 120              # four levels of 64 + 32 + 16 + 8 angles
+    total = torch.zeros_like(whole)
+    for piece in (1, 63, 4000, 300, n - 4364):
+        total += counts(ctx, x[at:at + piece])
+        at += piece
+    assert at == n and torch.equal(total, whole)
