@@ -19,7 +19,7 @@
  *   pq_attn_combine_kernel  merges the pieces of a (sequence, query head) in tile
  *                           order, divides by l, multiplies by S^T, bf16
  *
- * Partial kernel, per 64-token tile (the cache stores, per block of 16 coordinates, four 10-bit quarter
+ * Partial kernel for up to four (query token, head) pairs per kv head, per 64-token tile (the cache stores, per block of 16 coordinates, four 10-bit quarter
  * indices Q, one 6-bit block index B and the binary16 block radius: pq_layout.h):
  *   K:  one token per lane.  For each of the token's 32 quarters the lane fetches the quarter's table
  *       entry -- the four binary16 products (cos|sin) theta2 * (cos|sin) theta1 -- and hands it to
@@ -38,6 +38,10 @@
  *       (token, parity): operand rows are coordinate pairs, and the probability operand has one column per
  *       (pair, parity) with zeros in the slots of the other parity.  The result accumulates o' for the
  *       even coordinates in the parity-0 columns and for the odd ones in parity 1.
+ *
+ * With five to sixteen pairs ("wide"): a key is formed once, as two binary16 terms, and multiplied by all pairs on
+ * v_mfma_f32_16x16x32_f16 (wide_scores); the scores come out in the lanes that the value product wants the weights in,
+ * and the values are brought to one coordinate per register by permutes.
  */
 #include <type_traits>
 
@@ -53,8 +57,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 /* One workgroup per CU: the lookup tables are laid out in LDS with a private bank column per lane (see
  * stage_tables), which takes 48 KB, so all wavefronts resident on a CU share one copy: 4 SIMDs x the
  * wavefronts per SIMD that the variant's register budget allows. */
-constexpr int waves_per_simd(int NG) { return NG == 1 ? 4 : (NG == 2 ? 3 : 2); }
-constexpr int waves_per_block(int NG) { return 4 * waves_per_simd(NG); }
+constexpr int waves_per_simd(int pairs) { return pairs <= 4 ? 4 : (pairs <= 8 ? 3 : 2); }
 constexpr float kLog2e = 1.4426950408889634f;
 /* Probabilities are handed to the matrix cores as binary16.  They are computed
  * as 2^(s - m + kProbShift) against an exponent reference m that may lag the true
@@ -71,7 +74,7 @@ constexpr float kRefSlack = 6.0f;
  *   kTQ   [1024][2]       quarter table, by Q (8 KB, gathered as it is: 32 columns of it would be 256 KB)
  *   kTQA  [64][32]        first pair of a quarter, by Q & 63 = c2 << 4 | c1
  *   kTQB  [64][32]        second pair, by Q >> 4 = c1' << 2 | c2
- *   kTBF  [64][16][4]     block table of the keys (fp32), by B
+ *   kTBF  [64][16][4]     block table of the keys, by B: fp32; wide: two binary16 terms, the four first ones in front
  *   kTBH  [64][32]        block table of the values: column l holds the binary16 pair of half-block l & 1
  *   kTUp  [3][8][2]       levels 5..7 (full depth) */
 constexpr int kTQ = 0, kTQA = 2048, kTQB = 4096, kTBF = 6144, kTBH = 10240, kTUp = 12288, kLdsTabDwords = 12336;
@@ -243,6 +246,9 @@ __device__ __forceinline__ void load_k_tile(KTileRaw &t, __amdgpu_buffer_rsrc_t 
     else t.rad = load16(radii, lane * 16u, tile * (PQL_RADII * 2u));
 }
 
+/* vector memory instructions of a value tile: load_v_tile */
+constexpr int kValueLoads = 6, kValueLoadsDeep = 5;
+
 template <bool DEEP>
 __device__ __forceinline__ void load_v_tile(VTileRaw &t, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t radii,
                                             uint32_t tile, uint32_t lane)
@@ -265,6 +271,27 @@ __device__ __forceinline__ void load_v_tile(VTileRaw &t, __amdgpu_buffer_rsrc_t 
     }
 }
 
+/* Key tile of the wide kernel: to LDS as it is, by loads that write there and take no registers, requested by the wavefront that
+ * will read it while the tile before it is worked on. */
+template <bool DEEP> constexpr int key_tile_bytes() { return PQL_CODE_BYTES + (DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) * 2; }
+
+typedef __attribute__((address_space(3))) void *LdsPtr;
+
+template <bool DEEP>
+__device__ __forceinline__ void request_k_tile(uint32_t *dst, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t radii,
+                                               uint32_t tile, uint32_t lane)
+{
+    asm volatile("" : "+v"(lane));
+    const uint32_t co = tile * PQL_CODE_BYTES, off = lane * 16u;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(codes, (LdsPtr)dst, 16, off, co, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(codes, (LdsPtr)(dst + 256), 16, off, co + 1024u, 0, 0);
+    if (lane < (PQL_CODE_BYTES - 2048) / 16)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(codes, (LdsPtr)(dst + 512), 16, off, co + 2048u, 0, 0);
+    if (lane < (DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) / 8)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(radii, (LdsPtr)(dst + PQL_CODE_BYTES / 4), 16, off,
+                                                 tile * ((DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) * 2u), 0, 0);
+}
+
 __device__ __forceinline__ void wave_lds_fence()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -279,6 +306,7 @@ __device__ __forceinline__ void wave_lds_fence()
  * vrad[(8 g + b) * 16 + 4 i + e] = radius of block b of token 16 i + 4 g + e. */
 struct DeepRadii {
     uint16_t *vrad;    /* [512] */
+    uint32_t *krad;    /* wide kernel: [64 tokens][8 blocks] */
     int b5, b6, b7;
 };
 
@@ -327,23 +355,23 @@ __device__ __forceinline__ uint32_t sel4(uint4 v, int c)
 __device__ __forceinline__ float half_lo_to_float(uint32_t u) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(u & 0xFFFFu)); }
 __device__ __forceinline__ float half_hi_to_float(uint32_t u) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(u >> 16)); }
 
-/* Query operand of the scores: for column group k, a[k][set] holds in lane (i = lane >> 2, slot = lane & 3) the four
- * rotated query coordinates 4 x .. 4 x + 3 of quarter x = 16 set + i for pair 4 k + slot, in binary16.
+/* Query operand of the scores: a[set] holds in lane (i = lane >> 2, slot = lane & 3) the four
+ * rotated query coordinates 4 x .. 4 x + 3 of quarter x = 16 set + i for pair `slot`, in binary16.
  * v_mfma_f32_4x4x4_16b_f16 multiplies 16 independent 4x4 blocks; with the A block of one lane group broadcast to
  * all sixteen (cbsz = 4, abid = i) one register pair serves sixteen quarters. */
-template <int NG> struct QueryOperand { H4 a[NG][2]; };
+struct QueryOperand { H4 a[2]; };
 
 /* Scores of one 64-token tile, one token per lane (Eq. 5 with DeQuant unrolled into table products):
  *   s_pair(tau) = sum_b r_b(tau) sum_j T43[B_b][j] * < q'[16 b + 4 j .. + 3], T21[Q_{b,j}] >
  * T21[Q] (binary16, from LDS) = the four products (cos|sin) theta2 * (cos|sin) theta1 of a quarter -- it is the B
  * operand of the matrix instruction as fetched; T43[B] (fp32) = the four products (cos|sin) theta4 * (cos|sin)
  * theta3 of a block.  The matrix cores form the 4-coordinate inner products of a quarter for four (query token,
- * head) pairs per group; each is scaled in fp32
+ * head) pairs; each is scaled in fp32
  * by r_b T43[B_b][j] and summed.  A key element is therefore never rounded beyond its table entry.
  * s comes in holding the negated exponent reference (the first product of a tile adds to it). */
-template <int NG, bool DEEP>
-__device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &k, const QueryOperand<NG> &qo,
-                                           float (&s)[NG][4], const DeepRadii &dr, int lane)
+template <bool DEEP>
+__device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &k, const QueryOperand &qo,
+                                           float (&s)[4], const DeepRadii &dr, int lane)
 {
     const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
     float rb[8];
@@ -370,37 +398,108 @@ __device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &
         for (int j = 0; j < 4; ++j) {
             constexpr int set = b >> 2;         /* quarters 0..15 | 16..31 */
             const int abid = (4 * b + j) & 15;  /* compile-time after unrolling */
-            /* the groups' products first, then their sums: a sum would wait for the product just before it, and with two
-               wavefronts per SIMD nobody fills that wait (115.4 -> 112.4 us for the case above) */
-            f4 dg[NG];
-#pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                f4 d;
-                switch (abid) { /* the broadcast selector is an immediate of the instruction */
+            f4 d;
+            switch (abid) { /* the broadcast selector is an immediate of the instruction */
 #define PQ_SCORE_CASE(N)                                                                                     \
     case N:                                                                                                  \
-        d = __builtin_amdgcn_mfma_f32_4x4x4f16(qo.a[g][set].v, kq[j].v, zero, 4, N, 0);                         \
+        d = __builtin_amdgcn_mfma_f32_4x4x4f16(qo.a[set].v, kq[j].v, zero, 4, N, 0);                            \
         break;
-                    PQ_SCORE_CASE(0) PQ_SCORE_CASE(1) PQ_SCORE_CASE(2) PQ_SCORE_CASE(3)
-                    PQ_SCORE_CASE(4) PQ_SCORE_CASE(5) PQ_SCORE_CASE(6) PQ_SCORE_CASE(7)
-                    PQ_SCORE_CASE(8) PQ_SCORE_CASE(9) PQ_SCORE_CASE(10) PQ_SCORE_CASE(11)
-                    PQ_SCORE_CASE(12) PQ_SCORE_CASE(13) PQ_SCORE_CASE(14)
-                    default: PQ_SCORE_CASE(15)
+                PQ_SCORE_CASE(0) PQ_SCORE_CASE(1) PQ_SCORE_CASE(2) PQ_SCORE_CASE(3)
+                PQ_SCORE_CASE(4) PQ_SCORE_CASE(5) PQ_SCORE_CASE(6) PQ_SCORE_CASE(7)
+                PQ_SCORE_CASE(8) PQ_SCORE_CASE(9) PQ_SCORE_CASE(10) PQ_SCORE_CASE(11)
+                PQ_SCORE_CASE(12) PQ_SCORE_CASE(13) PQ_SCORE_CASE(14)
+                default: PQ_SCORE_CASE(15)
 #undef PQ_SCORE_CASE
-                }
-                dg[g] = d;
             }
-            if (NG > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
-#pragma unroll
-                for (int h = 0; h < 4; ++h) s[g][h] = __builtin_fmaf(dg[g][h], rq[j], s[g][h]);
+            for (int h = 0; h < 4; ++h) s[h] = __builtin_fmaf(d[h], rq[j], s[h]);
         }
     };
     block(std::integral_constant<int, 0>{}); block(std::integral_constant<int, 1>{});
     block(std::integral_constant<int, 2>{}); block(std::integral_constant<int, 3>{});
     block(std::integral_constant<int, 4>{}); block(std::integral_constant<int, 5>{});
     block(std::integral_constant<int, 6>{}); block(std::integral_constant<int, 7>{});
+}
+
+/* ---- more than four pairs: dense scores ----
+ * Scores of 64 tokens for sixteen pairs.  The 4x4x4 form above costs a scaling in fp32 per quarter and pair, 512 for
+ * sixteen pairs; here a key is formed once and multiplied by all pairs on v_mfma_f32_16x16x32_f16, in four passes of sixteen
+ * tokens: lane (g, n) rebuilds blocks 2 g and 2 g + 1 of token 16 i + n.  Nothing is rounded that is not rounded
+ * above: radius times block-table entry and that times the quarter-table entry are each two binary16 terms (a product and its
+ * exact rest, with the small factors' products added to the rest), the block table holds two terms, and both terms are
+ * multiplied by q'.  The result is in the order in which the value product takes its weights: lane (g, n) holds
+ * pair n, tokens 16 i + 4 g + e.
+ * The key tile lies in LDS (request_k_tile): bits [92 g, 92 g + 92) of a token's string are fetched as four dwords and
+ * brought to bit 0, so that every field sits at a fixed position. */
+struct WideQuery { H8 q[4]; /* lane (g, n): coordinates 32 g + 8 c .. + 7 of pair n */ };
+
+template <bool DEEP>
+__device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t *kt, const WideQuery &wq, float start, f4 (&s)[4],
+                                            const DeepRadii &dr, int lane)
+{
+    const uint32_t n = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4, col16 = n * 16u;
+    const char *base = reinterpret_cast<const char *>(kt);
+    /* string dwords 0 .. 2 | 2 .. 5 | 5 .. 8 | 8 .. 11 */
+    uint32_t o01 = g == 3u ? PQL_OFF_P2 + 12u * n : (g == 2u ? PQL_OFF_P1 + 4u : 8u * g) + 16u * n;
+    uint32_t o2 = g == 1u ? PQL_OFF_P1 + 16u * n : o01 + 8u;
+    uint32_t o3 = g == 3u ? PQL_OFF_KP3 + 4u * (n >> 1) : (g == 2u ? PQL_OFF_P2 + 12u * n : o2 + 4u);
+    const uint32_t step = g == 3u ? 192u : 256u, step3 = g == 3u ? 32u : (g == 2u ? 192u : 256u);
+    const uint32_t sh = g == 0u ? 0u : 32u - 4u * g, sh3 = g == 3u ? 16u * (n & 1u) : 0u;
+    const f4 c0 = f4{start, start, start, start};
+    if (DEEP) { /* lane tau rebuilds the radii of token tau's blocks and leaves them as two binary16 terms each */
+        float r[8];
+        pq_deep_block_radii(kt[PQL_CODE_BYTES / 4 + lane], dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + kTUp), r);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const _Float16 hi = (_Float16)r[b];
+            dr.krad[8 * lane + b] = __builtin_bit_cast(uint32_t, h2{hi, (_Float16)(r[b] - (float)hi)});
+        }
+        wave_lds_fence();
+    }
+    auto pass = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const uint32_t w0 = *reinterpret_cast<const uint32_t *>(base + o01), w1 = *reinterpret_cast<const uint32_t *>(base + o01 + 4);
+        const uint32_t w2 = *reinterpret_cast<const uint32_t *>(base + o2), w3 = *reinterpret_cast<const uint32_t *>(base + o3) >> sh3;
+        o01 += step; o2 += step; o3 += step3;
+        const uint32_t x[3] = {__builtin_amdgcn_alignbit(w1, w0, sh), __builtin_amdgcn_alignbit(w2, w1, sh),
+                               __builtin_amdgcn_alignbit(w3, w2, sh)};
+        /* radii of blocks 2 g, 2 g + 1: stored ones, or of rebuilt ones a first and a second term each */
+        const h2 ra = as_h2(DEEP ? dr.krad[(16 * i + n) * 8 + 2 * g] : kt[PQL_CODE_BYTES / 4 + 4 * (16 * i + n) + g]);
+        const h2 rb = DEEP ? as_h2(dr.krad[(16 * i + n) * 8 + 2 * g + 1]) : ra;
+        s[i] = c0;
+        auto block = [&](auto bc) {
+            constexpr int b = decltype(bc)::value, at = PQL_BLOCK_BITS * b;
+            const H8 t43 = [&] {
+                H8 t;
+                t.q = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(tab + kTBF) + table_offset<at + 40, 6, 8>(x, col16));
+                return t;
+            }(); /* quarters 0, 1 | 2, 3, then their second terms */
+            const h2 rr = b && !DEEP ? bcast_hi(ra) : bcast_lo(b ? rb : ra), rrl = bcast_hi(b ? rb : ra);
+            auto half = [&](auto hc) {
+                constexpr int h = decltype(hc)::value;
+                const h2 ph = rr * t43.p[h]; /* radii of the half's two quarters */
+                h2 pl = __builtin_elementwise_fma(rr, t43.p[2 + h], __builtin_elementwise_fma(rr, t43.p[h], -ph));
+                if (DEEP) pl = __builtin_elementwise_fma(rrl, t43.p[h], pl);
+                H4 ta, tb;
+                ta.d = quarter_entry<at + 20 * h, false>(tab, x, 0u);
+                tb.d = quarter_entry<at + 20 * h + 10, false>(tab, x, 0u);
+                H8 hi, lo;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const h2 t = k < 2 ? ta.p[k & 1] : tb.p[k & 1];
+                    const h2 qh = k < 2 ? bcast_lo(ph) : bcast_hi(ph), ql = k < 2 ? bcast_lo(pl) : bcast_hi(pl);
+                    hi.p[k] = t * qh;
+                    lo.p[k] = __builtin_elementwise_fma(t, ql, __builtin_elementwise_fma(t, qh, -hi.p[k]));
+                }
+                s[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo.v, wq.q[2 * b + h].v, s[i], 0, 0, 0);
+                s[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi.v, wq.q[2 * b + h].v, s[i], 0, 0, 0);
+            };
+            half(std::integral_constant<int, 0>{}); half(std::integral_constant<int, 1>{});
+        };
+        block(std::integral_constant<int, 0>{}); block(std::integral_constant<int, 1>{});
+    };
+    pass(std::integral_constant<int, 0>{}); pass(std::integral_constant<int, 1>{});
+    pass(std::integral_constant<int, 2>{}); pass(std::integral_constant<int, 3>{});
 }
 
 /* A operands of the weighted value sum of pass i: the rebuilt values of tokens 16 i + 4 g + e, e = 0..3, for
@@ -457,8 +556,8 @@ __device__ __forceinline__ float wave_max_f(float x)
     return x;
 }
 
-/* G query heads per kv head, M query tokens per sequence (a.M), NG column groups with
- * M * G <= 4 * NG.  Query token m of a sequence is its (M-1-m)-th newest token and sees
+/* G query heads per kv head, M query tokens per sequence (a.M), up to four pairs per kv head, or WIDE: up to
+ * sixteen.  Query token m of a sequence is its (M-1-m)-th newest token and sees
  * the cache up to and including its own key: ctx - (M-1-m) tokens.
  *
  * Per 64-token tile: scores with one token per lane (key_scores), probabilities
@@ -469,33 +568,36 @@ __device__ __forceinline__ float wave_max_f(float x)
  * v_mfma_f32_16x16x32_f16.  The (cos, sin)-like pairs of a table entry are two coordinates of one
  * token, while a matrix-core operand wants several tokens of one coordinate per lane; instead of
  * transposing, the contraction index is widened to (token, parity): operand rows are coordinate
- * pairs, and the probability operand has one column per (pair, parity) -- up to eight pairs -- with zeros in the
+ * pairs, and the probability operand has one column per (pair, parity) with zeros in the
  * slots of the other parity.  The result accumulates o' for the even coordinates in the parity-0 columns and
- * for the odd ones in parity 1. */
-template <int NG, bool DEEP>
-__global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_kernel(AttnArgs a)
+ * for the odd ones in parity 1.
+ *
+ * WIDE: lane (g, n) holds the scores of pair n for tokens 16 i + 4 g + e, so a pair's reference and sum are the lane's own and its weights
+ * are the value product's operand as they are (no LDS); the values of two passes are transposed by permutes (64 per
+ * tile) and contracted over tokens, half of the matrix work of the widened contraction.  Both kinds are bound by instruction issue: per tile
+ * some 700 vector instructions for any number of pairs up to sixteen, where the form for four pairs, its groups of four repeated, took 820 for
+ * two groups and 1090 for four.  Four query tokens of four heads, 16 sequences of 12700 tokens: 107 -> 78 us per call; ten pairs at
+ * 32768 tokens 198 -> 158; eight pairs 73.6 -> 69.3; at depth 7 twelve pairs 106 -> 85, eight 75.7 -> 75.5.  Key tiles that went to LDS ahead of
+ * their use made four pairs slower (35.1 -> 36.7 us for 32 short sequences, 112.6 -> 114.9 at 65536 tiles: the LDS is as busy as the vector
+ * ALU there). */
+template <bool WIDE, int WAVES_PER_SIMD, bool DEEP>
+__global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_kernel(AttnArgs a)
 {
-    constexpr int kWavesPerBlock = waves_per_block(NG), kThreads = kWavesPerBlock * 64;
-    /* The sixteen columns of a value product are up to eight pairs times two parities (with four pairs half of the columns
-       repeat the other half): NV products serve the NG groups of four pairs.  Four query tokens of four heads: a product
-       per group of four kept half of the matrix work idle and 32 more registers, 126.9 -> 117.3 us per call; 224 against
-       248 at twice the context.  The registers freed do not pay for a third wavefront per SIMD (121.2, it spills), nor
-       do those of two groups for a fourth (80.5 against 77.8). */
-    constexpr int kCols = NG == 1 ? 8 : 16, kPairs = kCols / 2, NV = NG == 1 ? 1 : NG / 2;
+    constexpr int kWavesPerBlock = 4 * WAVES_PER_SIMD, kThreads = kWavesPerBlock * 64;
     const int G = a.Hq / a.Hkv; /* query heads per kv head: only the set-up and the epilogue of a piece depend on it */
-    /* One block, the tables first: the offset of a table inside LDS then fits a gather's 16-bit immediate.  (Laid out by
-       the compiler they came after the probabilities, beyond 64 KB with four groups: one more addition per gather, 117.3 against 115.4 us
-       for four query tokens of four heads.) */
+    /* One block, the tables first: the offset of a table inside LDS then fits a gather's 16-bit immediate. */
     struct Lds {
         __attribute__((aligned(16))) uint32_t tab[kLdsTabDwords];
-        __attribute__((aligned(16))) uint32_t p[kWavesPerBlock][NV][kCols][64];
+        __attribute__((aligned(16))) uint32_t p[WIDE ? 1 : kWavesPerBlock][8][64];
     };
     __shared__ Lds lds;
     uint32_t (&tab)[kLdsTabDwords] = lds.tab;
-    /* probabilities of a tile: sP[wave][product][column = pair slot + kPairs * parity][token] as dwords; a parity-0 column
+    /* four pairs: probabilities of a tile, sP[wave][column = pair + 4 * parity][token] as dwords; a parity-0 column
        keeps its binary16 value in the low half, a parity-1 column in the high half, and the other halves stay
        zero from the start of the kernel (nothing ever writes them) */
     auto &sP = lds.p;
+    __shared__ __attribute__((aligned(16))) uint32_t sK[WIDE ? kWavesPerBlock : 1][key_tile_bytes<DEEP>() / 4]; /* wide: the key tiles */
+    __shared__ __attribute__((aligned(16))) uint32_t sKrad[WIDE && DEEP ? kWavesPerBlock : 1][WIDE && DEEP ? 512 : 4];
     __shared__ __attribute__((aligned(16))) uint16_t sVrad[DEEP ? kWavesPerBlock : 1][DEEP ? 512 : 8];
     /* per-sequence data of batches of up to 64 sequences is staged in LDS with the tables, so that
        nothing between the barrier and the first tile request waits for global memory; its loads
@@ -528,26 +630,40 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
         for (int i = 0; i < kR2; ++i) {
             const int t = min((int)threadIdx.x + i * kThreads, 2047); /* entry t >> 5, column t & 31 */
             tq[i] = src[PQ_TAB_TQ + t];
-            tqa[i] = src[PQ_TAB_TQA + (t >> 5)];
-            tqb[i] = src[PQ_TAB_TQB + (t >> 5)];
+            if (!WIDE) {
+                tqa[i] = src[PQ_TAB_TQA + (t >> 5)];
+                tqb[i] = src[PQ_TAB_TQB + (t >> 5)];
+            }
             tbh[i] = src[PQ_TAB_TBH + 2 * (t >> 5) + (t & 1)];
         }
 #pragma unroll
         for (int i = 0; i < kR4; ++i) {
             const int t = min((int)threadIdx.x + i * kThreads, 4095); /* entry t >> 6, column (t >> 2) & 15, float t & 3 */
-            tbf[i] = src[PQ_TAB_TBF + 4 * (t >> 6) + (t & 3)];
+            if (WIDE) { /* two binary16 terms: dwords 0, 1 the four first terms, 2, 3 the second ones */
+                const uint32_t *f = src + PQ_TAB_TBF + 4 * (t >> 6) + 2 * (t & 1);
+                const float x = __uint_as_float(f[0]), y = __uint_as_float(f[1]);
+                h2 w = h2{(_Float16)x, (_Float16)y};
+                if (t & 2) w = h2{(_Float16)(x - (float)w.x), (_Float16)(y - (float)w.y)};
+                tbf[i] = __builtin_bit_cast(uint32_t, w);
+            } else {
+                tbf[i] = src[PQ_TAB_TBF + 4 * (t >> 6) + (t & 3)];
+            }
         }
         if (threadIdx.x < 48) tup = src[PQ_TAB_UP + threadIdx.x];
-        uint4 *pz = reinterpret_cast<uint4 *>(&sP[0][0][0][0]);
-        for (int t = threadIdx.x; t < kWavesPerBlock * NV * kCols * 64 / 4; t += kThreads) pz[t] = make_uint4(0, 0, 0, 0);
+        if (!WIDE) {
+            uint4 *pz = reinterpret_cast<uint4 *>(&sP[0][0][0]);
+            for (int t = threadIdx.x; t < kWavesPerBlock * 8 * 64 / 4; t += kThreads) pz[t] = make_uint4(0, 0, 0, 0);
+        }
         if (threadIdx.x < 16) sDone[threadIdx.x >> 2][threadIdx.x & 3] = threadIdx.x < kWavesPerBlock ? 0 : 0x7FFFFFFF;
 #pragma unroll
         for (int i = 0; i < kR2; ++i) {
             const int t = (int)threadIdx.x + i * kThreads;
             if (t < 2048) {
                 tab[kTQ + t] = tq[i];
-                tab[kTQA + t] = tqa[i];
-                tab[kTQB + t] = tqb[i];
+                if (!WIDE) {
+                    tab[kTQA + t] = tqa[i];
+                    tab[kTQB + t] = tqb[i];
+                }
                 tab[kTBH + t] = tbh[i];
             }
         }
@@ -574,10 +690,10 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
     const int base = working > 0 ? total / working : 0, rem = total - base * working;
     /* Short shares: consecutive ones go to different workgroups, so that fewer shares than the launch has wavefronts
        occupy every CU (and its four SIMDs in turn) instead of filling the first CUs, and the wavefronts with one tile
-       more spread evenly (8700 tiles: 35.3 us per decode step against 37.4; 2048 tiles in shares of four, four column groups:
+       more spread evenly (8700 tiles: 35.3 us per decode step against 37.4; 2048 tiles in shares of four, sixteen pairs:
        41.4 against 47.1).  From four tiles on, once every wavefront has a share, the order makes
        1 % at most, and a CU whose wavefronts read neighbouring tiles is the better one (117.0 against 117.8 us at
-       65536 tiles, 126.9 against 127.9 at 25400 in four column groups). */
+       65536 tiles, 126.9 against 127.9 at 25400 with sixteen pairs). */
     const bool spread = base < 4 || working < (int)gridDim.x * kWavesPerBlock;
     const int w = spread ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kWavesPerBlock + wave;
     if (w >= working) return;
@@ -625,11 +741,11 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
     }
     const int g = lane >> 4, n = lane & 15;
     constexpr int kRadiiHalves = DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII;
-    const DeepRadii dr{sVrad[DEEP ? wave : 0], a.up_b5, a.up_b6, a.up_b7};
+    const DeepRadii dr{sVrad[DEEP ? wave : 0], sKrad[WIDE && DEEP ? wave : 0], a.up_b5, a.up_b6, a.up_b7};
     const char *tbh = reinterpret_cast<const char *>(tab + kTBH);
     /* where this lane (token) leaves its probabilities and where it (column) picks its operand up */
-    uint32_t *p_mine = &sP[wave][0][0][lane];
-    const uint32_t *p_col = &sP[wave][0][n & (kCols - 1)][4 * g];
+    uint32_t *p_mine = &sP[WIDE ? 0 : wave][0][lane];
+    const uint32_t *p_col = &sP[WIDE ? 0 : wave][n & 7][4 * g];
     /* rotated queries and partial results: the launch code keeps all three below 4 GB */
     const __amdgpu_buffer_rsrc_t q_rsrc = stream_descriptor(a.qrot, (uint32_t)a.B * a.M * a.Hq * (PQ_D * 2u));
     const __amdgpu_buffer_rsrc_t o_rsrc = stream_descriptor(a.ws_o, (uint32_t)a.n_pieces * (a.M * G) * (PQ_D * 4u));
@@ -655,142 +771,213 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
         const __amdgpu_buffer_rsrc_t kr = stream_descriptor(a.k_radii + stream_tile0 * kRadiiHalves, radii_bytes);
         const __amdgpu_buffer_rsrc_t vr = stream_descriptor(a.v_radii + stream_tile0 * kRadiiHalves, radii_bytes);
 
-        /* ---- q' operands (see QueryOperand); pair p = (query token p / G, head p % G) ---- */
-        QueryOperand<NG> qo;
+        /* ---- q' operands (see QueryOperand, WideQuery); pair p = (query token p / G, head p % G) ---- */
+        std::conditional_t<WIDE, WideQuery, QueryOperand> qo;
         /* lane-dependent addresses of the piece's prologue and epilogue are formed from a copy of the lane
            number that the compiler cannot trace: hoisted out of the piece loop they would be spilled */
         int lane_q = lane;
         asm volatile("" : "+v"(lane_q));
-#pragma unroll
-        for (int k = 0; k < NG; ++k) {
-            const int slot = lane_q & 3, qi = lane_q >> 2;
-            const int pair = 4 * k + slot;
-            const bool real = pair < a.M * G;
-            const int m = real ? pair / G : 0, head = real ? pair % G : 0;
+        const int pair_q = WIDE ? lane_q & 15 : lane_q & 3;
+        const bool real_q = pair_q < a.M * G;
+        const int m_q = real_q ? pair_q / G : 0; /* query token of this lane's pair */
+        {
+            const int head = real_q ? pair_q % G : 0;
             /* 32-bit offsets into the rotated queries: lane part in bytes, (sequence, kv head) part scalar */
-            const uint32_t lane_off = (uint32_t)((m * a.Hq + head) * PQ_D + 4 * qi) * 2u;
+            const uint32_t lane_off = (uint32_t)((m_q * a.Hq + head) * PQ_D + (WIDE ? 32 * (lane_q >> 4) : 4 * (lane_q >> 2))) * 2u;
             const uint32_t row_off = (uint32_t)((b * a.M * a.Hq + hk * G) * PQ_D) * 2u;
+            if constexpr (WIDE) {
 #pragma unroll
-            for (int set = 0; set < 2; ++set) {
-                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(q_rsrc, lane_off + (uint32_t)(64 * set) * 2u, row_off, 0);
-                qo.a[k][set].w[0] = real ? v.x : 0u;
-                qo.a[k][set].w[1] = real ? v.y : 0u;
+                for (int c = 0; c < 4; ++c) {
+                    const uint4 v = load16(q_rsrc, lane_off + 16u * c, row_off);
+                    qo.q[c].q = real_q ? v : make_uint4(0, 0, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int set = 0; set < 2; ++set) {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(q_rsrc, lane_off + (uint32_t)(64 * set) * 2u, row_off, 0);
+                    qo.a[set].w[0] = real_q ? v.x : 0u;
+                    qo.a[set].w[1] = real_q ? v.y : 0u;
+                }
             }
         }
-        f4 acc_o[NV][4];
-        /* exponent reference of a pair: the same in all lanes; l: this lane's share of the sum of its token's weights */
-        float m_ref[NG][4], l_run[NG][4];
+        /* o': four pairs -- coordinates 2 c (parity-0 columns) and 2 c + 1 of the half-blocks; wide -- coordinates c */
+        f4 acc_o[WIDE ? 8 : 4];
+        /* exponent reference: of four pairs, the same in all lanes; wide: of the lane's pair n.  l: this lane's share of the sum
+           of its tokens' weights */
+        constexpr int kLanePairs = WIDE ? 1 : 4;
+        float m_ref[kLanePairs], l_run[kLanePairs];
 #pragma unroll
-        for (int v = 0; v < NV; ++v)
+        for (int c = 0; c < (WIDE ? 8 : 4); ++c) acc_o[c] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc_o[v][c] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < NG; ++k)
-#pragma unroll
-            for (int h = 0; h < 4; ++h) { m_ref[k][h] = 0.f; l_run[k][h] = 0.f; }
+        for (int h = 0; h < kLanePairs; ++h) { m_ref[h] = 0.f; l_run[h] = 0.f; }
         bool have_ref = false; /* m_ref is a place holder until the first tile of the piece has set it */
 
         /* One tile.  MASKED: the tile holds tokens beyond the context, or beyond what one of the query
-         * tokens may see (lim[k][h]: tokens of this tile that pair 4 k + h sees; nv: tokens inside the context). */
-        auto do_tile = [&](auto masked_c, const KTileRaw &kraw, const VTileRaw &vraw, const int (&lim)[NG][4], int nv) {
+         * tokens may see (lim[h]: tokens of this tile that the pair sees; nv: tokens inside the context). */
+        auto do_tile = [&](auto masked_c, const KTileRaw &kraw, const VTileRaw &vraw, const int (&lim)[kLanePairs], int nv,
+                           int next) {
             constexpr bool MASKED = decltype(masked_c)::value;
-            float s[NG][4];
+            if constexpr (!WIDE) {
+                float s[4];
 #pragma unroll
-            for (int k = 0; k < NG; ++k)
-#pragma unroll
-                for (int h = 0; h < 4; ++h) s[k][h] = kProbShift - m_ref[k][h];
-            key_scores<NG, DEEP>(tab, kraw, qo, s, dr, lane); /* s = score - m_ref + kProbShift */
-            if (MASKED) {
-#pragma unroll
-                for (int k = 0; k < NG; ++k)
+                for (int h = 0; h < 4; ++h) s[h] = kProbShift - m_ref[h];
+                key_scores<DEEP>(tab, kraw, qo, s, dr, lane); /* s = score - m_ref + kProbShift */
+                if (MASKED) {
 #pragma unroll
                     for (int h = 0; h < 4; ++h)
-                        if (lane >= lim[k][h]) s[k][h] = -INFINITY;
-            }
-            float top = s[0][0];
+                        if (lane >= lim[h]) s[h] = -INFINITY;
+                }
+                float top = s[0];
 #pragma unroll
-            for (int k = 0; k < NG; ++k)
-#pragma unroll
-                for (int h = 0; h < 4; ++h) top = fmaxf(top, s[k][h]);
-            if (!have_ref || __ballot(top > kProbShift + kRefSlack) != 0ull) { /* wave-uniform */
-                float alpha_lane[NV]; /* factor of this lane's output column (pair n & (kPairs - 1) of the product) */
-#pragma unroll
-                for (int v = 0; v < NV; ++v) alpha_lane[v] = 1.f;
-#pragma unroll
-                for (int k = 0; k < NG; ++k) {
+                for (int h = 0; h < 4; ++h) top = fmaxf(top, s[h]);
+                if (!have_ref || __ballot(top > kProbShift + kRefSlack) != 0ull) { /* wave-uniform */
+                    float alpha_lane = 1.f; /* factor of this lane's output column (pair n & 3) */
 #pragma unroll
                     for (int h = 0; h < 4; ++h) {
-                        const float smax = __builtin_amdgcn_readfirstlane(wave_max_f(s[k][h]));
+                        const float smax = __builtin_amdgcn_readfirstlane(wave_max_f(s[h]));
                         /* move the reference so that the largest weight of the tile is 2^kProbShift; a pair that has
                            seen no token yet (smax == -inf) keeps its place holder */
                         float delta = smax == -INFINITY ? 0.f : smax - kProbShift;
                         if (have_ref) delta = fmaxf(delta, 0.f);
                         const float alpha = have_ref ? __builtin_amdgcn_exp2f(-delta) : 1.f; /* nothing accumulated yet */
-                        m_ref[k][h] += delta;
-                        s[k][h] -= delta;
-                        l_run[k][h] *= alpha;
-                        if ((n & (kPairs - 1)) == 4 * (k & 1) + h) alpha_lane[k / 2] = alpha;
+                        m_ref[h] += delta;
+                        s[h] -= delta;
+                        l_run[h] *= alpha;
+                        if ((n & 3) == h) alpha_lane = alpha;
                     }
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc_o[c] *= alpha_lane;
+                    have_ref = true;
                 }
-#pragma unroll
-                for (int v = 0; v < NV; ++v)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) acc_o[v][c] *= alpha_lane[v];
-                have_ref = true;
-            }
-            wave_lds_fence(); /* the passes of the previous tile have read their operands */
-#pragma unroll
-            for (int k = 0; k < NG; ++k) {
+                wave_lds_fence(); /* the passes of the previous tile have read their operands */
                 _Float16 ph[4];
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
-                    const float p = __builtin_amdgcn_exp2f(s[k][h]); /* exp2(-inf) = 0 for masked tokens */
-                    l_run[k][h] += p;
+                    const float p = __builtin_amdgcn_exp2f(s[h]); /* exp2(-inf) = 0 for masked tokens */
+                    l_run[h] += p;
                     ph[h] = (_Float16)p;
                 }
-                _Float16 *dst = reinterpret_cast<_Float16 *>(p_mine + ((k / 2) * kCols + 4 * (k & 1)) * 64);
+                _Float16 *dst = reinterpret_cast<_Float16 *>(p_mine);
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
-                    dst[2 * (h * 64)] = ph[h];                     /* column (pair, parity 0): low half */
-                    dst[2 * ((kPairs + h) * 64) + 1] = ph[h];      /* column (pair, parity 1): high half */
+                    dst[2 * (h * 64)] = ph[h];                 /* column (pair, parity 0): low half */
+                    dst[2 * ((4 + h) * 64) + 1] = ph[h];       /* column (pair, parity 1): high half */
                 }
-            }
-            if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
-            wave_lds_fence();
-            auto pass = [&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                H8 va[4];
-                value_operand<i, MASKED, DEEP>(tab, tbh, vraw, va, nv, g, dr, lane);
-#pragma unroll
-                for (int w = 0; w < NV; ++w) {
+                if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
+                wave_lds_fence();
+                auto pass = [&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    H8 va[4];
+                    value_operand<i, MASKED, DEEP>(tab, tbh, vraw, va, nv, g, dr, lane);
                     H8 pb;
-                    pb.q = *reinterpret_cast<const uint4 *>(p_col + w * (kCols * 64) + 16 * i);
+                    pb.q = *reinterpret_cast<const uint4 *>(p_col + 16 * i);
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        acc_o[w][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[c].v, pb.v, acc_o[w][c], 0, 0, 0);
+                        acc_o[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[c].v, pb.v, acc_o[c], 0, 0, 0);
+                };
+                pass(std::integral_constant<int, 0>{}); pass(std::integral_constant<int, 1>{});
+                pass(std::integral_constant<int, 2>{}); pass(std::integral_constant<int, 3>{});
+            } else {
+                /* The keys are in LDS: their loads are older than the value loads, and loads complete in order. */
+                if (DEEP) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kValueLoadsDeep) : "memory");
+                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kValueLoads) : "memory");
+                f4 s[4]; /* lane (g, n): pair n, tokens 16 i + 4 g + e */
+                int lane_k = lane;
+                asm volatile("" : "+v"(lane_k));
+                wide_scores<DEEP>(tab, sK[wave], qo, kProbShift - m_ref[0], s, dr, lane_k);
+                if (next < tile_hi) { /* the next tile's keys, once every read of this one's has returned */
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    request_k_tile<DEEP>(sK[wave], kc, kr, next, lane);
                 }
-            };
-            pass(std::integral_constant<int, 0>{}); pass(std::integral_constant<int, 1>{});
-            pass(std::integral_constant<int, 2>{}); pass(std::integral_constant<int, 3>{});
+                if (MASKED) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (16 * i + 4 * g + e >= lim[0]) s[i][e] = -INFINITY;
+                }
+                float top = s[0][0];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) top = fmaxf(top, s[i][e]);
+                if (!have_ref || __ballot(top > kProbShift + kRefSlack) != 0ull) { /* as above, for the lane's pair */
+                    top = fmaxf(top, __shfl_xor(top, 16));
+                    top = fmaxf(top, __shfl_xor(top, 32));
+                    float delta = top == -INFINITY ? 0.f : top - kProbShift;
+                    if (have_ref) delta = fmaxf(delta, 0.f);
+                    const float alpha = have_ref ? __builtin_amdgcn_exp2f(-delta) : 1.f;
+                    m_ref[0] += delta;
+                    l_run[0] *= alpha;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) s[i] -= delta;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) acc_o[c] *= alpha;
+                    have_ref = true;
+                }
+                h2 ph[4][2]; /* the weights as they come are the value product's operand: contraction over tokens 4 g + e */
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float p = __builtin_amdgcn_exp2f(s[i][e]);
+                        l_run[0] += p;
+                        ph[i][e >> 1][e & 1] = (_Float16)p;
+                    }
+                if (DEEP) {
+                    wave_lds_fence(); /* the passes of the previous tile have read their radii */
+                    stage_deep_value_radii(tab, dr, vraw.top, lane);
+                    wave_lds_fence();
+                }
+                auto passes = [&](auto ic) { /* passes i and i + 1: the contraction of one product */
+                    constexpr int i = decltype(ic)::value;
+                    H8 vc[8]; /* coordinate c of the half-block: tokens 4 g + e of the two passes */
+                    auto transposed = [&](auto kc) {
+                        constexpr int k = decltype(kc)::value;
+                        H8 va[4];
+                        value_operand<i + k, MASKED, DEEP>(tab, tbh, vraw, va, nv, g, dr, lane);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+#pragma unroll
+                            for (int e = 0; e < 2; ++e) {
+                                vc[2 * c].w[2 * k + e] = __builtin_amdgcn_perm(va[c].w[2 * e + 1], va[c].w[2 * e], 0x05040100u);
+                                vc[2 * c + 1].w[2 * k + e] = __builtin_amdgcn_perm(va[c].w[2 * e + 1], va[c].w[2 * e], 0x07060302u);
+                            }
+                    };
+                    transposed(std::integral_constant<int, 0>{});
+                    transposed(std::integral_constant<int, 1>{});
+                    H8 pb;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) pb.p[k] = ph[i + (k >> 1)][k & 1];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+                        acc_o[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vc[c].v, pb.v, acc_o[c], 0, 0, 0);
+                };
+                passes(std::integral_constant<int, 0>{}); passes(std::integral_constant<int, 2>{});
+            }
         };
 
         /* Tiles tile_lo .. tile_hi-1.  A tile is full when every query token sees all of its 64
          * tokens; the tiles after that (the sequence's last one, or its last two when the M newest
          * tokens straddle a tile boundary) are masked per pair.
          * The raw tile registers are single buffered: the next tiles are requested once the
-         * last pass has consumed the current ones; the other wavefronts resident on the SIMD cover the latency. */
+         * last pass has consumed the current ones; the other wavefronts resident on the SIMD cover the latency.  (Wide: the
+         * next key tile as soon as the scores have read this one.) */
         const int n_full = min(tile_hi, max(ctx - (a.M - 1), 0) >> 6);
         KTileRaw kraw;
         VTileRaw vraw;
-        load_k_tile<DEEP>(kraw, kc, kr, tile_lo, lane);
-        load_v_tile<DEEP>(vraw, vc, vr, tile_lo, lane);
+        auto request_values = [&](int t) {
+            if (WIDE) asm volatile("" ::: "memory"); /* behind the keys' requests, see the wait in do_tile */
+            load_v_tile<DEEP>(vraw, vc, vr, t, lane);
+        };
+        if (WIDE) request_k_tile<DEEP>(sK[wave], kc, kr, tile_lo, lane);
+        else load_k_tile<DEEP>(kraw, kc, kr, tile_lo, lane);
+        request_values(tile_lo);
         int tile = tile_lo;
         {
-            int lim[NG][4];
+            int lim[kLanePairs];
 #pragma unroll
-            for (int k = 0; k < NG; ++k)
-#pragma unroll
-                for (int h = 0; h < 4; ++h) lim[k][h] = 64;
+            for (int h = 0; h < kLanePairs; ++h) lim[h] = 64;
             for (; tile < n_full; ++tile) {
                 /* Issue priority by rank among the wavefronts of the SIMD: the hardware prefers the oldest, which
                    would run ahead and leave the youngest to finish alone at a fraction of the SIMD's issue rate.
@@ -803,28 +990,25 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
                     const int ahead = (d4.x > done) + (d4.y > done) + (d4.z > done) + (d4.w > done);
                     set_wave_priority(min(__builtin_amdgcn_readfirstlane(ahead), 3));
                 }
-                do_tile(std::false_type{}, kraw, vraw, lim, 64);
+                do_tile(std::false_type{}, kraw, vraw, lim, 64, tile + 1);
                 if (tile + 1 < tile_hi) {
-                    load_k_tile<DEEP>(kraw, kc, kr, tile + 1, lane);
-                    load_v_tile<DEEP>(vraw, vc, vr, tile + 1, lane);
+                    if (!WIDE) load_k_tile<DEEP>(kraw, kc, kr, tile + 1, lane);
+                    request_values(tile + 1);
                 }
             }
         }
         for (; tile < tile_hi; ++tile) { /* the masked tiles at the end of the sequence */
             const int nv = min(ctx - tile * 64, 64);
-            int lim[NG][4]; /* tokens of this tile that pair 4 k + h may see */
+            int lim[kLanePairs]; /* tokens of this tile that the pair may see */
 #pragma unroll
-            for (int k = 0; k < NG; ++k)
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    const int pair = 4 * k + h;
-                    const int m = pair < a.M * G ? pair / G : 0;
-                    lim[k][h] = ctx - (a.M - 1 - m) - tile * 64;
-                }
-            do_tile(std::true_type{}, kraw, vraw, lim, nv);
+            for (int h = 0; h < kLanePairs; ++h) {
+                const int m = WIDE ? m_q : (h < a.M * G ? h / G : 0);
+                lim[h] = ctx - (a.M - 1 - m) - tile * 64;
+            }
+            do_tile(std::true_type{}, kraw, vraw, lim, nv, tile + 1);
             if (tile + 1 < tile_hi) {
-                load_k_tile<DEEP>(kraw, kc, kr, tile + 1, lane);
-                load_v_tile<DEEP>(vraw, vc, vr, tile + 1, lane);
+                if (!WIDE) load_k_tile<DEEP>(kraw, kc, kr, tile + 1, lane);
+                request_values(tile + 1);
             }
         }
 
@@ -832,36 +1016,48 @@ __global__ __launch_bounds__(waves_per_block(NG) * 64, 1) void pq_attn_partial_k
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));
         const int ne = lane_e & 15, ge = lane_e >> 4;
+        const int pair = WIDE ? ne : ne & 3, par = WIDE ? 0 : ne >> 2;
+        float mm = m_ref[0], ll = 0.f; /* of this lane's pair */
+        if constexpr (WIDE) {
+            ll = l_run[0];
+            ll += __shfl_xor(ll, 16);
+            ll += __shfl_xor(ll, 32);
+        } else {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const int slot = ne & (kPairs - 1), pair = kPairs * v + slot;
-            float mm = 0.f, ll = 0.f; /* of this lane's pair */
+            for (int h = 0; h < 4; ++h) {
+                float l = l_run[h];
 #pragma unroll
-            for (int k = 2 * v; k < 2 * v + kPairs / 4; ++k)
+                for (int d = 32; d >= 1; d >>= 1) l += __shfl_xor(l, d); /* the same order in every lane */
+                if (pair == h) { mm = m_ref[h]; ll = l; }
+            }
+        }
+        if (ne < (WIDE ? 16 : 8) && pair < a.M * G) {
+            /* stores through descriptors as well: scalar piece offset, 32-bit lane offset */
+            const uint32_t piece_o = (uint32_t)piece * (uint32_t)(a.M * G) * (PQ_D * 4u);
+            const uint32_t lane_o = (uint32_t)(pair * PQ_D + 2 * 16 * ge + par) * 4u;
+            if constexpr (WIDE) {
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    float l = l_run[k][h];
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int d = 32; d >= 1; d >>= 1) l += __shfl_xor(l, d); /* the same order in every lane */
-                    if (slot == 4 * (k & 1) + h) { mm = m_ref[k][h]; ll = l; }
-                }
-            if (ne < kCols && pair < a.M * G) {
-                const int par = ne / kPairs;
-                /* stores through descriptors as well: scalar piece offset, 32-bit lane offset */
-                const uint32_t piece_o = (uint32_t)piece * (uint32_t)(a.M * G) * (PQ_D * 4u);
-                const uint32_t lane_o = (uint32_t)(pair * PQ_D + 2 * 16 * ge + par) * 4u;
+                    for (int c = 0; c < 8; c += 4)
+                        /* No scalar offset: the registers of a 16-byte store must not be overwritten in the next instruction, and the
+                           compiler keeps that distance only for stores without one (pairs 12 to 15 got other coordinates' sums). */
+                        __builtin_amdgcn_raw_buffer_store_b128(
+                            u32x4{__float_as_uint(acc_o[c][e]), __float_as_uint(acc_o[c + 1][e]), __float_as_uint(acc_o[c + 2][e]),
+                                  __float_as_uint(acc_o[c + 3][e])}, o_rsrc, piece_o + lane_o + 4u * (8 * e + c), 0, 0);
+            } else {
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc_o[v][c][e]), o_rsrc,
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc_o[c][e]), o_rsrc,
                                                               lane_o + 8u * (4 * e + c), piece_o, 0);
-                if (ge == 0 && par == 0) {
-                    const uint32_t piece_ml = (uint32_t)piece * (uint32_t)(a.M * G) * 8u;
-                    /* a pair that saw no token reports (-inf, 0), which the combine step drops */
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ll > 0.f ? mm : -INFINITY), ml_rsrc, pair * 8u, piece_ml, 0);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ll), ml_rsrc, pair * 8u + 4u, piece_ml, 0);
-                }
+            }
+            if (ge == 0 && par == 0) {
+                const uint32_t piece_ml = (uint32_t)piece * (uint32_t)(a.M * G) * 8u;
+                /* a pair that saw no token reports (-inf, 0), which the combine step drops */
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ll > 0.f ? mm : -INFINITY), ml_rsrc, pair * 8u, piece_ml, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ll), ml_rsrc, pair * 8u + 4u, piece_ml, 0);
             }
         }
 
@@ -1389,8 +1585,7 @@ Plan make_plan_slots(int B, int Hq, int Hkv, int64_t max_ctx, int64_t win_cap, i
        work items measured slower on the 32k-context batch (143 us against 149-156 us for 3/2 or 2 times
        as many) and write more partial results.  Small problems: no more wavefronts than shares of
        min_share tiles. */
-    const int per_simd = pairs <= 4 ? 4 : (pairs <= 8 ? 3 : 2);
-    const int block_waves = 4 * per_simd; /* = waves_per_block of the variant: one workgroup fills a CU */
+    const int block_waves = 4 * waves_per_simd(pairs); /* one workgroup fills a CU */
     int64_t slots = 256 * block_waves;
     const int64_t most = ((int64_t)B * Hkv * max_tiles + min_share - 1) / min_share;
     if (slots > most) slots = (most + block_waves - 1) / block_waves * block_waves;
@@ -1473,17 +1668,12 @@ struct StepWindow {
 };
 
 template <bool DEEP>
-void launch_partial_depth(int NG, dim3 grid, dim3 blk, hipStream_t s, const AttnArgs &aa)
+void launch_partial_depth(int pairs, dim3 grid, hipStream_t s, const AttnArgs &aa)
 {
-    if (NG == 1) hipLaunchKernelGGL((pq_attn_partial_kernel<1, DEEP>), grid, blk, 0, s, aa);
-    else if (NG == 2) hipLaunchKernelGGL((pq_attn_partial_kernel<2, DEEP>), grid, blk, 0, s, aa);
-    else hipLaunchKernelGGL((pq_attn_partial_kernel<4, DEEP>), grid, blk, 0, s, aa);
-}
-
-void launch_partial(int NG, bool deep, dim3 grid, dim3 blk, hipStream_t s, const AttnArgs &aa)
-{
-    if (deep) launch_partial_depth<true>(NG, grid, blk, s, aa);
-    else launch_partial_depth<false>(NG, grid, blk, s, aa);
+    const dim3 blk((unsigned)(4 * waves_per_simd(pairs) * 64));
+    if (pairs <= 4) hipLaunchKernelGGL((pq_attn_partial_kernel<false, 4, DEEP>), grid, blk, 0, s, aa);
+    else if (pairs <= 8) hipLaunchKernelGGL((pq_attn_partial_kernel<true, 3, DEEP>), grid, blk, 0, s, aa);
+    else hipLaunchKernelGGL((pq_attn_partial_kernel<true, 2, DEEP>), grid, blk, 0, s, aa);
 }
 
 template <int ROWS>
@@ -1523,8 +1713,6 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
     const int G = Hq / Hkv;
     if (M < 1 || M * G > 16) return PQ_EUNSUPPORTED;   /* at most 16 (query token, head) pairs per kv head */
     if ((app || win) && M != 1) return PQ_EUNSUPPORTED;
-    const int NG = M * G <= 4 ? 1 : (M * G <= 8 ? 2 : 4);
-    const bool deep = ctx->depth == 7;
     if (!pq_aligned16(q) || !pq_aligned16(out) || !pq_aligned16(k_codes) || !pq_aligned16(k_radii) ||
         !pq_aligned16(v_codes) || !pq_aligned16(v_radii) || !pq_aligned16(workspace))
         return PQ_EALIGN;
@@ -1593,8 +1781,8 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
     aa.consts = ds->consts;
     aa.up_b5 = ctx->upper_bits[0]; aa.up_b6 = ctx->upper_bits[1]; aa.up_b7 = ctx->upper_bits[2];
     pq_prof_before(0, s);
-    const dim3 grid(p.blocks), blk((unsigned)(waves_per_block(NG) * 64));
-    launch_partial(NG, deep, grid, blk, s, aa);
+    if (ctx->depth == 7) launch_partial_depth<true>(M * G, dim3(p.blocks), s, aa);
+    else launch_partial_depth<false>(M * G, dim3(p.blocks), s, aa);
     pq_prof_after(0, s);
 
     CombineArgs ca{ws_ml, ws_o, B, Hq, Hkv, M, plan,

@@ -1,0 +1,55 @@
+"""GPU test of the attention kernel for more than four (query token, head) pairs per kv head against the one for up to four:
+the same cache, the pairs taken four at a time by calls of one query token and at most four heads."""
+import pytest
+import torch
+
+from paper_2502_02617_amd import Context, PQ_KEY, PQ_VALUE, synth
+from tests.test_gpu_parity import DEV, say
+
+pytestmark = pytest.mark.gpu
+SCALE = 128 ** -0.5
+
+
+def attend(ctx, q, caches, start, lens, max_ctx):
+    """q [B, M, Hq, 128] -> fp32 [B, M, Hq, 128]"""
+    B, M, Hq = q.shape[:3]
+    out = torch.empty(q.shape, dtype=torch.float32, device=DEV)
+    ws = torch.empty(Context.attn_mq_workspace_bytes(B, M, Hq, caches[0].shape[0], max_ctx), dtype=torch.uint8, device=DEV)
+    ctx.attn_decode_polar_mq(q, out, *caches, start, lens, max_ctx, SCALE, ws)
+    return out
+
+
+@pytest.mark.parametrize("depth", [4, 7])
+@pytest.mark.parametrize("G,M", [(5, 1), (2, 4), (7, 1), (3, 3), (16, 1), (4, 4), (1, 16)])
+def test_wide_pairs_are_those_of_four_at_a_time(G, M, depth):
+    say(f"wide attention, {G} heads, {M} query tokens, depth {depth}")
+    B, H, n = 16, 8, 3300                                  # some three tiles per wavefront: pieces cross streams
+    ctx = Context(seed=2)
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    lens = torch.tensor([n - 37 * b for b in range(B)], dtype=torch.int32)
+    lens[3], lens[4], lens[5] = M, 64, 65                  # every query token sees one token at least
+    start = torch.arange(B) * (-(-n // 64) * 64)
+    pool = B * (-(-n // 64) * 64)
+    caches = []
+    for kind in (PQ_KEY, PQ_VALUE):
+        codes, radii = ctx.alloc_cache_for(H, pool, DEV)
+        x = synth.kv_stream(pool, H, seed=20 + kind).permute(1, 0, 2).contiguous().to(DEV)
+        ctx.encode_kv(x, kind, codes, radii)
+        caches += [codes, radii]
+    q = torch.randn((B, M, H * G, 128), generator=torch.Generator().manual_seed(5)).bfloat16().to(DEV)
+    start_d = start.to(DEV)
+    got = attend(ctx, q, caches, start_d, lens.to(DEV), n)
+    ref = torch.empty_like(got)
+    for m in range(M):
+        seen = (lens - (M - 1 - m)).clamp(min=0).to(DEV)
+        by_head = q[:, m].unflatten(1, (H, G))
+        for g in range(0, G, 4):
+            part = by_head[:, :, g:g + 4].flatten(1, 2)[:, None].contiguous()
+            ref[:, m].unflatten(1, (H, G))[:, :, g:g + 4] = attend(ctx, part, caches, start_d, seen, n)[:, 0].unflatten(1, (H, -1))
+    # the two differ by the rounding of weights and values to binary16 against other references: each is 7e-4 off 64 bits,
+    # rows that rest on few tokens up to five times that
+    assert (got - ref).norm() <= 1.4e-3 * ref.norm()
+    assert ((got - ref).norm(dim=-1) <= 2e-2 * torch.maximum(ref.norm(dim=-1), ref.norm(dim=-1).square().mean().sqrt())).all()
+    again = attend(ctx, q, caches, start_d, lens.to(DEV), n)
+    assert torch.equal(got, again)                         # the split of the work is fixed: the same bits
