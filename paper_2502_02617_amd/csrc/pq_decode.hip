@@ -62,6 +62,18 @@ __device__ __forceinline__ int dq_lane()
     return lane;
 }
 
+/* A tile to LDS as it is (codes, then the radius plane of `radii_bytes`), by loads that write there and take no registers. */
+__device__ __forceinline__ void dq_request_tile(uint32_t *img, const uint8_t *tc, const uint16_t *tr, int radii_bytes, int lane)
+{
+    typedef const __attribute__((address_space(1))) void *Global;
+    typedef __attribute__((address_space(3))) void *Lds;
+    __builtin_amdgcn_global_load_lds((Global)(tc + 16 * lane), (Lds)img, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((Global)(tc + 1024 + 16 * lane), (Lds)(img + 256), 16, 0, 0);
+    if (lane < (PQL_CODE_BYTES - 2048) / 16) __builtin_amdgcn_global_load_lds((Global)(tc + 2048 + 16 * lane), (Lds)(img + 512), 16, 0, 0);
+    if (16 * lane < radii_bytes)
+        __builtin_amdgcn_global_load_lds((Global)(reinterpret_cast<const uint8_t *>(tr) + 16 * lane), (Lds)(img + PQL_CODE_BYTES / 4), 16, 0, 0);
+}
+
 /* `width` bits at bit BIT of a string of dwords */
 template <int BIT, int WIDTH>
 __device__ __forceinline__ uint32_t dq_field(const uint32_t *w)
@@ -177,9 +189,9 @@ __device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, fl
  * copy.  262144 vectors to bf16: 242 us with the generic bit reader and fp32 sums on 16 tokens per workgroup -> 33 us
  * for keys, 35 for values; to fp32 243 -> 48 and 51.  Every register counts: with what follows from the lane number kept
  * over the loop, up to 11 spilled registers cost values 39.5 us (fp32 57; Hadamard 34 against 28 now), and requesting the
- * next half tile ahead of the products spills more than it hides (45).  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
+ * next half tile ahead of the products in registers spills more than it hides (45).  AHEAD: it is requested to LDS, which takes none.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
  * spill 100 registers; value slots are read from an image in LDS because a token's 16 slots are spread over 16 strings. */
-template <int KIND, int OT, bool UNIT>
+template <int KIND, int OT, bool UNIT, bool AHEAD>
 __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs a)
 {
     constexpr int kChunks = 4 * 8 * 64; /* of eight halves: (64-coordinate group, parity), k-step, lane */
@@ -187,10 +199,20 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
     __shared__ __attribute__((aligned(16))) float tq[2][64][2], tb[64][4];
     __shared__ float2 tup[24];
     __shared__ __attribute__((aligned(16))) float sUn[kDecodeWaves][32];
-    __shared__ __attribute__((aligned(16))) uint32_t img[KIND == PQ_VALUE ? kDecodeWaves : 1][KIND == PQ_VALUE ? kTileDwords : 4];
+    __shared__ __attribute__((aligned(16))) uint32_t img[AHEAD || KIND == PQ_VALUE ? kDecodeWaves : 1][AHEAD || KIND == PQ_VALUE ? kTileDwords : 4];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const PqDeviceConsts &K = *a.consts;
+    /* consecutive half tiles go to different workgroups: a short range occupies every CU */
+    const int64_t stride = (int64_t)kDecodeWaves * gridDim.x;
+    const int radii_halves = a.deep ? PQ_DEEP_RADII_HALVES : PQL_RADII;
+    auto request = [&](int64_t item, int lane) {
+        const int64_t full_tile = item >> 1, head = full_tile / a.n_tiles, tile = a.first_tile + (full_tile - head * a.n_tiles);
+        const int64_t at = head * a.pool_tiles + tile;
+        dq_request_tile(img[wave], a.codes + at * PQL_CODE_BYTES, a.radii + at * radii_halves, 2 * radii_halves, lane);
+    };
+    int64_t item = (int64_t)wave * gridDim.x + blockIdx.x;
+    if (AHEAD && item < a.n_items) request(item, dq_lane()); /* under way while S is staged */
     {
         /* chunk (grp, par, ks, lane): S[64 grp + 2 (lane & 31) + par][64 (lane >> 5) + 8 ks .. + 7], the k order of the
            tokens' operand below */
@@ -226,30 +248,37 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
     const int b5 = K.up_bits[0], b6 = K.up_bits[1], b7 = K.up_bits[2];
     __syncthreads();
 
-    /* consecutive half tiles go to different workgroups: a short range occupies every CU */
-    for (int64_t item = (int64_t)wave * gridDim.x + blockIdx.x; item < a.n_items; item += (int64_t)kDecodeWaves * gridDim.x) {
+    for (; item < a.n_items; item += stride) {
         const int lane = dq_lane(), j = lane & 31, H = lane >> 5;
         const int64_t full_tile = item >> 1, head = full_tile / a.n_tiles, tile = a.first_tile + (full_tile - head * a.n_tiles);
         const int half = (int)(item & 1), tau = 32 * half + j;
         const int64_t row0 = tile * 64 + 32 * half - a.token0; /* output row of the half tile's first slot */
-        if (row0 + 32 <= 0 || row0 >= a.n_tokens) continue;
-        const uint8_t *tc = a.codes + (head * a.pool_tiles + tile) * PQL_CODE_BYTES;
-        const uint16_t *tr = a.radii + (head * a.pool_tiles + tile) * (a.deep ? PQ_DEEP_RADII_HALVES : PQL_RADII);
+        if (!AHEAD && (row0 + 32 <= 0 || row0 >= a.n_tokens)) continue;
         TokenHalf t;
-        if (KIND == PQ_KEY) {
-            dq_read_key(t, tc, tr, tau, H, a.deep != 0);
-        } else {
+        const uint8_t *tc = a.codes + (head * a.pool_tiles + tile) * PQL_CODE_BYTES;
+        const uint16_t *tr = a.radii + (head * a.pool_tiles + tile) * radii_halves;
+        if constexpr (AHEAD) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); /* the tile is in LDS */
+            tc = reinterpret_cast<const uint8_t *>(img[wave]);
+            tr = reinterpret_cast<const uint16_t *>(tc + PQL_CODE_BYTES);
+        } else if constexpr (KIND == PQ_VALUE) {
             uint4 *im = reinterpret_cast<uint4 *>(img[wave]);
             for (int c = lane; c < PQL_CODE_BYTES / 16; c += 64) im[c] = reinterpret_cast<const uint4 *>(tc)[c];
             if (!a.deep) im[PQL_CODE_BYTES / 16 + lane] = reinterpret_cast<const uint4 *>(tr)[lane];
             dq_wave_sync();
-            dq_read_value(t, img[wave], tau, H, a.deep != 0);
         }
+        if (KIND == PQ_KEY) dq_read_key(t, tc, tr, tau, H, a.deep != 0);
+        else dq_read_value(t, img[wave], tau, H, a.deep != 0);
         if (a.deep) {
             const uint32_t word = reinterpret_cast<const uint32_t *>(tr)[tau];
 #pragma unroll
             for (int b = 0; b < 4; ++b) t.r[b] = pq_deep_block_radius(word, b5, b6, b7, tup, 4 * H + b);
             t.top = (word >> 16) & 0x7FFFu;
+        }
+        if constexpr (AHEAD) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); /* and has been read: the next one may follow */
+            if (item + stride < a.n_items) request(item + stride, lane);
+            if (row0 + 32 <= 0 || row0 >= a.n_tokens) continue;
         }
         /* the token's largest radius goes to [2^14, 2^15) */
         const uint32_t exponent = max(t.top >> 10, 1u);
@@ -396,8 +425,15 @@ void launch_decode(const DecodeArgs &a, bool unit, int rotated, int n_heads, hip
         return;
     }
     const dim3 grid((unsigned)(a.n_items < 256 ? a.n_items : 256)); /* one workgroup per CU */
-    if (unit) hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, true>), grid, dim3(kDecodeThreads), 0, s, a);
-    else hipLaunchKernelGGL((pq_decode_kernel<KIND, OT, false>), grid, dim3(kDecodeThreads), 0, s, a);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kDecodeThreads), 0, s, a); };
+    /* The next tile ahead of the products: for fp32 output, once a wavefront has more than one (32768 tokens of 8 heads, us with and
+       without: values 45.1 / 51.0, keys with a +-1 S 38.3 / 43.3; to bf16 36.4 / 35.2, whose stores leave less to wait for than the
+       LDS pass costs; 3001 fp32 keys 11.1 / 10.6). */
+    const bool ahead = OT == PQ_F32 && a.n_items > 256 * kDecodeWaves;
+    if constexpr (OT == PQ_F32)
+        if (ahead) return unit ? launch(pq_decode_kernel<KIND, OT, true, true>) : launch(pq_decode_kernel<KIND, OT, false, true>);
+    if (unit) launch(pq_decode_kernel<KIND, OT, true, false>);
+    else launch(pq_decode_kernel<KIND, OT, false, false>);
 }
 
 struct ExportArgs {

@@ -53,3 +53,21 @@ def test_dequant_ranges_and_strides(which, kind):
                 norm = np.linalg.norm(ref, axis=2)
                 err = np.linalg.norm(got - ref, axis=2)
                 assert np.all(err <= bound * norm), (rotated, token0, n, dtype, width, float(np.max(err / np.maximum(norm, 1e-30))))
+
+
+@pytest.mark.parametrize("which", ["dense", "hadamard", "deep"])
+def test_a_long_range_is_its_pieces(which):
+    say(f"DeQuant of a long range, {which}")
+    ctx = make((2, 2, 2))[0] if which == "deep" else Context(seed=3, hadamard=which == "hadamard")
+    H, n, first = 8, 20000, 37                             # 5008 half tiles: more than one per wavefront; the pieces take one
+    pool = -(-(first + n) // 64) * 64
+    x = synth.kv_stream(pool, H, seed=4).permute(1, 0, 2).contiguous().to(DEV)
+    for kind in (PQ_KEY, PQ_VALUE):
+        codes, radii = ctx.alloc_cache_for(H, pool, DEV)
+        ctx.encode_kv(x, kind, codes, radii)
+        whole = torch.empty((n, H, 128), dtype=torch.float32, device=DEV)
+        parts = torch.empty_like(whole)
+        ctx.decode_kv(kind, codes, radii, first, n, whole)
+        for at in range(0, n, 5000):
+            ctx.decode_kv(kind, codes, radii, first + at, 5000, parts[at:at + 5000])
+        assert torch.equal(whole, parts)
