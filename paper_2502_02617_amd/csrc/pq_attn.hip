@@ -925,7 +925,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                         ph[i][e >> 1][e & 1] = (_Float16)p;
                     }
                 if (DEEP) {
-                    wave_lds_fence(); /* the passes of the previous tile have read their radii */
+                    /* the passes of the previous tile have read theirs: the fence of wide_scores lies in between */
                     stage_deep_value_radii(tab, dr, vraw.top, lane);
                     wave_lds_fence();
                 }
