@@ -575,8 +575,8 @@ __device__ __forceinline__ float wave_max_f(float x)
  * WIDE: lane (g, n) holds the scores of pair n for tokens 16 i + 4 g + e, so a pair's reference and sum are the lane's own and its weights
  * are the value product's operand as they are (no LDS); the values of two passes are transposed by permutes (64 per
  * tile) and contracted over tokens, half of the matrix work of the widened contraction.  Both kinds are bound by instruction issue: per tile
- * some 700 vector instructions for any number of pairs up to sixteen, where the form for four pairs, its groups of four repeated, took 820 for
- * two groups and 1090 for four.  Four query tokens of four heads, 16 sequences of 12700 tokens: 107 -> 78 us per call; ten pairs at
+ * some 740 vector and 48 matrix instructions for any number of pairs up to sixteen, where the form for four pairs, its groups of four repeated,
+ * took 716 and 80 for two groups and 1020 and 160 for four.  Four query tokens of four heads, 16 sequences of 12700 tokens: 107 -> 78 us per call; ten pairs at
  * 32768 tokens 198 -> 158; eight pairs 73.6 -> 69.3; at depth 7 twelve pairs 106 -> 85, eight 75.7 -> 75.5.  Key tiles that went to LDS ahead of
  * their use made four pairs slower (35.1 -> 36.7 us for 32 short sequences, 112.6 -> 114.9 at 65536 tiles: the LDS is as busy as the vector
  * ALU there). */
