@@ -421,13 +421,48 @@ __device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &
     block(std::integral_constant<int, 6>{}); block(std::integral_constant<int, 7>{});
 }
 
+/* The power of two that the wide kernel takes out of a key tile's radii, so that the largest of its `nv` tokens lies in
+ * [2^14, 2^15) -- 2^15 at most: smaller radii are next to the binary16 grid themselves.  Lane tau looks at token tau. */
+struct TileScale { float by, back; /* by * back = 1 */ };
+
+template <bool DEEP>
+__device__ __forceinline__ TileScale key_scale(const uint32_t *radii, int nv, int lane)
+{
+    uint32_t top;
+    if (DEEP) { /* the token's radius bounds those of its blocks */
+        top = radii[lane] >> 16 & 0x7FFFu;
+    } else {
+        typedef uint16_t us2 __attribute__((ext_vector_type(2)));
+        const uint4 r = *reinterpret_cast<const uint4 *>(radii + 4 * lane);
+        const uint32_t m = scalar_const(0x7FFF7FFFu);
+        const us2 a = __builtin_elementwise_max(__builtin_bit_cast(us2, r.x & m), __builtin_bit_cast(us2, r.y & m));
+        const us2 b = __builtin_elementwise_max(__builtin_bit_cast(us2, r.z & m), __builtin_bit_cast(us2, r.w & m));
+        const us2 c = __builtin_elementwise_max(a, b);
+        top = c.x > c.y ? c.x : c.y;
+    }
+    if (lane >= nv) top = 0u; /* what lies beyond the context decides nothing */
+    /* the wavefront's maximum: inside rows of 16 lanes, then from row to row (lane 63 has them all) */
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0xB1, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x4E, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x141, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x140, 0xF, 0xF, true));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x142, 0xA, 0xF, false));
+    top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x143, 0xC, 0xF, false));
+    const uint32_t e = max((uint32_t)__builtin_amdgcn_readlane((int)top, 63) >> 10, 14u); /* radii below 2^(e - 14) */
+    return TileScale{__uint_as_float((156u - e) << 23), __uint_as_float((98u + e) << 23)};
+}
+
 /* ---- more than four pairs: dense scores ----
  * Scores of 64 tokens for sixteen pairs.  The 4x4x4 form above costs a scaling in fp32 per quarter and pair, 512 for
  * sixteen pairs; here a key is formed once and multiplied by all pairs on v_mfma_f32_16x16x32_f16, in four passes of sixteen
- * tokens: lane (g, n) rebuilds blocks 2 g and 2 g + 1 of token 16 i + n.  Nothing is rounded that is not rounded
- * above: radius times block-table entry and that times the quarter-table entry are each two binary16 terms (a product and its
- * exact rest, with the small factors' products added to the rest), the block table holds two terms, and both terms are
- * multiplied by q'.  The result is in the order in which the value product takes its weights: lane (g, n) holds
+ * tokens: lane (g, n) rebuilds blocks 2 g and 2 g + 1 of token 16 i + n.  The block table, at depth 7 the radii, radius times
+ * block-table entry and that times the quarter-table entry are two binary16 terms each (a product and its
+ * rest, with the small factors' products added to the rest), and both terms of a key are multiplied by q'.  Each of these
+ * roundings leaves 2^-23 of its number, or 2^-39 of the tile's largest radius where that is more (key_scale); the form
+ * above rounds the first two to fp32 and adds 32 products to the reference one after the other.  Against 64 bits with the
+ * same tables a score is off by 1.6e-8 of |q'| |k| (1.9e-8 at depth 7) for keys of any size, 5.5e-8 in the form above; without
+ * the scale 5.6e-8, and 1.5e-6 for radii 2^-10 times as large.
+ * The result is in the order in which the value product takes its weights: lane (g, n) holds
  * pair n, tokens 16 i + 4 g + e.
  * The key tile lies in LDS (request_k_tile): bits [92 g, 92 g + 92) of a token's string are fetched as four dwords and
  * brought to bit 0, so that every field sits at a fixed position. */
@@ -435,27 +470,29 @@ struct WideQuery { H8 q[4]; /* lane (g, n): coordinates 32 g + 8 c .. + 7 of pai
 
 template <bool DEEP>
 __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t *kt, const WideQuery &wq, float start, f4 (&s)[4],
-                                            const DeepRadii &dr, int lane)
+                                            const DeepRadii &dr, int nv, int lane)
 {
     const uint32_t n = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4, col16 = n * 16u;
     const char *base = reinterpret_cast<const char *>(kt);
+    const TileScale scale = key_scale<DEEP>(kt + PQL_CODE_BYTES / 4, nv, lane);
     /* string dwords 0 .. 2 | 2 .. 5 | 5 .. 8 | 8 .. 11 */
     uint32_t o01 = g == 3u ? PQL_OFF_P2 + 12u * n : (g == 2u ? PQL_OFF_P1 + 4u : 8u * g) + 16u * n;
     uint32_t o2 = g == 1u ? PQL_OFF_P1 + 16u * n : o01 + 8u;
     uint32_t o3 = g == 3u ? PQL_OFF_KP3 + 4u * (n >> 1) : (g == 2u ? PQL_OFF_P2 + 12u * n : o2 + 4u);
     const uint32_t step = g == 3u ? 192u : 256u, step3 = g == 3u ? 32u : (g == 2u ? 192u : 256u);
     const uint32_t sh = g == 0u ? 0u : 32u - 4u * g, sh3 = g == 3u ? 16u * (n & 1u) : 0u;
-    const f4 c0 = f4{start, start, start, start};
-    if (DEEP) { /* lane tau rebuilds the radii of token tau's blocks and leaves them as two binary16 terms each */
+    if (DEEP) { /* lane tau rebuilds the radii of token tau's blocks and leaves them, scaled, as two binary16 terms each */
         float r[8];
         pq_deep_block_radii(kt[PQL_CODE_BYTES / 4 + lane], dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + kTUp), r);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
-            const _Float16 hi = (_Float16)r[b];
-            dr.krad[8 * lane + b] = __builtin_bit_cast(uint32_t, h2{hi, (_Float16)(r[b] - (float)hi)});
+            const float x = r[b] * scale.by;
+            const _Float16 hi = (_Float16)x;
+            dr.krad[8 * lane + b] = __builtin_bit_cast(uint32_t, h2{hi, (_Float16)(x - (float)hi)});
         }
         wave_lds_fence();
     }
+    const h2 by = h2{(_Float16)scale.by, (_Float16)scale.by};
     auto pass = [&](auto ic) {
         constexpr int i = decltype(ic)::value;
         const uint32_t w0 = *reinterpret_cast<const uint32_t *>(base + o01), w1 = *reinterpret_cast<const uint32_t *>(base + o01 + 4);
@@ -464,9 +501,9 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
         const uint32_t x[3] = {__builtin_amdgcn_alignbit(w1, w0, sh), __builtin_amdgcn_alignbit(w2, w1, sh),
                                __builtin_amdgcn_alignbit(w3, w2, sh)};
         /* radii of blocks 2 g, 2 g + 1: stored ones, or of rebuilt ones a first and a second term each */
-        const h2 ra = as_h2(DEEP ? dr.krad[(16 * i + n) * 8 + 2 * g] : kt[PQL_CODE_BYTES / 4 + 4 * (16 * i + n) + g]);
+        const h2 ra = DEEP ? as_h2(dr.krad[(16 * i + n) * 8 + 2 * g]) : as_h2(kt[PQL_CODE_BYTES / 4 + 4 * (16 * i + n) + g]) * by;
         const h2 rb = DEEP ? as_h2(dr.krad[(16 * i + n) * 8 + 2 * g + 1]) : ra;
-        s[i] = c0;
+        s[i] = f4{0.f, 0.f, 0.f, 0.f};
         auto block = [&](auto bc) {
             constexpr int b = decltype(bc)::value, at = PQL_BLOCK_BITS * b;
             const H8 t43 = [&] {
@@ -497,6 +534,8 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
             half(std::integral_constant<int, 0>{}); half(std::integral_constant<int, 1>{});
         };
         block(std::integral_constant<int, 0>{}); block(std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[i][e] = __builtin_fmaf(s[i][e], scale.back, start);
     };
     pass(std::integral_constant<int, 0>{}); pass(std::integral_constant<int, 1>{});
     pass(std::integral_constant<int, 2>{}); pass(std::integral_constant<int, 3>{});
@@ -884,7 +923,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                 f4 s[4]; /* lane (g, n): pair n, tokens 16 i + 4 g + e */
                 int lane_k = lane;
                 asm volatile("" : "+v"(lane_k));
-                wide_scores<DEEP>(tab, sK[wave], qo, kProbShift - m_ref[0], s, dr, lane_k);
+                wide_scores<DEEP>(tab, sK[wave], qo, kProbShift - m_ref[0], s, dr, MASKED ? nv : 64, lane_k);
                 if (next < tile_hi) { /* the next tile's keys, once every read of this one's has returned */
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     request_k_tile<DEEP>(sK[wave], kc, kr, next, lane);

@@ -53,3 +53,37 @@ def test_wide_pairs_are_those_of_four_at_a_time(G, M, depth):
     assert ((got - ref).norm(dim=-1) <= 2e-2 * torch.maximum(ref.norm(dim=-1), ref.norm(dim=-1).square().mean().sqrt())).all()
     again = attend(ctx, q, caches, start_d, lens.to(DEV), n)
     assert torch.equal(got, again)                         # the split of the work is fixed: the same bits
+
+
+@pytest.mark.parametrize("depth", [4, 7])
+@pytest.mark.parametrize("G", [5, 16])
+def test_small_keys_are_scored_as_large_ones(G, depth):
+    """Key radii times 2^-shift and queries times 2^shift, both exactly: the same scores but for their rounding, which is some 6e-8
+    of |q'| |k| = 16 each.  A weight moves to the next binary16 number, by 2^-10.5 of itself, where that makes it cross the
+    middle between two: a share of 2^11 4e-6 of them does if the scores differ by 4e-6."""
+    say(f"wide attention, {G} heads, keys of several sizes, depth {depth}")
+    B, H, n = 16, 8, 64
+    ctx = Context(seed=2)
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    caches = []
+    for kind in (PQ_KEY, PQ_VALUE):
+        codes, radii = ctx.alloc_cache_for(H, B * n, DEV)
+        x = torch.randn((B * n, H, 128), generator=torch.Generator().manual_seed(20 + kind)).to(DEV)
+        ctx.encode_kv(x, kind, codes, radii)
+        caches += [codes, radii]
+    radii = caches[1].clone()
+    small = caches[1].view(torch.float16)[..., 1::2] if depth == 7 else caches[1].view(torch.float16)
+    large = small.clone()
+    assert 1.0 < large.min() and large.max() < 32.0            # normal numbers at every shift
+    q = torch.randn((B, 1, H * G, 128), generator=torch.Generator().manual_seed(5)).bfloat16().to(DEV)
+    start, lens = torch.arange(B, device=DEV) * n, torch.full((B,), n, dtype=torch.int32, device=DEV)
+    lens[1::2] -= torch.arange(0, 56, 7, dtype=torch.int32, device=DEV)
+    ref = attend(ctx, q, caches, start, lens, n)
+    for shift in (4, 8, 12, 14):
+        small.copy_(large * 2.0 ** -shift)
+        got = attend(ctx, q * 2.0 ** shift, caches, start, lens, n)
+        rel = float((got - ref).norm() / ref.norm())
+        print(f"2^-{shift}: relative difference {rel:.2e}")
+        assert rel <= 2 ** -10.5 * (2 ** 11 * 4e-6) ** 0.5
+    assert not torch.equal(radii, caches[1])
