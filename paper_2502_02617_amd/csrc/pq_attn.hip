@@ -44,6 +44,7 @@
  * and the values are brought to one coordinate per register by permutes.
  */
 #include <type_traits>
+#include <utility>
 
 #include "pq_common.h"
 #include "pq_polar.h"
@@ -246,29 +247,46 @@ __device__ __forceinline__ void load_k_tile(KTileRaw &t, __amdgpu_buffer_rsrc_t 
     else t.rad = load16(radii, lane * 16u, tile * (PQL_RADII * 2u));
 }
 
-/* vector memory instructions of a value tile: load_v_tile */
-constexpr int kValueLoads = 6, kValueLoadsDeep = 5;
+/* Load number I of a value tile: one vector memory instruction.  The wide kernel counts them (keys_arrived): a tile takes
+ * value_loads<DEEP>() of them, and load_v_tile issues exactly those. */
+template <bool DEEP> constexpr int value_loads() { return DEEP ? 5 : 6; }
+
+template <bool DEEP, int I>
+__device__ __forceinline__ void load_v_part(VTileRaw &t, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t radii, uint32_t tile,
+                                            uint32_t lane)
+{
+    static_assert(I < value_loads<DEEP>(), "value_loads counts the parts");
+    constexpr int J = DEEP ? I - 1 : I; /* depth 7: the radii, from which others are rebuilt first, come first */
+    const uint32_t co = tile * PQL_CODE_BYTES;
+    if constexpr (J < 0) {
+        t.top = __builtin_amdgcn_raw_buffer_load_b32(radii, lane * 4u, tile * (PQ_DEEP_RADII_HALVES * 2u), 0);
+    } else if constexpr (J < 2) {
+        const uint4 a = load16(codes, lane * 16u, co + (J ? PQL_OFF_P1 : PQL_OFF_P0));
+        t.q[4 * J] = a.x; t.q[4 * J + 1] = a.y; t.q[4 * J + 2] = a.z; t.q[4 * J + 3] = a.w;
+    } else if constexpr (J == 2) {
+        const u32x2 c = __builtin_amdgcn_raw_buffer_load_b64(codes, lane * 8u, co + PQL_OFF_P2, 0);
+        t.q[8] = c.x; t.q[9] = c.y;
+    } else if constexpr (J == 3) {
+        const u32x3 x = __builtin_amdgcn_raw_buffer_load_b96(codes, (lane >> 1) * 12u, co + PQL_OFF_VB, 0);
+        t.b[0] = x.x; t.b[1] = x.y; t.b[2] = x.z;
+    } else {
+        (J == 4 ? t.rad0 : t.rad1) = load16(radii, (lane >> 1) * 32u, tile * (PQL_RADII * 2u) + (J == 4 ? 0u : 16u));
+    }
+}
+
+template <bool DEEP, int... I>
+__device__ __forceinline__ void load_v_parts(VTileRaw &t, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t radii, uint32_t tile,
+                                             uint32_t lane, std::integer_sequence<int, I...>)
+{
+    (load_v_part<DEEP, I>(t, codes, radii, tile, lane), ...);
+}
 
 template <bool DEEP>
 __device__ __forceinline__ void load_v_tile(VTileRaw &t, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t radii,
                                             uint32_t tile, uint32_t lane)
 {
     asm volatile("" : "+v"(lane));
-    const uint32_t co = tile * PQL_CODE_BYTES;
-    const uint4 a = load16(codes, lane * 16u, co + PQL_OFF_P0);
-    const uint4 b = load16(codes, lane * 16u, co + PQL_OFF_P1);
-    const u32x2 c = __builtin_amdgcn_raw_buffer_load_b64(codes, lane * 8u, co + PQL_OFF_P2, 0);
-    const u32x3 x = __builtin_amdgcn_raw_buffer_load_b96(codes, (lane >> 1) * 12u, co + PQL_OFF_VB, 0);
-    t.q[0] = a.x; t.q[1] = a.y; t.q[2] = a.z; t.q[3] = a.w;
-    t.q[4] = b.x; t.q[5] = b.y; t.q[6] = b.z; t.q[7] = b.w;
-    t.q[8] = c.x; t.q[9] = c.y;
-    t.b[0] = x.x; t.b[1] = x.y; t.b[2] = x.z;
-    if (DEEP) {
-        t.top = __builtin_amdgcn_raw_buffer_load_b32(radii, lane * 4u, tile * (PQ_DEEP_RADII_HALVES * 2u), 0);
-    } else {
-        t.rad0 = load16(radii, (lane >> 1) * 32u, tile * (PQL_RADII * 2u));
-        t.rad1 = load16(radii, (lane >> 1) * 32u, tile * (PQL_RADII * 2u) + 16u);
-    }
+    load_v_parts<DEEP>(t, codes, radii, tile, lane, std::make_integer_sequence<int, value_loads<DEEP>()>{});
 }
 
 /* Key tile of the wide kernel: to LDS as it is, by loads that write there and take no registers, requested by the wavefront that
@@ -291,6 +309,10 @@ __device__ __forceinline__ void request_k_tile(uint32_t *dst, __amdgpu_buffer_rs
         __builtin_amdgcn_raw_ptr_buffer_load_lds(radii, (LdsPtr)(dst + PQL_CODE_BYTES / 4), 16, off,
                                                  tile * ((DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) * 2u), 0, 0);
 }
+
+/* The key tile requested ahead of the values' loads is in LDS: vector memory instructions complete in order. */
+template <bool DEEP>
+__device__ __forceinline__ void keys_arrived() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(value_loads<DEEP>()) : "memory"); }
 
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -917,9 +939,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                 pass(std::integral_constant<int, 0>{}); pass(std::integral_constant<int, 1>{});
                 pass(std::integral_constant<int, 2>{}); pass(std::integral_constant<int, 3>{});
             } else {
-                /* The keys are in LDS: their loads are older than the value loads, and loads complete in order. */
-                if (DEEP) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kValueLoadsDeep) : "memory");
-                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kValueLoads) : "memory");
+                keys_arrived<DEEP>();
                 f4 s[4]; /* lane (g, n): pair n, tokens 16 i + 4 g + e */
                 int lane_k = lane;
                 asm volatile("" : "+v"(lane_k));
@@ -1006,7 +1026,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
         KTileRaw kraw;
         VTileRaw vraw;
         auto request_values = [&](int t) {
-            if (WIDE) asm volatile("" ::: "memory"); /* behind the keys' requests, see the wait in do_tile */
+            if (WIDE) asm volatile("" ::: "memory"); /* behind the keys' requests: keys_arrived */
             load_v_tile<DEEP>(vraw, vc, vr, t, lane);
         };
         if (WIDE) request_k_tile<DEEP>(sK[wave], kc, kr, tile_lo, lane);
