@@ -290,8 +290,11 @@ __device__ __forceinline__ void load_v_tile(VTileRaw &t, __amdgpu_buffer_rsrc_t 
 }
 
 /* Key tile of the wide kernel: to LDS as it is, by loads that write there and take no registers, requested by the wavefront that
- * will read it while the tile before it is worked on. */
-template <bool DEEP> constexpr int key_tile_bytes() { return PQL_CODE_BYTES + (DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) * 2; }
+ * will read it while the tile before it is worked on.  The loads are unconditional in all lanes -- the codes' last 896 bytes are
+ * followed by 128 that nobody reads -- and the tile loop requests its last tile a second time: behind a branch the compiler has
+ * to assume that loads may not have been issued, and its waits for older ones then wait for these too. */
+constexpr int kKeyRadii = 3072 / 4; /* dwords: where the radii lie in LDS */
+template <bool DEEP> constexpr int key_tile_dwords() { return kKeyRadii + (DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) / 2; }
 
 typedef __attribute__((address_space(3))) void *LdsPtr;
 
@@ -299,20 +302,27 @@ template <bool DEEP>
 __device__ __forceinline__ void request_k_tile(uint32_t *dst, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t radii,
                                                uint32_t tile, uint32_t lane)
 {
+    static_assert(PQL_CODE_BYTES == 2944 && PQL_RADII == 512 && PQ_DEEP_RADII_HALVES == 128, "the loads below");
     asm volatile("" : "+v"(lane));
     const uint32_t co = tile * PQL_CODE_BYTES, off = lane * 16u;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(codes, (LdsPtr)dst, 16, off, co, 0, 0);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(codes, (LdsPtr)(dst + 256), 16, off, co + 1024u, 0, 0);
-    if (lane < (PQL_CODE_BYTES - 2048) / 16)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(codes, (LdsPtr)(dst + 512), 16, off, co + 2048u, 0, 0);
-    if (lane < (DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) / 8)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(radii, (LdsPtr)(dst + PQL_CODE_BYTES / 4), 16, off,
-                                                 tile * ((DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) * 2u), 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(codes, (LdsPtr)(dst + 512), 16, min(off, 55u * 16u), co + 2048u, 0, 0);
+    if (DEEP) __builtin_amdgcn_raw_ptr_buffer_load_lds(radii, (LdsPtr)(dst + kKeyRadii), 4, lane * 4u, tile * 256u, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(radii, (LdsPtr)(dst + kKeyRadii), 16, off, tile * 1024u, 0, 0);
 }
 
 /* The key tile requested ahead of the values' loads is in LDS: vector memory instructions complete in order. */
 template <bool DEEP>
 __device__ __forceinline__ void keys_arrived() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(value_loads<DEEP>()) : "memory"); }
+
+/* Between a wavefront's own writes to LDS and its reads: LDS instructions of a wavefront are carried out in order, so the
+ * compiler's order is all that is asked for, and no load in flight is waited for. */
+__device__ __forceinline__ void own_lds_order()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
 
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -496,23 +506,28 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
 {
     const uint32_t n = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4, col16 = n * 16u;
     const char *base = reinterpret_cast<const char *>(kt);
-    const TileScale scale = key_scale<DEEP>(kt + PQL_CODE_BYTES / 4, nv, lane);
-    /* string dwords 0 .. 2 | 2 .. 5 | 5 .. 8 | 8 .. 11 */
-    uint32_t o01 = g == 3u ? PQL_OFF_P2 + 12u * n : (g == 2u ? PQL_OFF_P1 + 4u : 8u * g) + 16u * n;
-    uint32_t o2 = g == 1u ? PQL_OFF_P1 + 16u * n : o01 + 8u;
-    uint32_t o3 = g == 3u ? PQL_OFF_KP3 + 4u * (n >> 1) : (g == 2u ? PQL_OFF_P2 + 12u * n : o2 + 4u);
-    const uint32_t step = g == 3u ? 192u : 256u, step3 = g == 3u ? 32u : (g == 2u ? 192u : 256u);
-    const uint32_t sh = g == 0u ? 0u : 32u - 4u * g, sh3 = g == 3u ? 16u * (n & 1u) : 0u;
+    const TileScale scale = key_scale<DEEP>(kt + kKeyRadii, nv, lane);
+    /* string dwords 0 .. 3 | 2 .. 5 | 5 .. 8 | 8 .. 11 of the token: where the first two, the third and the fourth lie for n = 0, and
+       how far apart they are from token to token (16 times that: from pass to pass), picked by g from packed constants */
+    auto by_g = [g](uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+        return (uint32_t)(((uint64_t)(c | d << 16) << 32 | (a | b << 16)) >> (16u * g)) & 0xFFFFu;
+    };
+    const uint32_t step = g == 3u ? 12u * 16u : 16u * 16u, step3 = by_g(256u, 256u, 192u, 32u);
+    const uint32_t at = (step * n) >> 4;
+    uint32_t o01 = at + by_g(PQL_OFF_P0, PQL_OFF_P0 + 8u, PQL_OFF_P1 + 4u, PQL_OFF_P2);
+    uint32_t o2 = at + by_g(PQL_OFF_P0 + 8u, PQL_OFF_P1, PQL_OFF_P1 + 12u, PQL_OFF_P2 + 8u);
+    uint32_t o3 = ((step3 * n) >> 4 & ~3u) + by_g(PQL_OFF_P0 + 12u, PQL_OFF_P1 + 4u, PQL_OFF_P2, PQL_OFF_KP3);
+    const uint32_t sh = 0u - 4u * g /* mod 32 */, sh3 = ((g + 1u) >> 2 & n) * 16u; /* g = 3: the half dword of an odd token */
     if (DEEP) { /* lane tau rebuilds the radii of token tau's blocks and leaves them, scaled, as two binary16 terms each */
         float r[8];
-        pq_deep_block_radii(kt[PQL_CODE_BYTES / 4 + lane], dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + kTUp), r);
+        pq_deep_block_radii(kt[kKeyRadii + lane], dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + kTUp), r);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const float x = r[b] * scale.by;
             const _Float16 hi = (_Float16)x;
             dr.krad[8 * lane + b] = __builtin_bit_cast(uint32_t, h2{hi, (_Float16)(x - (float)hi)});
         }
-        wave_lds_fence();
+        own_lds_order();
     }
     const h2 by = h2{(_Float16)scale.by, (_Float16)scale.by};
     auto pass = [&](auto ic) {
@@ -523,7 +538,7 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
         const uint32_t x[3] = {__builtin_amdgcn_alignbit(w1, w0, sh), __builtin_amdgcn_alignbit(w2, w1, sh),
                                __builtin_amdgcn_alignbit(w3, w2, sh)};
         /* radii of blocks 2 g, 2 g + 1: stored ones, or of rebuilt ones a first and a second term each */
-        const h2 ra = DEEP ? as_h2(dr.krad[(16 * i + n) * 8 + 2 * g]) : as_h2(kt[PQL_CODE_BYTES / 4 + 4 * (16 * i + n) + g]) * by;
+        const h2 ra = DEEP ? as_h2(dr.krad[(16 * i + n) * 8 + 2 * g]) : as_h2(kt[kKeyRadii + 4 * (16 * i + n) + g]) * by;
         const h2 rb = DEEP ? as_h2(dr.krad[(16 * i + n) * 8 + 2 * g + 1]) : ra;
         s[i] = f4{0.f, 0.f, 0.f, 0.f};
         auto block = [&](auto bc) {
@@ -657,7 +672,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
        keeps its binary16 value in the low half, a parity-1 column in the high half, and the other halves stay
        zero from the start of the kernel (nothing ever writes them) */
     auto &sP = lds.p;
-    __shared__ __attribute__((aligned(16))) uint32_t sK[WIDE ? kWavesPerBlock : 1][key_tile_bytes<DEEP>() / 4]; /* wide: the key tiles */
+    __shared__ __attribute__((aligned(16))) uint32_t sK[WIDE ? kWavesPerBlock : 1][WIDE ? key_tile_dwords<DEEP>() : 4]; /* wide: the key tiles */
     __shared__ __attribute__((aligned(16))) uint32_t sKrad[WIDE && DEEP ? kWavesPerBlock : 1][WIDE && DEEP ? 512 : 4];
     __shared__ __attribute__((aligned(16))) uint16_t sVrad[DEEP ? kWavesPerBlock : 1][DEEP ? 512 : 8];
     /* per-sequence data of batches of up to 64 sequences is staged in LDS with the tables, so that
@@ -944,10 +959,11 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                 int lane_k = lane;
                 asm volatile("" : "+v"(lane_k));
                 wide_scores<DEEP>(tab, sK[wave], qo, kProbShift - m_ref[0], s, dr, MASKED ? nv : 64, lane_k);
-                if (next < tile_hi) { /* the next tile's keys, once every read of this one's has returned */
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    request_k_tile<DEEP>(sK[wave], kc, kr, next, lane);
-                }
+                /* ahead of the request: behind it the compiler waits for that, it takes both for writes to the same memory */
+                if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
+                /* the next tile's keys, once every read of this one's has returned */
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                request_k_tile<DEEP>(sK[wave], kc, kr, min(next, tile_hi - 1), lane);
                 if (MASKED) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
@@ -983,11 +999,6 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                         l_run[0] += p;
                         ph[i][e >> 1][e & 1] = (_Float16)p;
                     }
-                if (DEEP) {
-                    /* the passes of the previous tile have read theirs: the fence of wide_scores lies in between */
-                    stage_deep_value_radii(tab, dr, vraw.top, lane);
-                    wave_lds_fence();
-                }
                 auto passes = [&](auto ic) { /* passes i and i + 1: the contraction of one product */
                     constexpr int i = decltype(ic)::value;
                     H8 vc[8]; /* coordinate c of the half-block: tokens 4 g + e of the two passes */
@@ -1029,6 +1040,14 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
             if (WIDE) asm volatile("" ::: "memory"); /* behind the keys' requests: keys_arrived */
             load_v_tile<DEEP>(vraw, vc, vr, t, lane);
         };
+        auto request_next = [&](int t) {
+            if (WIDE) { /* without a branch: request_k_tile */
+                request_values(min(t, tile_hi - 1));
+            } else if (t < tile_hi) {
+                load_k_tile<DEEP>(kraw, kc, kr, t, lane);
+                request_values(t);
+            }
+        };
         if (WIDE) request_k_tile<DEEP>(sK[wave], kc, kr, tile_lo, lane);
         else load_k_tile<DEEP>(kraw, kc, kr, tile_lo, lane);
         request_values(tile_lo);
@@ -1050,10 +1069,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                     set_wave_priority(min(__builtin_amdgcn_readfirstlane(ahead), 3));
                 }
                 do_tile(std::false_type{}, kraw, vraw, lim, 64, tile + 1);
-                if (tile + 1 < tile_hi) {
-                    if (!WIDE) load_k_tile<DEEP>(kraw, kc, kr, tile + 1, lane);
-                    request_values(tile + 1);
-                }
+                request_next(tile + 1);
             }
         }
         for (; tile < tile_hi; ++tile) { /* the masked tiles at the end of the sequence */
@@ -1065,11 +1081,10 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                 lim[h] = ctx - (a.M - 1 - m) - tile * 64;
             }
             do_tile(std::true_type{}, kraw, vraw, lim, nv, tile + 1);
-            if (tile + 1 < tile_hi) {
-                if (!WIDE) load_k_tile<DEEP>(kraw, kc, kr, tile + 1, lane);
-                request_values(tile + 1);
-            }
+            request_next(tile + 1);
         }
+
+        if (WIDE) keys_arrived<DEEP>(); /* the last tile's, requested again: nothing writes to LDS any more */
 
         /* ---- partial results: l summed over the tokens (lanes); o' scattered to coordinate order ---- */
         int lane_e = lane;

@@ -192,21 +192,26 @@ static __device__ __forceinline__ float pq_half_bits_to_float(uint32_t h)
 static __device__ __forceinline__ void pq_deep_block_radii(uint32_t word, int b5, int b6, int b7, const float2 *cs,
                                                            float (&r)[8])
 {
-    const float R = pq_half_bits_to_float(word >> 16);
+    /* all entries are requested before the first product: one LDS round trip instead of three */
     const float2 t7 = cs[16 + __builtin_amdgcn_ubfe(word, 4 * b5 + 2 * b6, b7)];
+    float2 t6[2], t5[4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) t6[j] = cs[8 + __builtin_amdgcn_ubfe(word, 4 * b5 + j * b6, b6)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t5[j] = cs[__builtin_amdgcn_ubfe(word, j * b5, b5)];
+    __builtin_amdgcn_sched_barrier(0);
+    const float R = pq_half_bits_to_float(word >> 16);
     const float r6[2] = {R * t7.x, R * t7.y};
     float r5[4];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const float2 t6 = cs[8 + __builtin_amdgcn_ubfe(word, 4 * b5 + j * b6, b6)];
-        r5[2 * j] = r6[j] * t6.x;
-        r5[2 * j + 1] = r6[j] * t6.y;
+        r5[2 * j] = r6[j] * t6[j].x;
+        r5[2 * j + 1] = r6[j] * t6[j].y;
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const float2 t5 = cs[__builtin_amdgcn_ubfe(word, j * b5, b5)];
-        r[2 * j] = r5[j] * t5.x;
-        r[2 * j + 1] = r5[j] * t5.y;
+        r[2 * j] = r5[j] * t5[j].x;
+        r[2 * j + 1] = r5[j] * t5[j].y;
     }
 }
 
