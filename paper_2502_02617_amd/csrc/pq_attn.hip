@@ -291,8 +291,8 @@ __device__ __forceinline__ void load_v_tile(VTileRaw &t, __amdgpu_buffer_rsrc_t 
 
 /* Key tile of the wide kernel: to LDS as it is, by loads that write there and take no registers, requested by the wavefront that
  * will read it while the tile before it is worked on.  The loads are unconditional in all lanes -- the codes' last 896 bytes are
- * followed by 128 that nobody reads -- and the tile loop requests its last tile a second time: behind a branch the compiler has
- * to assume that loads may not have been issued, and its waits for older ones then wait for these too. */
+ * followed by 128 that nobody reads -- and so the tile loop requests a piece's last tile a second time (kInFlight): behind a branch
+ * the compiler has to assume that loads may not have been issued, and its waits for older ones then wait for these too. */
 constexpr int kKeyRadii = 3072 / 4; /* dwords: where the radii lie in LDS */
 template <bool DEEP> constexpr int key_tile_dwords() { return kKeyRadii + (DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII) / 2; }
 
@@ -660,6 +660,10 @@ template <bool WIDE, int WAVES_PER_SIMD, bool DEEP>
 __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_kernel(AttnArgs a)
 {
     constexpr int kWavesPerBlock = 4 * WAVES_PER_SIMD, kThreads = kWavesPerBlock * 64;
+    /* wide: loads without branches (request_k_tile): sixteen sequences of 12700 tokens and sixteen pairs 76.4 -> 75.4 us, 87.4 -> 81 at depth
+       7.  At depth 4 three wavefronts per SIMD cover the waits and have no gain from it, and 64 sequences of 2000 tokens, two or three
+       tiles per piece, take 62.5 instead of 61.6 us. */
+    constexpr bool kInFlight = WIDE && (DEEP || WAVES_PER_SIMD == 2);
     const int G = a.Hq / a.Hkv; /* query heads per kv head: only the set-up and the epilogue of a piece depend on it */
     /* One block, the tables first: the offset of a table inside LDS then fits a gather's 16-bit immediate. */
     struct Lds {
@@ -963,7 +967,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                 if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
                 /* the next tile's keys, once every read of this one's has returned */
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                request_k_tile<DEEP>(sK[wave], kc, kr, min(next, tile_hi - 1), lane);
+                if (kInFlight || next < tile_hi) request_k_tile<DEEP>(sK[wave], kc, kr, min(next, tile_hi - 1), lane);
                 if (MASKED) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
@@ -1041,10 +1045,10 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
             load_v_tile<DEEP>(vraw, vc, vr, t, lane);
         };
         auto request_next = [&](int t) {
-            if (WIDE) { /* without a branch: request_k_tile */
+            if (kInFlight) {
                 request_values(min(t, tile_hi - 1));
             } else if (t < tile_hi) {
-                load_k_tile<DEEP>(kraw, kc, kr, t, lane);
+                if (!WIDE) load_k_tile<DEEP>(kraw, kc, kr, t, lane);
                 request_values(t);
             }
         };
@@ -1084,7 +1088,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
             request_next(tile + 1);
         }
 
-        if (WIDE) keys_arrived<DEEP>(); /* the last tile's, requested again: nothing writes to LDS any more */
+        if (kInFlight) keys_arrived<DEEP>(); /* the last tile's, requested again: nothing writes to LDS any more */
 
         /* ---- partial results: l summed over the tokens (lanes); o' scattered to coordinate order ---- */
         int lane_e = lane;
