@@ -19,7 +19,7 @@
  *   pq_attn_combine_kernel  merges the pieces of a (sequence, query head) in tile
  *                           order, divides by l, multiplies by S^T, bf16
  *
- * Partial kernel for up to four (query token, head) pairs per kv head, per 64-token tile (the cache stores, per block of 16 coordinates, four 10-bit quarter
+ * Partial kernel for up to four (query token, head) pairs per kv head (eight in two groups), per 64-token tile (the cache stores, per block of 16 coordinates, four 10-bit quarter
  * indices Q, one 6-bit block index B and the binary16 block radius: pq_layout.h):
  *   K:  one token per lane.  For each of the token's 32 quarters the lane fetches the quarter's table
  *       entry -- the four binary16 products (cos|sin) theta2 * (cos|sin) theta1 -- and hands it to
@@ -39,7 +39,7 @@
  *       (pair, parity) with zeros in the slots of the other parity.  The result accumulates o' for the
  *       even coordinates in the parity-0 columns and for the odd ones in parity 1.
  *
- * With five to sixteen pairs ("wide"): a key is formed once, as two binary16 terms, and multiplied by all pairs on
+ * With more ("wide"): a key is formed once, as two binary16 terms, and multiplied by all pairs on
  * v_mfma_f32_16x16x32_f16 (wide_scores); the scores come out in the lanes that the value product wants the weights in,
  * and the values are brought to one coordinate per register by permutes.
  */
@@ -387,23 +387,23 @@ __device__ __forceinline__ uint32_t sel4(uint4 v, int c)
 __device__ __forceinline__ float half_lo_to_float(uint32_t u) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(u & 0xFFFFu)); }
 __device__ __forceinline__ float half_hi_to_float(uint32_t u) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(u >> 16)); }
 
-/* Query operand of the scores: a[set] holds in lane (i = lane >> 2, slot = lane & 3) the four
- * rotated query coordinates 4 x .. 4 x + 3 of quarter x = 16 set + i for pair `slot`, in binary16.
+/* Query operand of the scores: for group k of four pairs, a[k][set] holds in lane (i = lane >> 2, slot = lane & 3) the four
+ * rotated query coordinates 4 x .. 4 x + 3 of quarter x = 16 set + i for pair 4 k + slot, in binary16.
  * v_mfma_f32_4x4x4_16b_f16 multiplies 16 independent 4x4 blocks; with the A block of one lane group broadcast to
  * all sixteen (cbsz = 4, abid = i) one register pair serves sixteen quarters. */
-struct QueryOperand { H4 a[2]; };
+template <int NG> struct QueryOperand { H4 a[NG][2]; };
 
 /* Scores of one 64-token tile, one token per lane (Eq. 5 with DeQuant unrolled into table products):
  *   s_pair(tau) = sum_b r_b(tau) sum_j T43[B_b][j] * < q'[16 b + 4 j .. + 3], T21[Q_{b,j}] >
  * T21[Q] (binary16, from LDS) = the four products (cos|sin) theta2 * (cos|sin) theta1 of a quarter -- it is the B
  * operand of the matrix instruction as fetched; T43[B] (fp32) = the four products (cos|sin) theta4 * (cos|sin)
  * theta3 of a block.  The matrix cores form the 4-coordinate inner products of a quarter for four (query token,
- * head) pairs; each is scaled in fp32
+ * head) pairs per group; each is scaled in fp32
  * by r_b T43[B_b][j] and summed.  A key element is therefore never rounded beyond its table entry.
  * s comes in holding the negated exponent reference (the first product of a tile adds to it). */
-template <bool DEEP>
-__device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &k, const QueryOperand &qo,
-                                           float (&s)[4], const DeepRadii &dr, int lane)
+template <int NG, bool DEEP>
+__device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &k, const QueryOperand<NG> &qo,
+                                           float (&s)[4 * NG], const DeepRadii &dr, int lane)
 {
     const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
     float rb[8];
@@ -430,21 +430,26 @@ __device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &
         for (int j = 0; j < 4; ++j) {
             constexpr int set = b >> 2;         /* quarters 0..15 | 16..31 */
             const int abid = (4 * b + j) & 15;  /* compile-time after unrolling */
-            f4 d;
-            switch (abid) { /* the broadcast selector is an immediate of the instruction */
+            /* the groups' products first, then their sums: a sum would wait for the product just before it */
+            f4 d[NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                switch (abid) { /* the broadcast selector is an immediate of the instruction */
 #define PQ_SCORE_CASE(N)                                                                                     \
     case N:                                                                                                  \
-        d = __builtin_amdgcn_mfma_f32_4x4x4f16(qo.a[set].v, kq[j].v, zero, 4, N, 0);                            \
+        d[g] = __builtin_amdgcn_mfma_f32_4x4x4f16(qo.a[g][set].v, kq[j].v, zero, 4, N, 0);                      \
         break;
-                PQ_SCORE_CASE(0) PQ_SCORE_CASE(1) PQ_SCORE_CASE(2) PQ_SCORE_CASE(3)
-                PQ_SCORE_CASE(4) PQ_SCORE_CASE(5) PQ_SCORE_CASE(6) PQ_SCORE_CASE(7)
-                PQ_SCORE_CASE(8) PQ_SCORE_CASE(9) PQ_SCORE_CASE(10) PQ_SCORE_CASE(11)
-                PQ_SCORE_CASE(12) PQ_SCORE_CASE(13) PQ_SCORE_CASE(14)
-                default: PQ_SCORE_CASE(15)
+                    PQ_SCORE_CASE(0) PQ_SCORE_CASE(1) PQ_SCORE_CASE(2) PQ_SCORE_CASE(3)
+                    PQ_SCORE_CASE(4) PQ_SCORE_CASE(5) PQ_SCORE_CASE(6) PQ_SCORE_CASE(7)
+                    PQ_SCORE_CASE(8) PQ_SCORE_CASE(9) PQ_SCORE_CASE(10) PQ_SCORE_CASE(11)
+                    PQ_SCORE_CASE(12) PQ_SCORE_CASE(13) PQ_SCORE_CASE(14)
+                    default: PQ_SCORE_CASE(15)
 #undef PQ_SCORE_CASE
+                }
             }
+            if (NG > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int h = 0; h < 4; ++h) s[h] = __builtin_fmaf(d[h], rq[j], s[h]);
+            for (int h = 0; h < 4 * NG; ++h) s[h] = __builtin_fmaf(d[h >> 2][h & 3], rq[j], s[h]);
         }
     };
     block(std::integral_constant<int, 0>{}); block(std::integral_constant<int, 1>{});
@@ -632,7 +637,7 @@ __device__ __forceinline__ float wave_max_f(float x)
     return x;
 }
 
-/* G query heads per kv head, M query tokens per sequence (a.M), up to four pairs per kv head, or WIDE: up to
+/* G query heads per kv head, M query tokens per sequence (a.M), up to 4 NG pairs per kv head, or NG = 0, "wide": up to
  * sixteen.  Query token m of a sequence is its (M-1-m)-th newest token and sees
  * the cache up to and including its own key: ctx - (M-1-m) tokens.
  *
@@ -648,31 +653,34 @@ __device__ __forceinline__ float wave_max_f(float x)
  * slots of the other parity.  The result accumulates o' for the even coordinates in the parity-0 columns and
  * for the odd ones in parity 1.
  *
- * WIDE: lane (g, n) holds the scores of pair n for tokens 16 i + 4 g + e, so a pair's reference and sum are the lane's own and its weights
- * are the value product's operand as they are (no LDS); the values of two passes are transposed by permutes (64 per
- * tile) and contracted over tokens, half of the matrix work of the widened contraction.  Both kinds are bound by instruction issue: per tile
- * some 740 vector and 48 matrix instructions for any number of pairs up to sixteen, where the form for four pairs, its groups of four repeated,
- * took 716 and 80 for two groups and 1020 and 160 for four.  Four query tokens of four heads, 16 sequences of 12700 tokens: 107 -> 78 us per call; ten pairs at
- * 32768 tokens 198 -> 158; eight pairs 73.6 -> 69.3; at depth 7 twelve pairs 106 -> 85, eight 75.7 -> 75.5.  Key tiles that went to LDS ahead of
+ * Wide: lane (g, n) holds the scores of pair n for tokens 16 i + 4 g + e, so a pair's reference and sum are the lane's own and its
+ * weights are the value product's operand as they are (no LDS); the values of two passes are transposed by permutes (64 per
+ * tile) and contracted over tokens, half of the matrix work of the widened contraction.  Both kinds are bound by instruction issue: 762
+ * vector and 48 matrix instructions per tile for any number of pairs up to sixteen; two groups of four
+ * take 716 and 80, four groups took 1020 and 160.  Four query tokens of four heads, 16 sequences of 12700 tokens: 107 us in four groups, 76
+ * wide; at depth 7 108 and 81.  Five to eight pairs: wide_tiles.  Key tiles that went to LDS ahead of
  * their use made four pairs slower (35.1 -> 36.7 us for 32 short sequences, 112.6 -> 114.9 at 65536 tiles: the LDS is as busy as the vector
  * ALU there). */
-template <bool WIDE, int WAVES_PER_SIMD, bool DEEP>
+template <int NG, int WAVES_PER_SIMD, bool DEEP>
 __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_kernel(AttnArgs a)
 {
     constexpr int kWavesPerBlock = 4 * WAVES_PER_SIMD, kThreads = kWavesPerBlock * 64;
+    constexpr bool WIDE = NG == 0;
     /* wide: loads without branches (request_k_tile): sixteen sequences of 12700 tokens and sixteen pairs 76.4 -> 75.4 us, 87.4 -> 81 at depth
        7.  At depth 4 three wavefronts per SIMD cover the waits and have no gain from it, and 64 sequences of 2000 tokens, two or three
        tiles per piece, take 62.5 instead of 61.6 us. */
     constexpr bool kInFlight = WIDE && (DEEP || WAVES_PER_SIMD == 2);
+    /* narrow: the columns of a value product, pair + kPairs * parity (with four pairs half of the sixteen repeat the other half) */
+    constexpr int kPairs = WIDE ? 16 : 4 * NG, kCols = WIDE ? 16 : 2 * kPairs;
     const int G = a.Hq / a.Hkv; /* query heads per kv head: only the set-up and the epilogue of a piece depend on it */
     /* One block, the tables first: the offset of a table inside LDS then fits a gather's 16-bit immediate. */
     struct Lds {
         __attribute__((aligned(16))) uint32_t tab[kLdsTabDwords];
-        __attribute__((aligned(16))) uint32_t p[WIDE ? 1 : kWavesPerBlock][8][64];
+        __attribute__((aligned(16))) uint32_t p[WIDE ? 1 : kWavesPerBlock][kCols][64];
     };
     __shared__ Lds lds;
     uint32_t (&tab)[kLdsTabDwords] = lds.tab;
-    /* four pairs: probabilities of a tile, sP[wave][column = pair + 4 * parity][token] as dwords; a parity-0 column
+    /* narrow: probabilities of a tile, sP[wave][column = pair + kPairs * parity][token] as dwords; a parity-0 column
        keeps its binary16 value in the low half, a parity-1 column in the high half, and the other halves stay
        zero from the start of the kernel (nothing ever writes them) */
     auto &sP = lds.p;
@@ -732,7 +740,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
         if (threadIdx.x < 48) tup = src[PQ_TAB_UP + threadIdx.x];
         if (!WIDE) {
             uint4 *pz = reinterpret_cast<uint4 *>(&sP[0][0][0]);
-            for (int t = threadIdx.x; t < kWavesPerBlock * 8 * 64 / 4; t += kThreads) pz[t] = make_uint4(0, 0, 0, 0);
+            for (int t = threadIdx.x; t < kWavesPerBlock * kCols * 64 / 4; t += kThreads) pz[t] = make_uint4(0, 0, 0, 0);
         }
         if (threadIdx.x < 16) sDone[threadIdx.x >> 2][threadIdx.x & 3] = threadIdx.x < kWavesPerBlock ? 0 : 0x7FFFFFFF;
 #pragma unroll
@@ -825,7 +833,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
     const char *tbh = reinterpret_cast<const char *>(tab + kTBH);
     /* where this lane (token) leaves its probabilities and where it (column) picks its operand up */
     uint32_t *p_mine = &sP[WIDE ? 0 : wave][0][lane];
-    const uint32_t *p_col = &sP[WIDE ? 0 : wave][n & 7][4 * g];
+    const uint32_t *p_col = &sP[WIDE ? 0 : wave][n & (kCols - 1)][4 * g];
     /* rotated queries and partial results: the launch code keeps all three below 4 GB */
     const __amdgpu_buffer_rsrc_t q_rsrc = stream_descriptor(a.qrot, (uint32_t)a.B * a.M * a.Hq * (PQ_D * 2u));
     const __amdgpu_buffer_rsrc_t o_rsrc = stream_descriptor(a.ws_o, (uint32_t)a.n_pieces * (a.M * G) * (PQ_D * 4u));
@@ -852,39 +860,41 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
         const __amdgpu_buffer_rsrc_t vr = stream_descriptor(a.v_radii + stream_tile0 * kRadiiHalves, radii_bytes);
 
         /* ---- q' operands (see QueryOperand, WideQuery); pair p = (query token p / G, head p % G) ---- */
-        std::conditional_t<WIDE, WideQuery, QueryOperand> qo;
+        std::conditional_t<WIDE, WideQuery, QueryOperand<WIDE ? 1 : NG>> qo;
         /* lane-dependent addresses of the piece's prologue and epilogue are formed from a copy of the lane
            number that the compiler cannot trace: hoisted out of the piece loop they would be spilled */
         int lane_q = lane;
         asm volatile("" : "+v"(lane_q));
-        const int pair_q = WIDE ? lane_q & 15 : lane_q & 3;
-        const bool real_q = pair_q < a.M * G;
-        const int m_q = real_q ? pair_q / G : 0; /* query token of this lane's pair */
-        {
-            const int head = real_q ? pair_q % G : 0;
+        int m_q = 0; /* wide: query token of this lane's pair */
+#pragma unroll
+        for (int k = 0; k < (WIDE ? 1 : NG); ++k) {
+            const int pair = WIDE ? lane_q & 15 : 4 * k + (lane_q & 3);
+            const bool real = pair < a.M * G;
+            const int m = real ? pair / G : 0, head = real ? pair % G : 0;
+            if (WIDE) m_q = m;
             /* 32-bit offsets into the rotated queries: lane part in bytes, (sequence, kv head) part scalar */
-            const uint32_t lane_off = (uint32_t)((m_q * a.Hq + head) * PQ_D + (WIDE ? 32 * (lane_q >> 4) : 4 * (lane_q >> 2))) * 2u;
+            const uint32_t lane_off = (uint32_t)((m * a.Hq + head) * PQ_D + (WIDE ? 32 * (lane_q >> 4) : 4 * (lane_q >> 2))) * 2u;
             const uint32_t row_off = (uint32_t)((b * a.M * a.Hq + hk * G) * PQ_D) * 2u;
             if constexpr (WIDE) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const uint4 v = load16(q_rsrc, lane_off + 16u * c, row_off);
-                    qo.q[c].q = real_q ? v : make_uint4(0, 0, 0, 0);
+                    qo.q[c].q = real ? v : make_uint4(0, 0, 0, 0);
                 }
             } else {
 #pragma unroll
                 for (int set = 0; set < 2; ++set) {
                     const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(q_rsrc, lane_off + (uint32_t)(64 * set) * 2u, row_off, 0);
-                    qo.a[set].w[0] = real_q ? v.x : 0u;
-                    qo.a[set].w[1] = real_q ? v.y : 0u;
+                    qo.a[k][set].w[0] = real ? v.x : 0u;
+                    qo.a[k][set].w[1] = real ? v.y : 0u;
                 }
             }
         }
-        /* o': four pairs -- coordinates 2 c (parity-0 columns) and 2 c + 1 of the half-blocks; wide -- coordinates c */
+        /* o': narrow -- coordinates 2 c (parity-0 columns) and 2 c + 1 of the half-blocks; wide -- coordinates c */
         f4 acc_o[WIDE ? 8 : 4];
-        /* exponent reference: of four pairs, the same in all lanes; wide: of the lane's pair n.  l: this lane's share of the sum
+        /* exponent reference: narrow, of every pair, the same in all lanes; wide: of the lane's pair n.  l: this lane's share of the sum
            of its tokens' weights */
-        constexpr int kLanePairs = WIDE ? 1 : 4;
+        constexpr int kLanePairs = WIDE ? 1 : kPairs;
         float m_ref[kLanePairs], l_run[kLanePairs];
 #pragma unroll
         for (int c = 0; c < (WIDE ? 8 : 4); ++c) acc_o[c] = f4{0.f, 0.f, 0.f, 0.f};
@@ -898,22 +908,22 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                            int next) {
             constexpr bool MASKED = decltype(masked_c)::value;
             if constexpr (!WIDE) {
-                float s[4];
+                float s[kPairs];
 #pragma unroll
-                for (int h = 0; h < 4; ++h) s[h] = kProbShift - m_ref[h];
-                key_scores<DEEP>(tab, kraw, qo, s, dr, lane); /* s = score - m_ref + kProbShift */
+                for (int h = 0; h < kPairs; ++h) s[h] = kProbShift - m_ref[h];
+                key_scores<NG, DEEP>(tab, kraw, qo, s, dr, lane); /* s = score - m_ref + kProbShift */
                 if (MASKED) {
 #pragma unroll
-                    for (int h = 0; h < 4; ++h)
+                    for (int h = 0; h < kPairs; ++h)
                         if (lane >= lim[h]) s[h] = -INFINITY;
                 }
                 float top = s[0];
 #pragma unroll
-                for (int h = 0; h < 4; ++h) top = fmaxf(top, s[h]);
+                for (int h = 0; h < kPairs; ++h) top = fmaxf(top, s[h]);
                 if (!have_ref || __ballot(top > kProbShift + kRefSlack) != 0ull) { /* wave-uniform */
-                    float alpha_lane = 1.f; /* factor of this lane's output column (pair n & 3) */
+                    float alpha_lane = 1.f; /* factor of this lane's output column (pair n & (kPairs - 1)) */
 #pragma unroll
-                    for (int h = 0; h < 4; ++h) {
+                    for (int h = 0; h < kPairs; ++h) {
                         const float smax = __builtin_amdgcn_readfirstlane(wave_max_f(s[h]));
                         /* move the reference so that the largest weight of the tile is 2^kProbShift; a pair that has
                            seen no token yet (smax == -inf) keeps its place holder */
@@ -923,25 +933,25 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                         m_ref[h] += delta;
                         s[h] -= delta;
                         l_run[h] *= alpha;
-                        if ((n & 3) == h) alpha_lane = alpha;
+                        if ((n & (kPairs - 1)) == h) alpha_lane = alpha;
                     }
 #pragma unroll
                     for (int c = 0; c < 4; ++c) acc_o[c] *= alpha_lane;
                     have_ref = true;
                 }
                 wave_lds_fence(); /* the passes of the previous tile have read their operands */
-                _Float16 ph[4];
+                _Float16 ph[kPairs];
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
+                for (int h = 0; h < kPairs; ++h) {
                     const float p = __builtin_amdgcn_exp2f(s[h]); /* exp2(-inf) = 0 for masked tokens */
                     l_run[h] += p;
                     ph[h] = (_Float16)p;
                 }
                 _Float16 *dst = reinterpret_cast<_Float16 *>(p_mine);
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
+                for (int h = 0; h < kPairs; ++h) {
                     dst[2 * (h * 64)] = ph[h];                 /* column (pair, parity 0): low half */
-                    dst[2 * ((4 + h) * 64) + 1] = ph[h];       /* column (pair, parity 1): high half */
+                    dst[2 * ((kPairs + h) * 64) + 1] = ph[h];       /* column (pair, parity 1): high half */
                 }
                 if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
                 wave_lds_fence();
@@ -1094,7 +1104,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));
         const int ne = lane_e & 15, ge = lane_e >> 4;
-        const int pair = WIDE ? ne : ne & 3, par = WIDE ? 0 : ne >> 2;
+        const int pair = ne & (kPairs - 1), par = ne / kPairs;
         float mm = m_ref[0], ll = 0.f; /* of this lane's pair */
         if constexpr (WIDE) {
             ll = l_run[0];
@@ -1102,14 +1112,14 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
             ll += __shfl_xor(ll, 32);
         } else {
 #pragma unroll
-            for (int h = 0; h < 4; ++h) {
+            for (int h = 0; h < kPairs; ++h) {
                 float l = l_run[h];
 #pragma unroll
                 for (int d = 32; d >= 1; d >>= 1) l += __shfl_xor(l, d); /* the same order in every lane */
                 if (pair == h) { mm = m_ref[h]; ll = l; }
             }
         }
-        if (ne < (WIDE ? 16 : 8) && pair < a.M * G) {
+        if (ne < kCols && pair < a.M * G) {
             /* stores through descriptors as well: scalar piece offset, 32-bit lane offset */
             const uint32_t piece_o = (uint32_t)piece * (uint32_t)(a.M * G) * (PQ_D * 4u);
             const uint32_t lane_o = (uint32_t)(pair * PQ_D + 2 * 16 * ge + par) * 4u;
@@ -1745,13 +1755,22 @@ struct StepWindow {
     int64_t win_cap;
 };
 
+/* Tiles per wavefront up to which five to eight pairs take the wide form: it starts sooner (fewer tables, no clearing) and is
+   bound by fewer waits, the two groups of four take fewer instructions per tile.  Sequences of one length, wide against groups, us: depth 4,
+   eight heads 4 tiles 43.7 / 47.9, 8 67.6 / 71.9, 12 90.7 / 93.1, 16 114 / 115, 32 209 / 205 (five heads 42.4 / 44.3, 65.6 / 68.5, 88.2 /
+   89.1, 112 / 111, 205 / 198); depth 7, eight heads 44.2 / 48.1, 70.3 / 73.9, 94.9 / 95.8, 121 / 118, 226 / 213.  The rule counts
+   the tiles of the largest context for all, as many as twice those of a mixed batch: the lines lie a little beyond the crossings at 14 and 11. */
+template <bool DEEP> constexpr int wide_tiles() { return DEEP ? 14 : 18; }
+
 template <bool DEEP>
-void launch_partial_depth(int pairs, dim3 grid, hipStream_t s, const AttnArgs &aa)
+void launch_partial_depth(int pairs, int slots, dim3 grid, hipStream_t s, const AttnArgs &aa)
 {
-    const dim3 blk((unsigned)(4 * waves_per_simd(pairs) * 64));
-    if (pairs <= 4) hipLaunchKernelGGL((pq_attn_partial_kernel<false, 4, DEEP>), grid, blk, 0, s, aa);
-    else if (pairs <= 8) hipLaunchKernelGGL((pq_attn_partial_kernel<true, 3, DEEP>), grid, blk, 0, s, aa);
-    else hipLaunchKernelGGL((pq_attn_partial_kernel<true, 2, DEEP>), grid, blk, 0, s, aa);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3((unsigned)(4 * waves_per_simd(pairs) * 64)), 0, s, aa); };
+    const int64_t most_tiles = (int64_t)aa.B * aa.Hkv * ((aa.max_ctx + 63) / 64);
+    if (pairs <= 4) launch(pq_attn_partial_kernel<1, 4, DEEP>);
+    else if (pairs > 8) launch(pq_attn_partial_kernel<0, 2, DEEP>);
+    else if (most_tiles <= (int64_t)wide_tiles<DEEP>() * slots) launch(pq_attn_partial_kernel<0, 3, DEEP>);
+    else launch(pq_attn_partial_kernel<2, 3, DEEP>);
 }
 
 template <int ROWS>
@@ -1859,8 +1878,8 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
     aa.consts = ds->consts;
     aa.up_b5 = ctx->upper_bits[0]; aa.up_b6 = ctx->upper_bits[1]; aa.up_b7 = ctx->upper_bits[2];
     pq_prof_before(0, s);
-    if (ctx->depth == 7) launch_partial_depth<true>(M * G, dim3(p.blocks), s, aa);
-    else launch_partial_depth<false>(M * G, dim3(p.blocks), s, aa);
+    if (ctx->depth == 7) launch_partial_depth<true>(M * G, p.slots, dim3(p.blocks), s, aa);
+    else launch_partial_depth<false>(M * G, p.slots, dim3(p.blocks), s, aa);
     pq_prof_after(0, s);
 
     CombineArgs ca{ws_ml, ws_o, B, Hq, Hkv, M, plan,

@@ -56,6 +56,41 @@ def test_wide_pairs_are_those_of_four_at_a_time(G, M, depth):
 
 
 @pytest.mark.parametrize("depth", [4, 7])
+@pytest.mark.parametrize("G,M", [(5, 1), (8, 1), (2, 4), (1, 7)])
+def test_long_calls_of_five_to_eight_pairs(G, M, depth):
+    """More than 18 tiles for each of the 3072 wavefronts, which then take the pairs in two groups of four; the sequences share
+    their tiles."""
+    say(f"long attention, {G} heads, {M} query tokens, depth {depth}")
+    B, H, n = 64, 8, 7000
+    ctx = Context(seed=2)
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    lens = torch.tensor([n - 11 * b for b in range(B)], dtype=torch.int32)
+    pool = -(-n // 64) * 64
+    assert B * H * (pool // 64) > 18 * 3072
+    caches = []
+    for kind in (PQ_KEY, PQ_VALUE):
+        codes, radii = ctx.alloc_cache_for(H, pool, DEV)
+        x = synth.kv_stream(pool, H, seed=20 + kind).permute(1, 0, 2).contiguous().to(DEV)
+        ctx.encode_kv(x, kind, codes, radii)
+        caches += [codes, radii]
+    q = torch.randn((B, M, H * G, 128), generator=torch.Generator().manual_seed(5)).bfloat16().to(DEV)
+    start = torch.zeros(B, dtype=torch.int64, device=DEV)
+    got = attend(ctx, q, caches, start, lens.to(DEV), n)
+    ref = torch.empty_like(got)
+    for m in range(M):
+        seen = (lens - (M - 1 - m)).to(DEV)
+        by_head = q[:, m].unflatten(1, (H, G))
+        for g in range(0, G, 4):
+            part = by_head[:, :, g:g + 4].flatten(1, 2)[:, None].contiguous()
+            ref[:, m].unflatten(1, (H, G))[:, :, g:g + 4] = attend(ctx, part, caches, start, seen, n)[:, 0].unflatten(1, (H, -1))
+    # as above
+    assert (got - ref).norm() <= 1.4e-3 * ref.norm()
+    assert ((got - ref).norm(dim=-1) <= 2e-2 * torch.maximum(ref.norm(dim=-1), ref.norm(dim=-1).square().mean().sqrt())).all()
+    assert torch.equal(got, attend(ctx, q, caches, start, lens.to(DEV), n))
+
+
+@pytest.mark.parametrize("depth", [4, 7])
 @pytest.mark.parametrize("G", [5, 16])
 def test_small_keys_are_scored_as_large_ones(G, depth):
     """Key radii times 2^-shift and queries times 2^shift, both exactly: the same scores but for their rounding, which is some 6e-8
