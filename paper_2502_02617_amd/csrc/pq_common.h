@@ -101,8 +101,8 @@ struct pq_ctx {
        exact in bf16 and the encode kernel multiplies by one term instead of three */
     bool unit_entries;
     /* S spreads every coordinate over every pair (2 p, 2 p + 1) of the result: the larger of the pair's two entries is
-       2^-16 at least.  An error of 2^-40 of a vector's largest coordinate is then below the fp32 rounding of any
-       rotated pair. */
+       2^-16 at least.  Errors of up to 2^-39 of a vector's largest coordinate in each coordinate are then below the fp32
+       rounding of any rotated pair (derived at Operands, pq_encode.hip). */
     bool mixing;
     PqHadamard hadamard;    /* on: S is D H / sqrt(d) exactly (found by comparing the entries) */
     bool general_codebooks; /* codebooks replaced by pq_set_codebooks */

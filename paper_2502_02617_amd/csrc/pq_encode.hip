@@ -10,9 +10,10 @@
  *   1. y = x * S on the matrix cores.  S is held as three bf16 terms
  *      S1 + S2 + S3 (24 significant bits) so that bf16 MFMAs with fp32
  *      accumulation reproduce an fp32-accurate rotation; bf16 inputs are
- *      exact operands.  fp32 inputs and S are two binary16 terms each and the
- *      three products above 2^-24 are accumulated (three bf16 terms and six
- *      products where S leaves coordinates unmixed).
+ *      exact operands.  fp32 inputs and S are two binary16 terms each and three
+ *      products are accumulated, all but that of the two second terms, 2^-22 of
+ *      the whole at most (three bf16 terms and six products where S leaves
+ *      coordinates unmixed).
  *      The product is computed transposed, D = S^T-tile (32 rotated
  *      coordinates) x X^T (32 vectors), with the rows of each S^T tile
  *      ordered so that a lane ends up with complete blocks of 16 consecutive
@@ -259,10 +260,16 @@ __device__ __forceinline__ uint32_t from_other_half(uint32_t x, int upper_half)
    fp32 input with NTERMS = 1 or 2 is two binary16 terms as well, after a power of two has brought the vector's
    largest coordinate to [2^14, 2^15) (the factor comes out of the radius, the angles do not see it): three products
    (two for a +-1 S) instead of the six (three) that three bf16 terms of 8 bits take, and a third of the vector
-   instructions to split an input: keys and values of 32768 tokens of 8 heads 116 -> 82 us, 89 -> 72 with a +-1 S.  Its error
-   against 64 bits is no larger: of 4.2 M radii 292 differ by a last bit, 341 with three bf16 terms.  A coordinate's two terms leave 2^-24 of it, or 2^-40 of the vector's
-   largest where that is more: an S that spreads every coordinate over all pairs of the result (pq_ctx::mixing) does not see
-   the latter; any other keeps NTERMS = 3. */
+   instructions to split an input: keys and values of 32768 tokens of 8 heads 116 -> 82 us, 89 -> 72 with a +-1 S.
+   Operands: two terms leave up to 2^-23 of a number (three bf16 terms 2^-25), or 2^-39 of the vector's largest coordinate where that
+   is more, and the product that is left out is 2^-22 of its whole at most; rms 7e-8 of a product, ten times that of three bf16 terms.
+   The fp32 sums, which are half as many, round by more: of 268 M radii of vectors with outlier channels 7.2e-5 differ by a last
+   bit from 64 bits (three bf16 terms 8.0e-5), of coordinates spread over 2^12 4.7e-5 (5.1e-5); with a Hadamard S, whose entries
+   are exact, 7.0e-5 (7.2e-5) and, spread, 4.68e-5 (4.53e-5: there it is larger, by 3 %).
+   2^-39 of the largest coordinate per coordinate is 2^-40 of it rms in a rotated one (the columns of S have norm 1).  Sums that pass
+   2^-16 of it round by 2^-41 rms at each of the products behind, a dozen on average of 24: 2^-39.  So an S that
+   spreads every coordinate over all pairs of the result by 2^-16 at least (pq_ctx::mixing) does not see it; any other keeps
+   NTERMS = 3. */
 template <int XT, int NTERMS> struct Operands {
     static constexpr bool half = XT == PQ_F32 && NTERMS <= 2;             /* binary16 terms, else bf16 */
     static constexpr int x_terms = XT == PQ_BF16 ? 1 : (half ? 2 : 3);
@@ -608,7 +615,7 @@ __device__ __forceinline__ void encode_tiles(const EncodeArgs &a, int block, int
                             for (int v = 0; v < NVT; ++v)
 #pragma unroll
                                 for (int xt = 0; xt < NXT; ++xt) {
-                                    if (xt + term > Op::top) continue; /* below 2^-24 of the leading product */
+                                    if (xt + term > Op::top) continue; /* Operands: what is left out */
                                     /* the first product of a row tile starts from a zero accumulator operand */
                                     const bool first = (ks == 0 && term == NTERMS - 1 && xt == 0);
                                     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
