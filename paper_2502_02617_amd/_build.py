@@ -67,8 +67,23 @@ def build_ldsbench():
     return LDSBENCH_PATH
 
 
+ROOTCHECK_PATH = os.path.join(LIB_DIR, "pq_rootcheck")
+
+
+def build_rootcheck():
+    """Stand-alone comparison of the angle counting's two square roots (see csrc/pq_rootcheck.hip)."""
+    os.makedirs(LIB_DIR, exist_ok=True)
+    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           os.path.join(CSRC, "pq_rootcheck.hip"), "-o", ROOTCHECK_PATH]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+    return ROOTCHECK_PATH
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
     print(build_membench())
     print(build_issuebench())
     print(build_ldsbench())
+    print(build_rootcheck())

@@ -37,6 +37,7 @@
  * 32.8 -> 23.9, 59.5 -> 54.5.
  */
 #include "pq_common.h"
+#include "pq_root.h"
 
 #include <algorithm>
 #include <cmath>
@@ -79,17 +80,7 @@ __device__ __forceinline__ uint32_t fit_bf16_rne(float f)
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-/* (u^2 + v^2)^(1/2), correctly rounded.  MID: the square lies in [2^-100, 2^101], and one correction of the hardware's
-   reciprocal root gives the rounded root (five instructions instead of sqrtf's fourteen): compared with sqrtf for all 2^24
-   significands and parities of the exponent, at exponents from -100 to 101, without a difference. */
-template <bool MID = false>
-__device__ __forceinline__ float fit_root(float x)
-{
-    if (!MID) return sqrtf(x);
-    const float y = __builtin_amdgcn_rsqf(x), s = x * y;
-    return __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
-}
-
+/* (u^2 + v^2)^(1/2), correctly rounded; MID: see fit_root */
 template <bool MID = false>
 __device__ __forceinline__ float fit_radius(float u, float v) { return fit_root<MID>(__builtin_fmaf(u, u, v * v)); }
 

@@ -1,9 +1,12 @@
 """GPU test of the angle counts of vectors so small that the squares of their coordinates are subnormal numbers."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 import torch
 
-from paper_2502_02617_amd import Context
+from paper_2502_02617_amd import Context, _build
 from tests.test_gpu_parity import DEV, say
 
 pytestmark = pytest.mark.gpu
@@ -36,7 +39,7 @@ def test_counts_do_not_depend_on_the_scale_of_the_vectors(dtype, depth):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_counts_of_pieces_add_up(dtype):
     say(f"angle counts of a long input and of its pieces, {dtype}")
-    ctx, n = Context(seed=4), 12800                # 8 heads: 1600 tiles; the pieces take 8 to 1408 of them
+    ctx, n = Context(seed=4), 12800                # 8 heads: 1600 tiles; the pieces take 8 to 1056 of them
     x = torch.randn((n, 8, 128), generator=torch.Generator().manual_seed(6)).to(dtype)
     x[5], x[6], x[7, 0, :16], x[8] = 0.0, 1e30, 0.0, 1e-25     # zeros and squares outside the range of the short roots
     whole, at = counts(ctx, x), 0
@@ -46,3 +49,25 @@ def test_counts_of_pieces_add_up(dtype):
         total += counts(ctx, x[at:at + piece])
         at += piece
     assert at == n and torch.equal(total, whole)
+
+
+def test_short_roots_are_the_rounded_ones():
+    say("the short square root against sqrtf, all numbers of its range")
+    path = _build.ROOTCHECK_PATH if os.path.exists(_build.ROOTCHECK_PATH) else _build.build_rootcheck()
+    res = subprocess.run([path], capture_output=True, text=True, timeout=60)
+    print(res.stdout, res.stderr)
+    assert res.returncode == 0
+    assert f"compared {201 * 2 ** 23 + 1} numbers, 0 different" in res.stdout
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -52, 2.0 ** 50])
+@pytest.mark.parametrize("depth", [4, 7])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_both_kinds_of_roots_count_the_same(dtype, depth, scale):
+    """Squares around 1 take the short root, those around 2^-104 and 2^100 sqrtf; every operation scales exactly."""
+    say(f"angle counts with either root, {dtype}, depth {depth}, vectors times {scale:.1e}")
+    ctx = Context(seed=4)
+    if depth == 7:
+        ctx.set_recursion_depth(7, (2, 2, 2))
+    x = torch.randn((6001, 8, 128), generator=torch.Generator().manual_seed(7)).to(dtype)
+    assert torch.equal(counts(ctx, x), counts(ctx, x * scale))
