@@ -189,7 +189,8 @@ __device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, fl
  * copy.  262144 vectors to bf16: 242 us with the generic bit reader and fp32 sums on 16 tokens per workgroup -> 33 us
  * for keys, 35 for values; to fp32 243 -> 48 and 51.  Every register counts: with what follows from the lane number kept
  * over the loop, up to 11 spilled registers cost values 39.5 us (fp32 57; Hadamard 34 against 28 now), and requesting the
- * next half tile ahead of the products in registers spills more than it hides (45).  AHEAD: it is requested to LDS, which takes none.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
+ * next half tile ahead of the products in registers spills more than it hides (45).  AHEAD: it is requested to LDS, which takes none; it
+ * travels under the rebuild of this half tile, the fence ahead of the products waits for it.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
  * spill 100 registers; value slots are read from an image in LDS because a token's 16 slots are spread over 16 strings. */
 template <int KIND, int OT, bool UNIT, bool AHEAD>
 __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs a)
@@ -426,8 +427,8 @@ void launch_decode(const DecodeArgs &a, bool unit, int rotated, int n_heads, hip
     }
     const dim3 grid((unsigned)(a.n_items < 256 ? a.n_items : 256)); /* one workgroup per CU */
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kDecodeThreads), 0, s, a); };
-    /* The next tile ahead of the products: for fp32 output, once a wavefront has more than one (32768 tokens of 8 heads, us with and
-       without: values 45.1 / 51.0, keys with a +-1 S 38.3 / 43.3; to bf16 36.4 / 35.2, whose stores leave less to wait for than the
+    /* The next tile ahead of this one's rebuild: for fp32 output, once a wavefront has more than one (32768 tokens of 8 heads, us with
+       and without: values 44.8 / 50.3, keys with a +-1 S 38.0 / 44.5; to bf16 36.4 / 35.2, whose stores leave less to wait for than the
        LDS pass costs; 3001 fp32 keys 11.1 / 10.6). */
     const bool ahead = OT == PQ_F32 && a.n_items > 256 * kDecodeWaves;
     if constexpr (OT == PQ_F32)
