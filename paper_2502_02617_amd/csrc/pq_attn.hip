@@ -668,7 +668,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
     constexpr bool WIDE = NG == 0;
     /* wide: loads without branches (request_k_tile): sixteen sequences of 12700 tokens and sixteen pairs 76.4 -> 75.4 us, 87.4 -> 81 at depth
        7.  At depth 4 three wavefronts per SIMD cover the waits and have no gain from it, and 64 sequences of 2000 tokens, two or three
-       tiles per piece, take 62.5 instead of 61.6 us. */
+       tiles per piece, take 66.3 instead of 63.7 us. */
     constexpr bool kInFlight = WIDE && (DEEP || WAVES_PER_SIMD == 2);
     /* narrow: the columns of a value product, pair + kPairs * parity (with four pairs half of the sixteen repeat the other half) */
     constexpr int kPairs = WIDE ? 16 : 4 * NG, kCols = WIDE ? 16 : 2 * kPairs;
