@@ -114,90 +114,103 @@ __device__ __forceinline__ int gen_bit_pos(const GenFormat &f, int l, int j)
 }
 
 /* ---- encode: sixteen vectors per workgroup of 512 threads ----
- * Thread (g, c) sums column c of four vectors (y_c = sum_i x_i S[i][c], i ascending), so that an element of S is fetched
- * once for the sixteen; the nodes of a level are spread over all threads, and the codes are OR-ed into an image
- * of the sixteen records, which lie one after another.
- * Bound by the fetches of S (64 KB per workgroup from L2) and the chain of levels.  4096 vectors 21.1 -> 10.1 us,
- * 65536 236 -> 62 us (one wavefront per vector, S fetched for each -> this).  Same operations in the same order: the
- * records are those of one wavefront per vector, bit for bit. */
+ * Wavefront w forms columns 16 w .. 16 w + 15 of the sixteen products on v_mfma_f32_16x16x4_f32 (fp32 products and sums, y_c =
+ * sum_i x_i S[i][c], i ascending); S comes straight from memory, each element once per workgroup.  Then thread (vector, quarter)
+ * takes four coordinates through levels 1 and 2, and the levels above join neighbouring lanes: a level's inputs never leave
+ * the wavefront.  The codes are OR-ed into an image of the sixteen records, which lie one after another.
+ * Bound by the launch and the chain of loads and levels up to some 4096 vectors, by vector instructions (the arctangents)
+ * beyond.  bf16, depth 5: 4096 vectors 10.1 -> 7.2 us, 65536 62 -> 50 (products on the vector ALU with the vectors broadcast from LDS,
+ * 1024 reads of sixteen bytes per workgroup, and a barrier per level -> this).  Same sums in the same order: the records are the
+ * same, bit for bit, infinities, subnormal vectors and NaN included. */
 constexpr int kGenEncVecs = 16, kGenEncThreads = 512;
+constexpr int kGenRow = PQ_D + 4; /* floats from vector to vector in LDS: lanes of neighbouring vectors read neighbouring banks */
+
+typedef float gen_f4 __attribute__((ext_vector_type(4)));
+
+/* number of the first N boundaries below the angle: nearest centroid, ties to the lower cell (boundaries that a level does not
+   have are +inf; reading them all at once is a third of the time of a loop over those it has) */
+template <int N>
+__device__ __forceinline__ uint32_t gen_cell(const float (&bound)[kGenMaxCells - 1], float ang)
+{
+    uint32_t code = 0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) code += ang > bound[k] ? 1u : 0u;
+    return code;
+}
+
+__device__ __forceinline__ void gen_emit(uint32_t *image, int pos, uint32_t v, int width)
+{
+    atomicOr(&image[pos >> 5], v << (pos & 31));
+    if ((pos & 31) + width > 32) atomicOr(&image[(pos >> 5) + 1], v >> (32 - (pos & 31)));
+}
 
 template <int XT>
 __global__ __launch_bounds__(kGenEncThreads) void pq_general_encode_kernel(GenFormat f, const void *x, int64_t ld_vector, int64_t n,
                                                                            const float *S, uint8_t *rec)
 {
-    __shared__ __attribute__((aligned(16))) float buf[2][kGenEncVecs][PQ_D];
+    __shared__ __attribute__((aligned(16))) float buf[kGenEncVecs][kGenRow], sy[kGenEncVecs][kGenRow];
     __shared__ uint32_t srec[kGenEncVecs * kGenMaxRecord / 4 + 1];
     const int64_t v0 = (int64_t)blockIdx.x * kGenEncVecs;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nv = (int)(n - v0 < kGenEncVecs ? n - v0 : kGenEncVecs);
-    for (int t = tid; t < kGenEncVecs * PQ_D; t += kGenEncThreads) {
-        const int v = t >> 7, c = t & 127;
-        float val = 0.f; /* vectors beyond the last one: computed along, not written */
+    float val[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int v = 4 * i + (tid >> 7), c = tid & 127;
+        val[i] = 0.f; /* vectors beyond the last one: computed along, not written */
         if (v < nv) {
             const int64_t at = (v0 + v) * ld_vector + c;
-            val = XT == PQ_BF16 ? __uint_as_float((uint32_t)static_cast<const uint16_t *>(x)[at] << 16)
-                                : static_cast<const float *>(x)[at];
+            val[i] = XT == PQ_BF16 ? __uint_as_float((uint32_t)static_cast<const uint16_t *>(x)[at] << 16)
+                                   : static_cast<const float *>(x)[at];
         }
-        buf[1][v][c] = val;
     }
+    float s[PQ_D / 4]; /* all of the lane's elements of S in flight */
+#pragma unroll
+    for (int k = 0; k < PQ_D / 4; ++k) s[k] = S[(4 * k + (lane >> 4)) * PQ_D + 16 * wave + (lane & 15)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) buf[4 * i + (tid >> 7)][tid & 127] = val[i];
     for (int c = tid; c < kGenEncVecs * kGenMaxRecord / 4 + 1; c += kGenEncThreads) srec[c] = 0u;
     __syncthreads();
     {
-        const int g = tid >> 7, c = tid & 127;
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 16
-        for (int i = 0; i < PQ_D; i += 4) { /* 64 elements of S in flight */
-            float s[4];
+        gen_f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) s[k] = S[(i + k) * PQ_D + c];
+        for (int k = 0; k < PQ_D / 4; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(buf[lane & 15][4 * k + (lane >> 4)], s[k], acc, 0, 0, 0);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float4 xv = *reinterpret_cast<const float4 *>(&buf[1][4 * g + v][i]);
-                acc[v] = fmaf(xv.x, s[0], acc[v]);
-                acc[v] = fmaf(xv.y, s[1], acc[v]);
-                acc[v] = fmaf(xv.z, s[2], acc[v]);
-                acc[v] = fmaf(xv.w, s[3], acc[v]);
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) buf[0][4 * g + v][c] = acc[v];
+        for (int i = 0; i < 4; ++i) sy[4 * (lane >> 4) + i][16 * wave + (lane & 15)] = acc[i];
     }
     __syncthreads();
-    int cur = 0;
-    for (int l = 0; l < f.depth; ++l) {
-        const int shift = 6 - l, n_ang = PQ_D >> (l + 1);
-        for (int t = tid; t < kGenEncVecs * n_ang; t += kGenEncThreads) {
-            const int v = t >> shift, j = t & (n_ang - 1);
-            const float a = buf[cur][v][2 * j], b = buf[cur][v][2 * j + 1];
-            float ang = atan2f(b, a);
-            if (l == 0 && ang < 0.f) ang += 6.28318530717958647692f;
-            uint32_t code = 0;
-            /* nearest centroid, ties to the lower cell; boundaries a level does not have are +inf (reading them all at
-               once is a third of the time of a loop over those it has) */
+    {
+        const int v = tid >> 5, q = tid & 31, base = 8 * f.rec_bytes * v;
+        const float4 y = *reinterpret_cast<const float4 *>(&sy[v][4 * q]);
+        auto angle1 = [](float a, float b) {
+            const float ang = atan2f(b, a);
+            return ang < 0.f ? ang + 6.28318530717958647692f : ang;
+        };
+        /* level 1: two angles, next to each other in the stream */
+        const uint32_t c0 = gen_cell<kGenMaxCells - 1>(f.bound[0], angle1(y.x, y.y));
+        const uint32_t c1 = gen_cell<kGenMaxCells - 1>(f.bound[0], angle1(y.z, y.w));
+        gen_emit(srec, base + 2 * q * f.bits[0], c0 | c1 << f.bits[0], 2 * f.bits[0]);
+        float a = sqrtf(y.x * y.x + y.y * y.y), b = sqrtf(y.z * y.z + y.w * y.w);
+        gen_emit(srec, base + f.bit_off[1] + q * f.bits[1], gen_cell<7>(f.bound[1], atan2f(b, a)), f.bits[1]);
+        float r = sqrtf(a * a + b * b);
 #pragma unroll
-            for (int k = 0; k < 7; ++k) code += ang > f.bound[l][k] ? 1u : 0u;
-            if (l == 0) {
-#pragma unroll
-                for (int k = 7; k < kGenMaxCells - 1; ++k) code += ang > f.bound[0][k] ? 1u : 0u;
+        for (int l = 2; l < 7; ++l) { /* the 2^(l-1) lanes of a node all know its radius, the first of them has the code to write */
+            if (l < f.depth) {
+                const float other = __shfl_xor(r, 1 << (l - 2));
+                const bool up = (q >> (l - 2)) & 1;
+                a = up ? other : r;
+                b = up ? r : other;
+                const uint32_t code = gen_cell<7>(f.bound[l], atan2f(b, a));
+                if ((q & ((1 << (l - 1)) - 1)) == 0) gen_emit(srec, base + f.bit_off[l] + (q >> (l - 1)) * f.bits[l], code, f.bits[l]);
+                r = sqrtf(a * a + b * b);
             }
-            const int pos = 8 * f.rec_bytes * v + f.bit_off[l] + j * f.bits[l];
-            atomicOr(&srec[pos >> 5], code << (pos & 31));
-            if ((pos & 31) + f.bits[l] > 32) atomicOr(&srec[(pos >> 5) + 1], code >> (32 - (pos & 31)));
-            buf[cur ^ 1][v][j] = sqrtf(a * a + b * b);
         }
-        cur ^= 1;
-        __syncthreads();
-    }
-    uint8_t *img = reinterpret_cast<uint8_t *>(srec);
-    if (tid < kGenEncVecs * f.n_radii) {
-        const int v = tid / f.n_radii, k = tid - v * f.n_radii;
-        const uint16_t h = gen_radius_bits(buf[cur][v][k]);
-        const int at = v * f.rec_bytes + f.code_bytes + 2 * k;
-        img[at] = (uint8_t)(h & 0xFF);
-        img[at + 1] = (uint8_t)(h >> 8);
+        const int per = f.depth - 2; /* 2^per quarters to a radius */
+        if ((q & ((1 << per) - 1)) == 0) gen_emit(srec, base + 8 * f.code_bytes + 16 * (q >> per), gen_radius_bits(r), 16);
     }
     __syncthreads();
+    const uint8_t *img = reinterpret_cast<const uint8_t *>(srec);
     uint8_t *out = rec + v0 * f.rec_bytes;
     const int n_bytes = nv * f.rec_bytes;
     int done = 0;
