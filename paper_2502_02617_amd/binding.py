@@ -124,6 +124,11 @@ def library():
     L.pq_general_decode.argtypes = [vp, vp, vp, vp, i64, i32, vp, vp]
     L.pq_general_attn_decode.restype = i32
     L.pq_general_attn_decode.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, i32, i64, ctypes.c_float, vp]
+    L.pq_general_attn_workspace_bytes.restype = ctypes.c_size_t
+    L.pq_general_attn_workspace_bytes.argtypes = [i32, i32, i32, i64]
+    L.pq_general_attn_decode_ws.restype = i32
+    L.pq_general_attn_decode_ws.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, i32, i64, ctypes.c_float, vp,
+                                            ctypes.c_size_t, vp]
     L.pq_profile_begin.restype = i32
     L.pq_profile_begin.argtypes = [i32]
     L.pq_profile_begin_sampled.restype = i32
@@ -579,10 +584,18 @@ def general_decode(ctx, fmt, cbg, records, n, out, rotated=False):
 
 
 def general_attn_decode(ctx, fmt, cbg, q, out, k_records, v_records, seq_start, ctx_len, scale):
-    """q bf16 [B, Hq, 128]; records uint8 [Hkv, pool_tokens, record bytes]; out fp32 [B, Hq, 128]."""
+    """q bf16 [B, Hq, 128]; records uint8 [Hkv, pool_tokens, record bytes]; out fp32 [B, Hq, 128].  The workspace that lets few
+    rows occupy the chip comes from torch's allocator, in the order of the stream; a stream that is being captured gets none (a
+    graph outlives it)."""
+    import torch
+
     cb = _cbg(cbg)
     B, Hq, _ = q.shape
-    _check(library().pq_general_attn_decode(ctx._h, ctypes.byref(fmt), cb.ctypes.data, q.data_ptr(),
-                                            out.data_ptr(), k_records.data_ptr(), v_records.data_ptr(),
-                                            seq_start.data_ptr(), ctx_len.data_ptr(), int(B), int(Hq),
-                                            int(k_records.shape[0]), int(k_records.shape[1]), float(scale), _stream()))
+    Hkv, pool_tokens = k_records.shape[0], k_records.shape[1]
+    L = library()
+    n = L.pq_general_attn_workspace_bytes(B, Hq, Hkv, pool_tokens)
+    ws = torch.empty(n, dtype=torch.uint8, device=q.device) if n and not torch.cuda.is_current_stream_capturing() else None
+    _check(L.pq_general_attn_decode_ws(ctx._h, ctypes.byref(fmt), cb.ctypes.data, q.data_ptr(),
+                                       out.data_ptr(), k_records.data_ptr(), v_records.data_ptr(), seq_start.data_ptr(),
+                                       ctx_len.data_ptr(), int(B), int(Hq), int(Hkv), int(pool_tokens), float(scale),
+                                       ws.data_ptr() if ws is not None else None, n if ws is not None else 0, _stream()))

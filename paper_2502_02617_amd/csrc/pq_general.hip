@@ -277,15 +277,54 @@ __global__ __launch_bounds__(64) void pq_general_decode_kernel(GenFormat f, cons
     out[v * PQ_D + 2 * tid + 1] = a1;
 }
 
+/* x of the lane that the DPP control names, inside rows of sixteen lanes */
+template <int CTRL>
+__device__ __forceinline__ float gen_dpp(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+
+/* sum of lanes i, i ^ 16, i ^ 32, i ^ 48 */
+__device__ __forceinline__ float gen_rows_sum(float x)
+{
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
 __device__ __forceinline__ float gen_wave_sum(float x)
 {
+    x += gen_dpp<0xB1>(x);
+    x += gen_dpp<0x4E>(x);
+    x += gen_dpp<0x141>(x);
+    x += gen_dpp<0x140>(x);
+    return gen_rows_sum(x);
+}
+
+__device__ __forceinline__ float gen_wave_max(float x)
+{
+    x = fmaxf(x, gen_dpp<0xB1>(x));
+    x = fmaxf(x, gen_dpp<0x4E>(x));
+    x = fmaxf(x, gen_dpp<0x141>(x));
+    x = fmaxf(x, gen_dpp<0x140>(x));
+    x = fmaxf(x, __shfl_xor(x, 16));
+    return fmaxf(x, __shfl_xor(x, 32));
+}
+
+/* Of 2 HALF values a lane keeps the half that bit HALF of its lane number names, summed with those of the lane that CTRL pairs
+   it with, which keeps the other half. */
+template <int HALF, int CTRL>
+__device__ __forceinline__ void gen_halve(float (&a)[16], int lane)
+{
+    const bool up = (lane & HALF) != 0;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
-    return x;
+    for (int c = 0; c < HALF; ++c) {
+        const float keep = up ? a[c + HALF] : a[c], give = up ? a[c] : a[c + HALF];
+        a[c] = keep + gen_dpp<CTRL>(give);
+    }
 }
 
 /* ---- attention: one workgroup of eight or sixteen wavefronts per (sequence, HEADS query heads of one kv head) ----
- * The entry point has no workspace, so a sequence is not split over workgroups; inside one, wavefront (tg, b) takes block
+ * Without a workspace a sequence is not split over workgroups (pq_general_piece_kernel does that); inside one, wavefront (tg, b) takes block
  * b (sixteen coordinates) of 64 tokens at a time, one token per lane:
  *   - the records of 64 or 128 tokens are copied to LDS, every record on a dword boundary, while those before are worked on;
  *   - a lane rebuilds its block from the codes on the path from the top radius down (the same fp32 products in the same
@@ -355,12 +394,68 @@ __device__ __forceinline__ uint32_t gen_load_dword(const uint8_t *rec, int k, in
 
 __device__ __forceinline__ int gen_dword_shift(int k, int rec_bytes) { return 8 * max(4 * k + 4 - rec_bytes, 0); }
 
+/* tokens of a sequence that take part: one outside the pool is treated as empty */
+__device__ __forceinline__ int gen_tokens(int64_t n, int64_t t0, int64_t pool_tokens)
+{
+    return n < 0 || t0 < 0 || t0 + n > pool_tokens ? 0 : (int)n;
+}
+
+/* ---- the same over several workgroups per sequence, for callers with a workspace ----
+ * The chunks of kGenChunk tokens of all sequences are dealt out in pieces of `share` chunks (the last of a sequence may be
+ * smaller), so that there are at most `slots` pieces and one more per sequence, numbered along the sequences.  Every wavefront
+ * forms that by itself from the lengths, which the host does not know: lane b looks after sequence b. */
+constexpr int kGenChunk = 64, kGenSplitBatch = 64; /* tokens; sequences of a split call */
+constexpr int kGenWhole = 2; /* chunks up to which no sequence is split */
+
+__device__ __forceinline__ int gen_wave_scan(int x) /* inclusive sum over the lanes */
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
+    return x;
+}
+
+struct GenPlan {
+    int len; /* as loaded */
+    int64_t t0;
+    int tokens, upto, share; /* of the lane's sequence; pieces of the sequences up to it; chunks per piece */
+
+    __device__ __forceinline__ void load(const int64_t *seq_start, const int32_t *ctx_len, int B)
+    {
+        const int b = min((int)(threadIdx.x & 63), B - 1);
+        len = ctx_len[b];
+        t0 = seq_start[b];
+    }
+    __device__ __forceinline__ void form(int B, int64_t pool_tokens, int slots)
+    {
+        tokens = (int)(threadIdx.x & 63) < B ? gen_tokens(len, t0, pool_tokens) : 0;
+        const int chunks = (tokens + kGenChunk - 1) / kGenChunk;
+        const int sum = __builtin_amdgcn_readlane(gen_wave_scan(chunks), 63);
+        share = __ballot(chunks > kGenWhole) == 0ull ? kGenWhole : max((sum + slots - 1) / slots, 1);
+        upto = gen_wave_scan((chunks + share - 1) / share);
+    }
+    __device__ __forceinline__ int first(int b) const { return b > 0 ? __builtin_amdgcn_readlane(upto, b - 1) : 0; }
+    __device__ __forceinline__ int pieces(int b) const { return __builtin_amdgcn_readlane(upto, b) - first(b); }
+    __device__ __forceinline__ int tokens_of(int b) const { return __builtin_amdgcn_readlane(tokens, b); }
+    __device__ __forceinline__ int64_t start_of(int b) const
+    {
+        return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(t0 >> 32), b) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane((int)t0, b));
+    }
+};
+
+struct GenSplit {
+    int B, slots, pieces; /* pieces: the most there can be */
+    float *o, *ml;        /* [piece][query head][128], [piece][query head][2]: weighted values, reference and sum of the weights */
+};
+
 template <int HEADS, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_attn_kernel(GenFormat f, const uint16_t *q, float *out,
-                                                                                     const uint8_t *k_rec, const uint8_t *v_rec,
-                                                                                     const int64_t *seq_start, const int32_t *ctx_len,
-                                                                                     int Hq, int Hkv, int64_t pool_tokens, float scale,
-                                                                                     const float *S, const float *St)
+__global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_attn_kernel(
+    GenFormat f, const uint16_t *q, float *out, const uint8_t *k_rec, const uint8_t *v_rec, const int64_t *seq_start,
+    const int32_t *ctx_len, int Hq, int Hkv, int64_t pool_tokens, float scale, const float *S, const float *St)
 {
     constexpr int kThreads = WAVES * 64, kTokens = kThreads / 8; /* eight blocks of a token, one per wavefront */
     constexpr int kGroups = kTokens / 64;
@@ -370,13 +465,21 @@ __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_att
     __shared__ __attribute__((aligned(16))) float sq[HEADS][PQ_D];
     __shared__ float so[HEADS][PQ_D]; /* sq: q, then its rotation; so: the weighted values */
     __shared__ float part_o[HEADS][kGroups][PQ_D], part_m[HEADS][kGroups], part_l[HEADS][kGroups];
-    const int groups = Hq / HEADS, b = blockIdx.x / groups, head0 = (blockIdx.x % groups) * HEADS, hk = head0 / (Hq / Hkv);
-    const int64_t row0 = (int64_t)b * Hq + head0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tg = wave >> 3, blk = wave & 7;
-    int64_t n = ctx_len[b];
+    /* products with a matrix: thread (part, c) sums kTerms terms of column c; its slice is requested ahead */
+    constexpr int kParts = kThreads / PQ_D, kTerms = PQ_D / kParts;
+    const int my_part = tid >> 7, my_col = tid & 127;
+    float slice[kTerms];
+    auto load_slice = [&](const float *M) {
+#pragma unroll
+        for (int k = 0; k < kTerms; ++k) slice[k] = M[(kTerms * my_part + k) * PQ_D + my_col];
+    };
+    load_slice(S);
+    const int groups = Hq / HEADS, b = blockIdx.x / groups, head0 = (blockIdx.x % groups) * HEADS, hk = head0 / (Hq / Hkv);
     const int64_t t0 = seq_start[b];
-    if (n < 0 || t0 < 0 || t0 + n > pool_tokens) n = 0; /* a sequence outside the pool is treated as empty */
+    const int64_t n = gen_tokens(ctx_len[b], t0, pool_tokens);
+    const int64_t row0 = (int64_t)b * Hq + head0;
 
     /* records of tokens [first, first + kTokens) of the sequence: dword (stream, token, k) -> registers -> LDS */
     const int per_stream = kTokens * f.rec_dwords;
@@ -412,32 +515,29 @@ __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_att
     if (tid < 7 * kGenMaxCells) cs[tid >> 4][tid & 15] = make_float2((&f.cosv[0][0])[tid], (&f.sinv[0][0])[tid]);
     for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = __uint_as_float((uint32_t)q[row0 * PQ_D + t] << 16);
     __syncthreads();
-    /* product of HEADS vectors with a matrix: thread (part, c) sums sixteen terms of column c, eight parts */
-    auto times_matrix = [&](const float (&in)[HEADS][PQ_D], const float *M) {
-        const int c = tid & 127;
+    auto times_slice = [&](const float (&in)[HEADS][PQ_D]) {
+        float acc[HEADS];
 #pragma unroll
-        for (int part = tid >> 7; part < 8; part += kThreads / PQ_D) {
-            float acc[HEADS];
+        for (int h = 0; h < HEADS; ++h) acc[h] = 0.f;
 #pragma unroll
-            for (int h = 0; h < HEADS; ++h) acc[h] = 0.f;
+        for (int k = 0; k < kTerms; ++k)
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const float m = M[(16 * part + k) * PQ_D + c];
+            for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(in[h][kTerms * my_part + k], slice[k], acc[h]);
 #pragma unroll
-                for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(in[h][16 * part + k], m, acc[h]);
-            }
-#pragma unroll
-            for (int h = 0; h < HEADS; ++h) spart[h][part][c] = acc[h];
-        }
+        for (int h = 0; h < HEADS; ++h) spart[h][my_part][my_col] = acc[h];
         __syncthreads();
     };
     auto product = [&](int h, int c) {
-        float a[8];
+        float a[kParts];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) a[k] = spart[h][k][c];
-        return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+        for (int k = 0; k < kParts; ++k) a[k] = spart[h][k][c];
+#pragma unroll
+        for (int d = kParts / 2; d >= 1; d >>= 1)
+#pragma unroll
+            for (int k = 0; k < d; ++k) a[k] = a[2 * k] + a[2 * k + 1];
+        return a[0];
     };
-    times_matrix(sq, S); /* q' = q S */
+    times_slice(sq); /* q' = q S */
     for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = product(t >> 7, t & 127);
     if (n > 0) store(0);
     __syncthreads();
@@ -510,32 +610,23 @@ __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_att
         }
         __syncthreads(); /* the next records are in place, and the parts have been read */
     }
-    /* the lanes of a wavefront: everything to one reference, then sums; after four halving steps a lane holds the
-       coordinate that its upper four lane bits name */
+    load_slice(St);
+    /* the lanes of a wavefront: everything to one reference, then sums; after four halving steps inside the rows of sixteen
+       lanes a lane holds the coordinate that its lower four lane bits name */
 #pragma unroll
     for (int h = 0; h < HEADS; ++h) {
-        float mw = m[h];
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) mw = fmaxf(mw, __shfl_xor(mw, d));
+        const float mw = gen_wave_max(m[h]);
         const float w = m[h] == -INFINITY ? 0.f : expf(m[h] - mw);
         const float lw = gen_wave_sum(l[h] * w);
         float a[16];
 #pragma unroll
         for (int c = 0; c < 16; ++c) a[c] = acc[h][c] * w;
-#pragma unroll
-        for (int half = 8; half >= 1; half >>= 1) {
-            const bool up = (lane & (4 * half)) != 0;
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                if (c < half) {
-                    const float keep = up ? a[c + half] : a[c], give = up ? a[c] : a[c + half];
-                    a[c] = keep + __shfl_xor(give, 4 * half);
-                }
-        }
-        float o = a[0];
-        o += __shfl_xor(o, 2);
-        o += __shfl_xor(o, 1);
-        if ((lane & 3) == 0) part_o[h][tg][16 * blk + (lane >> 2)] = o;
+        gen_halve<8, 0x140>(a, lane); /* with lane 15 - i of the row */
+        gen_halve<4, 0x141>(a, lane); /* 7 - i of the half row */
+        gen_halve<2, 0x1B>(a, lane);  /* 3 - i of the quad */
+        gen_halve<1, 0xB1>(a, lane);  /* i ^ 1 */
+        const float o = gen_rows_sum(a[0]);
+        if (lane < 16) part_o[h][tg][16 * blk + lane] = o;
         if (blk == 0 && lane == 0) {
             part_m[h][tg] = mw;
             part_l[h][tg] = lw;
@@ -555,18 +646,268 @@ __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_att
         so[h][c] = lt > 0.f ? a / lt : 0.f;
     }
     __syncthreads();
-    times_matrix(so, St);
+    times_slice(so);
     for (int t = tid; t < HEADS * PQ_D; t += kThreads) out[row0 * PQ_D + t] = product(t >> 7, t & 127);
 }
 
-template <int HEADS, int WAVES>
-void launch_general_attn(const GenFormat &g, const void *q, float *out, const uint8_t *k, const uint8_t *v, const int64_t *start,
-                         const int32_t *len, int64_t rows, int Hq, int Hkv, int64_t pool, float scale, const PqDeviceState *ds,
-                         hipStream_t s)
+/* A piece and HEADS query heads of its kv head: sixteen wavefronts, chunks of 64 tokens, one token per lane.  Wavefront b < 8
+ * rebuilds block b of the keys and forms its part of the scores, wavefront 8 + b rebuilds block b of the values meanwhile; one
+ * wavefront per head turns the parts into weights, and the value wavefronts multiply them with their values on
+ * v_mfma_f32_16x16x4_f32 (fp32 products and sums; the values change places by way of LDS) while the others are at the next keys.
+ * A sequence that is one piece is finished here.
+ * Bound by the chain of a piece: lengths 1 us, records and S 1.4, q S 1.2, a chunk 2.4, the end 1.  4 sequences of 2048 tokens, 8
+ * query heads: 45.2 us on 32 workgroups -> 14.6 for this and the launch that joins the pieces; one sequence of 8000 tokens and 16 heads
+ * 148.8 -> 17.3.  Against 64 bits 3.1e-7 to 4.5e-7, one workgroup per row 3.2e-7 to 5.4e-7.  Weights against a reference per lane, sums
+ * in the lanes and eight wavefronts for keys and values one after the other: 15.8 us for this launch alone, now 10.7. */
+constexpr int kGenSplitThreads = 1024;
+
+template <int HEADS>
+__global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
+    GenFormat f, const uint16_t *q, float *out, const uint8_t *k_rec, const uint8_t *v_rec, const int64_t *seq_start,
+    const int32_t *ctx_len, int Hq, int Hkv, int64_t pool_tokens, float scale, const float *S, const float *St, GenSplit split)
 {
-    hipLaunchKernelGGL((pq_general_attn_kernel<HEADS, WAVES>), dim3((unsigned)(rows / HEADS)), dim3(WAVES * 64), 0, s, g,
-                       static_cast<const uint16_t *>(q), out, k, v, start, len, Hq, Hkv, pool, scale, ds->S_f32, ds->St_f32);
+    constexpr int kThreads = kGenSplitThreads, kParts = kThreads / PQ_D, kTerms = PQ_D / kParts;
+    __shared__ uint32_t srec[2][2][kGenChunk * kGenMaxDwords + 1]; /* [buffer][keys, values] */
+    __shared__ float2 cs[7][kGenMaxCells];
+    __shared__ float spart[HEADS][kParts][PQ_D]; /* partial products with S; a block's part of the scores in its first 64 */
+    __shared__ __attribute__((aligned(16))) float sq[HEADS][PQ_D]; /* q, then its rotation; at the end the weighted values */
+    /* values of a wavefront's block, sixteen floats per token, and as many to spare after sixteen tokens: four tokens sixteen apart
+       are read at a time, each from its own sixteen banks */
+    __shared__ __attribute__((aligned(16))) float sv[8][(kGenChunk + 4) * 16];
+    __shared__ __attribute__((aligned(16))) float sw[HEADS][kGenChunk], salpha[4]; /* weights of the chunk; factors on what was summed before */
+    __shared__ float sm[HEADS], sl[HEADS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), blk = wave & 7;
+    const int my_part = tid >> 7, my_col = tid & 127;
+    GenPlan plan;
+    plan.load(seq_start, ctx_len, split.B); /* ahead of the loads below: they come back in order */
+    float slice[kTerms];
+    auto load_slice = [&](const float *M) {
+#pragma unroll
+        for (int k = 0; k < kTerms; ++k) slice[k] = M[(kTerms * my_part + k) * PQ_D + my_col];
+    };
+    load_slice(S);
+    if (tid < 7 * kGenMaxCells) cs[tid >> 4][tid & 15] = make_float2((&f.cosv[0][0])[tid], (&f.sinv[0][0])[tid]);
+    const int groups = Hq / HEADS, item = blockIdx.x / groups, head0 = (blockIdx.x % groups) * HEADS, hk = head0 / (Hq / Hkv);
+    plan.form(split.B, pool_tokens, split.slots);
+    const int b = __popcll(__ballot(plan.upto <= item));
+    if (b >= split.B) return; /* fewer pieces than there could be */
+    const bool whole = plan.pieces(b) == 1;
+    const int begin = (item - plan.first(b)) * plan.share * kGenChunk;
+    const int n = (int)min((int64_t)plan.tokens_of(b), (int64_t)begin + (int64_t)plan.share * kGenChunk); /* begin < n */
+    const int64_t row0 = (int64_t)b * Hq + head0, slot0 = (int64_t)hk * pool_tokens + plan.start_of(b);
+
+    /* records of tokens [first, first + 64): dword (stream, token, k) -> registers -> LDS */
+    const int per_stream = kGenChunk * f.rec_dwords;
+    constexpr int kMaxStage = (2 * kGenChunk * (kGenMaxDwords - 1) + kThreads - 1) / kThreads;
+    uint32_t stage[kMaxStage];
+    struct Place { int stream, t, k; };
+    auto place = [&](int at) { /* threads beyond the last dword repeat it */
+        at = min(at, 2 * per_stream - 1);
+        Place p;
+        p.stream = at >= per_stream ? 1 : 0;
+        const int in = at - p.stream * per_stream; /* below 1152: the multiplication by the inverse is exact */
+        p.t = (int)(((uint32_t)in * (uint32_t)f.rec_inv) >> 16);
+        p.k = in - p.t * f.rec_dwords;
+        return p;
+    };
+    auto fetch = [&](int first) {
+#pragma unroll
+        for (int i = 0; i < kMaxStage; ++i) {
+            const Place p = place(tid + i * kThreads);
+            const int t = min(first + p.t, n - 1); /* tokens beyond the piece repeat its last one */
+            stage[i] = gen_load_dword((p.stream ? v_rec : k_rec) + (slot0 + t) * f.rec_bytes, p.k, f.rec_bytes);
+        }
+    };
+    auto store = [&](int buffer) {
+#pragma unroll
+        for (int i = 0; i < kMaxStage; ++i) {
+            const Place p = place(tid + i * kThreads);
+            srec[buffer][p.stream][p.t * kGenMaxDwords + p.k] = stage[i] >> gen_dword_shift(p.k, f.rec_bytes);
+        }
+    };
+    fetch(begin);
+    for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = __uint_as_float((uint32_t)q[row0 * PQ_D + t] << 16);
+    __syncthreads();
+    auto times_slice = [&](const float (&in)[HEADS][PQ_D]) {
+        float acc[HEADS];
+#pragma unroll
+        for (int h = 0; h < HEADS; ++h) acc[h] = 0.f;
+#pragma unroll
+        for (int k = 0; k < kTerms; ++k)
+#pragma unroll
+            for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(in[h][kTerms * my_part + k], slice[k], acc[h]);
+#pragma unroll
+        for (int h = 0; h < HEADS; ++h) spart[h][my_part][my_col] = acc[h];
+        __syncthreads();
+    };
+    auto product = [&](int h, int c) {
+        float a[kParts];
+#pragma unroll
+        for (int k = 0; k < kParts; ++k) a[k] = spart[h][k][c];
+        return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+    };
+    times_slice(sq); /* q' = q S */
+    for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = product(t >> 7, t & 127);
+    store(0);
+    __syncthreads();
+    if (whole) load_slice(St);
+
+    float m = -INFINITY, l = 0.f; /* wavefront h < HEADS: reference and sum of the weights of head h, for the lane's tokens */
+    gen_f4 acc = {0.f, 0.f, 0.f, 0.f}; /* wavefront 8 + b, lane j < 16: coordinate 16 b + j for head 0, 1, ... */
+    int cur = 0;
+    for (int first = begin; first < n; first += kGenChunk, cur ^= 1) { /* n is the same in all threads */
+        const bool more = first + kGenChunk < n;
+        if (more) fetch(first + kGenChunk);
+        float v[16];
+        gen_block(f, srec[cur][wave >> 3] + lane * kGenMaxDwords, cs, blk, v);
+        if (wave < 8) {
+#pragma unroll
+            for (int h = 0; h < HEADS; ++h) {
+                float d[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < 16; c += 4) {
+                    const float4 qc = *reinterpret_cast<const float4 *>(&sq[h][16 * blk + c]);
+                    d[0] = fmaf(qc.x, v[c], d[0]);
+                    d[1] = fmaf(qc.y, v[c + 1], d[1]);
+                    d[2] = fmaf(qc.z, v[c + 2], d[2]);
+                    d[3] = fmaf(qc.w, v[c + 3], d[3]);
+                }
+                spart[h][blk][lane] = (d[0] + d[1]) + (d[2] + d[3]);
+            }
+        } else {
+            float4 *to = reinterpret_cast<float4 *>(&sv[blk][16 * (lane + (lane >> 4))]);
+#pragma unroll
+            for (int c = 0; c < 16; c += 4) to[c / 4] = make_float4(v[c], v[c + 1], v[c + 2], v[c + 3]);
+        }
+        __syncthreads(); /* the parts are written, and everyone is through with the other buffer */
+        if (more) store(cur ^ 1);
+        if (wave < HEADS) {
+            const bool valid = first + lane < n;
+            /* The parts are summed, scaled and compared with the reference in 64 bits: a score of 20 rounded to fp32
+               would put 1e-6 on its token's weight, the largest error of the whole result. */
+            double sum = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sum += (double)spart[wave][k][lane];
+            const double s = sum * (double)scale;
+            const float top = gen_wave_max(valid ? (float)s : -INFINITY);
+            float alpha = 1.f;
+            if (top > m + kGenSlack || m == -INFINITY) { /* the same in all lanes */
+                alpha = m == -INFINITY ? 0.f : expf(m - top);
+                m = top;
+            }
+            const float p = valid ? expf((float)(s - (double)m)) : 0.f;
+            l = l * alpha + p;
+            sw[wave][lane] = p;
+            if (lane == 0) salpha[wave] = alpha;
+        }
+        __syncthreads(); /* the next records are in place, the parts have been read, the weights are written */
+        if (wave >= 8) { /* contraction: step k takes tokens k, 16 + k, 32 + k and 48 + k */
+            const int g = lane >> 4, j = lane & 15;
+            gen_f4 o = {0.f, 0.f, 0.f, 0.f};
+            const float4 *w4 = reinterpret_cast<const float4 *>(&sw[min(j, HEADS - 1)][16 * g]);
+            const float *from = &sv[blk][16 * 17 * g + j];
+#pragma unroll
+            for (int k = 0; k < 16; k += 4) {
+                float4 w = w4[k / 4];
+                if (j >= HEADS) w = make_float4(0.f, 0.f, 0.f, 0.f);
+                o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, from[16 * k], o, 0, 0, 0);
+                o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, from[16 * k + 16], o, 0, 0, 0);
+                o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, from[16 * k + 32], o, 0, 0, 0);
+                o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, from[16 * k + 48], o, 0, 0, 0);
+            }
+#pragma unroll
+            for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(acc[h], salpha[h], o[h]);
+        }
+    }
+    if (wave < HEADS) {
+        l = gen_wave_sum(l);
+        if (lane == 0) {
+            sm[wave] = m;
+            sl[wave] = l;
+        }
+    }
+    __syncthreads();
+    if (wave >= 8 && lane < 16) {
+#pragma unroll
+        for (int h = 0; h < HEADS; ++h) sq[h][16 * blk + lane] = whole ? acc[h] / sl[h] : acc[h]; /* a piece has a token: sl > 0 */
+    }
+    __syncthreads();
+    if (whole) {
+        times_slice(sq);
+        for (int t = tid; t < HEADS * PQ_D; t += kThreads) out[row0 * PQ_D + t] = product(t >> 7, t & 127);
+    } else {
+        const int64_t at = (int64_t)item * Hq + head0;
+        for (int t = tid; t < HEADS * PQ_D; t += kThreads) split.o[at * PQ_D + t] = sq[t >> 7][t & 127];
+        if (tid < 2 * HEADS) split.ml[at * 2 + tid] = (tid & 1) ? sl[tid >> 1] : sm[tid >> 1];
+    }
 }
+
+/* Second launch of a split call: a row's pieces brought to one reference, divided by the sum of the weights, times S^T.  One
+   row per workgroup of 512 threads; thread (part, c) takes pieces part, part + 4, ... of column c, then a quarter of the product
+   for it. */
+__global__ __launch_bounds__(512) void pq_general_combine_kernel(GenSplit split, const int64_t *seq_start, const int32_t *ctx_len,
+                                                                 int Hq, int64_t pool_tokens, const float *St, float *out)
+{
+    __shared__ float so[PQ_D], spart[4][PQ_D], sl[4];
+    const int row = blockIdx.x, b = row / Hq, head = row % Hq;
+    const int tid = threadIdx.x, part = tid >> 7, c = tid & 127;
+    GenPlan plan;
+    plan.load(seq_start, ctx_len, split.B);
+    plan.form(split.B, pool_tokens, split.slots);
+    const int first = plan.first(b), used = plan.pieces(b);
+    if (used == 1) return;
+    MatrixSlice ms;
+    matrix_slice_load(ms, St, tid);
+    const float *ml = split.ml + ((int64_t)first * Hq + head) * 2, *op = split.o + ((int64_t)first * Hq + head) * PQ_D + c;
+    float m = -INFINITY;
+    for (int p = tid & 63; p < used; p += 64) m = fmaxf(m, ml[(int64_t)p * Hq * 2]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+    float l = 0.f, o = 0.f;
+#pragma unroll 4
+    for (int p = part; p < used; p += 4) {
+        const float2 v = *reinterpret_cast<const float2 *>(ml + (int64_t)p * Hq * 2);
+        const float w = expf(v.x - m); /* a piece has at least one token: its reference is finite */
+        l = fmaf(v.y, w, l);
+        o = fmaf(op[(int64_t)p * Hq * PQ_D], w, o);
+    }
+    spart[part][c] = o;
+    if (c == 0) sl[part] = l;
+    __syncthreads();
+    if (part == 0) {
+        const float lt = (sl[0] + sl[1]) + (sl[2] + sl[3]);
+        const float a = (spart[0][c] + spart[1][c]) + (spart[2][c] + spart[3][c]);
+        so[c] = lt > 0.f ? a / lt : 0.f;
+    }
+    __syncthreads();
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < 32; ++k) acc = fmaf(so[32 * part + k], ms.m[k], acc);
+    spart[part][c] = acc;
+    __syncthreads();
+    if (part == 0) out[(int64_t)row * PQ_D + c] = (spart[0][c] + spart[1][c]) + (spart[2][c] + spart[3][c]);
+}
+
+/* heads of a kv head that a workgroup of a split call takes together */
+int gen_split_heads(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }
+
+/* How a call is split: not at all (slots 0) where the heads alone occupy half of the CUs, or where the pool holds no more than
+   eight chunks per sequence (three sequences, 8 heads, us for the call, split and not: 2000 tokens 13.5 / 45.2, 500 13.3 / 17.0, 300 13.4 /
+   14.7, 200 13.4 / 12.3; the lengths are on the device, so the pool stands for them, and sequences far shorter than their share
+   of it wait for the host's second launch: 13.4 / 10.6). */
+GenSplit general_split(int B, int Hq, int Hkv, int64_t pool_tokens)
+{
+    GenSplit p{};
+    p.B = B;
+    const int64_t rows = (int64_t)B * Hq, chunks = (pool_tokens + kGenChunk - 1) / kGenChunk;
+    if (rows > 128 || B > kGenSplitBatch || chunks <= 8 * (int64_t)B) return p;
+    const int groups = Hq / gen_split_heads(Hq / Hkv);
+    p.slots = groups < 256 ? 256 / groups : 1;
+    p.pieces = p.slots + B;
+    return p;
+}
+
+size_t general_split_bytes(const GenSplit &p, int Hq) { return (size_t)p.pieces * Hq * (PQ_D + 2) * sizeof(float); }
 
 } // namespace
 
@@ -643,10 +984,26 @@ extern "C" pq_status pq_general_decode(const pq_ctx *ctx, const pq_general_forma
     return PQ_OK;
 }
 
+extern "C" size_t pq_general_attn_workspace_bytes(int B, int Hq, int Hkv, int64_t pool_tokens)
+{
+    if (B <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || pool_tokens <= 0) return 0;
+    return general_split_bytes(general_split(B, Hq, Hkv, pool_tokens), Hq);
+}
+
 extern "C" pq_status pq_general_attn_decode(const pq_ctx *ctx, const pq_general_format *f, const double *cbg, const void *q,
                                             float *out, const uint8_t *k_records, const uint8_t *v_records,
                                             const int64_t *seq_start, const int32_t *ctx_len, int B, int Hq, int Hkv,
                                             int64_t pool_tokens, float softmax_scale, void *hip_stream)
+{
+    return pq_general_attn_decode_ws(ctx, f, cbg, q, out, k_records, v_records, seq_start, ctx_len, B, Hq, Hkv, pool_tokens,
+                                     softmax_scale, nullptr, 0, hip_stream);
+}
+
+extern "C" pq_status pq_general_attn_decode_ws(const pq_ctx *ctx, const pq_general_format *f, const double *cbg, const void *q,
+                                               float *out, const uint8_t *k_records, const uint8_t *v_records,
+                                               const int64_t *seq_start, const int32_t *ctx_len, int B, int Hq, int Hkv,
+                                               int64_t pool_tokens, float softmax_scale, void *workspace, size_t workspace_bytes,
+                                               void *hip_stream)
 {
     if (!ctx || !q || !out || !k_records || !v_records || !seq_start || !ctx_len) return PQ_EINVAL;
     if (B <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || pool_tokens <= 0) return PQ_EINVAL;
@@ -665,9 +1022,31 @@ extern "C" pq_status pq_general_attn_decode(const pq_ctx *ctx, const pq_general_
     const int64_t rows = (int64_t)B * Hq;
     const int G = Hq / Hkv;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    GenSplit split = workspace ? general_split(B, Hq, Hkv, pool_tokens) : GenSplit{};
+    if (split.slots && workspace_bytes < general_split_bytes(split, Hq)) split = GenSplit{};
+    if (split.slots && !pq_aligned16(workspace)) return PQ_EALIGN;
+    if (split.slots) {
+        split.o = static_cast<float *>(workspace);
+        split.ml = split.o + (size_t)split.pieces * Hq * PQ_D;
+        const int heads = gen_split_heads(G);
+        const dim3 grid((unsigned)((int64_t)split.pieces * (Hq / heads))), blk(kGenSplitThreads);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, blk, 0, stream, g, static_cast<const uint16_t *>(q), out, k_records, v_records, seq_start,
+                               ctx_len, Hq, Hkv, pool_tokens, softmax_scale, ds->S_f32, ds->St_f32, split);
+        };
+        if (heads == 4) launch(pq_general_piece_kernel<4>);
+        else if (heads == 2) launch(pq_general_piece_kernel<2>);
+        else launch(pq_general_piece_kernel<1>);
+        hipLaunchKernelGGL(pq_general_combine_kernel, dim3((unsigned)rows), dim3(512), 0, stream, split, seq_start, ctx_len, Hq,
+                           pool_tokens, ds->St_f32, out);
+        PQ_HIP_TRY(hipGetLastError());
+        return PQ_OK;
+    }
     auto launch = [&](auto heads, auto waves) {
-        launch_general_attn<decltype(heads)::value, decltype(waves)::value>(g, q, out, k_records, v_records, seq_start, ctx_len, rows,
-                                                                            Hq, Hkv, pool_tokens, softmax_scale, ds, stream);
+        constexpr int H = decltype(heads)::value, W = decltype(waves)::value;
+        hipLaunchKernelGGL((pq_general_attn_kernel<H, W>), dim3((unsigned)(rows / H)), dim3(W * 64), 0, stream, g,
+                           static_cast<const uint16_t *>(q), out, k_records, v_records, seq_start, ctx_len, Hq, Hkv, pool_tokens,
+                           softmax_scale, ds->S_f32, ds->St_f32);
     };
     constexpr std::integral_constant<int, 1> one{};
     constexpr std::integral_constant<int, 2> two{};
