@@ -15,11 +15,13 @@
  *     16-byte aligned (PQ_EALIGN otherwise); "host" pointers are ordinary
  *     memory.  The library allocates device memory only for the constants of
  *     a pq_ctx (< 1 MB per device, on the first call that uses that device).
+ *     pq_fit_codebooks(_deep) also take 130 KB of page-locked host memory
+ *     per call under way, of which the library keeps up to four such blocks.
  *   - Kernels are enqueued on the caller's hipStream_t (passed as void*; NULL
  *     is the default stream).  The library does not synchronise the stream and
  *     records no memset or copy nodes, so its calls can be captured into a HIP
  *     graph -- with one exception, stated where it is declared:
- *     pq_fit_codebooks(_deep) copy their histograms to the host and wait.
+ *     pq_fit_codebooks(_deep) bring their histograms to the host and wait.
  *   - A pq_ctx is configured (pq_set_codebooks, pq_set_recursion_depth,
  *     pq_set_upper_codebooks) before its first launch; from then on it is
  *     immutable and may be shared by threads.
@@ -146,7 +148,7 @@ pq_status pq_set_codebooks(pq_ctx *ctx, const double *cb);
  * centroids; NULL: the context's current codebooks).  The paper seeds k-means++ at
  * random; a fixed seed codebook makes the result a function of the data.  cb_out
  * (host): 28 centroids, ready for pq_set_codebooks on a fresh context.  workspace
- * (device): pq_fit_workspace_bytes() bytes.  This call copies the histograms
+ * (device): pq_fit_workspace_bytes() bytes.  This call brings the histograms
  * to the host and WAITS for the stream (it cannot be captured into a graph);
  * pq_fit_count_angles and pq_fit_cluster below are its two halves for callers
  * that place the wait themselves.  x, ld_token, ld_head aligned as for

@@ -7,9 +7,9 @@
  * 120 angles are formed (procedure Polar) and counted into fine histograms,
  * one per level (8192 bins over [0, 2 pi) for level 1, 2048 over [0, pi/2] for
  * levels 2-4; for a full-depth context 2048 more for each of levels 5-7, see
- * pq_fit_codebooks_deep).  The k-means rounds then run on the bin counts on the host
- * in fp64, which costs well under a millisecond and is where the result is
- * wanted (pq_set_codebooks takes host centroids).
+ * pq_fit_codebooks_deep).  A second kernel forms the running sums of the counts and
+ * leaves both in host memory, and the k-means rounds then look up what they need there,
+ * in fp64 on the host, where the result is wanted (pq_set_codebooks takes host centroids).
  *
  * Kernel: one wavefront per tile of 64 vectors, sixteen wavefronts per
  * workgroup, S and the histograms in LDS.
@@ -42,8 +42,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <memory>
-#include <new>
+#include <mutex>
 #include <vector>
 
 namespace {
@@ -329,32 +328,34 @@ const Bins &bins_of(bool level1)
    themselves; the whole bins come from running sums of counts and of counts times middles, which are integers (below 2^45 and
    2^108), so that their differences are exact: a cell of a sliver of one bin keeps its centroid next to any count elsewhere.
    (Running sums make a round a few lookups; walking over all bins in every round, and forming the edges in every call,
-   took 430 us for ten rounds on the four histograms of 262144 vectors; pq_fit_codebooks as a whole 565 -> 115 us.) */
-void lloyd_on_histogram(const uint32_t *hist, int bins, bool level1, int K, int iterations, double *c)
+   took 430 us for ten rounds on the four histograms of 262144 vectors; pq_fit_codebooks as a whole 565 -> 115 us.  A round takes
+   some 0.4 us.) */
+constexpr int kRunBins = 8;
+
+struct BinSum { /* of the bins below kRunBins r of a level */
+    uint64_t lo;
+    uint32_t hi, count; /* moment, 2^64 hi + lo: below 2^96, and a level's angles fit 32 bits, where the device counted */
+};
+
+typedef unsigned __int128 wide;
+
+struct Sum {
+    uint64_t count;
+    wide moment;
+};
+
+/* run(r): the sum below bin kRunBins r */
+template <class Run>
+void lloyd_rounds(const uint32_t *hist, int bins, bool level1, int K, int iterations, double *c, const Run &run)
 {
-    typedef unsigned __int128 wide;
     const std::vector<double> &edge = bins_of(level1).edge;
     const std::vector<uint64_t> &middle = bins_of(level1).middle;
-    struct Sum {
-        uint64_t count;
-        wide moment;
-    };
-    std::vector<Sum> run((size_t)bins / 8 + 1); /* of the bins below 8 r */
-    auto grow = [&](Sum &s, int b, int end) {
-        for (; b < end; ++b) {
-            s.count += hist[b];
-            s.moment += (wide)middle[b] * hist[b];
-        }
-    };
-    Sum all{0, 0};
-    for (int b = 0; b < bins; b += 8) {
-        run[b / 8] = all;
-        grow(all, b, b + 8);
-    }
-    run[bins / 8] = all;
     auto below = [&](int b) {
-        Sum s = run[b / 8];
-        grow(s, b & ~7, b);
+        Sum s = run(b / kRunBins);
+        for (int i = b / kRunBins * kRunBins; i < b; ++i) {
+            s.count += hist[i];
+            s.moment += (wide)middle[i] * hist[i];
+        }
         return s;
     };
     auto bin_at = [&](double x) { return (int)(std::upper_bound(edge.begin(), edge.end(), x) - edge.begin()) - 1; };
@@ -388,6 +389,21 @@ void lloyd_on_histogram(const uint32_t *hist, int bins, bool level1, int K, int 
         }
         for (int k = 0; k < K; ++k) c[k] = next[k];
     }
+}
+
+/* the running sums of a histogram in host memory, and the rounds */
+void lloyd_on_histogram(const uint32_t *hist, int bins, bool level1, int K, int iterations, double *c)
+{
+    const std::vector<uint64_t> &middle = bins_of(level1).middle;
+    std::vector<Sum> sums((size_t)bins / kRunBins + 1);
+    Sum all{0, 0};
+    for (int b = 0; b < bins; ++b) {
+        if (b % kRunBins == 0) sums[b / kRunBins] = all;
+        all.count += hist[b];
+        all.moment += (wide)middle[b] * hist[b];
+    }
+    sums[bins / kRunBins] = all;
+    lloyd_rounds(hist, bins, level1, K, iterations, c, [&](int r) { return sums[r]; });
 }
 
 } // namespace
@@ -500,7 +516,131 @@ extern "C" pq_status pq_fit_cluster(const pq_ctx *ctx, const uint32_t *hist, con
 
 namespace {
 
-/* the two steps with a copy of the histograms and a wait for the stream in between */
+/* ---- what the rounds look at, brought to the host by a kernel: the counts and their running sums ----
+ * One workgroup per level: a thread takes eight bins, a scan over the workgroup gives the sums below them, and both go
+ * straight to host memory that the device writes to: 5.5 us, where a copy of the counts to pageable memory took 12 us beyond
+ * the wait and forming the sums on the host some 7.  262144 bf16 vectors, ten rounds: 81.5 -> 73.6 us for the call, 8000 vectors
+ * 56 -> 48.  (The rounds themselves are a chain of divisions and lookups for 28 numbers: 22 us as a kernel for ten of them, some 4 on
+ * the host.) */
+constexpr int kLevels = 7, kSumThreads = 1024;
+
+struct FitResult { /* in host memory */
+    uint32_t hist[kHistSize + kHistUpper]; /* as in the workspace */
+    BinSum run1[kBins1 / kRunBins + 1], run_upper[kLevels - 1][kBinsU / kRunBins + 1];
+};
+
+__device__ __forceinline__ void bin_add(BinSum &s, const BinSum &t)
+{
+    s.count += t.count;
+    s.lo += t.lo;
+    s.hi += t.hi + (s.lo < t.lo ? 1u : 0u);
+}
+
+__global__ __launch_bounds__(kSumThreads) void pq_fit_sums_kernel(const uint32_t *hist, const uint64_t *middles, FitResult *out)
+{
+    static_assert(kBins1 == kRunBins * kSumThreads && kRunBins == 8, "a thread takes one run of bins, two 16-byte loads");
+    __shared__ BinSum wave_sum[kSumThreads / 64];
+    const int level = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int runs = (level == 0 ? kBins1 : kBinsU) / kRunBins, first = level == 0 ? 0 : kBins1 + (level - 1) * kBinsU;
+    BinSum mine{0, 0, 0};
+    if (tid < runs) {
+        const uint64_t *m = middles + (level == 0 ? 0 : kBins1) + kRunBins * tid;
+        const uint4 a = *reinterpret_cast<const uint4 *>(hist + first + kRunBins * tid);
+        const uint4 b = *reinterpret_cast<const uint4 *>(hist + first + kRunBins * tid + 4);
+        const uint32_t n[kRunBins] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int i = 0; i < kRunBins; ++i) bin_add(mine, BinSum{m[i] * n[i], (uint32_t)__umul64hi(m[i], n[i]), n[i]});
+        *reinterpret_cast<uint4 *>(out->hist + first + kRunBins * tid) = a;
+        *reinterpret_cast<uint4 *>(out->hist + first + kRunBins * tid + 4) = b;
+    }
+    BinSum upto = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        BinSum t;
+        t.lo = __shfl_up((unsigned long long)upto.lo, d);
+        t.hi = __shfl_up(upto.hi, d);
+        t.count = __shfl_up(upto.count, d);
+        if (lane >= d) bin_add(upto, t);
+    }
+    if (lane == 63) wave_sum[wave] = upto;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSumThreads / 64 - 1; ++w) {
+        const BinSum t = wave_sum[w];
+        if (w < wave) bin_add(upto, t);
+    }
+    BinSum *run = level == 0 ? out->run1 : out->run_upper[level - 1];
+    if (tid < runs) run[tid + 1] = upto; /* up to and with this thread: below the next one's bins */
+    if (tid == 0) run[0] = BinSum{0, 0, 0};
+}
+
+/* the middles of the bins on every device, level 1 and then the others, uploaded by the first call there */
+__device__ uint64_t g_middles[kBins1 + kBinsU];
+
+pq_status device_middles(const uint64_t **out)
+{
+    static std::mutex mu;
+    static bool ready[PQ_MAX_DEVICES];
+    int dev = -1;
+    PQ_HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= PQ_MAX_DEVICES) return PQ_EUNSUPPORTED;
+    void *at = nullptr;
+    PQ_HIP_TRY(hipGetSymbolAddress(&at, HIP_SYMBOL(g_middles)));
+    std::lock_guard<std::mutex> lock(mu);
+    if (!ready[dev]) {
+        const std::vector<uint64_t> &first = bins_of(true).middle, &upper = bins_of(false).middle;
+        PQ_HIP_TRY(hipMemcpy(at, first.data(), first.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
+        PQ_HIP_TRY(hipMemcpy(static_cast<uint64_t *>(at) + kBins1, upper.data(), upper.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
+        ready[dev] = true;
+    }
+    *out = static_cast<const uint64_t *>(at);
+    return PQ_OK;
+}
+
+/* Host memory for a FitResult: one block per call under way, kept for the next call (four of 130 KB at most; more callers at a
+   time allocate and free their own). */
+class ResultBlock {
+  public:
+    ResultBlock()
+    {
+        {
+            std::lock_guard<std::mutex> lock(pool().mu);
+            if (pool().n > 0) p_ = pool().kept[--pool().n];
+        }
+        if (!p_ && hipHostMalloc(reinterpret_cast<void **>(&p_), sizeof(FitResult), hipHostMallocPortable) != hipSuccess) p_ = nullptr;
+    }
+    ~ResultBlock()
+    {
+        if (!p_) return;
+        {
+            std::lock_guard<std::mutex> lock(pool().mu);
+            if (pool().n < kKept) {
+                pool().kept[pool().n++] = p_;
+                return;
+            }
+        }
+        (void)hipHostFree(p_);
+    }
+    ResultBlock(const ResultBlock &) = delete;
+    ResultBlock &operator=(const ResultBlock &) = delete;
+    FitResult *get() const { return p_; }
+
+  private:
+    static constexpr int kKept = 4;
+    struct Pool { /* what is kept goes with the process */
+        std::mutex mu;
+        FitResult *kept[kKept];
+        int n = 0;
+    };
+    static Pool &pool()
+    {
+        static Pool p;
+        return p;
+    }
+    FitResult *p_ = nullptr;
+};
+
+/* counting, sums, a wait for the stream, the rounds */
 pq_status fit_codebooks(const pq_ctx *ctx, const void *x, pq_dtype xt, int64_t n_tokens, int n_heads,
                         int64_t ld_token, int64_t ld_head, const double *cb_init, const double *cbt_init, bool upper,
                         int iterations, double *cb_out, double *cbt_out, void *workspace, size_t workspace_bytes,
@@ -508,19 +648,37 @@ pq_status fit_codebooks(const pq_ctx *ctx, const void *x, pq_dtype xt, int64_t n
 {
     if (!ctx || !cb_out || (upper && !cbt_out) || iterations < 0) return PQ_EINVAL;
     if (upper && ctx->depth != 7) return PQ_EINVAL;
-    double unused_upper[3][8];
-    if (!upper && ctx->depth == 7) cbt_out = &unused_upper[0][0]; /* levels 1..4 only were asked for */
     double c[28], ct[3][8] = {};
     pq_status st = check_start(ctx, cb_init, cbt_init, upper, c, ct); /* before anything is launched */
     if (st != PQ_OK) return st;
     st = pq_fit_count_angles(ctx, x, xt, n_tokens, n_heads, ld_token, ld_head, workspace, workspace_bytes, hip_stream);
     if (st != PQ_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const size_t n_counts = ctx->depth == 7 ? kHistSize + kHistUpper : kHistSize; /* what pq_fit_cluster looks at */
-    std::unique_ptr<uint32_t[]> h(new (std::nothrow) uint32_t[n_counts]);
-    if (!h) return PQ_ENOMEM;
-    PQ_HIP_TRY(hipMemcpyWithStream(h.get(), workspace, n_counts * sizeof(uint32_t), hipMemcpyDeviceToHost, s)); /* waits */
-    return pq_fit_cluster(ctx, h.get(), cb_init, cbt_init, iterations, cb_out, cbt_out);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return PQ_EHIP; /* no results to wait for */
+    const uint64_t *middles = nullptr;
+    st = device_middles(&middles);
+    if (st != PQ_OK) return st;
+    ResultBlock result;
+    FitResult *r = result.get();
+    if (!r) return PQ_ENOMEM;
+    hipLaunchKernelGGL(pq_fit_sums_kernel, dim3(upper ? kLevels : 4), dim3(kSumThreads), 0, s, static_cast<const uint32_t *>(workspace),
+                       middles, r);
+    PQ_HIP_TRY(hipGetLastError());
+    PQ_HIP_TRY(hipStreamSynchronize(s));
+    auto rounds = [&](int level, int K, double *centroids) {
+        const BinSum *run = level == 0 ? r->run1 : r->run_upper[level - 1];
+        lloyd_rounds(r->hist + (level == 0 ? 0 : kBins1 + (level - 1) * kBinsU), level == 0 ? kBins1 : kBinsU, level == 0, K, iterations,
+                     centroids, [&](int i) { return Sum{run[i].count, (wide)run[i].hi << 64 | run[i].lo}; });
+    };
+    rounds(0, 16, c);
+    for (int l = 1; l < 4; ++l) rounds(l, 4, c + 12 + 4 * l);
+    memcpy(cb_out, c, sizeof(c));
+    if (upper) {
+        for (int l = 0; l < 3; ++l) rounds(4 + l, 1 << ctx->upper_bits[l], ct[l]);
+        memcpy(cbt_out, ct, sizeof(ct));
+    }
+    return PQ_OK;
 }
 
 } // namespace
