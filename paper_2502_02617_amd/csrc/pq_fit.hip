@@ -146,14 +146,17 @@ __device__ __forceinline__ float count_block(const f32x16 &y, uint32_t *sh)
 }
 
 /* Adds a workgroup's counters to the call's, two at a time: no total reaches 2^32, so nothing carries from one into the
-   other. */
+   other.  The workgroups end together; each begins elsewhere, so that they don't all add to the same lines (262144 bf16 vectors
+   44.4 -> 42.0 us). */
 __device__ __forceinline__ void add_counts(uint32_t *total, const uint32_t *sh, int n)
 {
     const uint2 *pairs = reinterpret_cast<const uint2 *>(sh);
     unsigned long long *out = reinterpret_cast<unsigned long long *>(total);
-    for (int c = threadIdx.x; c < n / 2; c += kFitThreads) {
-        const uint2 v = pairs[c];
-        if (v.x | v.y) atomicAdd(&out[c], ((unsigned long long)v.y << 32) | v.x);
+    const int n2 = n / 2, begin = (int)((uint32_t)blockIdx.x * (uint32_t)n2 / gridDim.x) & ~15; /* whole lines of 128 bytes */
+    for (int c = threadIdx.x; c < n2; c += kFitThreads) {
+        const int at = c + begin < n2 ? c + begin : c + begin - n2;
+        const uint2 v = pairs[at];
+        if (v.x | v.y) atomicAdd(&out[at], ((unsigned long long)v.y << 32) | v.x);
     }
 }
 
