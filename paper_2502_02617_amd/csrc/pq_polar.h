@@ -274,6 +274,14 @@ __device__ __forceinline__ void pql_put_block(uint32_t *tile_dwords, int kind, i
     }
 }
 
+/* x of the lane that the DPP control names, inside rows of sixteen lanes */
+template <int CTRL, class T>
+__device__ __forceinline__ T pq_dpp(T x)
+{
+    static_assert(sizeof(T) == 4, "a register");
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+
 /* NV (sequence, head) vectors of kind `kind`, vec0 .. vec0 + NV - 1 as far as they are below n_vec, by one workgroup of
  * 512 threads: the 64 KB of S are fetched once for the NV products, then wavefront r runs the recursion of vector r.
  * Per vector the operations and their order do not depend on NV. */
@@ -290,6 +298,11 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
     const int vec = min(vec0 + min(wv, NV - 1), n_vec - 1);
     const int seq = vec / a.n_heads, head = vec % a.n_heads;
     const int64_t dst = a.dst_token[seq];
+    /* the constants as well come with the first trip to memory (and siblings by DPP below: one sequence's decode step
+       16.05 -> 15.8 us) */
+    const float radius_scale = a.had.on ? PQ_INV_SQRT_D : 1.0f;
+    const Thresholds th = load_thresholds(*a.consts, radius_scale);
+    const bool deep = a.consts->depth == 7, general = a.consts->general != 0;
     for (int t = tid; t < NV * PQ_D; t += 512) {
         const int64_t at = (int64_t)min(vec0 + (t >> 7), n_vec - 1) * PQ_D + (t & 127);
         if (XT == PQ_BF16) sx[t >> 7][t & 127] = __uint_as_float((uint32_t)static_cast<const uint16_t *>(a.x)[at] << 16);
@@ -298,7 +311,6 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
     __syncthreads();
     /* y_j = sum_i x_i S[i][j].  Hadamard S: the transform of D x, left unscaled -- the angles do not see the
        common factor 1/sqrt(128), which goes into the radius (as in the encode kernel's one-term product) */
-    float radius_scale = 1.0f;
     if (a.had.on) {
         if (wv < NV) {
             float lo = sx[wv][lane] * pq_hadamard_sign(a.had, lane), hi = sx[wv][lane + 64] * pq_hadamard_sign(a.had, lane + 64);
@@ -306,7 +318,6 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
             sy[wv][lane] = lo;
             sy[wv][lane + 64] = hi;
         }
-        radius_scale = PQ_INV_SQRT_D;
     } else {
         const int kq = tid >> 7, j = tid & 127;
         float acc[NV];
@@ -326,7 +337,6 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
     }
     __syncthreads();
     __shared__ float sq4[NV][8];
-    const bool deep = a.consts->depth == 7;
     /* a vector beyond the range or a slot outside the pool: nothing is written */
     const bool write = wv < NV && vec0 + wv < n_vec && dst >= 0 && dst < a.pool_tokens;
     const int64_t tile = dst >> 6;
@@ -334,13 +344,12 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
     if (write) {
         /* The wavefront runs the recursion with one lane per level-1 pair: lane p holds pair p & 7
            of block p >> 3; the nodes of the upper levels sit in the lanes of their first leaf and fetch
-           the sibling's squared radius with a shuffle (the other lanes compute along and are ignored).
+           the sibling's squared radius by DPP (the other lanes of a node compute the same along).
            Operations and operand order per node are those of polar_quant_block. */
         const int p = lane, i = p & 7, b = p >> 3;
-        const Thresholds th = load_thresholds(*a.consts, radius_scale);
         const float ya = sy[wv][2 * p], yb = sy[wv][2 * p + 1];
         uint32_t code1;
-        if (a.consts->general) { /* the level-1 table is read from the constants in global memory */
+        if (general) { /* the level-1 table is read from the constants in global memory */
             code1 = level1_code_general(ya, yb, th.lut1);
         } else {
             const uint32_t mq = quant3(fabsf(ya), fabsf(yb), th.t1a, th.t1c);
@@ -349,15 +358,15 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
             code1 = (mq ^ f7) | ((bb >> 28) & 8u);
         }
         const float q1 = __builtin_fmaf(ya, ya, yb * yb);
-        const float q1s = __shfl_xor(q1, 1);
-        const uint32_t c2 = a.consts->general ? quant3g(q1, q1s, th.t2a, th.t2b, th.t2c) : quant3(q1, q1s, th.t2a, th.t2c);
+        const float q1s = pq_dpp<0xB1>(q1); /* lane ^ 1 */
+        const uint32_t c2 = general ? quant3g(q1, q1s, th.t2a, th.t2b, th.t2c) : quant3(q1, q1s, th.t2a, th.t2c);
         const float q2 = q1 + q1s;
-        const float q2s = __shfl_xor(q2, 2);
-        const uint32_t c3 = a.consts->general ? quant3g(q2, q2s, th.t3a, th.t3b, th.t3c) : quant3(q2, q2s, th.t3a, th.t3c);
+        const float q2s = pq_dpp<0x4E>(q2); /* lane ^ 2 */
+        const uint32_t c3 = general ? quant3g(q2, q2s, th.t3a, th.t3b, th.t3c) : quant3(q2, q2s, th.t3a, th.t3c);
         const float q3 = q2 + q2s;
-        const float q3s = __shfl_xor(q3, 4);
+        const float q3s = pq_dpp<0x141>(q3); /* lane 7 - i of eight: any lane of the other quad */
         PqBlockFields bc;
-        bc.c4 = a.consts->general ? quant3g(q3, q3s, th.t4a, th.t4b, th.t4c) : quant3(q3, q3s, th.t4a, th.t4c);
+        bc.c4 = general ? quant3g(q3, q3s, th.t4a, th.t4b, th.t4c) : quant3(q3, q3s, th.t4a, th.t4c);
         const float q4 = q3 + q3s;
         const _Float16 rh = (_Float16)pq_saturate_radius(__builtin_amdgcn_sqrtf(q4) * th.radius_scale); /* round to nearest even */
         bc.radius = __builtin_bit_cast(uint16_t, rh);
@@ -365,11 +374,9 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
            groups [c2(2h) | c3(h) | c2(2h+1)] of half-block h at bits [8h, 8h+6) of a second word */
         uint32_t l1 = code1 << (4 * i);
         uint32_t gw = (i & 1) ? 0u : ((i & 2) ? c2 : ((c2 << 4) | (c3 << 2))) << (2 * (i & 4));
-#pragma unroll
-        for (int d = 1; d < 8; d <<= 1) {
-            l1 |= __shfl_xor(l1, d);
-            gw |= __shfl_xor(gw, d);
-        }
+        l1 |= pq_dpp<0xB1>(l1); gw |= pq_dpp<0xB1>(gw);
+        l1 |= pq_dpp<0x4E>(l1); gw |= pq_dpp<0x4E>(gw);
+        l1 |= pq_dpp<0x141>(l1); gw |= pq_dpp<0x141>(gw);
         bc.l1 = l1;
         bc.g6[0] = gw & 63u;
         bc.g6[1] = (gw >> 8) & 63u;
