@@ -192,7 +192,7 @@ __device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, fl
  * for keys, 35 for values; to fp32 243 -> 48 and 51.  Every register counts: with what follows from the lane number kept
  * over the loop, up to 11 spilled registers cost values 39.5 us (fp32 57; Hadamard 34 against 28 now), and requesting the
  * next half tile ahead of the products in registers spills more than it hides (45).  AHEAD: it is requested to LDS, which takes none; it
- * travels under the rebuild of this half tile, the fence ahead of the products waits for it.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
+ * travels under the rebuild and the products of this half tile.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
  * spill 100 registers; value slots are read from an image in LDS because a token's 16 slots are spread over 16 strings. */
 template <int KIND, int OT, bool UNIT, bool AHEAD>
 __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs a)
@@ -215,7 +215,10 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
         dq_request_tile(img[wave], a.codes + at * PQL_CODE_BYTES, a.radii + at * radii_halves, 2 * radii_halves, lane);
     };
     int64_t item = (int64_t)wave * gridDim.x + blockIdx.x;
-    if (AHEAD && item < a.n_items) request(item, dq_lane()); /* under way while S is staged */
+    /* The wavefront's first tile is under way to LDS while S is staged (without, values to bf16: 32768 tokens of 8 heads 34.8
+       instead of 34.3 us, 12000 of 4 12.4 instead of 11.7). */
+    bool requested = KIND == PQ_VALUE || AHEAD;
+    if (requested && item < a.n_items) request(item, dq_lane());
     {
         /* chunk (grp, par, ks, lane): S[64 grp + 2 (lane & 31) + par][64 (lane >> 5) + 8 ks .. + 7], the k order of the
            tokens' operand below.  A wavefront fetches eight rows of one parity, 128 bytes each: whole lines, and 32 LDS banks
@@ -266,7 +269,11 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
         const int64_t full_tile = item >> 1, head = full_tile / a.n_tiles, tile = a.first_tile + (full_tile - head * a.n_tiles);
         const int half = (int)(item & 1), tau = 32 * half + j;
         const int64_t row0 = tile * 64 + 32 * half - a.token0; /* output row of the half tile's first slot */
-        if (!AHEAD && (row0 + 32 <= 0 || row0 >= a.n_tokens)) continue;
+        if (!AHEAD && (row0 + 32 <= 0 || row0 >= a.n_tokens)) {
+            if (requested) asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); /* nothing writes to LDS behind the wavefront's back */
+            requested = false;
+            continue;
+        }
         TokenHalf t;
         const uint8_t *tc = a.codes + (head * a.pool_tiles + tile) * PQL_CODE_BYTES;
         const uint16_t *tr = a.radii + (head * a.pool_tiles + tile) * radii_halves;
@@ -275,10 +282,14 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
             tc = reinterpret_cast<const uint8_t *>(img[wave]);
             tr = reinterpret_cast<const uint16_t *>(tc + PQL_CODE_BYTES);
         } else if constexpr (KIND == PQ_VALUE) {
-            uint4 *im = reinterpret_cast<uint4 *>(img[wave]);
-            for (int c = lane; c < PQL_CODE_BYTES / 16; c += 64) im[c] = reinterpret_cast<const uint4 *>(tc)[c];
-            if (!a.deep) im[PQL_CODE_BYTES / 16 + lane] = reinterpret_cast<const uint4 *>(tr)[lane];
-            dq_own_order();
+            if (!requested) {
+                uint4 *im = reinterpret_cast<uint4 *>(img[wave]);
+                for (int c = lane; c < PQL_CODE_BYTES / 16; c += 64) im[c] = reinterpret_cast<const uint4 *>(tc)[c];
+                if (!a.deep) im[PQL_CODE_BYTES / 16 + lane] = reinterpret_cast<const uint4 *>(tr)[lane];
+                dq_own_order();
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); /* a requested tile is in LDS */
+            requested = false;
         }
         if (KIND == PQ_KEY) dq_read_key(t, tc, tr, tau, H, a.deep != 0);
         else dq_read_value(t, img[wave], tau, H, a.deep != 0);
