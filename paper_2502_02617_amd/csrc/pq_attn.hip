@@ -72,21 +72,21 @@ constexpr float kRefSlack = 6.0f;
  * time, a 16-byte gather 16 lanes at a time, so the small tables are replicated into one column per lane (mod 32,
  * mod 16) -- entry e of lane l at row e, column l -- and their gathers never collide (2.4 instead of 4.1 cycles
  * per 4-byte gather from 64 entries, 4.6 instead of 10.4 per 16-byte gather).
- *   kTQ   [1024][2]       quarter table, by Q (8 KB, gathered as it is: 32 columns of it would be 256 KB)
- *   kTQA  [64][32]        first pair of a quarter, by Q & 63 = c2 << 4 | c1
- *   kTQB  [64][32]        second pair, by Q >> 4 = c1' << 2 | c2
- *   kTBF  [64][16][4]     block table of the keys, by B: fp32; wide: two binary16 terms, the four first ones in front
- *   kTBH  [64][32]        block table of the values: column l holds the binary16 pair of half-block l & 1
- *   kTUp  [3][8][2]       levels 5..7 (full depth) */
-constexpr int kTQ = 0, kTQA = 2048, kTQB = 4096, kTBF = 6144, kTBH = 10240, kTUp = 12288, kLdsTabDwords = 12336;
-/* how a quarter's table entry is fetched: as one 8-byte gather from kTQ (bank conflicts, but one index), or as
-   two conflict-free 4-byte gathers from the pair tables (two indices) */
-#ifndef PQ_KEY_PAIRS
-#define PQ_KEY_PAIRS 1
-#endif
-#ifndef PQ_VALUE_PAIRS
-#define PQ_VALUE_PAIRS 0
-#endif
+ *   kTBF  [64][16][4]        block table of the keys, by B: fp32; wide: two binary16 terms, the four first ones in front
+ *   kTBH  [64][32]           block table of the values: column l holds the binary16 pair of half-block l & 1
+ *   kTUp  [3][8][2]          levels 5..7 (full depth)
+ *   kTQ   [1024][COPIES][2]  quarter table, by Q: 32 columns of it would be 256 KB.  Lane l reads copy l mod COPIES: of 32 lanes four
+ *                            then choose among four bank pairs, instead of all among 32 with one copy.
+ * Eight copies make a quarter one gather and one index for keys and values alike.  With one copy the values' gathers kept the LDS busy
+ * with conflicts, and the keys fetched a quarter's two pairs from two 64-entry tables, two indices for them: steps of 16 x 32768
+ * tokens 115.8 us, now 113.4, 64 sequences of 1k-64k 482 and 467, depth 7 16 x 14200 67.0 and 65.0; eight heads, 16 x 35000, 150.4
+ * and 144.8 (four copies 116.4, -, 69.1, 145.2).  They take 0.3 us longer to lay out than four: see launch_partial_depth.  The wide form is
+ * bound by vector instructions and has no gain from copies, whose index takes a three-operand instruction (draft tokens
+ * 74.9 us, 75.2 with eight): one copy, and the tables where its code is the shorter by four registers. */
+template <int COPIES> struct Tab {
+    static constexpr int kTBF = COPIES == 1 ? 6144 : 0, kTBH = kTBF + 4096, kTUp = kTBF + 6144, kTQ = COPIES == 1 ? 0 : 6192;
+    static constexpr int kDwords = COPIES == 1 ? 12336 : 6192 + 2048 * COPIES;
+};
 
 struct AttnArgs {
     const uint16_t *qrot; /* [B][M][Hq][128] binary16: rotated, pre-scaled q' */
@@ -173,19 +173,16 @@ __device__ __forceinline__ uint32_t table_offset(const uint32_t *w, uint32_t col
     return (v & mask) | column; /* column: the lane's byte offset inside a row of a table with a column per lane */
 }
 
-/* The four binary16 values of a quarter from the 10-bit index stored at bit BIT of the string w: either entry Q of
- * the quarter table, or entries Q & 63 and Q >> 4 of the two pair tables (col4 = 4 * (lane & 31)). */
-template <int BIT, bool PAIRS>
-__device__ __forceinline__ uint2 quarter_entry(const uint32_t *tab, const uint32_t *w, uint32_t col4)
+/* The four binary16 values of a quarter from the 10-bit index stored at bit BIT of the string w, out of the lane's copy of
+ * the quarter table (column = quarter_column). */
+template <int COPIES> __device__ __forceinline__ uint32_t quarter_column(int lane) { return (uint32_t)(lane & (COPIES - 1)) * 8u; }
+
+template <int BIT, int COPIES>
+__device__ __forceinline__ uint2 quarter_entry(const uint32_t *tab, const uint32_t *w, uint32_t column)
 {
-    if constexpr (PAIRS) {
-        const uint32_t oa = table_offset<BIT, 6, 7>(w, col4), ob = table_offset<BIT + 4, 6, 7>(w, col4);
-        return make_uint2(*reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(tab + kTQA) + oa),
-                          *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(tab + kTQB) + ob));
-    } else {
-        const uint32_t o = table_offset<BIT, 10, 3>(w);
-        return *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(tab + kTQ) + o);
-    }
+    static_assert(COPIES == 1 || COPIES == 4 || COPIES == 8, "a power of two");
+    const uint32_t o = table_offset<BIT, 10, COPIES == 8 ? 6 : (COPIES == 4 ? 5 : 3)>(w, column);
+    return *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(tab + Tab<COPIES>::kTQ) + o);
 }
 
 /* Raw registers of a key tile: lane tau holds token tau -- its 46 code bytes (12 dwords, the last one
@@ -342,9 +339,9 @@ struct DeepRadii {
     int b5, b6, b7;
 };
 
-__device__ __forceinline__ void stage_deep_value_radii(const uint32_t *tab, const DeepRadii &dr, uint32_t vtop, int lane)
+__device__ __forceinline__ void stage_deep_value_radii(const uint32_t *upper, const DeepRadii &dr, uint32_t vtop, int lane)
 {
-    const float2 *cs = reinterpret_cast<const float2 *>(tab + kTUp);
+    const float2 *cs = reinterpret_cast<const float2 *>(upper);
     float r[8];
     pq_deep_block_radii(vtop, dr.b5, dr.b6, dr.b7, cs, r);
     const int i = lane >> 4, g = (lane >> 2) & 3, e = lane & 3;
@@ -401,31 +398,31 @@ template <int NG> struct QueryOperand { H4 a[NG][2]; };
  * head) pairs per group; each is scaled in fp32
  * by r_b T43[B_b][j] and summed.  A key element is therefore never rounded beyond its table entry.
  * s comes in holding the negated exponent reference (the first product of a tile adds to it). */
-template <int NG, bool DEEP>
+template <int NG, bool DEEP, int COPIES>
 __device__ __forceinline__ void key_scores(const uint32_t *tab, const KTileRaw &k, const QueryOperand<NG> &qo,
                                            float (&s)[4 * NG], const DeepRadii &dr, int lane)
 {
     const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
     float rb[8];
     if (DEEP) {
-        pq_deep_block_radii(k.top, dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + kTUp), rb);
+        pq_deep_block_radii(k.top, dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + Tab<COPIES>::kTUp), rb);
     } else {
         rb[0] = half_lo_to_float(k.rad.x); rb[1] = half_hi_to_float(k.rad.x);
         rb[2] = half_lo_to_float(k.rad.y); rb[3] = half_hi_to_float(k.rad.y);
         rb[4] = half_lo_to_float(k.rad.z); rb[5] = half_hi_to_float(k.rad.z);
         rb[6] = half_lo_to_float(k.rad.w); rb[7] = half_hi_to_float(k.rad.w);
     }
-    const uint32_t col4 = (uint32_t)(lane & 31) * 4u, col16 = (uint32_t)(lane & 15) * 16u;
+    const uint32_t colq = quarter_column<COPIES>(lane), col16 = (uint32_t)(lane & 15) * 16u;
     auto block = [&](auto bc) {
         constexpr int b = decltype(bc)::value;
         const uint32_t boff = table_offset<PQL_BLOCK_BITS * b + 40, 6, 8>(k.w, col16);
-        const float4 t43 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(tab + kTBF) + boff);
+        const float4 t43 = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(tab + Tab<COPIES>::kTBF) + boff);
         const float rq[4] = {rb[b] * t43.x, rb[b] * t43.y, rb[b] * t43.z, rb[b] * t43.w};
         H4 kq[4];
-        kq[0].d = quarter_entry<PQL_BLOCK_BITS * b + 0, PQ_KEY_PAIRS != 0>(tab, k.w, col4);
-        kq[1].d = quarter_entry<PQL_BLOCK_BITS * b + 10, PQ_KEY_PAIRS != 0>(tab, k.w, col4);
-        kq[2].d = quarter_entry<PQL_BLOCK_BITS * b + 20, PQ_KEY_PAIRS != 0>(tab, k.w, col4);
-        kq[3].d = quarter_entry<PQL_BLOCK_BITS * b + 30, PQ_KEY_PAIRS != 0>(tab, k.w, col4);
+        kq[0].d = quarter_entry<PQL_BLOCK_BITS * b + 0, COPIES>(tab, k.w, colq);
+        kq[1].d = quarter_entry<PQL_BLOCK_BITS * b + 10, COPIES>(tab, k.w, colq);
+        kq[2].d = quarter_entry<PQL_BLOCK_BITS * b + 20, COPIES>(tab, k.w, colq);
+        kq[3].d = quarter_entry<PQL_BLOCK_BITS * b + 30, COPIES>(tab, k.w, colq);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             constexpr int set = b >> 2;         /* quarters 0..15 | 16..31 */
@@ -505,11 +502,11 @@ __device__ __forceinline__ TileScale key_scale(const uint32_t *radii, int nv, in
  * brought to bit 0, so that every field sits at a fixed position. */
 struct WideQuery { H8 q[4]; /* lane (g, n): coordinates 32 g + 8 c .. + 7 of pair n */ };
 
-template <bool DEEP>
+template <bool DEEP, int COPIES>
 __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t *kt, const WideQuery &wq, float start, f4 (&s)[4],
                                             const DeepRadii &dr, int nv, int lane)
 {
-    const uint32_t n = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4, col16 = n * 16u;
+    const uint32_t n = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4, col16 = n * 16u, colq = quarter_column<COPIES>(lane);
     const char *base = reinterpret_cast<const char *>(kt);
     const TileScale scale = key_scale<DEEP>(kt + kKeyRadii, nv, lane);
     /* string dwords 0 .. 3 | 2 .. 5 | 5 .. 8 | 8 .. 11 of the token: where the first two, the third and the fourth lie for n = 0, and
@@ -525,7 +522,7 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
     const uint32_t sh = 0u - 4u * g /* mod 32 */, sh3 = ((g + 1u) >> 2 & n) * 16u; /* g = 3: the half dword of an odd token */
     if (DEEP) { /* lane tau rebuilds the radii of token tau's blocks and leaves them, scaled, as two binary16 terms each */
         float r[8];
-        pq_deep_block_radii(kt[kKeyRadii + lane], dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + kTUp), r);
+        pq_deep_block_radii(kt[kKeyRadii + lane], dr.b5, dr.b6, dr.b7, reinterpret_cast<const float2 *>(tab + Tab<COPIES>::kTUp), r);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const float x = r[b] * scale.by;
@@ -550,7 +547,7 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
             constexpr int b = decltype(bc)::value, at = PQL_BLOCK_BITS * b;
             const H8 t43 = [&] {
                 H8 t;
-                t.q = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(tab + kTBF) + table_offset<at + 40, 6, 8>(x, col16));
+                t.q = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(tab + Tab<COPIES>::kTBF) + table_offset<at + 40, 6, 8>(x, col16));
                 return t;
             }(); /* quarters 0, 1 | 2, 3, then their second terms */
             const h2 rr = b && !DEEP ? bcast_hi(ra) : bcast_lo(b ? rb : ra), rrl = bcast_hi(b ? rb : ra);
@@ -560,8 +557,8 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
                 h2 pl = __builtin_elementwise_fma(rr, t43.p[2 + h], __builtin_elementwise_fma(rr, t43.p[h], -ph));
                 if (DEEP) pl = __builtin_elementwise_fma(rrl, t43.p[h], pl);
                 H4 ta, tb;
-                ta.d = quarter_entry<at + 20 * h, false>(tab, x, 0u);
-                tb.d = quarter_entry<at + 20 * h + 10, false>(tab, x, 0u);
+                ta.d = quarter_entry<at + 20 * h, COPIES>(tab, x, colq);
+                tb.d = quarter_entry<at + 20 * h + 10, COPIES>(tab, x, colq);
                 H8 hi, lo;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -588,7 +585,7 @@ __device__ __forceinline__ void wide_scores(const uint32_t *tab, const uint32_t 
  * entry of this half (one packed product: the two quarter radii), times the two quarter entries T21[Q]
  * (four packed products).  MASKED zeroes the radii of slots beyond the sequence's context so that stale
  * cache bytes there cannot reach the sum. */
-template <int i, bool MASKED, bool DEEP>
+template <int i, bool MASKED, bool DEEP, int COPIES>
 __device__ __forceinline__ void value_operand(const uint32_t *tab, const char *tbh /* block table of the values */,
                                               const VTileRaw &v, H8 (&va)[4], int n_valid, int g, const DeepRadii &dr,
                                               int lane)
@@ -603,7 +600,7 @@ __device__ __forceinline__ void value_operand(const uint32_t *tab, const char *t
         rpair[1] = sel4(rq, 2 * (i & 1) + 1);
     }
     h2 ve[4][4]; /* [token e][pair c] */
-    const uint32_t col4 = (uint32_t)(lane & 31) * 4u;
+    const uint32_t col4 = (uint32_t)(lane & 31) * 4u, colq = quarter_column<COPIES>(lane);
     auto token = [&](auto ec) {
         constexpr int e = decltype(ec)::value, s = 4 * i + e;
         const h2 rad = as_h2(rpair[e >> 1]);
@@ -613,8 +610,8 @@ __device__ __forceinline__ void value_operand(const uint32_t *tab, const char *t
         }
         const uint32_t boff = table_offset<6 * s, 6, 7>(v.b, col4);
         const h2 t43 = as_h2(*reinterpret_cast<const uint32_t *>(tbh + boff));
-        const uint2 ta = quarter_entry<PQL_SLOT_BITS * s, PQ_VALUE_PAIRS != 0>(tab, v.q, col4);
-        const uint2 tb = quarter_entry<PQL_SLOT_BITS * s + 10, PQ_VALUE_PAIRS != 0>(tab, v.q, col4);
+        const uint2 ta = quarter_entry<PQL_SLOT_BITS * s, COPIES>(tab, v.q, colq);
+        const uint2 tb = quarter_entry<PQL_SLOT_BITS * s + 10, COPIES>(tab, v.q, colq);
         const h2 rq = r * t43; /* radii of the half-block's two quarters */
         const h2 ra = bcast_lo(rq), rbq = bcast_hi(rq);
         ve[e][0] = ra * as_h2(ta.x);
@@ -661,11 +658,12 @@ __device__ __forceinline__ float wave_max_f(float x)
  * wide; at depth 7 108 and 81.  Five to eight pairs: wide_tiles.  Key tiles that went to LDS ahead of
  * their use made four pairs slower (35.1 -> 36.7 us for 32 short sequences, 112.6 -> 114.9 at 65536 tiles: the LDS is as busy as the vector
  * ALU there). */
-template <int NG, int WAVES_PER_SIMD, bool DEEP>
+template <int NG, int WAVES_PER_SIMD, bool DEEP, int COPIES>
 __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_kernel(AttnArgs a)
 {
     constexpr int kWavesPerBlock = 4 * WAVES_PER_SIMD, kThreads = kWavesPerBlock * 64;
     constexpr bool WIDE = NG == 0;
+    typedef Tab<COPIES> T;
     /* wide: loads without branches (request_k_tile): sixteen sequences of 12700 tokens and sixteen pairs 76.4 -> 75.4 us, 87.4 -> 81 at depth
        7.  At depth 4 three wavefronts per SIMD cover the waits and have no gain from it, and 64 sequences of 2000 tokens, two or three
        tiles per piece, take 66.3 instead of 63.7 us. */
@@ -675,11 +673,11 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
     const int G = a.Hq / a.Hkv; /* query heads per kv head: only the set-up and the epilogue of a piece depend on it */
     /* One block, the tables first: the offset of a table inside LDS then fits a gather's 16-bit immediate. */
     struct Lds {
-        __attribute__((aligned(16))) uint32_t tab[kLdsTabDwords];
+        __attribute__((aligned(16))) uint32_t tab[T::kDwords];
         __attribute__((aligned(16))) uint32_t p[WIDE ? 1 : kWavesPerBlock][kCols][64];
     };
     __shared__ Lds lds;
-    uint32_t (&tab)[kLdsTabDwords] = lds.tab;
+    uint32_t (&tab)[T::kDwords] = lds.tab;
     /* narrow: probabilities of a tile, sP[wave][column = pair + kPairs * parity][token] as dwords; a parity-0 column
        keeps its binary16 value in the low half, a parity-1 column in the high half, and the other halves stay
        zero from the start of the kernel (nothing ever writes them) */
@@ -713,16 +711,23 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
            entry. */
         const uint32_t *src = a.consts->attn_tab;
         constexpr int kR2 = (2048 + kThreads - 1) / kThreads, kR4 = (4096 + kThreads - 1) / kThreads;
-        uint32_t tq[kR2], tqa[kR2], tqb[kR2], tbh[kR2], tbf[kR4], tup = 0;
+        constexpr int kQuads = 1024 * COPIES / 2, kRQ = (kQuads + kThreads - 1) / kThreads; /* sixteen bytes: an entry twice, or two */
+        uint32_t tbh[kR2], tbf[kR4], tup = 0;
+        uint4 tq[kRQ];
 #pragma unroll
         for (int i = 0; i < kR2; ++i) {
             const int t = min((int)threadIdx.x + i * kThreads, 2047); /* entry t >> 5, column t & 31 */
-            tq[i] = src[PQ_TAB_TQ + t];
-            if (!WIDE) {
-                tqa[i] = src[PQ_TAB_TQA + (t >> 5)];
-                tqb[i] = src[PQ_TAB_TQB + (t >> 5)];
-            }
             tbh[i] = src[PQ_TAB_TBH + 2 * (t >> 5) + (t & 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < kRQ; ++i) {
+            const int t = min((int)threadIdx.x + i * kThreads, kQuads - 1);
+            if (COPIES == 1) {
+                tq[i] = reinterpret_cast<const uint4 *>(src + PQ_TAB_TQ)[t];
+            } else {
+                const uint2 e = reinterpret_cast<const uint2 *>(src + PQ_TAB_TQ)[2 * t / COPIES];
+                tq[i] = make_uint4(e.x, e.y, e.x, e.y);
+            }
         }
 #pragma unroll
         for (int i = 0; i < kR4; ++i) {
@@ -746,21 +751,19 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
 #pragma unroll
         for (int i = 0; i < kR2; ++i) {
             const int t = (int)threadIdx.x + i * kThreads;
-            if (t < 2048) {
-                tab[kTQ + t] = tq[i];
-                if (!WIDE) {
-                    tab[kTQA + t] = tqa[i];
-                    tab[kTQB + t] = tqb[i];
-                }
-                tab[kTBH + t] = tbh[i];
-            }
+            if (t < 2048) tab[T::kTBH + t] = tbh[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kRQ; ++i) {
+            const int t = (int)threadIdx.x + i * kThreads;
+            if (t < kQuads) reinterpret_cast<uint4 *>(tab + T::kTQ)[t] = tq[i];
         }
 #pragma unroll
         for (int i = 0; i < kR4; ++i) {
             const int t = (int)threadIdx.x + i * kThreads;
-            if (t < 4096) tab[kTBF + t] = tbf[i];
+            if (t < 4096) tab[T::kTBF + t] = tbf[i];
         }
-        if (threadIdx.x < 48) tab[kTUp + threadIdx.x] = tup;
+        if (threadIdx.x < 48) tab[T::kTUp + threadIdx.x] = tup;
     }
     if (staged && threadIdx.x >= kStager) {
         const int bb = (int)threadIdx.x - kStager;
@@ -830,7 +833,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
     const int g = lane >> 4, n = lane & 15;
     constexpr int kRadiiHalves = DEEP ? PQ_DEEP_RADII_HALVES : PQL_RADII;
     const DeepRadii dr{sVrad[DEEP ? wave : 0], sKrad[WIDE && DEEP ? wave : 0], a.up_b5, a.up_b6, a.up_b7};
-    const char *tbh = reinterpret_cast<const char *>(tab + kTBH);
+    const char *tbh = reinterpret_cast<const char *>(tab + T::kTBH);
     /* where this lane (token) leaves its probabilities and where it (column) picks its operand up */
     uint32_t *p_mine = &sP[WIDE ? 0 : wave][0][lane];
     const uint32_t *p_col = &sP[WIDE ? 0 : wave][n & (kCols - 1)][4 * g];
@@ -911,7 +914,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                 float s[kPairs];
 #pragma unroll
                 for (int h = 0; h < kPairs; ++h) s[h] = kProbShift - m_ref[h];
-                key_scores<NG, DEEP>(tab, kraw, qo, s, dr, lane); /* s = score - m_ref + kProbShift */
+                key_scores<NG, DEEP, COPIES>(tab, kraw, qo, s, dr, lane); /* s = score - m_ref + kProbShift */
                 if (MASKED) {
 #pragma unroll
                     for (int h = 0; h < kPairs; ++h)
@@ -953,12 +956,12 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                     dst[2 * (h * 64)] = ph[h];                 /* column (pair, parity 0): low half */
                     dst[2 * ((kPairs + h) * 64) + 1] = ph[h];       /* column (pair, parity 1): high half */
                 }
-                if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
+                if (DEEP) stage_deep_value_radii(tab + T::kTUp, dr, vraw.top, lane);
                 wave_lds_fence();
                 auto pass = [&](auto ic) {
                     constexpr int i = decltype(ic)::value;
                     H8 va[4];
-                    value_operand<i, MASKED, DEEP>(tab, tbh, vraw, va, nv, g, dr, lane);
+                    value_operand<i, MASKED, DEEP, COPIES>(tab, tbh, vraw, va, nv, g, dr, lane);
                     H8 pb;
                     pb.q = *reinterpret_cast<const uint4 *>(p_col + 16 * i);
 #pragma unroll
@@ -972,9 +975,9 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                 f4 s[4]; /* lane (g, n): pair n, tokens 16 i + 4 g + e */
                 int lane_k = lane;
                 asm volatile("" : "+v"(lane_k));
-                wide_scores<DEEP>(tab, sK[wave], qo, kProbShift - m_ref[0], s, dr, MASKED ? nv : 64, lane_k);
+                wide_scores<DEEP, COPIES>(tab, sK[wave], qo, kProbShift - m_ref[0], s, dr, MASKED ? nv : 64, lane_k);
                 /* ahead of the request: behind it the compiler waits for that, it takes both for writes to the same memory */
-                if (DEEP) stage_deep_value_radii(tab, dr, vraw.top, lane);
+                if (DEEP) stage_deep_value_radii(tab + T::kTUp, dr, vraw.top, lane);
                 /* the next tile's keys, once every read of this one's has returned */
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 if (kInFlight || next < tile_hi) request_k_tile<DEEP>(sK[wave], kc, kr, min(next, tile_hi - 1), lane);
@@ -1019,7 +1022,7 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
                     auto transposed = [&](auto kc) {
                         constexpr int k = decltype(kc)::value;
                         H8 va[4];
-                        value_operand<i + k, MASKED, DEEP>(tab, tbh, vraw, va, nv, g, dr, lane);
+                        value_operand<i + k, MASKED, DEEP, COPIES>(tab, tbh, vraw, va, nv, g, dr, lane);
 #pragma unroll
                         for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -1767,10 +1770,13 @@ void launch_partial_depth(int pairs, int slots, dim3 grid, hipStream_t s, const 
 {
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3((unsigned)(4 * waves_per_simd(pairs) * 64)), 0, s, aa); };
     const int64_t most_tiles = (int64_t)aa.B * aa.Hkv * ((aa.max_ctx + 63) / 64);
-    if (pairs <= 4) launch(pq_attn_partial_kernel<1, 4, DEEP>);
-    else if (pairs > 8) launch(pq_attn_partial_kernel<0, 2, DEEP>);
-    else if (most_tiles <= (int64_t)wide_tiles<DEEP>() * slots) launch(pq_attn_partial_kernel<0, 3, DEEP>);
-    else launch(pq_attn_partial_kernel<2, 3, DEEP>);
+    /* Up to two tiles per wavefront of the largest context the shorter start counts more than the gathers (copies of the quarter table, four
+       against eight, us: one sequence of 1000 tokens 15.8 / 16.1, two of 2000 16.9 / 17.3; 32 of 200 to 4096, four tiles at most, 35.0 / 34.9). */
+    if (pairs <= 4 && most_tiles <= 2 * (int64_t)slots) launch(pq_attn_partial_kernel<1, 4, DEEP, 4>);
+    else if (pairs <= 4) launch(pq_attn_partial_kernel<1, 4, DEEP, 8>);
+    else if (pairs > 8) launch(pq_attn_partial_kernel<0, 2, DEEP, 1>);
+    else if (most_tiles <= (int64_t)wide_tiles<DEEP>() * slots) launch(pq_attn_partial_kernel<0, 3, DEEP, 1>);
+    else launch(pq_attn_partial_kernel<2, 3, DEEP, 8>);
 }
 
 template <int ROWS>

@@ -17,17 +17,15 @@
  * over a column per lane when it copies them into LDS.
  *   TQ  [1024][2]: quarter table, by the stored quarter index Q = c1' << 6 | c2 << 4 | c1: the four binary16 products
  *                  (cos t2 cos t1, cos t2 sin t1, sin t2 cos t1', sin t2 sin t1') -- the level-2 x level-1 part of
- *                  the four coordinates of a quarter.  Values multiply an entry by the quarter's radius.
- *   TQA [64]:      its first pair alone, by Q & 63 = c2 << 4 | c1; TQB [64]: its second pair, by Q >> 4 = c1' << 2 | c2.
- *                  Keys fetch the two and use them as a matrix-core operand as they are.
+ *                  the four coordinates of a quarter.  Values multiply an entry by the quarter's radius; keys use it
+ *                  as a matrix-core operand as it is.
  *   TBF [64][4]:   block table for the keys, by the stored block index B = c4 << 4 | c3 << 2 | c3': the four fp32
  *                  products (cos t4 cos t3, cos t4 sin t3, sin t4 cos t3', sin t4 sin t3') -- what the block radius
  *                  is multiplied by to give the radii of its four quarters.
  *   TBH [64][2]:   the same as binary16 pairs for the values: dword 0 the first half-block's two, dword 1 the second's.
  *   UP  [3][8][2]: full-depth recursion: fp32 (cos, sin) of the centroids of levels 5, 6, 7. */
 enum {
-    PQ_TAB_TQ = 0, PQ_TAB_TQA = 2048, PQ_TAB_TQB = 2112, PQ_TAB_TBF = 2176, PQ_TAB_TBH = 2432, PQ_TAB_UP = 2560,
-    PQ_TAB_DWORDS = 2608
+    PQ_TAB_TQ = 0, PQ_TAB_TBF = 2048, PQ_TAB_TBH = 2304, PQ_TAB_UP = 2432, PQ_TAB_DWORDS = 2480
 };
 
 /* Constants every kernel reads; one copy per device in global memory. */

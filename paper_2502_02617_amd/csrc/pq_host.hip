@@ -292,13 +292,11 @@ void build_tables(pq_ctx *ctx)
     for (int e = 0; e < 64; ++e) {
         {   /* e = c2 << 4 | c1 */
             const double t2 = ctx->centroids[1][e >> 4], t1 = ctx->centroids[0][e & 15];
-            c.attn_tab[PQ_TAB_TQA + e] = pack_h2(cos(t2) * cos(t1), cos(t2) * sin(t1));
             c.dq_quarter[0][e][0] = (float)(cos(t2) * cos(t1));
             c.dq_quarter[0][e][1] = (float)(cos(t2) * sin(t1));
         }
         {   /* e = c1' << 2 | c2 */
             const double t2 = ctx->centroids[1][e & 3], t1 = ctx->centroids[0][e >> 2];
-            c.attn_tab[PQ_TAB_TQB + e] = pack_h2(sin(t2) * cos(t1), sin(t2) * sin(t1));
             c.dq_quarter[1][e][0] = (float)(sin(t2) * cos(t1));
             c.dq_quarter[1][e][1] = (float)(sin(t2) * sin(t1));
         }
