@@ -1514,8 +1514,7 @@ __device__ __forceinline__ float wave_sum_fixed(float x)
     return x;
 }
 
-/* G = query heads handled by one wavefront: the group of a kv head (Hq/Hkv), or half of it when the group
-   has four heads -- the kernel has little work per launch and runs faster spread over more wavefronts */
+/* G = query heads handled by one wavefront: one or two of a kv head's group (attention_launches) */
 constexpr int kWindowWaves = 4; /* work items per workgroup: one per SIMD, as many workgroups as possible */
 
 template <int G>
@@ -1534,16 +1533,10 @@ __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, i
     const int n_valid = min(W - t0, 64);
     if (n_valid <= 0) return; /* the combine kernel reads only the chunks below win_len */
 
-    /* q of the group's heads, scaled, as fp32 in LDS */
+    /* q of the group's heads, scaled, as fp32 in LDS: requested ahead of the rows, stored behind their requests */
+    uint32_t two_q[G];
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-        const uint32_t two = reinterpret_cast<const uint32_t *>(a.q + ((int64_t)b * a.Hq + head0 + h) * PQ_D)[lane];
-        sq[wave][h][2 * lane] = __uint_as_float(two << 16) * a.scale;
-        sq[wave][h][2 * lane + 1] = __uint_as_float(two & 0xFFFF0000u) * a.scale;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    for (int h = 0; h < G; ++h) two_q[h] = reinterpret_cast<const uint32_t *>(a.q + ((int64_t)b * a.Hq + head0 + h) * PQ_D)[lane];
 
     /* scores: lane t takes window token t0 + t (lanes beyond the window re-read the last row) */
     const int64_t plane = ((int64_t)b * a.Hkv + hk) * a.win_cap;
@@ -1563,6 +1556,12 @@ __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, i
 #pragma unroll
     for (int t = 0; t < 64; ++t) vrow[t] = vbase[(int64_t)min(t, n_valid - 1) * (PQ_D / 2)];
     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+        sq[wave][h][2 * lane] = __uint_as_float(two_q[h] << 16) * a.scale;
+        sq[wave][h][2 * lane + 1] = __uint_as_float(two_q[h] & 0xFFFF0000u) * a.scale;
+    }
+    own_lds_order();
 #pragma unroll
     for (int c = 0; c < 16; ++c) { /* 8 coordinates per step */
         const uint4 kv = krow_v[c];
@@ -1593,9 +1592,7 @@ __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, i
         l[h] = wave_sum_fixed(p);
         sp[wave][h][lane] = p;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    own_lds_order();
 
     /* weighted values: lane c owns coordinates 2c, 2c+1; tokens in order */
     float o0[G], o1[G];
@@ -1861,7 +1858,10 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
                       static_cast<const uint16_t *>(win->win_v), win->win_len, B, Hq, Hkv, (int)win->win_cap,
                       p.n_wchunks, softmax_scale * kLog2e, reinterpret_cast<float *>(ws + p.off_wml),
                       reinterpret_cast<float *>(ws + p.off_wo)};
-        const int per_wave = (G >= 4 && G % 2 == 0) ? 2 : 1; /* query heads per wavefront (of one kv head's group) */
+        /* Query heads per wavefront (of one kv head's group): two fetch a row once for both, one has the shorter chain while every
+           wavefront finds a SIMD (us per call, one against two: 4 sequences of 2000 tokens with windows of 256, 256 items of two heads,
+           21.1 / 22.0; 16 of 8000, 8 heads, 1024 items 36.3 / 36.9; 64 of 2000 with 512, 8192 items 110 / 82). */
+        const int per_wave = G >= 4 && G % 2 == 0 && (int64_t)B * (Hq / 2) * p.n_wchunks > 1024 ? 2 : 1;
         const int64_t witems = (int64_t)B * (Hq / per_wave) * p.n_wchunks;
         const int64_t wblocks = (witems + kWindowWaves - 1) / kWindowWaves;
         if (wblocks + row_blocks + 1 > 0x7FFFFFFF) return PQ_EINVAL;
