@@ -30,18 +30,25 @@
 
 namespace {
 
-constexpr int kGenMaxCells = 16;
+constexpr int kGenMaxCells = 16, kGenUpperCells = 8; /* of level 1, of the levels above */
 constexpr int kGenMaxRecord = 96; /* bytes: depth 4 with bits 4/3/3/3 needs 53 + 16 */
 
+/* Kernel arguments are copied for every launch: a kernel gets the format and, of the codebooks, the boundaries or the centroids'
+   cosines and sines, whichever it looks at (1.3 KB with both: the attention call took the host 13.1 us, now 11.9, an encode 7.2, now 6.6). */
 struct GenFormat {
     int depth;
     int bits[7];
-    int level_off[7];  /* first angle of level l inside the level-major numbering */
     int bit_off[7];    /* first bit of level l in the record's bit stream */
     int code_bytes, rec_bytes, n_radii;
     int rec_dwords, rec_inv; /* dwords of a record (the last may be partial); 65536 / rec_dwords, rounded up */
-    float bound[7][kGenMaxCells - 1]; /* inner cell boundaries, +inf beyond the level's last one */
-    float cosv[7][kGenMaxCells], sinv[7][kGenMaxCells];
+};
+
+struct GenBounds { /* inner cell boundaries, +inf beyond the level's last one */
+    float first[kGenMaxCells - 1], upper[6][kGenUpperCells - 1];
+};
+
+struct GenCentroids { /* (cos, sin): 16 of level 1, then eight each of the levels above */
+    float2 cs[kGenMaxCells + 6 * kGenUpperCells];
 };
 
 bool general_format_ok(const pq_general_format *f)
@@ -67,22 +74,16 @@ pq_status make_format(const pq_general_format *f, const double *cbg, GenFormat *
     if (!general_format_ok(f) || !cbg) return PQ_EINVAL;
     memset(g, 0, sizeof(*g));
     g->depth = f->depth;
-    int off = 0, cboff = 0;
+    int cboff = 0;
     const double half_pi = 1.57079632679489661923, two_pi = 6.28318530717958647692;
     for (int l = 0; l < f->depth; ++l) {
         const int K = 1 << f->bits[l];
         g->bits[l] = f->bits[l];
-        for (int k = K - 1; k < kGenMaxCells - 1; ++k) g->bound[l][k] = INFINITY;
-        g->level_off[l] = off;
         g->bit_off[l] = l == 0 ? 0 : g->bit_off[l - 1] + (PQ_D >> l) * f->bits[l - 1];
-        off += PQ_D >> (l + 1);
         for (int k = 0; k < K; ++k) {
             const double c = cbg[cboff + k];
             if (!std::isfinite(c) || c < 0.0 || c > (l == 0 ? two_pi : half_pi)) return PQ_EINVAL;
             if (k > 0 && !(c > cbg[cboff + k - 1])) return PQ_EINVAL;
-            g->cosv[l][k] = (float)cos(c);
-            g->sinv[l][k] = (float)sin(c);
-            if (k > 0) g->bound[l][k - 1] = (float)(0.5 * (c + cbg[cboff + k - 1]));
         }
         cboff += K;
     }
@@ -94,6 +95,29 @@ pq_status make_format(const pq_general_format *f, const double *cbg, GenFormat *
     return PQ_OK;
 }
 
+/* of a format and codebooks that make_format has accepted */
+GenBounds make_bounds(const GenFormat &g, const double *cbg)
+{
+    GenBounds b;
+    for (int l = 0; l < 7; ++l) {
+        const int K = l < g.depth ? 1 << g.bits[l] : 1, most = l == 0 ? kGenMaxCells : kGenUpperCells;
+        float *to = l == 0 ? b.first : b.upper[l - 1];
+        for (int k = 1; k < most; ++k) to[k - 1] = k < K ? (float)(0.5 * (cbg[k] + cbg[k - 1])) : INFINITY;
+        if (l < g.depth) cbg += K;
+    }
+    return b;
+}
+
+GenCentroids make_centroids(const GenFormat &g, const double *cbg)
+{
+    GenCentroids c{};
+    for (int l = 0; l < g.depth; ++l) {
+        float2 *to = l == 0 ? c.cs : c.cs + kGenMaxCells + (l - 1) * kGenUpperCells;
+        for (int k = 0; k < 1 << g.bits[l]; ++k, ++cbg) to[k] = make_float2((float)cos(*cbg), (float)sin(*cbg));
+    }
+    return c;
+}
+
 __device__ __forceinline__ uint32_t gen_get_bits(const uint8_t *stream, int pos, int width)
 {
     uint32_t v = stream[pos >> 3] | ((uint32_t)stream[(pos >> 3) + 1] << 8); /* width <= 4: two bytes suffice */
@@ -103,14 +127,6 @@ __device__ __forceinline__ uint32_t gen_get_bits(const uint8_t *stream, int pos,
 __device__ __forceinline__ uint16_t gen_radius_bits(float r)
 {
     return __builtin_bit_cast(uint16_t, (_Float16)fminf(r, 65504.f)); /* saturates at the largest finite binary16 */
-}
-
-/* position of angle j of level l in the record's bit stream */
-__device__ __forceinline__ int gen_bit_pos(const GenFormat &f, int l, int j)
-{
-    int pos = 0;
-    for (int m = 0; m < l; ++m) pos += (PQ_D >> (m + 1)) * f.bits[m];
-    return pos + j * f.bits[l];
 }
 
 /* ---- encode: sixteen vectors per workgroup of 512 threads ----
@@ -130,7 +146,7 @@ typedef float gen_f4 __attribute__((ext_vector_type(4)));
 /* number of the first N boundaries below the angle: nearest centroid, ties to the lower cell (boundaries that a level does not
    have are +inf; reading them all at once is a third of the time of a loop over those it has) */
 template <int N>
-__device__ __forceinline__ uint32_t gen_cell(const float (&bound)[kGenMaxCells - 1], float ang)
+__device__ __forceinline__ uint32_t gen_cell(const float (&bound)[N], float ang)
 {
     uint32_t code = 0;
 #pragma unroll
@@ -145,7 +161,7 @@ __device__ __forceinline__ void gen_emit(uint32_t *image, int pos, uint32_t v, i
 }
 
 template <int XT>
-__global__ __launch_bounds__(kGenEncThreads) void pq_general_encode_kernel(GenFormat f, const void *x, int64_t ld_vector, int64_t n,
+__global__ __launch_bounds__(kGenEncThreads) void pq_general_encode_kernel(GenFormat f, GenBounds bounds, const void *x, int64_t ld_vector, int64_t n,
                                                                            const float *S, uint8_t *rec)
 {
     __shared__ __attribute__((aligned(16))) float buf[kGenEncVecs][kGenRow], sy[kGenEncVecs][kGenRow];
@@ -188,11 +204,11 @@ __global__ __launch_bounds__(kGenEncThreads) void pq_general_encode_kernel(GenFo
             return ang < 0.f ? ang + 6.28318530717958647692f : ang;
         };
         /* level 1: two angles, next to each other in the stream */
-        const uint32_t c0 = gen_cell<kGenMaxCells - 1>(f.bound[0], angle1(y.x, y.y));
-        const uint32_t c1 = gen_cell<kGenMaxCells - 1>(f.bound[0], angle1(y.z, y.w));
+        const uint32_t c0 = gen_cell(bounds.first, angle1(y.x, y.y));
+        const uint32_t c1 = gen_cell(bounds.first, angle1(y.z, y.w));
         gen_emit(srec, base + 2 * q * f.bits[0], c0 | c1 << f.bits[0], 2 * f.bits[0]);
         float a = sqrtf(y.x * y.x + y.y * y.y), b = sqrtf(y.z * y.z + y.w * y.w);
-        gen_emit(srec, base + f.bit_off[1] + q * f.bits[1], gen_cell<7>(f.bound[1], atan2f(b, a)), f.bits[1]);
+        gen_emit(srec, base + f.bit_off[1] + q * f.bits[1], gen_cell(bounds.upper[0], atan2f(b, a)), f.bits[1]);
         float r = sqrtf(a * a + b * b);
 #pragma unroll
         for (int l = 2; l < 7; ++l) { /* the 2^(l-1) lanes of a node all know its radius, the first of them has the code to write */
@@ -201,7 +217,7 @@ __global__ __launch_bounds__(kGenEncThreads) void pq_general_encode_kernel(GenFo
                 const bool up = (q >> (l - 2)) & 1;
                 a = up ? other : r;
                 b = up ? r : other;
-                const uint32_t code = gen_cell<7>(f.bound[l], atan2f(b, a));
+                const uint32_t code = gen_cell(bounds.upper[l - 1], atan2f(b, a));
                 if ((q & ((1 << (l - 1)) - 1)) == 0) gen_emit(srec, base + f.bit_off[l] + (q >> (l - 1)) * f.bits[l], code, f.bits[l]);
                 r = sqrtf(a * a + b * b);
             }
@@ -231,7 +247,7 @@ __device__ __forceinline__ void gen_wave_sync()
 
 /* DeQuant's loops for one record by one wavefront (lane = 0..63): r^(0) (rotated domain) into
    buf[returned index][0..127]; buf is the wavefront's own */
-__device__ __forceinline__ int gen_dequant_rotated(const GenFormat &f, const uint8_t *rec, float (&buf)[2][PQ_D], int lane)
+__device__ __forceinline__ int gen_dequant_rotated(const GenFormat &f, const GenCentroids &centroids, const uint8_t *rec, float (&buf)[2][PQ_D], int lane)
 {
     int cur = 0;
     if (lane < f.n_radii) {
@@ -242,10 +258,11 @@ __device__ __forceinline__ int gen_dequant_rotated(const GenFormat &f, const uin
     for (int l = f.depth - 1; l >= 0; --l) {
         const int n_ang = PQ_D >> (l + 1);
         if (lane < n_ang) {
-            const uint32_t code = gen_get_bits(rec, gen_bit_pos(f, l, lane), f.bits[l]);
+            const uint32_t code = gen_get_bits(rec, f.bit_off[l] + lane * f.bits[l], f.bits[l]);
             const float r = buf[cur][lane];
-            buf[cur ^ 1][2 * lane] = r * f.cosv[l][code];
-            buf[cur ^ 1][2 * lane + 1] = r * f.sinv[l][code];
+            const float2 t = centroids.cs[(l == 0 ? 0 : kGenMaxCells + (l - 1) * kGenUpperCells) + code];
+            buf[cur ^ 1][2 * lane] = r * t.x;
+            buf[cur ^ 1][2 * lane + 1] = r * t.y;
         }
         cur ^= 1;
         gen_wave_sync();
@@ -254,14 +271,14 @@ __device__ __forceinline__ int gen_dequant_rotated(const GenFormat &f, const uin
 }
 
 /* ---- decode: one wavefront per record; out[i] = sum_j y_j S[i][j] with St[j][i] = S[i][j] ---- */
-__global__ __launch_bounds__(64) void pq_general_decode_kernel(GenFormat f, const uint8_t *rec, int64_t n, const float *St,
+__global__ __launch_bounds__(64) void pq_general_decode_kernel(GenFormat f, GenCentroids centroids, const uint8_t *rec, int64_t n, const float *St,
                                                                int rotated, float *out)
 {
     __shared__ float buf[2][PQ_D];
     const int64_t v = blockIdx.x;
     const int tid = threadIdx.x;
     if (v >= n) return;
-    const int cur = gen_dequant_rotated(f, rec + v * f.rec_bytes, buf, tid);
+    const int cur = gen_dequant_rotated(f, centroids, rec + v * f.rec_bytes, buf, tid);
     float a0 = 0.f, a1 = 0.f;
     if (rotated) {
         a0 = buf[cur][2 * tid];
@@ -454,7 +471,7 @@ struct GenSplit {
 
 template <int HEADS, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_attn_kernel(
-    GenFormat f, const uint16_t *q, float *out, const uint8_t *k_rec, const uint8_t *v_rec, const int64_t *seq_start,
+    GenFormat f, GenCentroids centroids, const uint16_t *q, float *out, const uint8_t *k_rec, const uint8_t *v_rec, const int64_t *seq_start,
     const int32_t *ctx_len, int Hq, int Hkv, int64_t pool_tokens, float scale, const float *S, const float *St)
 {
     constexpr int kThreads = WAVES * 64, kTokens = kThreads / 8; /* eight blocks of a token, one per wavefront */
@@ -512,7 +529,7 @@ __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_att
         }
     };
     if (n > 0) fetch(0);
-    if (tid < 7 * kGenMaxCells) cs[tid >> 4][tid & 15] = make_float2((&f.cosv[0][0])[tid], (&f.sinv[0][0])[tid]);
+    if (tid < kGenMaxCells + 6 * kGenUpperCells) (tid < kGenMaxCells ? cs[0][tid] : cs[(tid >> 3) - 1][tid & 7]) = centroids.cs[tid];
     for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = __uint_as_float((uint32_t)q[row0 * PQ_D + t] << 16);
     __syncthreads();
     auto times_slice = [&](const float (&in)[HEADS][PQ_D]) {
@@ -656,14 +673,14 @@ __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_att
  * v_mfma_f32_16x16x4_f32 (fp32 products and sums; the values change places by way of LDS) while the others are at the next keys.
  * A sequence that is one piece is finished here.
  * Bound by the chain of a piece: lengths 1 us, records and S 1.4, q S 1.2, a chunk 2.4, the end 1.  4 sequences of 2048 tokens, 8
- * query heads: 45.2 us on 32 workgroups -> 14.6 for this and the launch that joins the pieces; one sequence of 8000 tokens and 16 heads
+ * query heads: 45.2 us on 32 workgroups -> 13.9 for this and the launch that joins the pieces; one sequence of 8000 tokens and 16 heads
  * 148.8 -> 17.3.  Against 64 bits 3.1e-7 to 4.5e-7, one workgroup per row 3.2e-7 to 5.4e-7.  Weights against a reference per lane, sums
  * in the lanes and eight wavefronts for keys and values one after the other: 15.8 us for this launch alone, now 10.7. */
 constexpr int kGenSplitThreads = 1024;
 
 template <int HEADS>
 __global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
-    GenFormat f, const uint16_t *q, float *out, const uint8_t *k_rec, const uint8_t *v_rec, const int64_t *seq_start,
+    GenFormat f, GenCentroids centroids, const uint16_t *q, float *out, const uint8_t *k_rec, const uint8_t *v_rec, const int64_t *seq_start,
     const int32_t *ctx_len, int Hq, int Hkv, int64_t pool_tokens, float scale, const float *S, const float *St, GenSplit split)
 {
     constexpr int kThreads = kGenSplitThreads, kParts = kThreads / PQ_D, kTerms = PQ_D / kParts;
@@ -686,7 +703,7 @@ __global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
         for (int k = 0; k < kTerms; ++k) slice[k] = M[(kTerms * my_part + k) * PQ_D + my_col];
     };
     load_slice(S);
-    if (tid < 7 * kGenMaxCells) cs[tid >> 4][tid & 15] = make_float2((&f.cosv[0][0])[tid], (&f.sinv[0][0])[tid]);
+    if (tid < kGenMaxCells + 6 * kGenUpperCells) (tid < kGenMaxCells ? cs[0][tid] : cs[(tid >> 3) - 1][tid & 7]) = centroids.cs[tid];
     const int groups = Hq / HEADS, item = blockIdx.x / groups, head0 = (blockIdx.x % groups) * HEADS, hk = head0 / (Hq / Hkv);
     plan.form(split.B, pool_tokens, split.slots);
     const int b = __popcll(__ballot(plan.upto <= item));
@@ -892,9 +909,9 @@ __global__ __launch_bounds__(512) void pq_general_combine_kernel(GenSplit split,
 int gen_split_heads(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }
 
 /* How a call is split: not at all (slots 0) where the heads alone occupy half of the CUs, or where the pool holds no more than
-   eight chunks per sequence (three sequences, 8 heads, us for the call, split and not: 2000 tokens 13.5 / 45.2, 500 13.3 / 17.0, 300 13.4 /
-   14.7, 200 13.4 / 12.3; the lengths are on the device, so the pool stands for them, and sequences far shorter than their share
-   of it wait for the host's second launch: 13.4 / 10.6). */
+   eight chunks per sequence (three sequences, 8 heads, us for the call, split and not: 2000 tokens 12.8 / 45.2, 500 12.3 / 17.0, 300 12.0 /
+   14.7, 200 12.0 / 12.3; the lengths are on the device, so the pool stands for them, and sequences far shorter than their share
+   of it wait for the host's second launch: 12.1 / 10.6). */
 GenSplit general_split(int B, int Hq, int Hkv, int64_t pool_tokens)
 {
     GenSplit p{};
@@ -958,10 +975,11 @@ extern "C" pq_status pq_general_encode(const pq_ctx *ctx, const pq_general_forma
     st = pq_device_state(ctx, &ds);
     if (st != PQ_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    const GenBounds bounds = make_bounds(g, cbg);
     if (xt == PQ_BF16)
-        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_BF16>, dim3((unsigned)((n_vectors + kGenEncVecs - 1) / kGenEncVecs)), dim3(kGenEncThreads), 0, s, g, x, ld_vector, n_vectors, ds->S_f32, records);
+        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_BF16>, dim3((unsigned)((n_vectors + kGenEncVecs - 1) / kGenEncVecs)), dim3(kGenEncThreads), 0, s, g, bounds, x, ld_vector, n_vectors, ds->S_f32, records);
     else
-        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_F32>, dim3((unsigned)((n_vectors + kGenEncVecs - 1) / kGenEncVecs)), dim3(kGenEncThreads), 0, s, g, x, ld_vector, n_vectors, ds->S_f32, records);
+        hipLaunchKernelGGL(pq_general_encode_kernel<PQ_F32>, dim3((unsigned)((n_vectors + kGenEncVecs - 1) / kGenEncVecs)), dim3(kGenEncThreads), 0, s, g, bounds, x, ld_vector, n_vectors, ds->S_f32, records);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
 }
@@ -979,7 +997,7 @@ extern "C" pq_status pq_general_decode(const pq_ctx *ctx, const pq_general_forma
     st = pq_device_state(ctx, &ds);
     if (st != PQ_OK) return st;
     hipLaunchKernelGGL(pq_general_decode_kernel, dim3((unsigned)n_vectors), dim3(64), 0, static_cast<hipStream_t>(hip_stream),
-                       g, records, n_vectors, ds->St_f32, rotated, out);
+                       g, make_centroids(g, cbg), records, n_vectors, ds->St_f32, rotated, out);
     PQ_HIP_TRY(hipGetLastError());
     return PQ_OK;
 }
@@ -1022,6 +1040,7 @@ extern "C" pq_status pq_general_attn_decode_ws(const pq_ctx *ctx, const pq_gener
     const int64_t rows = (int64_t)B * Hq;
     const int G = Hq / Hkv;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const GenCentroids centroids = make_centroids(g, cbg);
     GenSplit split = workspace ? general_split(B, Hq, Hkv, pool_tokens) : GenSplit{};
     if (split.slots && workspace_bytes < general_split_bytes(split, Hq)) split = GenSplit{};
     if (split.slots && !pq_aligned16(workspace)) return PQ_EALIGN;
@@ -1031,7 +1050,7 @@ extern "C" pq_status pq_general_attn_decode_ws(const pq_ctx *ctx, const pq_gener
         const int heads = gen_split_heads(G);
         const dim3 grid((unsigned)((int64_t)split.pieces * (Hq / heads))), blk(kGenSplitThreads);
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, grid, blk, 0, stream, g, static_cast<const uint16_t *>(q), out, k_records, v_records, seq_start,
+            hipLaunchKernelGGL(kernel, grid, blk, 0, stream, g, centroids, static_cast<const uint16_t *>(q), out, k_records, v_records, seq_start,
                                ctx_len, Hq, Hkv, pool_tokens, softmax_scale, ds->S_f32, ds->St_f32, split);
         };
         if (heads == 4) launch(pq_general_piece_kernel<4>);
@@ -1044,7 +1063,7 @@ extern "C" pq_status pq_general_attn_decode_ws(const pq_ctx *ctx, const pq_gener
     }
     auto launch = [&](auto heads, auto waves) {
         constexpr int H = decltype(heads)::value, W = decltype(waves)::value;
-        hipLaunchKernelGGL((pq_general_attn_kernel<H, W>), dim3((unsigned)(rows / H)), dim3(W * 64), 0, stream, g,
+        hipLaunchKernelGGL((pq_general_attn_kernel<H, W>), dim3((unsigned)(rows / H)), dim3(W * 64), 0, stream, g, centroids,
                            static_cast<const uint16_t *>(q), out, k_records, v_records, seq_start, ctx_len, Hq, Hkv, pool_tokens,
                            softmax_scale, ds->S_f32, ds->St_f32);
     };
