@@ -77,11 +77,12 @@ constexpr float kRefSlack = 6.0f;
  *   kTUp  [3][8][2]          levels 5..7 (full depth)
  *   kTQ   [1024][COPIES][2]  quarter table, by Q: 32 columns of it would be 256 KB.  Lane l reads copy l mod COPIES: of 32 lanes four
  *                            then choose among four bank pairs, instead of all among 32 with one copy.
- * Eight copies make a quarter one gather and one index for keys and values alike.  With one copy the values' gathers kept the LDS busy
- * with conflicts, and the keys fetched a quarter's two pairs from two 64-entry tables, two indices for them: steps of 16 x 32768
- * tokens 115.8 us, now 113.4, 64 sequences of 1k-64k 482 and 467, depth 7 16 x 14200 67.0 and 65.0; eight heads, 16 x 35000, 150.4
- * and 144.8 (four copies 116.4, -, 69.1, 145.2).  They take 0.3 us longer to lay out than four: see launch_partial_depth.  The wide form is
- * bound by vector instructions and has no gain from copies, whose index takes a three-operand instruction (draft tokens
+ * With eight copies a quarter is one gather and one index for keys and values alike: 540 vector and 106 LDS instructions per tile, the
+ * vector ALU active 75 % of a launch and the LDS 85 %.  (With one copy the keys fetched a quarter's two pairs from two
+ * conflict-free 64-entry tables, two indices for them: 606 and 138, 83 % and 79 %.)  Steps of 16 x 32768
+ * tokens 115.8 us -> 113.4, 64 sequences of 1k-64k 482 -> 467, depth 7 16 x 14200 67.0 -> 65.0; eight heads, 16 x 35000, 150.4
+ * -> 144.8 (four copies, more collisions: 116.4, -, 69.1, 145.2).  They take 0.3 us longer to lay out than four: see launch_partial_depth.
+ * The wide form is bound by vector instructions and has no gain from copies, whose index takes a three-operand instruction (draft tokens
  * 74.9 us, 75.2 with eight): one copy, and the tables where its code is the shorter by four registers. */
 template <int COPIES> struct Tab {
     static constexpr int kTBF = COPIES == 1 ? 6144 : 0, kTBH = kTBF + 4096, kTUp = kTBF + 6144, kTQ = COPIES == 1 ? 0 : 6192;
@@ -1858,10 +1859,10 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
                       static_cast<const uint16_t *>(win->win_v), win->win_len, B, Hq, Hkv, (int)win->win_cap,
                       p.n_wchunks, softmax_scale * kLog2e, reinterpret_cast<float *>(ws + p.off_wml),
                       reinterpret_cast<float *>(ws + p.off_wo)};
-        /* Query heads per wavefront (of one kv head's group): two fetch a row once for both, one has the shorter chain while every
-           wavefront finds a SIMD (us per call, one against two: 4 sequences of 2000 tokens with windows of 256, 256 items of two heads,
-           21.1 / 22.0; 16 of 8000, 8 heads, 1024 items 36.3 / 36.9; 64 of 2000 with 512, 8192 items 110 / 82). */
-        const int per_wave = G >= 4 && G % 2 == 0 && (int64_t)B * (Hq / 2) * p.n_wchunks > 1024 ? 2 : 1;
+        /* Query heads per wavefront (of one kv head's group): two fetch a row once for both, one has the shorter chain while the
+           items leave SIMDs idle (us per call, one against two: 4 sequences of 2000 tokens with windows of 256, 256 items of two heads,
+           21.1 / 22.0; 16 with 256, 1024 items, the first launch 15.4 / 11.7; 64 of 2000 with 512, 8192 items 110 / 82). */
+        const int per_wave = G >= 4 && G % 2 == 0 && (int64_t)B * (Hq / 2) * p.n_wchunks > 512 ? 2 : 1;
         const int64_t witems = (int64_t)B * (Hq / per_wave) * p.n_wchunks;
         const int64_t wblocks = (witems + kWindowWaves - 1) / kWindowWaves;
         if (wblocks + row_blocks + 1 > 0x7FFFFFFF) return PQ_EINVAL;
