@@ -459,8 +459,8 @@ size_t pq_attn_hybrid_workspace_bytes(int B, int Hq, int Hkv, int64_t max_ctx, i
  * pq_general_attn_workspace_bytes(B, Hq, Hkv, pool_tokens) bytes, with which a few
  * rows of long sequences occupy the whole chip: a sequence is worked on by several
  * workgroups, and a second launch joins their sums.  NULL, or one that is too small,
- * is not used; 0 bytes: nothing to split at these sizes.  The results differ from
- * those without by the rounding of the sums.
+ * is not used; 0 bytes: nothing to split at these sizes, or a pool of more than 2^30
+ * tokens.  The results differ from those without by the rounding of the sums.
  * ------------------------------------------------------------------------- */
 typedef struct pq_general_format {
     int depth;

@@ -911,13 +911,17 @@ int gen_split_heads(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }
 /* How a call is split: not at all (slots 0) where the heads alone occupy half of the CUs, or where the pool holds no more than
    eight chunks per sequence (three sequences, 8 heads, us for the call, split and not: 2000 tokens 12.8 / 45.2, 500 12.3 / 17.0, 300 12.0 /
    14.7, 200 12.0 / 12.3; the lengths are on the device, so the pool stands for them, and sequences far shorter than their share
-   of it wait for the host's second launch: 12.1 / 10.6). */
+   of it wait for the host's second launch: 12.1 / 10.6).  Nor in a pool of more than kGenSplitTokens: the split kernels count
+   tokens in 32 bits, and up to there a token plus a chunk, and the chunks of kGenSplitBatch sequences that overlap (2^30 of them),
+   stay below 2^31.  The row kernel counts in 64. */
+constexpr int64_t kGenSplitTokens = (int64_t)1 << 30;
+
 GenSplit general_split(int B, int Hq, int Hkv, int64_t pool_tokens)
 {
     GenSplit p{};
     p.B = B;
     const int64_t rows = (int64_t)B * Hq, chunks = (pool_tokens + kGenChunk - 1) / kGenChunk;
-    if (rows > 128 || B > kGenSplitBatch || chunks <= 8 * (int64_t)B) return p;
+    if (rows > 128 || B > kGenSplitBatch || chunks <= 8 * (int64_t)B || pool_tokens > kGenSplitTokens) return p;
     const int groups = Hq / gen_split_heads(Hq / Hkv);
     p.slots = groups < 256 ? 256 / groups : 1;
     p.pieces = p.slots + B;
