@@ -453,11 +453,8 @@ pq_status check_start(const pq_ctx *ctx, const double *cb_init, const double *cb
     return PQ_OK;
 }
 
-} // namespace
-
-extern "C" pq_status pq_fit_count_angles(const pq_ctx *ctx, const void *x, pq_dtype xt, int64_t n_tokens, int n_heads,
-                                         int64_t ld_token, int64_t ld_head, void *workspace, size_t workspace_bytes,
-                                         void *hip_stream)
+pq_status check_count(const pq_ctx *ctx, const void *x, pq_dtype xt, int64_t n_tokens, int n_heads, int64_t ld_token, int64_t ld_head,
+                      const void *workspace, size_t workspace_bytes)
 {
     if (!ctx || !x || !workspace) return PQ_EINVAL;
     if (xt != PQ_F32 && xt != PQ_BF16) return PQ_EINVAL;
@@ -467,6 +464,17 @@ extern "C" pq_status pq_fit_count_angles(const pq_ctx *ctx, const void *x, pq_dt
     if (!pq_aligned16(workspace) || !pq_aligned16(x) || (ld_token % elems16) || (ld_head % elems16)) return PQ_EALIGN;
     /* every bin counter must hold the angles of a level: 64 per vector at level 1 */
     if ((double)n_tokens * n_heads * 64.0 >= 4294967295.0) return PQ_EUNSUPPORTED;
+    return PQ_OK;
+}
+
+} // namespace
+
+extern "C" pq_status pq_fit_count_angles(const pq_ctx *ctx, const void *x, pq_dtype xt, int64_t n_tokens, int n_heads,
+                                         int64_t ld_token, int64_t ld_head, void *workspace, size_t workspace_bytes,
+                                         void *hip_stream)
+{
+    const pq_status args = check_count(ctx, x, xt, n_tokens, n_heads, ld_token, ld_head, workspace, workspace_bytes);
+    if (args != PQ_OK) return args;
     const bool upper = ctx->depth == 7;
     const PqDeviceState *ds = nullptr;
     pq_status st = pq_device_state(ctx, &ds);
@@ -652,19 +660,23 @@ pq_status fit_codebooks(const pq_ctx *ctx, const void *x, pq_dtype xt, int64_t n
     if (!ctx || !cb_out || (upper && !cbt_out) || iterations < 0) return PQ_EINVAL;
     if (upper && ctx->depth != 7) return PQ_EINVAL;
     double c[28], ct[3][8] = {};
-    pq_status st = check_start(ctx, cb_init, cbt_init, upper, c, ct); /* before anything is launched */
+    pq_status st = check_start(ctx, cb_init, cbt_init, upper, c, ct);
     if (st != PQ_OK) return st;
-    st = pq_fit_count_angles(ctx, x, xt, n_tokens, n_heads, ld_token, ld_head, workspace, workspace_bytes, hip_stream);
+    st = check_count(ctx, x, xt, n_tokens, n_heads, ld_token, ld_head, workspace, workspace_bytes);
     if (st != PQ_OK) return st;
+    /* Everything that can be refused is, before the first launch: a capturing stream, which has no results to wait for, would
+       otherwise keep the launches in its graph, and every replay would write to the workspace. */
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return PQ_EHIP; /* no results to wait for */
+    if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return PQ_EHIP;
     const uint64_t *middles = nullptr;
     st = device_middles(&middles);
     if (st != PQ_OK) return st;
     ResultBlock result;
     FitResult *r = result.get();
     if (!r) return PQ_ENOMEM;
+    st = pq_fit_count_angles(ctx, x, xt, n_tokens, n_heads, ld_token, ld_head, workspace, workspace_bytes, hip_stream);
+    if (st != PQ_OK) return st;
     hipLaunchKernelGGL(pq_fit_sums_kernel, dim3(upper ? kLevels : 4), dim3(kSumThreads), 0, s, static_cast<const uint32_t *>(workspace),
                        middles, r);
     PQ_HIP_TRY(hipGetLastError());

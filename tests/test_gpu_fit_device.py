@@ -59,3 +59,25 @@ def test_fit_is_refused_on_a_capturing_stream():
         graph.capture_end()
     torch.cuda.synchronize()
     assert np.array_equal(ctx.fit_codebooks(x, 3, workspace=ws), want)
+
+
+def test_a_refused_fit_leaves_nothing_in_the_graph():
+    ctx, x = Context(seed=2), torch.randn((64, 1, 128), device=DEV)
+    ws = torch.empty(ctx.fit_workspace_bytes(), dtype=torch.uint8, device=DEV)
+    ctx.fit_codebooks(x, 3, workspace=ws)
+    ws.fill_(0x5A)
+    beside = torch.zeros(256, device=DEV)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        graph = torch.cuda.CUDAGraph()
+        graph.capture_begin(capture_error_mode="relaxed")
+        beside.add_(1.0)
+        with pytest.raises(PolarQuantError):
+            ctx.fit_codebooks(x, 3, workspace=ws)
+        graph.capture_end()
+    for r in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool((beside == r + 1).all())
+        assert bool((ws == 0x5A).all())
