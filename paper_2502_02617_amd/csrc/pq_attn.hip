@@ -1522,11 +1522,14 @@ template <int G>
 __device__ __forceinline__ void window_item(const WindowArgs &a, int64_t item, int wave, int lane,
                                             float (&sq)[kWindowWaves][G][PQ_D], float (&sp)[kWindowWaves][G][64])
 {
-    const int n_hg = a.Hq / G; /* head groups of G heads; head0 = first query head of this wavefront */
-    const int wc = (int)(item % a.n_wchunks);
-    const int head0 = (int)((item / a.n_wchunks) % n_hg) * G;
-    const int hk = head0 / (a.Hq / a.Hkv);
-    const int b = (int)(item / ((int64_t)a.n_wchunks * n_hg));
+    /* The heads that share rows lie next to each other: wavefronts of one workgroup fetch them, from one L2.  (With a head's chunks next
+       to each other the rows were fetched for every head on another XCD: 64 sequences with windows of 512 57.7 us, now 49.9; 8 with 256 and
+       one head per item 20.4, now 19.1.) */
+    const int group = a.Hq / a.Hkv, per_kv = group / G; /* wavefronts of a kv head's group */
+    const int64_t chunk = item / per_kv, stream = chunk / a.n_wchunks;
+    const int wc = (int)(chunk - stream * a.n_wchunks);
+    const int b = (int)(stream / a.Hkv), hk = (int)(stream - (int64_t)b * a.Hkv);
+    const int head0 = hk * group + (int)(item - chunk * per_kv) * G; /* first query head of this wavefront */
     if (b >= a.B) return;
     int W = a.win_len[b];
     W = W < 0 ? 0 : (W > a.win_cap ? a.win_cap : W);
@@ -1859,9 +1862,10 @@ pq_status attention_launches(const pq_ctx *ctx, const StepAppend *app, const Ste
                       static_cast<const uint16_t *>(win->win_v), win->win_len, B, Hq, Hkv, (int)win->win_cap,
                       p.n_wchunks, softmax_scale * kLog2e, reinterpret_cast<float *>(ws + p.off_wml),
                       reinterpret_cast<float *>(ws + p.off_wo)};
-        /* Query heads per wavefront (of one kv head's group): two fetch a row once for both, one has the shorter chain while the
-           items leave SIMDs idle (us per call, one against two: 4 sequences of 2000 tokens with windows of 256, 256 items of two heads,
-           21.1 / 22.0; 16 with 256, 1024 items, the first launch 15.4 / 11.7; 64 of 2000 with 512, 8192 items 110 / 82). */
+        /* Query heads per wavefront (of one kv head's group): two fetch a row once for both, one has the shorter chain while its
+           items, twice as many, are no more than a workgroup per CU (us per call, one against two, of 512 items of two heads:
+           4 sequences with windows of 512 18.7 / 19.4, 8 with 256 19.0 / 19.7, 16 with 128 19.1 / 19.8, 32 with 64 20.6 / 21.3; of 576: 9 with 256
+           20.9 / 19.7, 18 with 128 21.7 / 20.8, 36 with 64 22.1 / 21.7; of 256, 4 with 256 18.1 / 19.3; of 8192, 64 with 512 68 / 50). */
         const int per_wave = G >= 4 && G % 2 == 0 && (int64_t)B * (Hq / 2) * p.n_wchunks > 512 ? 2 : 1;
         const int64_t witems = (int64_t)B * (Hq / per_wave) * p.n_wchunks;
         const int64_t wblocks = (witems + kWindowWaves - 1) / kWindowWaves;
