@@ -81,7 +81,7 @@ constexpr float kRefSlack = 6.0f;
  * vector ALU active 75 % of a launch and the LDS 85 %.  (With one copy the keys fetched a quarter's two pairs from two
  * conflict-free 64-entry tables, two indices for them: 606 and 138, 83 % and 79 %.)  Steps of 16 x 32768
  * tokens 115.8 us -> 113.4, 64 sequences of 1k-64k 482 -> 467, depth 7 16 x 14200 67.0 -> 65.0; eight heads, 16 x 35000, 150.4
- * -> 144.8 (four copies, more collisions: 116.4, -, 69.1, 145.2).  They take 0.3 us longer to lay out than four: see launch_partial_depth.
+ * -> 144.8 (four copies, more collisions: 116.4, -, 69.1, 145.2).  They take 0.1 to 0.2 us longer to lay out than four: see launch_partial_depth.
  * The wide form is bound by vector instructions and has no gain from copies, whose index takes a three-operand instruction (draft tokens
  * 74.9 us, 75.2 with eight): one copy, and the tables where its code is the shorter by four registers. */
 template <int COPIES> struct Tab {
@@ -709,39 +709,34 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
     }
     {   /* tables: the image in global memory is compact (PQ_TAB_*); the small ones are spread over a column per lane.
            All of a thread's entries are requested before the first one is stored: one trip to memory, not one per
-           entry. */
+           entry.  Entries are fetched whole and written sixteen bytes at a time (a dword at a time, and an entry of the quarter table
+           again for every two copies: seven loads more and 0.2 us, a call of one sequence 15.1 us instead of 14.9). */
         const uint32_t *src = a.consts->attn_tab;
-        constexpr int kR2 = (2048 + kThreads - 1) / kThreads, kR4 = (4096 + kThreads - 1) / kThreads;
-        constexpr int kQuads = 1024 * COPIES / 2, kRQ = (kQuads + kThreads - 1) / kThreads; /* sixteen bytes: an entry twice, or two */
-        uint32_t tbh[kR2], tbf[kR4], tup = 0;
+        constexpr int kTQs = COPIES == 1 ? 512 : 1024; /* sixteen bytes of the quarter table as it is, or an entry for all its copies */
+        constexpr int kR1 = (1024 + kThreads - 1) / kThreads, kRH = (512 + kThreads - 1) / kThreads, kRQ = (kTQs + kThreads - 1) / kThreads;
+        uint2 tbh[kRH];
+        float4 tbf[kR1];
         uint4 tq[kRQ];
+        uint32_t tup = 0;
 #pragma unroll
-        for (int i = 0; i < kR2; ++i) {
-            const int t = min((int)threadIdx.x + i * kThreads, 2047); /* entry t >> 5, column t & 31 */
-            tbh[i] = src[PQ_TAB_TBH + 2 * (t >> 5) + (t & 1)];
+        for (int i = 0; i < kRH; ++i) { /* entry t >> 3, columns 4 (t & 7) .. + 3 */
+            const int t = min((int)threadIdx.x + i * kThreads, 511);
+            tbh[i] = reinterpret_cast<const uint2 *>(src + PQ_TAB_TBH)[t >> 3];
         }
 #pragma unroll
         for (int i = 0; i < kRQ; ++i) {
-            const int t = min((int)threadIdx.x + i * kThreads, kQuads - 1);
+            const int t = min((int)threadIdx.x + i * kThreads, kTQs - 1);
             if (COPIES == 1) {
                 tq[i] = reinterpret_cast<const uint4 *>(src + PQ_TAB_TQ)[t];
             } else {
-                const uint2 e = reinterpret_cast<const uint2 *>(src + PQ_TAB_TQ)[2 * t / COPIES];
+                const uint2 e = reinterpret_cast<const uint2 *>(src + PQ_TAB_TQ)[t];
                 tq[i] = make_uint4(e.x, e.y, e.x, e.y);
             }
         }
 #pragma unroll
-        for (int i = 0; i < kR4; ++i) {
-            const int t = min((int)threadIdx.x + i * kThreads, 4095); /* entry t >> 6, column (t >> 2) & 15, float t & 3 */
-            if (WIDE) { /* two binary16 terms: dwords 0, 1 the four first terms, 2, 3 the second ones */
-                const uint32_t *f = src + PQ_TAB_TBF + 4 * (t >> 6) + 2 * (t & 1);
-                const float x = __uint_as_float(f[0]), y = __uint_as_float(f[1]);
-                h2 w = h2{(_Float16)x, (_Float16)y};
-                if (t & 2) w = h2{(_Float16)(x - (float)w.x), (_Float16)(y - (float)w.y)};
-                tbf[i] = __builtin_bit_cast(uint32_t, w);
-            } else {
-                tbf[i] = src[PQ_TAB_TBF + 4 * (t >> 6) + (t & 3)];
-            }
+        for (int i = 0; i < kR1; ++i) { /* entry t >> 4, column t & 15 */
+            const int t = min((int)threadIdx.x + i * kThreads, 1023);
+            tbf[i] = reinterpret_cast<const float4 *>(src + PQ_TAB_TBF)[t >> 4];
         }
         if (threadIdx.x < 48) tup = src[PQ_TAB_UP + threadIdx.x];
         if (!WIDE) {
@@ -750,19 +745,36 @@ __global__ __launch_bounds__(WAVES_PER_SIMD * 4 * 64, 1) void pq_attn_partial_ke
         }
         if (threadIdx.x < 16) sDone[threadIdx.x >> 2][threadIdx.x & 3] = threadIdx.x < kWavesPerBlock ? 0 : 0x7FFFFFFF;
 #pragma unroll
-        for (int i = 0; i < kR2; ++i) {
+        for (int i = 0; i < kRH; ++i) {
             const int t = (int)threadIdx.x + i * kThreads;
-            if (t < 2048) tab[T::kTBH + t] = tbh[i];
+            if (t < 512) reinterpret_cast<uint4 *>(tab + T::kTBH)[t] = make_uint4(tbh[i].x, tbh[i].y, tbh[i].x, tbh[i].y);
         }
 #pragma unroll
         for (int i = 0; i < kRQ; ++i) {
             const int t = (int)threadIdx.x + i * kThreads;
-            if (t < kQuads) reinterpret_cast<uint4 *>(tab + T::kTQ)[t] = tq[i];
+            if (t < kTQs) {
+                uint4 *to = reinterpret_cast<uint4 *>(tab + T::kTQ);
+                if (COPIES == 1) {
+                    to[t] = tq[i];
+                } else { /* sixteen lanes that follow each other write to all 64 banks, each two copies at a time beginning elsewhere */
+                    constexpr int kPairsOf = COPIES == 1 ? 1 : COPIES / 2;
+#pragma unroll
+                    for (int c = 0; c < kPairsOf; ++c) to[t * kPairsOf + ((t / (16 / kPairsOf) + c) & (kPairsOf - 1))] = tq[i];
+                }
+            }
         }
 #pragma unroll
-        for (int i = 0; i < kR4; ++i) {
+        for (int i = 0; i < kR1; ++i) {
             const int t = (int)threadIdx.x + i * kThreads;
-            if (t < 4096) tab[T::kTBF + t] = tbf[i];
+            float4 f = tbf[i];
+            if (WIDE) { /* two binary16 terms: dwords 0, 1 the four first terms, 2, 3 the second ones */
+                const h2 a0 = h2{(_Float16)f.x, (_Float16)f.y}, a1 = h2{(_Float16)f.z, (_Float16)f.w};
+                const h2 b0 = h2{(_Float16)(f.x - (float)a0.x), (_Float16)(f.y - (float)a0.y)};
+                const h2 b1 = h2{(_Float16)(f.z - (float)a1.x), (_Float16)(f.w - (float)a1.y)};
+                f = make_float4(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1), __builtin_bit_cast(float, b0),
+                                __builtin_bit_cast(float, b1));
+            }
+            if (t < 1024) reinterpret_cast<float4 *>(tab + T::kTBF)[t] = f;
         }
         if (threadIdx.x < 48) tab[T::kTUp + threadIdx.x] = tup;
     }
@@ -1772,7 +1784,8 @@ void launch_partial_depth(int pairs, int slots, dim3 grid, hipStream_t s, const 
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3((unsigned)(4 * waves_per_simd(pairs) * 64)), 0, s, aa); };
     const int64_t most_tiles = (int64_t)aa.B * aa.Hkv * ((aa.max_ctx + 63) / 64);
     /* Up to two tiles per wavefront of the largest context the shorter start counts more than the gathers (copies of the quarter table, four
-       against eight, us: one sequence of 1000 tokens 15.8 / 16.1, two of 2000 16.9 / 17.3; 32 of 200 to 4096, four tiles at most, 35.0 / 34.9). */
+       against eight, us: one sequence of 1000 tokens 14.8 / 15.0, of 100 14.4 / 14.6; 32 of 200 to 4096, four tiles at most, 35.0 / 34.9).  The
+       lengths are on the device: short sequences under a large largest context take eight. */
     if (pairs <= 4 && most_tiles <= 2 * (int64_t)slots) launch(pq_attn_partial_kernel<1, 4, DEEP, 4>);
     else if (pairs <= 4) launch(pq_attn_partial_kernel<1, 4, DEEP, 8>);
     else if (pairs > 8) launch(pq_attn_partial_kernel<0, 2, DEEP, 1>);
