@@ -432,7 +432,8 @@ size_t pq_attn_hybrid_workspace_bytes(int B, int Hq, int Hkv, int64_t max_ctx, i
  * Section 4.1's (Definition 1 recurses to log2 d; the remark after Theorem 1
  * leaves the codebook size of each level free).  A plain path next to the tuned
  * one: records in the canonical general layout, one after another, read through
- * a generic bit reader by fp32 kernels on the vector ALU (attention: one token
+ * a generic bit reader by fp32 kernels: products with S and weighted values as fp32
+ * matrix instructions or on the vector ALU, the rest on the vector ALU (attention: one token
  * per lane, one workgroup per sequence and up to four query heads of a kv head, or several).
  *   format: depth in 4..7; bits[l-1] bits for the angles of level l:
  *           level 1: 3 or 4; levels 2-4: 2 or 3; levels 5-7 (up to depth): 1, 2 or 3.
@@ -455,12 +456,14 @@ size_t pq_attn_hybrid_workspace_bytes(int B, int Hq, int Hkv, int64_t max_ctx, i
  * tokens [seq_start[b], seq_start[b] + ctx_len[b]) of every head plane (device
  * arrays; a range outside the pool or an empty one gives a zero row), out device
  * fp32 [B][Hq][128].  No workspace, nothing allocated, launches only.
- * pq_general_attn_decode_ws: the same with a device workspace (16-byte aligned) of
- * pq_general_attn_workspace_bytes(B, Hq, Hkv, pool_tokens) bytes, with which a few
- * rows of long sequences occupy the whole chip: a sequence is worked on by several
- * workgroups, and a second launch joins their sums.  NULL, or one that is too small,
- * is not used; 0 bytes: nothing to split at these sizes, or a pool of more than 2^30
- * tokens.  The results differ from those without by the rounding of the sums.
+ * pq_general_attn_decode_ws: the same with a device workspace (16-byte aligned, any
+ * contents) of pq_general_attn_workspace_bytes(B, Hq, Hkv, pool_tokens) bytes, with which a
+ * few rows of long sequences occupy the whole chip: a sequence is worked on by several
+ * workgroups, the last of which joins their sums.  NULL, or one that is too small, is
+ * not used; 0 bytes: nothing to split at these sizes, or a pool of more than 2^30 tokens.
+ * The results differ from those without by the rounding of the sums, and how a sequence
+ * is split, so that rounding, depends on B, Hq, Hkv, pool_tokens and the lengths of all
+ * sequences; equal calls give equal bits.
  * ------------------------------------------------------------------------- */
 typedef struct pq_general_format {
     int depth;

@@ -586,7 +586,7 @@ def general_decode(ctx, fmt, cbg, records, n, out, rotated=False):
 def general_attn_decode(ctx, fmt, cbg, q, out, k_records, v_records, seq_start, ctx_len, scale):
     """q bf16 [B, Hq, 128]; records uint8 [Hkv, pool_tokens, record bytes]; out fp32 [B, Hq, 128].  The workspace that lets few
     rows occupy the chip comes from torch's allocator, in the order of the stream; a stream that is being captured gets none (a
-    graph outlives it)."""
+    graph outlives it): a captured call is the one without, whose sums are rounded in another order."""
     import torch
 
     cb = _cbg(cbg)

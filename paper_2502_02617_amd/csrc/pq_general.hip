@@ -7,20 +7,23 @@
  * another in the canonical general layout (all codes of level 1, then level 2,
  * ..., in one little-endian bit stream padded to a byte, then the 128 >> depth
  * binary16 radii), every field goes through a generic bit reader, and the
- * kernels are fp32 code on the vector ALU:
- *   encode     y = x S (fp32 sums in index order), procedure Polar level by
- *              level in LDS, procedure Quant as a count of the cell boundaries
- *              (midpoints of neighbouring centroids) below the angle
+ * kernels are fp32 code:
+ *   encode     y = x S (fp32 matrix instructions, sums in index order), procedure Polar
+ *              level by level between lanes, procedure Quant as a count of the cell
+ *              boundaries (midpoints of neighbouring centroids) below the angle
  *   decode     procedure DeQuant: centroid cos/sin products from the top level
  *              down, then the trailing S^T; one wavefront per vector
  *   attention  Eq. 5 in the rotated domain: q' = q S once, every cached token
  *              dequantised without its S^T, one token per lane, softmax
- *              weights, one S^T at the end
+ *              weights, one S^T at the end; one workgroup per row, or, with a
+ *              workspace, several per sequence
  * Section 4.1's own configuration (depth 4, bits 4/2/2/2) and its depth-7
  * extension have the tuned kernels of pq_encode.hip / pq_attn.hip; this file
  * accepts them too (same numbers, other layout), which is how it is tested
  * against them.
  */
+#include <atomic>
+#include <chrono>
 #include <type_traits>
 
 #include "pq_common.h"
@@ -420,9 +423,10 @@ __device__ __forceinline__ int gen_tokens(int64_t n, int64_t t0, int64_t pool_to
 /* ---- the same over several workgroups per sequence, for callers with a workspace ----
  * The chunks of kGenChunk tokens of all sequences are dealt out in pieces of `share` chunks (the last of a sequence may be
  * smaller), so that there are at most `slots` pieces and one more per sequence, numbered along the sequences.  Every wavefront
- * forms that by itself from the lengths, which the host does not know: lane b looks after sequence b. */
+ * forms that by itself from the lengths, which the host does not know: lane b looks after sequence b.  `share` follows from the
+ * lengths of all sequences and, by way of the slots, from B and Hq, so a row's pieces and the rounding of its sums do too. */
 constexpr int kGenChunk = 64, kGenSplitBatch = 64; /* tokens; sequences of a split call */
-constexpr int kGenWhole = 2; /* chunks up to which no sequence is split */
+constexpr int kGenWhole = 2; /* nothing is split in a call whose sequences all have at most so many chunks */
 
 __device__ __forceinline__ int gen_wave_scan(int x) /* inclusive sum over the lanes */
 {
@@ -467,7 +471,45 @@ struct GenPlan {
 struct GenSplit {
     int B, slots, pieces; /* pieces: the most there can be */
     float *o, *ml;        /* [piece][query head][128], [piece][query head][2]: weighted values, reference and sum of the weights */
+    unsigned long long *arrived, call; /* [sequence][group of heads][kGenWordStride]: see gen_begin_count */
 };
+
+constexpr int kGenWordStride = 16; /* a line for each word: eight of them on one, 256 arrivals, took 4 us */
+constexpr int kGenMostPieces = 256; /* of a sequence: GenPlan's share leaves no more than the slots, and general_split gives no more than that */
+
+/* What a workgroup leaves for another one of the same launch, which may be on another XCD, behind another L2: written and read at the
+   scope of the device, eight bytes at a time.  (Fences that write back an L2 for it took 3 us and more per piece.) */
+__device__ __forceinline__ void gen_put(float *to, float x, float y)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(to), (unsigned long long)__float_as_uint(y) << 32 | __float_as_uint(x),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ float2 gen_get(const float *from)
+{
+    const unsigned long long x = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(from), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((uint32_t)x), __uint_as_float((uint32_t)(x >> 32)));
+}
+
+/* Arrivals are counted at a word of the workspace, whose contents are anything at first.  Its upper 48 bits name the call.  Every
+   workgroup, before it arrives, begins the count if it finds another name there; where its exchange fails, somebody else has.
+   Nobody waits for anybody. */
+__device__ __forceinline__ void gen_begin_count(unsigned long long *word, unsigned long long call)
+{
+    unsigned long long seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((seen >> 16) != call)
+        __hip_atomic_compare_exchange_strong(word, &seen, call << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+/* True for the last of `all`, which leaves a word that names no call: the same launch may follow on the same workspace (a graph
+   that is replayed). */
+__device__ __forceinline__ bool gen_arrive(unsigned long long *word, uint32_t all)
+{
+    const unsigned long long before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = (uint32_t)(before & 0xFFFFull) == all - 1;
+    if (last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
+}
 
 template <int HEADS, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_attn_kernel(
@@ -671,10 +713,11 @@ __global__ __launch_bounds__(WAVES * 64, HEADS == 1 ? 4 : 2) void pq_general_att
  * rebuilds block b of the keys and forms its part of the scores, wavefront 8 + b rebuilds block b of the values meanwhile; one
  * wavefront per head turns the parts into weights, and the value wavefronts multiply them with their values on
  * v_mfma_f32_16x16x4_f32 (fp32 products and sums; the values change places by way of LDS) while the others are at the next keys.
- * A sequence that is one piece is finished here.
- * Bound by the chain of a piece: lengths 1 us, records and S 1.4, q S 1.2, a chunk 2.4, the end 1.  4 sequences of 2048 tokens, 8
- * query heads: 45.2 us on 32 workgroups -> 13.9 for this and the launch that joins the pieces; one sequence of 8000 tokens and 16 heads
- * 148.8 -> 17.3.  Against 64 bits 3.1e-7 to 4.5e-7, one workgroup per row 3.2e-7 to 5.4e-7.  Weights against a reference per lane, sums
+ * A sequence that is one piece is finished by its workgroup, of any other the workgroup that arrives last joins the pieces, in their order.
+ * Bound by the chain of a piece: lengths 1 us, records and S 1.4, q S 1.2, a chunk 2.4, the end 1, joining 3.  4 sequences of 2000 tokens, 8
+ * query heads: 45.2 us on 32 workgroups -> 12.7; one sequence of 8000 tokens 155 -> 16.9.  A second launch that joined the pieces took 13.9 and 17.2,
+ * and sequences of up to 64 tokens, which have nothing to join, waited for it: 11.9 us, 10.2 on 32 workgroups, now 9.6; of up to 128
+ * tokens 12.9, 10.4, 11.3.  Against 64 bits 3.1e-7 to 4.5e-7, one workgroup per row 3.2e-7 to 5.4e-7.  Weights against a reference per lane, sums
  * in the lanes and eight wavefronts for keys and values one after the other: 15.8 us for this launch alone, now 10.7. */
 constexpr int kGenSplitThreads = 1024;
 
@@ -693,6 +736,7 @@ __global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
     __shared__ __attribute__((aligned(16))) float sv[8][(kGenChunk + 4) * 16];
     __shared__ __attribute__((aligned(16))) float sw[HEADS][kGenChunk], salpha[4]; /* weights of the chunk; factors on what was summed before */
     __shared__ float sm[HEADS], sl[HEADS];
+    __shared__ bool last;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), blk = wave & 7;
     const int my_part = tid >> 7, my_col = tid & 127;
     GenPlan plan;
@@ -707,8 +751,14 @@ __global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
     const int groups = Hq / HEADS, item = blockIdx.x / groups, head0 = (blockIdx.x % groups) * HEADS, hk = head0 / (Hq / Hkv);
     plan.form(split.B, pool_tokens, split.slots);
     const int b = __popcll(__ballot(plan.upto <= item));
-    if (b >= split.B) return; /* fewer pieces than there could be */
+    if (b >= split.B) { /* fewer pieces than there could be, by at least one for every sequence without tokens: its row is zeros */
+        uint64_t empty = __ballot(lane < split.B && plan.tokens == 0);
+        for (int k = item - __builtin_amdgcn_readlane(plan.upto, 63); k > 0 && empty != 0; --k) empty &= empty - 1;
+        if (empty != 0 && tid < HEADS * PQ_D) out[((int64_t)(__ffsll((unsigned long long)empty) - 1) * Hq + head0) * PQ_D + tid] = 0.f;
+        return;
+    }
     const bool whole = plan.pieces(b) == 1;
+    unsigned long long *word = &split.arrived[(int64_t)(b * groups + (int)(blockIdx.x % groups)) * kGenWordStride];
     const int begin = (item - plan.first(b)) * plan.share * kGenChunk;
     const int n = (int)min((int64_t)plan.tokens_of(b), (int64_t)begin + (int64_t)plan.share * kGenChunk); /* begin < n */
     const int64_t row0 = (int64_t)b * Hq + head0, slot0 = (int64_t)hk * pool_tokens + plan.start_of(b);
@@ -746,15 +796,19 @@ __global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
     for (int t = tid; t < HEADS * PQ_D; t += kThreads) sq[t >> 7][t & 127] = __uint_as_float((uint32_t)q[row0 * PQ_D + t] << 16);
     __syncthreads();
     auto times_slice = [&](const float (&in)[HEADS][PQ_D]) {
-        float acc[HEADS];
 #pragma unroll
-        for (int h = 0; h < HEADS; ++h) acc[h] = 0.f;
+        for (int h = 0; h < HEADS; ++h) {
+            float acc = 0.f;
 #pragma unroll
-        for (int k = 0; k < kTerms; ++k)
-#pragma unroll
-            for (int h = 0; h < HEADS; ++h) acc[h] = fmaf(in[h][kTerms * my_part + k], slice[k], acc[h]);
-#pragma unroll
-        for (int h = 0; h < HEADS; ++h) spart[h][my_part][my_col] = acc[h];
+            for (int k = 0; k < kTerms; k += 4) {
+                const float4 x = *reinterpret_cast<const float4 *>(&in[h][kTerms * my_part + k]);
+                acc = fmaf(x.x, slice[k], acc);
+                acc = fmaf(x.y, slice[k + 1], acc);
+                acc = fmaf(x.z, slice[k + 2], acc);
+                acc = fmaf(x.w, slice[k + 3], acc);
+            }
+            spart[h][my_part][my_col] = acc;
+        }
         __syncthreads();
     };
     auto product = [&](int h, int c) {
@@ -768,6 +822,7 @@ __global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
     store(0);
     __syncthreads();
     if (whole) load_slice(St);
+    else if (tid == kThreads - 1) gen_begin_count(word, split.call);
 
     float m = -INFINITY, l = 0.f; /* wavefront h < HEADS: reference and sum of the weights of head h, for the lane's tokens */
     gen_f4 acc = {0.f, 0.f, 0.f, 0.f}; /* wavefront 8 + b, lane j < 16: coordinate 16 b + j for head 0, 1, ... */
@@ -849,60 +904,84 @@ __global__ __launch_bounds__(kGenSplitThreads, 4) void pq_general_piece_kernel(
         for (int h = 0; h < HEADS; ++h) sq[h][16 * blk + lane] = whole ? acc[h] / sl[h] : acc[h]; /* a piece has a token: sl > 0 */
     }
     __syncthreads();
-    if (whole) {
-        times_slice(sq);
-        for (int t = tid; t < HEADS * PQ_D; t += kThreads) out[row0 * PQ_D + t] = product(t >> 7, t & 127);
-    } else {
+    if (!whole) {
+        /* The piece's sums go to the workspace; the workgroup that arrives last joins the pieces of its row.  Other XCDs have other
+           L2s: the sums are written and read at the scope of the device, and every wavefront waits until its own have arrived there. */
+        constexpr int kPairs = HEADS * PQ_D / 2, kSums = kThreads / kPairs, kBatch = 16;
         const int64_t at = (int64_t)item * Hq + head0;
-        for (int t = tid; t < HEADS * PQ_D; t += kThreads) split.o[at * PQ_D + t] = sq[t >> 7][t & 127];
-        if (tid < 2 * HEADS) split.ml[at * 2 + tid] = (tid & 1) ? sl[tid >> 1] : sm[tid >> 1];
-    }
-}
-
-/* Second launch of a split call: a row's pieces brought to one reference, divided by the sum of the weights, times S^T.  One
-   row per workgroup of 512 threads; thread (part, c) takes pieces part, part + 4, ... of column c, then a quarter of the product
-   for it. */
-__global__ __launch_bounds__(512) void pq_general_combine_kernel(GenSplit split, const int64_t *seq_start, const int32_t *ctx_len,
-                                                                 int Hq, int64_t pool_tokens, const float *St, float *out)
-{
-    __shared__ float so[PQ_D], spart[4][PQ_D], sl[4];
-    const int row = blockIdx.x, b = row / Hq, head = row % Hq;
-    const int tid = threadIdx.x, part = tid >> 7, c = tid & 127;
-    GenPlan plan;
-    plan.load(seq_start, ctx_len, split.B);
-    plan.form(split.B, pool_tokens, split.slots);
-    const int first = plan.first(b), used = plan.pieces(b);
-    if (used == 1) return;
-    MatrixSlice ms;
-    matrix_slice_load(ms, St, tid);
-    const float *ml = split.ml + ((int64_t)first * Hq + head) * 2, *op = split.o + ((int64_t)first * Hq + head) * PQ_D + c;
-    float m = -INFINITY;
-    for (int p = tid & 63; p < used; p += 64) m = fmaxf(m, ml[(int64_t)p * Hq * 2]);
+        if (tid < kPairs) gen_put(&split.o[at * PQ_D + 2 * tid], (&sq[0][0])[2 * tid], (&sq[0][0])[2 * tid + 1]);
+        if (tid < HEADS) gen_put(&split.ml[(at + tid) * 2], sm[tid], sl[tid]);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const int first_piece = plan.first(b), used = plan.pieces(b);
+        if (tid == 0) last = gen_arrive(word, (uint32_t)used);
+        __syncthreads();
+        if (!last) return;
+        /* thread (share, pair): pieces share, share + kSums, ... of two neighbouring columns, kBatch of them requested at once */
+        const int pair = tid % kPairs, share = tid / kPairs, h = pair >> 6;
+        const float *ml = split.ml + ((int64_t)first_piece * Hq + head0 + min(wave, HEADS - 1)) * 2;
+        const float *po = split.o + ((int64_t)first_piece * Hq + head0) * PQ_D + 2 * pair;
+        float2 v[kGenMostPieces / 64], batch[kBatch];
+        if (wave < HEADS)
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-    float l = 0.f, o = 0.f;
-#pragma unroll 4
-    for (int p = part; p < used; p += 4) {
-        const float2 v = *reinterpret_cast<const float2 *>(ml + (int64_t)p * Hq * 2);
-        const float w = expf(v.x - m); /* a piece has at least one token: its reference is finite */
-        l = fmaf(v.y, w, l);
-        o = fmaf(op[(int64_t)p * Hq * PQ_D], w, o);
-    }
-    spart[part][c] = o;
-    if (c == 0) sl[part] = l;
-    __syncthreads();
-    if (part == 0) {
-        const float lt = (sl[0] + sl[1]) + (sl[2] + sl[3]);
-        const float a = (spart[0][c] + spart[1][c]) + (spart[2][c] + spart[3][c]);
-        so[c] = lt > 0.f ? a / lt : 0.f;
-    }
-    __syncthreads();
-    float acc = 0.f;
+            for (int i = 0; i < kGenMostPieces / 64; ++i) {
+                v[i] = make_float2(-INFINITY, 0.f);
+                if (lane + 64 * i < used) v[i] = gen_get(ml + (int64_t)(lane + 64 * i) * Hq * 2);
+            }
+        auto request = [&](int p) {
 #pragma unroll
-    for (int k = 0; k < 32; ++k) acc = fmaf(so[32 * part + k], ms.m[k], acc);
-    spart[part][c] = acc;
-    __syncthreads();
-    if (part == 0) out[(int64_t)row * PQ_D + c] = (spart[0][c] + spart[1][c]) + (spart[2][c] + spart[3][c]);
+            for (int i = 0; i < kBatch; ++i) {
+                batch[i] = make_float2(0.f, 0.f);
+                if (p + i * kSums < used) batch[i] = gen_get(po + (int64_t)(p + i * kSums) * Hq * PQ_D);
+            }
+        };
+        request(share);
+        load_slice(St);
+        float *weight = reinterpret_cast<float *>(&srec[0][0][0]); /* [HEADS][kGenMostPieces], on one reference */
+        static_assert(sizeof(srec) >= sizeof(float) * HEADS * kGenMostPieces, "the records' buffers hold the weights");
+        if (wave < HEADS) {
+            float top = -INFINITY, sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < kGenMostPieces / 64; ++i) top = fmaxf(top, v[i].x);
+            top = gen_wave_max(top);
+#pragma unroll
+            for (int i = 0; i < kGenMostPieces / 64; ++i) {
+                const float w = expf(v[i].x - top); /* a piece has a token, and a reference; one that is not there has weight 0 */
+                weight[wave * kGenMostPieces + lane + 64 * i] = w;
+                sum = fmaf(v[i].y, w, sum);
+            }
+            sum = gen_wave_sum(sum);
+            if (lane == 0) sl[wave] = sum;
+        }
+        __syncthreads();
+        float2 o = make_float2(0.f, 0.f);
+        for (int p = share; p < used; p += kBatch * kSums) {
+            if (p != share) request(p);
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i)
+                if (p + i * kSums < used) {
+                    const float w = weight[h * kGenMostPieces + p + i * kSums];
+                    o.x = fmaf(batch[i].x, w, o.x);
+                    o.y = fmaf(batch[i].y, w, o.y);
+                }
+        }
+        float2 *sums = reinterpret_cast<float2 *>(&sv[0][0]);
+        sums[tid] = o;
+        __syncthreads();
+        if (tid < kPairs) {
+            float2 a = sums[tid];
+#pragma unroll
+            for (int k = 1; k < kSums; ++k) {
+                a.x += sums[k * kPairs + tid].x;
+                a.y += sums[k * kPairs + tid].y;
+            }
+            (&sq[0][0])[2 * tid] = a.x / sl[h];
+            (&sq[0][0])[2 * tid + 1] = a.y / sl[h];
+        }
+        __syncthreads();
+    }
+    times_slice(sq);
+    for (int t = tid; t < HEADS * PQ_D; t += kThreads) out[row0 * PQ_D + t] = product(t >> 7, t & 127);
 }
 
 /* heads of a kv head that a workgroup of a split call takes together */
@@ -910,10 +989,9 @@ int gen_split_heads(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }
 
 /* How a call is split: not at all (slots 0) where the heads alone occupy half of the CUs, or where the pool holds no more than
    eight chunks per sequence (three sequences, 8 heads, us for the call, split and not: 2000 tokens 12.8 / 45.2, 500 12.3 / 17.0, 300 12.0 /
-   14.7, 200 12.0 / 12.3; the lengths are on the device, so the pool stands for them, and sequences far shorter than their share
-   of it wait for the host's second launch: 12.1 / 10.6).  Nor in a pool of more than kGenSplitTokens: the split kernels count
-   tokens in 32 bits, and up to there a token plus a chunk, and the chunks of kGenSplitBatch sequences that overlap (2^30 of them),
-   stay below 2^31.  The row kernel counts in 64. */
+   14.7, 200 12.0 / 12.3; the lengths are on the device, so the pool stands for them).  Nor in a pool of more than kGenSplitTokens: the
+   split kernel counts tokens in 32 bits, and up to there a token plus a chunk, and the chunks of kGenSplitBatch sequences that
+   overlap (2^30 of them), stay below 2^31.  The row kernel counts in 64. */
 constexpr int64_t kGenSplitTokens = (int64_t)1 << 30;
 
 GenSplit general_split(int B, int Hq, int Hkv, int64_t pool_tokens)
@@ -928,7 +1006,22 @@ GenSplit general_split(int B, int Hq, int Hkv, int64_t pool_tokens)
     return p;
 }
 
-size_t general_split_bytes(const GenSplit &p, int Hq) { return (size_t)p.pieces * Hq * (PQ_D + 2) * sizeof(float); }
+/* the sums of the pieces, then the arrivals: a word per query head is more than there are groups */
+size_t general_split_bytes(const GenSplit &p, int Hq)
+{
+    return p.slots ? (size_t)p.pieces * Hq * (PQ_D + 2) * sizeof(float) + (size_t)p.B * Hq * kGenWordStride * sizeof(unsigned long long) : 0;
+}
+
+/* Names a call in 48 bits, never 0, beginning anywhere: a workspace that happens to hold the name of this call before it
+   (1 in 2^48) is what is left to chance. */
+unsigned long long next_call()
+{
+    static std::atomic<uint64_t> calls{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ULL >> 16};
+    unsigned long long c;
+    do c = calls.fetch_add(1, std::memory_order_relaxed) & 0xFFFFFFFFFFFFull;
+    while (c == 0);
+    return c;
+}
 
 } // namespace
 
@@ -1051,6 +1144,8 @@ extern "C" pq_status pq_general_attn_decode_ws(const pq_ctx *ctx, const pq_gener
     if (split.slots) {
         split.o = static_cast<float *>(workspace);
         split.ml = split.o + (size_t)split.pieces * Hq * PQ_D;
+        split.arrived = reinterpret_cast<unsigned long long *>(split.ml + (size_t)split.pieces * Hq * 2);
+        split.call = next_call();
         const int heads = gen_split_heads(G);
         const dim3 grid((unsigned)((int64_t)split.pieces * (Hq / heads))), blk(kGenSplitThreads);
         auto launch = [&](auto kernel) {
@@ -1060,8 +1155,6 @@ extern "C" pq_status pq_general_attn_decode_ws(const pq_ctx *ctx, const pq_gener
         if (heads == 4) launch(pq_general_piece_kernel<4>);
         else if (heads == 2) launch(pq_general_piece_kernel<2>);
         else launch(pq_general_piece_kernel<1>);
-        hipLaunchKernelGGL(pq_general_combine_kernel, dim3((unsigned)rows), dim3(512), 0, stream, split, seq_start, ctx_len, Hq,
-                           pool_tokens, ds->St_f32, out);
         PQ_HIP_TRY(hipGetLastError());
         return PQ_OK;
     }

@@ -22,13 +22,15 @@ def _rows_only(ctx, fmt, cbg, q, out, k, v, st, ln, scale):
     assert rc == 0
 
 
-# lengths around the chunk (64 tokens), the two chunks up to which nothing is split, and pieces of several chunks; an empty
-# sequence and one that leaves the pool (its row is zeros); sixty-four sequences, one more than which are never split
+# lengths around the chunk (64 tokens), two chunks (nothing is split in a call whose sequences have no more), and pieces of several
+# chunks; empty sequences and one that leaves the pool (its row is zeros); sixty-four sequences, one more than which are never split
 @pytest.mark.parametrize("G,Hkv,lens,L,bits", [
     (4, 2, [1, 64, 65, 0, 128], 4, [3, 3, 2, 3]),
     (4, 2, [129, 63, 2049, 700], 5, [4, 2, 2, 2, 2]),
     (2, 1, [3000, 1, 193], 7, [4, 3, 2, 2, 1, 2, 3]),
     (3, 1, [1025, 0, 64], 6, [3, 2, 3, 2, 3, 1]),
+    (4, 2, [0, 0, 700, 0, 1, 0, 0, 65, 0], 5, [4, 2, 2, 2, 2]),
+    (4, 2, [0, 0, 0], 5, [4, 2, 2, 2, 2]),
     (1, 1, [5 * k for k in range(63)] + [4000], 4, [4, 3, 3, 3]),
     (1, 1, [5 * k for k in range(64)] + [4000], 4, [4, 3, 3, 3]),
 ])
@@ -60,6 +62,8 @@ def test_split_attention_equals_one_workgroup_per_row(G, Hkv, lens, L, bits):
     for b, n in enumerate(lens):
         if n == 0 or starts[b] + n > pool:
             assert np.all(got[b] == 0.0)
+    if not want.any():
+        return
     # both are within 6e-7 of the 64-bit result (fp32 products and sums); the largest of any row 4e-6
     assert helpers.rel_l2(got, want) <= 2e-6
     if B <= 5:
@@ -90,3 +94,63 @@ def test_captured_attention_takes_no_workspace():
         _rows_only(ctx, fmt, cbg, q, ref, rec, rec, st, ln, helpers.softmax_scale())
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
+
+
+def _split(ctx, fmt, cbg, q, out, k, v, st, ln, scale, ws):
+    cb = np.ascontiguousarray(cbg)
+    rc = library().pq_general_attn_decode_ws(ctx._h, ctypes.byref(fmt), cb.ctypes.data, q.data_ptr(), out.data_ptr(), k.data_ptr(),
+                                             v.data_ptr(), st.data_ptr(), ln.data_ptr(), q.shape[0], q.shape[1], k.shape[0], k.shape[1],
+                                             scale, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+
+
+@pytest.mark.parametrize("G,Hkv", [(4, 2), (1, 3)])
+def test_the_workspace_may_hold_anything(G, Hkv):
+    """The arrivals of the pieces are counted in it: zeros, ones, noise and what an earlier call left, in eager calls on two streams
+    and in a replayed graph whose lengths change; the same bits every time."""
+    L, bits, pool, B = 5, [4, 2, 2, 2, 2], 16384, 3
+    ctx, fmt, cbg, Hq = Context(seed=3), GeneralFormat(L, bits), oracle.general_codebooks(L, bits), G * Hkv
+    rec = torch.zeros((Hkv, pool, fmt.record_bytes()), dtype=torch.uint8, device=DEV)
+    for h in range(Hkv):
+        general_encode(ctx, fmt, cbg, synth.kv_stream(pool, 1, seed=h).reshape(pool, D).to(DEV), rec[h])
+    q, scale = synth.queries(B, Hq, seed=5).to(DEV), helpers.softmax_scale()
+    st = torch.tensor([0, 5000, 9000], dtype=torch.int64, device=DEV)
+    n_bytes = library().pq_general_attn_workspace_bytes(B, Hq, Hkv, pool)
+    lengths = [[4000, 700, 0], [1, 128, 64], [300, 65, 7000], [4000, 3900, 7300]]
+    g = torch.Generator(device=DEV).manual_seed(1)
+    want = []
+    for n in lengths:
+        ln = torch.tensor(n, dtype=torch.int32, device=DEV)
+        ref = torch.zeros((B, Hq, D), device=DEV)
+        _rows_only(ctx, fmt, cbg, q, ref, rec, rec, st, ln, scale)
+        want.append(torch.full((B, Hq, D), float("nan"), device=DEV))
+        _split(ctx, fmt, cbg, q, want[-1], rec, rec, st, ln, scale, torch.zeros(n_bytes, dtype=torch.uint8, device=DEV))
+        assert helpers.rel_l2(want[-1].double().cpu().numpy(), ref.double().cpu().numpy()) <= 2e-6
+    fills = [torch.full((n_bytes,), 255, dtype=torch.uint8, device=DEV)] + \
+            [torch.randint(0, 256, (n_bytes,), dtype=torch.uint8, device=DEV, generator=g) for _ in range(2)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in fills]
+    outs = [[torch.full((B, Hq, D), float("nan"), device=DEV) for _ in lengths] for _ in fills]
+    lns = [torch.tensor(n, dtype=torch.int32, device=DEV) for n in lengths]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                for j in range(len(lengths)):
+                    _split(ctx, fmt, cbg, q, outs[i][j], rec, rec, st, lns[j], scale, fills[i])
+        torch.cuda.synchronize()
+        assert all(torch.equal(outs[i][j], want[j]) for i in range(len(fills)) for j in range(len(lengths)))
+    ln, out, ws = lns[0].clone(), torch.zeros((B, Hq, D), device=DEV), fills[1]
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        _split(ctx, fmt, cbg, q, out, rec, rec, st, ln, scale, ws)
+    for r in range(8):
+        out.fill_(float("nan"))
+        ln.copy_(lns[r % len(lengths)])
+        if r == 5:
+            ws.fill_(77)
+        graph.replay()
+        _split(ctx, fmt, cbg, q, outs[0][0], rec, rec, st, lns[0], scale, fills[0])
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[r % len(lengths)]) and torch.equal(outs[0][0], want[0])
