@@ -529,7 +529,7 @@ extern "C" pq_status pq_decode_kv(const pq_ctx *ctx, pq_kind kind, const uint8_t
     if (kind != PQ_KEY && kind != PQ_VALUE) return PQ_EINVAL;
     if (ot != PQ_F32 && ot != PQ_BF16) return PQ_EINVAL;
     if (n_tokens < 0 || n_heads <= 0 || n_heads > 65535 || pool_tokens <= 0 || (pool_tokens & 63) || token0 < 0) return PQ_EINVAL;
-    if (token0 + n_tokens > pool_tokens || ld_token < 0 || ld_head < 0) return PQ_EINVAL;
+    if (n_tokens > pool_tokens || token0 > pool_tokens - n_tokens || ld_token < 0 || ld_head < 0) return PQ_EINVAL;
     if (!pq_aligned16(codes) || !pq_aligned16(radii) || !pq_aligned16(out)) return PQ_EALIGN;
     if (n_tokens == 0) return PQ_OK;
     const PqDeviceState *ds = nullptr;
@@ -564,7 +564,7 @@ extern "C" pq_status pq_export_canonical(const pq_ctx *ctx, pq_kind kind, const 
     if (!ctx || !codes || !radii || !rec) return PQ_EINVAL;
     if (kind != PQ_KEY && kind != PQ_VALUE) return PQ_EINVAL;
     if (n_tokens < 0 || n_heads <= 0 || n_heads > 65535 || pool_tokens <= 0 || (pool_tokens & 63) || token0 < 0) return PQ_EINVAL;
-    if (token0 + n_tokens > pool_tokens) return PQ_EINVAL;
+    if (n_tokens > pool_tokens || token0 > pool_tokens - n_tokens) return PQ_EINVAL;
     if (!pq_aligned16(codes) || !pq_aligned16(radii)) return PQ_EALIGN;
     if (n_tokens == 0) return PQ_OK;
     ExportArgs a{codes, radii, pool_tokens / 64, token0, n_tokens, rec, ctx->depth == 7 ? 1 : 0};

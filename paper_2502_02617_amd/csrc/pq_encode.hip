@@ -1003,7 +1003,7 @@ pq_status make_encode_args(const void *x, pq_dtype xt, int64_t n_tokens, int n_h
 {
     if (!x || !codes || !radii) return PQ_EINVAL;
     if (n_tokens < 0 || n_heads <= 0 || pool_tokens <= 0 || (pool_tokens & 63) || dst_token0 < 0) return PQ_EINVAL;
-    if (dst_token0 + n_tokens > pool_tokens) return PQ_EINVAL;
+    if (n_tokens > pool_tokens || dst_token0 > pool_tokens - n_tokens) return PQ_EINVAL;
     if (ld_token < 0 || ld_head < 0) return PQ_EINVAL;
     const int64_t elems16 = xt == PQ_BF16 ? 8 : 4;
     if (!pq_aligned16(x) || !pq_aligned16(codes) || !pq_aligned16(radii)) return PQ_EALIGN;

@@ -107,6 +107,15 @@ def test_unsupported_dimension_and_null_arguments():
     assert "PQ_EALIGN" in binding.pq_status_string(-3)
 
 
+def test_a_range_whose_end_is_beyond_64_bits_is_refused():
+    L, c, fake = library(), Context(seed=0), ctypes.c_void_p(0x1000)
+    far, pool = (1 << 63) - 5, 1 << 20
+    for first, n in ((far, 64), (far, pool), (pool - 63, 64), (0, far), (64, far)):
+        assert L.pq_decode_kv(c._h, 0, fake, fake, pool, first, n, 1, fake, 0, 128, 128, 0, None) == -1
+        assert L.pq_export_canonical(c._h, 0, fake, fake, pool, first, n, 1, fake, None) == -1
+        assert L.pq_encode_kv(c._h, fake, 1, 0, n, 1, 128, 128, fake, fake, pool, first, None) == -1
+
+
 def test_workspace_size_grows_with_problem():
     a = Context.attn_workspace_bytes(1, 4, 1, 64)
     b = Context.attn_workspace_bytes(16, 32, 8, 32768)
