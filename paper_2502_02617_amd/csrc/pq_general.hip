@@ -417,7 +417,7 @@ __device__ __forceinline__ int gen_dword_shift(int k, int rec_bytes) { return 8 
 /* tokens of a sequence that take part: one outside the pool is treated as empty */
 __device__ __forceinline__ int gen_tokens(int64_t n, int64_t t0, int64_t pool_tokens)
 {
-    return n < 0 || t0 < 0 || t0 + n > pool_tokens ? 0 : (int)n;
+    return n < 0 || t0 < 0 || n > pool_tokens || t0 > pool_tokens - n ? 0 : (int)n; /* t0 + n could overflow */
 }
 
 /* ---- the same over several workgroups per sequence, for callers with a workspace ----

@@ -154,3 +154,18 @@ def test_the_workspace_may_hold_anything(G, Hkv):
         _split(ctx, fmt, cbg, q, outs[0][0], rec, rec, st, lns[0], scale, fills[0])
         torch.cuda.synchronize()
         assert torch.equal(out, want[r % len(lengths)]) and torch.equal(outs[0][0], want[0])
+
+
+@pytest.mark.parametrize("pool", [512, 8192])                    # one workgroup per row, and split
+def test_a_start_near_the_largest_number_gives_a_zero_row(pool):
+    ctx, fmt, B, Hq = Context(seed=3), GeneralFormat(5, [4, 2, 2, 2, 2]), 3, 2
+    cbg = oracle.general_codebooks(5, [4, 2, 2, 2, 2])
+    rec = torch.zeros((1, pool, fmt.record_bytes()), dtype=torch.uint8, device=DEV)
+    general_encode(ctx, fmt, cbg, synth.kv_stream(pool, 1, seed=1).reshape(pool, D).to(DEV), rec[0])
+    assert (library().pq_general_attn_workspace_bytes(B, Hq, 1, pool) > 0) == (pool == 8192)
+    st = torch.tensor([0, (1 << 63) - 5, (1 << 63) - 1], dtype=torch.int64, device=DEV)
+    ln = torch.tensor([100, 100, 1], dtype=torch.int32, device=DEV)
+    out = torch.full((B, Hq, D), float("nan"), device=DEV)
+    general_attn_decode(ctx, fmt, cbg, synth.queries(B, Hq, seed=5).to(DEV), out, rec, rec, st, ln, helpers.softmax_scale())
+    torch.cuda.synchronize()
+    assert bool(out[0].any()) and bool((out[1:] == 0).all())
