@@ -83,10 +83,11 @@ constexpr float kRefSlack = 6.0f;
  * tokens 115.8 us -> 113.4, 64 sequences of 1k-64k 482 -> 467, depth 7 16 x 14200 67.0 -> 65.0; eight heads, 16 x 35000, 150.4
  * -> 144.8 (four copies, more collisions: 116.4, -, 69.1, 145.2).  They take 0.1 to 0.2 us longer to lay out than four: see launch_partial_depth.
  * The wide form is bound by vector instructions and has no gain from copies, whose index takes a three-operand instruction (draft tokens
- * 74.9 us, 75.2 with eight): one copy, and the tables where its code is the shorter by four registers. */
+ * 74.9 us, 75.2 with eight): one copy, ahead of the other tables, whose entries it gathers most (behind them 64 sequences of 2000
+ * tokens and seven heads 58.5 us instead of 56.5). */
 template <int COPIES> struct Tab {
-    static constexpr int kTBF = COPIES == 1 ? 6144 : 0, kTBH = kTBF + 4096, kTUp = kTBF + 6144, kTQ = COPIES == 1 ? 0 : 6192;
-    static constexpr int kDwords = COPIES == 1 ? 12336 : 6192 + 2048 * COPIES;
+    static constexpr int kTQ = COPIES == 1 ? 0 : 6192, kTBF = COPIES == 1 ? 2048 : 0, kTBH = kTBF + 4096, kTUp = kTBF + 6144;
+    static constexpr int kDwords = 6192 + 2048 * COPIES;
 };
 
 struct AttnArgs {
