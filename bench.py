@@ -227,25 +227,29 @@ def main():
     g_n, g_B, g_ctx, g_hq, g_hkv = 65536, 4, 2048, 8, 2
     gx = enc_inputs[0][0].reshape(-1, D)[:g_n]
     grec = torch.empty((g_n, gfmt.record_bytes()), dtype=torch.uint8, device=dev)
+    g_reps = 20  # calls between two events: one call would be timed with the host's share of its launch
     general_encode(ctx, gfmt, gcb, gx, grec)
     torch.cuda.synchronize()
     ev0.record()
-    general_encode(ctx, gfmt, gcb, gx, grec)
+    for i in range(g_reps):
+        general_encode(ctx, gfmt, gcb, gx, grec)
     ev1.record()
     torch.cuda.synchronize()
-    g_enc_ms = ev0.elapsed_time(ev1)
+    g_enc_ms = ev0.elapsed_time(ev1) / g_reps
     gk = grec[:g_hkv * g_B * g_ctx].reshape(g_hkv, g_B * g_ctx, -1)
     gv = grec[g_hkv * g_B * g_ctx:2 * g_hkv * g_B * g_ctx].reshape(g_hkv, g_B * g_ctx, -1)
     g_start = torch.arange(g_B, dtype=torch.int64, device=dev) * g_ctx
     g_len = torch.full((g_B,), g_ctx, dtype=torch.int32, device=dev)
     g_out = torch.empty((g_B, g_hq, D), dtype=torch.float32, device=dev)
-    general_attn_decode(ctx, gfmt, gcb, q[:g_B, :g_hq].contiguous(), g_out, gk, gv, g_start, g_len, scale)
+    g_q = q[:g_B, :g_hq].contiguous()
+    general_attn_decode(ctx, gfmt, gcb, g_q, g_out, gk, gv, g_start, g_len, scale)
     torch.cuda.synchronize()
     ev0.record()
-    general_attn_decode(ctx, gfmt, gcb, q[:g_B, :g_hq].contiguous(), g_out, gk, gv, g_start, g_len, scale)
+    for i in range(g_reps):
+        general_attn_decode(ctx, gfmt, gcb, g_q, g_out, gk, gv, g_start, g_len, scale)
     ev1.record()
     torch.cuda.synchronize()
-    g_attn_ms = ev0.elapsed_time(ev1)
+    g_attn_ms = ev0.elapsed_time(ev1) / g_reps
     del grec
 
     # ---- hybrid line: the same quantised 32k-token prefix plus a bf16 window of 256 recent tokens per
@@ -546,7 +550,7 @@ def main():
         "general_format": {
             "workload": "the plain path for other bit widths and recursion depths (pq_general_*), depth 5, bits 4/2/2/2/2 "
                         "(55 bytes per vector): encode of 65536 bf16 vectors; attention of 4 sequences x 2048 tokens, "
-                        "8 q / 2 kv heads; fp32, sixteen vectors per workgroup (encode), one workgroup per (sequence, head) (attention)",
+                        "8 q / 2 kv heads; fp32, sixteen vectors per workgroup (encode), a sequence and four heads split over workgroups (attention)",
             "encode_ms": round(g_enc_ms, 4),
             "encode_m_vectors_per_s": round(g_n / (g_enc_ms * 1e-3) / 1e6, 1),
             "attention_ms": round(g_attn_ms, 4),

@@ -192,7 +192,8 @@ __device__ __forceinline__ void dq_store_pair(void *out, int64_t at, float a, fl
  * for keys, 35 for values; to fp32 243 -> 48 and 51.  Every register counts: with what follows from the lane number kept
  * over the loop, up to 11 spilled registers cost values 39.5 us (fp32 57; Hadamard 34 against 28 now), and requesting the
  * next half tile ahead of the products in registers spills more than it hides (45).  AHEAD: it is requested to LDS, which takes none; it
- * travels under the rebuild and the products of this half tile.  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
+ * travels under the rebuild and the products of this half tile.  (Values spill one register to bf16 and three with AHEAD, keys
+ * one with AHEAD; measured as they are.)  Whole tiles on eight wavefronts of 256 registers (S fetched half as often)
  * spill 100 registers; value slots are read from an image in LDS because a token's 16 slots are spread over 16 strings. */
 template <int KIND, int OT, bool UNIT, bool AHEAD>
 __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs a)
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
                 if (!a.deep) im[PQL_CODE_BYTES / 16 + lane] = reinterpret_cast<const uint4 *>(tr)[lane];
                 dq_own_order();
             }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); /* a requested tile is in LDS */
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); /* a requested tile is in LDS (and the stores of the half tile before are out) */
             requested = false;
         }
         if (KIND == PQ_KEY) dq_read_key(t, tc, tr, tau, H, a.deep != 0);

@@ -1,4 +1,5 @@
-"""Codebook fit: the k-means rounds on the device against pq_fit_cluster on a copy of the same counts, bit for bit."""
+"""Codebook fit: the rounds on the running sums that the device forms against pq_fit_cluster, which forms them on the host from a
+copy of the same counts, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +23,7 @@ def _vectors(kind, n, g):
 
 @pytest.mark.parametrize("kind,n", [("gauss", 3000), ("outliers", 700), ("few", 513), ("zeros", 1000), ("gauss", 1)])
 @pytest.mark.parametrize("deep", [False, True])
-def test_device_rounds_equal_the_host_rounds(kind, n, deep):
+def test_sums_formed_on_the_device_give_the_rounds_of_the_host(kind, n, deep):
     g = torch.Generator().manual_seed(n)
     ctx = Context(seed=2)
     if deep:
