@@ -298,11 +298,18 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
     const int vec = min(vec0 + min(wv, NV - 1), n_vec - 1);
     const int seq = vec / a.n_heads, head = vec % a.n_heads;
     const int64_t dst = a.dst_token[seq];
-    /* the constants as well come with the first trip to memory (and siblings by DPP below: one sequence's decode step
-       16.05 -> 15.8 us) */
+    /* One vector per workgroup: the constants as well come with the first trip to memory (and siblings by DPP below: the launch for one
+       sequence 4.9 -> 4.6 us).  Not with four, where they would take 17 registers more over the product and leave two workgroups on a CU
+       instead of three (64 sequences of 8 heads 7.2 us, with them 8.9). */
     const float radius_scale = a.had.on ? PQ_INV_SQRT_D : 1.0f;
-    const Thresholds th = load_thresholds(*a.consts, radius_scale);
-    const bool deep = a.consts->depth == 7, general = a.consts->general != 0;
+    Thresholds th{};
+    bool deep = false, general = false;
+    auto load_constants = [&] {
+        th = load_thresholds(*a.consts, radius_scale);
+        deep = a.consts->depth == 7;
+        general = a.consts->general != 0;
+    };
+    if (NV == 1) load_constants();
     for (int t = tid; t < NV * PQ_D; t += 512) {
         const int64_t at = (int64_t)min(vec0 + (t >> 7), n_vec - 1) * PQ_D + (t & 127);
         if (XT == PQ_BF16) sx[t >> 7][t & 127] = __uint_as_float((uint32_t)static_cast<const uint16_t *>(a.x)[at] << 16);
@@ -336,6 +343,7 @@ __device__ __forceinline__ void append_vectors(const AppendArgs &a, int kind, in
         }
     }
     __syncthreads();
+    if (NV > 1) load_constants();
     __shared__ float sq4[NV][8];
     /* a vector beyond the range or a slot outside the pool: nothing is written */
     const bool write = wv < NV && vec0 + wv < n_vec && dst >= 0 && dst < a.pool_tokens;
