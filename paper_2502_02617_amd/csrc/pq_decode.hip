@@ -216,15 +216,15 @@ __global__ __launch_bounds__(kDecodeThreads, 1) void pq_decode_kernel(DecodeArgs
         dq_request_tile(img[wave], a.codes + at * PQL_CODE_BYTES, a.radii + at * radii_halves, 2 * radii_halves, lane);
     };
     int64_t item = (int64_t)wave * gridDim.x + blockIdx.x;
-    /* The wavefront's first tile is under way to LDS while S is staged (without, values to bf16: 32768 tokens of 8 heads 34.8
-       instead of 34.3 us, 12000 of 4 12.4 instead of 11.7). */
+    /* The wavefront's first tile is under way to LDS while S is staged (without, values to bf16: 12000 tokens of 8 heads 17.6
+       instead of 17.2 us, 3000 of 8 9.8 instead of 9.6; 32768 of 8 within the spread, 35.2 and 35.4). */
     bool requested = KIND == PQ_VALUE || AHEAD;
     if (requested && item < a.n_items) request(item, dq_lane());
     {
         /* chunk (grp, par, ks, lane): S[64 grp + 2 (lane & 31) + par][64 (lane >> 5) + 8 ks .. + 7], the k order of the
            tokens' operand below.  A wavefront fetches eight rows of one parity, 128 bytes each: whole lines, and 32 LDS banks
-           when they are written (a chunk per lane touched 64 lines per load, each line in four loads: 10.8 us for 24000 values, now
-           10.0; 262144 35.5, now 34.8). */
+           when they are written (a chunk per lane touched 64 lines per load, each line in four loads: 10.5 us for 24000 values, now
+           9.8; 96000 18.4, now 17.6; 262144 within the spread, from 35.3 on and from 34.6 on). */
         float4 s[4]; /* all requested before the first is stored */
         const int lane = tid & 63, kk = lane & 7;
         auto place = [&](int i, int &row, int &k, int &chunk) {
