@@ -77,8 +77,8 @@ constexpr float kRefSlack = 6.0f;
  *   kTUp  [3][8][2]          levels 5..7 (full depth)
  *   kTQ   [1024][COPIES][2]  quarter table, by Q: 32 columns of it would be 256 KB.  Lane l reads copy l mod COPIES: of 32 lanes four
  *                            then choose among four bank pairs, instead of all among 32 with one copy.
- * With eight copies a quarter is one gather and one index for keys and values alike: 540 vector and 106 LDS instructions per tile, the
- * vector ALU active 75 % of a launch and the LDS 85 %.  (With one copy the keys fetched a quarter's two pairs from two
+ * With eight copies a quarter is one gather and one index for keys and values alike: 539 vector and 106 LDS instructions per tile, the
+ * vector ALU active 74 % of a launch and the LDS 84 %.  (With one copy the keys fetched a quarter's two pairs from two
  * conflict-free 64-entry tables, two indices for them: 606 and 138, 83 % and 79 %.)  Steps of 16 x 32768
  * tokens 115.8 us -> 113.4, 64 sequences of 1k-64k 482 -> 467, depth 7 16 x 14200 67.0 -> 65.0; eight heads, 16 x 35000, 150.4
  * -> 144.8 (four copies, more collisions: 116.4, -, 69.1, 145.2).  They take 0.1 to 0.2 us longer to lay out than four: see launch_partial_depth.
